@@ -38,7 +38,7 @@ template <typename F> int timed(int id, hipStream_t st, F &&launch) {
 struct Layout {
     size_t Qg, Kg, Kd, gamC, dgamC;                                      // per-channel state gate
     size_t tables;                                                       // packed sequences: the index tables
-    size_t kt, d_ckpt, tok_scalars, Wt, Ktr, Ut, Et, S_ckpt;       // forward
+    size_t kt, d_ckpt, tok_scalars, Wn, Tu, gates, Et, S_ckpt;        // forward
     size_t piece_start, piece_map, piece_flags;                          // phase 1 as sweeps over the whole sequence
     size_t Tm, Pm;                                                       // written by the forward pass for the backward pass only
     size_t dEt, dS_ckpt, dk_read, dkt, masks, a_ckpt;                    // backward only
@@ -139,9 +139,9 @@ Layout make_layout(const osdn_params *p, const Packing &pk) {
     L.kt = take(B * T * H * K * es);
     L.d_ckpt = take(B * H * N * K * 4);
     L.tok_scalars = take(B * T * H * 4 * 4);
-    L.Wt = take(B * T * H * K * es);
-    L.Ktr = take(B * T * H * K * es);
-    L.Ut = take(B * T * H * V * es);
+    L.Wn = take(B * T * H * K * es);
+    L.Tu = take(B * H * N * C * C * es);
+    L.gates = take(B * T * H * 3 * 4);
     L.Et = take(B * T * H * V * es);
     L.S_ckpt = take(B * H * N * V * K * es);
     if (p->gate_per_channel) {
@@ -201,8 +201,8 @@ ChunkArgs chunk_args(const osdn_params *p, const Layout &L, char *ws) {      // 
     ChunkArgs c{};
     c.B = p->B; c.T = p->T; c.H = p->H; c.K = p->K; c.V = p->V; c.N = p->T / C;
     c.scale = p->scale;
-    c.kt = ws + L.kt; c.Wt = ws + L.Wt; c.Ktr = ws + L.Ktr;
-    c.Ut = ws + L.Ut; c.Et = ws + L.Et;
+    c.kt = ws + L.kt; c.Wn = ws + L.Wn; c.Tu = ws + L.Tu;
+    c.gates = reinterpret_cast<float *>(ws + L.gates); c.Et = ws + L.Et;
     c.S_ckpt = ws + L.S_ckpt;
     return c;
 }
@@ -527,7 +527,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
 
     PrecondArgs pa = precond_args(p);
     pa.k = k; pa.beta = beta; pa.retention = retention;
-    pa.k_tilde = ws + L.kt; pa.d_out = d_out; pa.d_ckpt = reinterpret_cast<float *>(ws + L.d_ckpt);
+    pa.k_tilde = ws + L.kt; pa.kt_tiles = 1; pa.d_out = d_out; pa.d_ckpt = reinterpret_cast<float *>(ws + L.d_ckpt);
     pa.tok_scalars = reinterpret_cast<float *>(ws + L.tok_scalars);
     pa.n_seqs = pk.n_seqs; pa.seq_chunks = seq_chunks; pa.d_first = d_in;
     ChunkArgs c = chunk_args(p, L, ws);
@@ -710,7 +710,6 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         un.B = p->B; un.T = p->T; un.H = p->H; un.K = p->K; un.N = p->T / C;
         un.log_alpha = log_alpha; un.q = q; un.k = k; un.kt = c.kt;
         un.dq = dq; un.dk_read = c.dk_read; un.dkt = c.dkt;
-        un.gamC = reinterpret_cast<const float *>(ws + L.gamC);
         un.dgamC = reinterpret_cast<const float *>(ws + L.dgamC);
         un.dlog_alpha = dlog_alpha;
         c.gate_vec = 1;

@@ -19,10 +19,11 @@
 //
 // With one state gate per key channel (GV) the same kernels run, ungated, on the operands in
 // which the forward pass folded the channel decays (Gamma . Q, Gamma . K, K~ / Gamma); the
-// state adjoint decays per channel between chunks, the write rows carry the chunk's decay per
-// channel in place of rho, and the unfold kernel at the end of this file maps the gradients
-// back to q, k, k~ and log alpha.
+// adjoint at a chunk's end is kept as D = gamma_C . dS' (the chunk's decay per channel; S' =
+// (S + E^T K~/Gamma) Diag(gamma_C)), which takes the place of dS' and rho everywhere, and the unfold
+// kernel at the end of this file maps the gradients back to q, k, k~ and log alpha.
 #include "osdn_kernels.h"
+#include "osdn_tile.h"
 
 namespace osdn {
 
@@ -36,51 +37,57 @@ __device__ __forceinline__ float row16_sum(float x) {
     return x;
 }
 
-// a one-value (fp32) MFMA fragment times a scalar; the 8-value bf16 fragments are never scaled
-__device__ __forceinline__ float scale_frag(float f, float s) { return f * s; }
-__device__ __forceinline__ bf16x8 scale_frag(bf16x8 f, float) { return f; }
+// a fragment times one factor per value of the contraction index (rounded once more to the I/O type)
+__device__ __forceinline__ bf16x8 scale_frag(bf16x8 f, const float *g) {      // g: 8 factors, 32-byte aligned, in LDS
+    const f32x4 g0 = *reinterpret_cast<const f32x4 *>(g), g1 = *reinterpret_cast<const f32x4 *>(g + 4);
+    const u32x4 w = __builtin_bit_cast(u32x4, f);
+    bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = (bf16)(vec_get<bf16>(w, e) * (e < 4 ? g0[e & 3] : g1[e & 3]));
+    return o;
+}
+__device__ __forceinline__ float scale_frag(float f, const float *g) { return f * *g; }
 
 // ------------------------------------------------------------- bwd_chain ----
-// Mirror image of state_fwd, right to left: wavefronts 0-3 carry dS (transposed, fp32, in
-// MFMA accumulators), wavefronts 4-7 bring the next chunk's operand tiles into the other LDS
-// buffer and write the dS' checkpoint and dE^T back.  The operands come as the forward pass and
-// the caller left them: (rho . K~)^T and -W^T from chunk_prep, P from output_fwd, q and the
-// slice of dO in their natural [token][feature] layout (operands whose contraction index runs
-// along the rows are fetched with the LDS transpose read), so no kernel has to run ahead of this
-// one.  The local part of dE, scale P^T dO, is formed here as well.  The loader wavefronts move
-// the three [64 x K] tiles; the small ones (P, the slice of dO) are fetched by the compute
-// wavefronts themselves, a chunk ahead, into registers they have to spare.
-constexpr int CT_ = 512, CL_ = 256;
+// Mirror image of state_fwd, right to left: eight wavefronts on the chain (two barriers per chunk),
+// four that move the operands in and the dS' checkpoint and dE^T out:
+//   A  dS', rounded to the I/O type, into LDS                                        | barrier 1
+//   B  dE = scale P^T dO + rho . (K~ dS'^T), one 16x16 tile per wavefront, into LDS  | barrier 2
+//   C  dS <- gamma_C dS' + scale (gamma . dO)^T Q - dE^T W in the MFMA accumulators (the part
+//      without dE already in phase B)
+// The operands come as the forward pass and the caller left them (K~, -W, P, q, the slice of dO, all
+// in their natural [token][feature] layout; those whose contraction index runs down the rows are
+// fetched with the LDS transpose read), by direct global -> LDS loads into two rings, and are in
+// registers when the phase that multiplies them begins, as in state_fwd: what phase B needs (K~; P
+// and dO, whose product and whose scaled fragments are formed at once; the gates) is prepared in
+// phase C of the chunk before, what phase C needs (-W, q) in phase B.  64 chains of 64 chunks, K = V =
+// 128 in bf16: 134 us; with the tiles staged through registers by loader wavefronts, 157 us (16 chains of
+// 128 chunks, V = 256: 206 against 282 us).
+constexpr int CW_ = 8, CM_ = 2, CS_ = 2, CT_ = (CW_ + CM_ + CS_) * 64;     // wavefronts that compute, load, store; threads
+// ring depths, from what fits the LDS (see state_fwd)
+template <typename T, int K> constexpr int BC_NSB = sizeof(T) == 2 ? 2 : (K == 64 ? 2 : 1);
+template <typename T, int K> constexpr int BC_NSC = sizeof(T) == 2 ? 2 : 1;
 
-// GV: one state gate per key channel (the chunk's decay per channel comes from chunk_prep).
+// GV: one state gate per key channel.  The state adjoint at the end of a chunk then only enters
+// multiplied by the chunk's decay per channel, D = gamma_C . dS': the accumulators carry D at the
+// chunk boundaries, and D is what the checkpoint holds.
 // VS: rows of S (values) owned by one workgroup, 32 or 16 (the narrow slice when the chains are few:
 // twice the workgroups, each with half the work on the dependent path per chunk).
 template <typename T, int K, bool GV, int VS>
 __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
-    constexpr int NVT = VS / 16;                    // value tiles per compute wave
-    constexpr int PAD = Pad<T>::v, LDK = K + PAD, LDC = C + PAD, LDS_ = VS + PAD;
-    constexpr int VN = 16 / sizeof(T);
-    constexpr int NKT = K / 64;
-    constexpr int KS = Mfma<T>::KSTEP;
-    constexpr bool BF = sizeof(T) == 2;
-    constexpr int NB = BF ? 2 : 1;
-    constexpr int LTN = NB == 2 ? CL_ / 2 : CL_;    // two loader groups (one per chunk parity) when double-buffered
-    constexpr int NWV = C * K / VN / LTN;           // vectors per loader thread: a [64 x K] or [K x 64] tile
-    constexpr int NCW = CT_ - CL_;                  // compute threads
-    constexpr int NPV = C * C / VN / NCW;           // vectors per compute thread: the [64 x 64] tile P
-    constexpr int NOV = C * VS / VN;                // vectors of the [64 x VS] slice of dO
-    constexpr int NUV = (NOV + NCW - 1) / NCW;      // ... per compute thread (NOV < NCW: the upper threads repeat the lower ones' vectors)
-    static_assert(C * K / VN % LTN == 0 && (NOV % NCW == 0 || NCW % NOV == 0) && C * C / VN % NCW == 0, "tiles must split evenly");
-    __shared__ __attribute__((aligned(16))) T Krt[NB][K * LDC];     // (rho . K~)^T   [kf][i], as chunk_prep left it
-    __shared__ __attribute__((aligned(16))) T Wtt[NB][K * LDC];     // -W^T           [kf][i]
-    __shared__ __attribute__((aligned(16))) T Qn[NB][C * LDK];      // q              [i][kf]
-    __shared__ __attribute__((aligned(16))) T Pn[NB][C * LDC];      // P              [i][j]
-    __shared__ __attribute__((aligned(16))) T dOn[NB][C * LDS_];    // dO slice       [i][v]
-    __shared__ __attribute__((aligned(16))) T dOg[BF ? NB : 1][BF ? C * LDS_ : 1];   // scale gamma_i dO (bf16: a tile of its own)
-    __shared__ __attribute__((aligned(16))) T dSb[VS * LDK];        // dS' in the I/O type [v][kf]
-    __shared__ __attribute__((aligned(16))) T dEt[VS * LDC];        // dE^T [v][i]
-    __shared__ float gCs[NB];
-    __shared__ float sgam[NB][C];                                   // scale gamma_i
+    constexpr int ES = sizeof(T), RK = K * ES, RC = C * ES, RV = VS * ES;      // bytes per row of a tile
+    constexpr int NVT = VS / 16, NFB = K / 16;
+    constexpr int NTC = NFB * NVT, TPW = NTC > CW_ ? NTC / CW_ : 1;            // state tiles, ... per wavefront
+    constexpr int KS = Mfma<T>::KSTEP, NKK = K / KS, NKC = C / KS;
+    typedef typename Mfma<T>::Frag Frag;
+    constexpr bool PRE = sizeof(T) == 2;        // operands in registers ahead of their phase (fp32: they would not fit)
+    constexpr int NSB = BC_NSB<T, K>, NSC = BC_NSC<T, K>;
+    constexpr int B_K = 0, B_P = B_K + C * RK, B_O = B_P + C * RC, B_G = B_O + C * RV, B_BYTES = B_G + 2 * C * 4;
+    constexpr int C_W = 0, C_Q = C_W + C * RK, C_D = C_Q + C * RK, C_BYTES = C_D + (GV ? K * 4 : 0);
+    __shared__ __attribute__((aligned(1024))) char ringB[NSB * B_BYTES];
+    __shared__ __attribute__((aligned(1024))) char ringC[NSC * C_BYTES];
+    __shared__ __attribute__((aligned(1024))) char dSb[VS * RK];        // dS' in the I/O type [v][kf]
+    __shared__ __attribute__((aligned(1024))) char dEs[VS * RC];        // dE^T [v][i]
 
     int chain, slice;
     chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
@@ -92,214 +99,206 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
         a.dS_out = ends ? a.dS_last : a.dS_in;
         bt = 0;
     }
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const bool loader = wave >= 4;
-    const int lt = tid - CL_;
-    const int lgrp = NB == 2 ? (lt >> 7) & 1 : 0;
-    const int lti = NB == 2 ? lt & 127 : lt;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const bool loader = wave >= CW_ && wave < CW_ + CM_, storer = wave >= CW_ + CM_;
+    const int mw = wave - CW_, mt = tid - (CW_ + CM_) * 64;     // loader wavefront, storer thread
     const size_t bh = (size_t)b * a.H + h;      // the chain: indexes dS_out / dS_in
-    const size_t bth = (size_t)bt * a.H + h;    // indexes the per-chunk buffers
-    const size_t tstride = a.H;
+    const uint32_t gK = (uint32_t)a.H * RK, gV = (uint32_t)a.H * (uint32_t)a.V * ES;   // bytes between tokens
+    const bool wideO = (reinterpret_cast<uintptr_t>(a.dO) & 15) == 0, wideQ = (reinterpret_cast<uintptr_t>(a.q) & 15) == 0;
 
-    f32x4 dSt[NVT][NKT];                  // rows = features, cols = values
-    if (!loader) {
+    LdsLoad<RK, C, CM_> lK, lQ;                 // (tiles of the workspace; q where the caller put it)
+    LdsLoad<RC, C, CM_> lP;
+    LdsLoad<RV, C, CM_> lO;
+    lK.init(RK, mw, lane); lQ.init(gK, mw, lane); lP.init(RC, mw, lane); lO.init(gV, mw, lane);
+    auto loadB = [&](int n, int slot) {
+        const size_t bhn = ((size_t)bt * a.N + n) * a.H + h, tok = ((size_t)bt * a.T + (size_t)n * C) * a.H + h;
+        char *s = ringB + slot * B_BYTES;
+        lK.issue(s + B_K, static_cast<const char *>(a.kt) + bhn * C * RK, RK, mw, lane, slice);
+        lP.issue(s + B_P, static_cast<const char *>(a.Pm) + bhn * C * RC, RC, mw, lane, slice);
+        lO.issue(s + B_O, static_cast<const char *>(a.dO) + tok * a.V * ES + (size_t)vs * ES, gV, mw, lane, 0, wideO);
+        if (!GV && mw < 2) {                    // gamma (loader 0) and rho (1)
+            const int w = mw;
+            load_lds4(a.gates + (bhn * 3 + 1 + w) * C, lane * 4, lds_offset(s + B_G + w * C * 4));
+        }
+    };
+    // (GV: with the operands of chunk n come the decays of the chunk to its left, whose D follows)
+    auto loadC = [&](int n, int slot) {
+        const size_t bhn = ((size_t)bt * a.N + n) * a.H + h, tok = ((size_t)bt * a.T + (size_t)n * C) * a.H + h;
+        char *s = ringC + slot * C_BYTES;
+        lK.issue(s + C_W, static_cast<const char *>(a.Wn) + bhn * C * RK, RK, mw, lane, slice);
+        if (GV) lK.issue(s + C_Q, static_cast<const char *>(a.q) + bhn * C * RK, RK, mw, lane, slice);
+        else lQ.issue(s + C_Q, static_cast<const char *>(a.q) + tok * RK, gK, mw, lane, slice, wideQ);
+        if (GV && mw < K / 64)
+            load_lds4(a.gamC + (((size_t)bt * a.N + max(n - 1, 0)) * a.H + h) * K, mw * 256 + lane * 4, lds_offset(s + C_D + mw * 256));
+    };
+    // loads of a loader that are newer than the tiles it waits for (at least)
+    constexpr int LB = LdsLoad<RK, C, CM_>::MIN + LdsLoad<RC, C, CM_>::MIN + LdsLoad<RV, C, CM_>::MIN, LC = 2 * LdsLoad<RK, C, CM_>::MIN;
+    constexpr int NMAX = NSB > NSC ? NSB : NSC;
+    constexpr int NEWER_B = (NSB - 1) * (LB + LC), NEWER_C = (NSC - 1) * (LB + LC);
+    static_assert(NEWER_B < 64 && NEWER_C < 64, "the counter has six bits");
 #pragma unroll
-        for (int vt = 0; vt < NVT; ++vt)
+    for (int j = 0; j < NMAX; ++j) {
+        if (loader && j < NSB && a.n1 - 1 - j >= a.n0) loadB(a.n1 - 1 - j, j);
+        if (loader && j < (PRE ? NSC : NSC - 1) && a.n1 - 1 - j >= a.n0) loadC(a.n1 - 1 - j, j);
+    }
+
+    // this wavefront's tiles of dS (feature block fb, value blocks vtC ..) and of dE (row block rb, value block vtB)
+    const bool inC = wave * TPW < NTC, inB = wave < 4 * NVT;
+    const int fb = wave % NFB, vtC = wave / NFB;
+    const int rb = wave & 3, vtB = wave >> 2;
+    f32x4 dSt[TPW] = {};                        // rows = features, cols = values
+    if (inC) {
 #pragma unroll
-            for (int q = 0; q < NKT; ++q) {
-                const int v = vs + vt * 16 + acc_col(lane), c0 = (wave * NKT + q) * 16 + acc_row(lane, 0);
-                if (a.dS_out) dSt[vt][q] = *reinterpret_cast<const f32x4 *>(a.dS_out + (bh * a.V + v) * K + c0);
-                else dSt[vt][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < TPW; ++q) {
+            const int v = vs + (vtC + q) * 16 + acc_col(lane), c0 = fb * 16 + acc_row(lane, 0);
+            if (a.dS_out) dSt[q] = *reinterpret_cast<const f32x4 *>(a.dS_out + (bh * a.V + v) * K + c0);
+            if (GV) {
+                const f32x4 dc = *reinterpret_cast<const f32x4 *>(a.gamC + (((size_t)bt * a.N + a.n1 - 1) * a.H + h) * K + c0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dSt[q][r] *= dc[r];
             }
-    }
-    u32x4 kreg[NWV], wreg[NWV], qreg[NWV];          // loaders
-    u32x4 preg[NPV], oreg[NUV];                     // compute wavefronts
-    float greg = 0.f;
-#define OSDN_BC_LOAD(n_)                                                                         \
-    {                                                                                            \
-        const size_t bhn_ = bth * a.N + (n_);                                                    \
-        const size_t tok_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                     \
-        const T *kg = static_cast<const T *>(a.Ktr) + bhn_ * K * C;                              \
-        const T *wg = static_cast<const T *>(a.Wt) + bhn_ * K * C;                               \
-        const T *qg = static_cast<const T *>(a.q) + tok_ * K;                                    \
-        _Pragma("unroll") for (int m = 0; m < NWV; ++m) {                                        \
-            const int i = lti + m * LTN;                                                          \
-            kreg[m] = *reinterpret_cast<const u32x4 *>(kg + (size_t)i * VN);                     \
-            wreg[m] = *reinterpret_cast<const u32x4 *>(wg + (size_t)i * VN);                     \
-            qreg[m] = *tile_vec(qg, tstride * K, i / (K / VN), (i % (K / VN)) * VN);             \
-        }                                                                                        \
-        greg = a.log_alpha ? a.log_alpha[tok_ + (size_t)lane * tstride] : 0.f;                   \
-    }
-#define OSDN_BC_STORE(buf_)                                                                      \
-    {                                                                                            \
-        const float G_ = wave_cumsum(greg, lane);                                                \
-        const float GC_ = __shfl(G_, 63, 64);                                                    \
-        const float sg_ = a.scale * __expf(G_);              /* scale gamma of token `lane` */   \
-        _Pragma("unroll") for (int m = 0; m < NWV; ++m) {                                        \
-            const int i = lti + m * LTN;                                                          \
-            { const int r = i / (C / VN), c = (i % (C / VN)) * VN;                               \
-              *reinterpret_cast<u32x4 *>(&Krt[buf_][r * LDC + c]) = kreg[m];                     \
-              *reinterpret_cast<u32x4 *>(&Wtt[buf_][r * LDC + c]) = wreg[m]; }                   \
-            { const int r = i / (K / VN), c = (i % (K / VN)) * VN;                               \
-              *reinterpret_cast<u32x4 *>(&Qn[buf_][r * LDK + c]) = qreg[m]; }                    \
-        }                                                                                        \
-        if (lti < C) sgam[buf_][lti] = sg_;              /* (the first wave of the group: lane = lti) */ \
-        if (lti == 0) gCs[buf_] = __expf(GC_);                                                   \
-    }
-    // the compute wavefronts' own operands: P and the slice of dO of chunk n_ into registers, and
-    // from there into the LDS buffer of that chunk (bf16: also dO with its rows scaled by scale gamma)
-#define OSDN_BC_CLOAD(n_)                                                                        \
-    {                                                                                            \
-        const size_t bhn_ = bth * a.N + (n_);                                                    \
-        const size_t tok_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                     \
-        const T *pg = static_cast<const T *>(a.Pm) + bhn_ * C * C;                               \
-        const T *og = static_cast<const T *>(a.dO) + tok_ * a.V + vs;                            \
-        _Pragma("unroll") for (int m = 0; m < NPV; ++m)                                          \
-            preg[m] = *reinterpret_cast<const u32x4 *>(pg + (size_t)(tid + m * NCW) * VN);       \
-        _Pragma("unroll") for (int m = 0; m < NUV; ++m) {                                        \
-            const int i = (tid + m * NCW) % NOV;                                                  \
-            oreg[m] = *tile_vec(og, tstride * a.V, i / (VS / VN), (i % (VS / VN)) * VN);         \
-        }                                                                                        \
-    }
-#define OSDN_BC_CSTORE(buf_)                                                                     \
-    {                                                                                            \
-        _Pragma("unroll") for (int m = 0; m < NPV; ++m) {                                        \
-            const int i = tid + m * NCW, r = i / (C / VN), c = (i % (C / VN)) * VN;               \
-            *reinterpret_cast<u32x4 *>(&Pn[buf_][r * LDC + c]) = preg[m];                        \
-        }                                                                                        \
-        _Pragma("unroll") for (int m = 0; m < NUV; ++m) {                                        \
-            const int i = (tid + m * NCW) % NOV, r = i / (VS / VN), c = (i % (VS / VN)) * VN;     \
-            *reinterpret_cast<u32x4 *>(&dOn[buf_][r * LDS_ + c]) = oreg[m];                      \
-            if (BF) {                                                                            \
-                const float f_ = sgam[buf_][r];                                                  \
-                float o_[VN];                                                                    \
-                _Pragma("unroll") for (int e = 0; e < VN; ++e) o_[e] = f_ * vec_get<T>(oreg[m], e); \
-                store_vec_t(&dOg[BF ? buf_ : 0][BF ? r * LDS_ + c : 0], o_);                     \
-            }                                                                                    \
-        }                                                                                        \
-    }
-    if (!loader) OSDN_BC_CLOAD(a.n1 - 1)
-    if (loader) {
-        if (NB == 2) {
-            if (lgrp == ((a.n1 - 1) & 1)) {
-                OSDN_BC_LOAD(a.n1 - 1)
-                OSDN_BC_STORE((a.n1 - 1) & 1)
-                OSDN_BC_LOAD(max(a.n1 - 3, a.n0))
-            } else {
-                OSDN_BC_LOAD(max(a.n1 - 2, a.n0))
-            }
-        } else {
-            OSDN_BC_LOAD(a.n1 - 1)
-            OSDN_BC_STORE(0)
-            OSDN_BC_LOAD(max(a.n1 - 2, a.n0))
         }
     }
-
-    __syncthreads();                    // (scale gamma of the first chunk is in LDS)
-    if (!loader) {
-        OSDN_BC_CSTORE(NB == 2 ? (a.n1 - 1) & 1 : 0)
-        OSDN_BC_CLOAD(max(a.n1 - 2, a.n0))
+    if (loader) wait_vm<0>();
+    __syncthreads();
+    int sb = 0, sc = 0;                         // ring slots of chunk n
+    if (loader) {
+        for (int n = a.n1 - 1; n >= a.n0; --n) {
+            const bool full = n - NMAX >= a.n0; // everything counted as newer has been asked for
+            if (full) wait_vm<PRE ? NEWER_C : NEWER_B>(); else wait_vm<0>();   // (as in state_fwd)
+            __syncthreads();                                        // barrier 1
+            if (PRE && n - NSB >= a.n0) loadB(n - NSB, sb);
+            if (!PRE && n + 1 - NSC >= a.n0) loadC(n + 1 - NSC, sc == 0 ? NSC - 1 : sc - 1);
+            if (full) wait_vm<PRE ? NEWER_B : NEWER_C>(); else wait_vm<0>();
+            __syncthreads();                                        // barrier 2
+            if (PRE && n - NSC >= a.n0) loadC(n - NSC, sc);
+            if (!PRE && n - NSB >= a.n0) loadB(n - NSB, sb);
+            sb = sb + 1 == NSB ? 0 : sb + 1;
+            sc = sc + 1 == NSC ? 0 : sc + 1;
+        }
+        return;
     }
-
-    for (int n = a.n1 - 1; n >= a.n0; --n) {
-        const int buf = NB == 2 ? (n & 1) : 0;
-        const size_t bhn = bth * a.N + n;
-        // ---- phase A (compute): dS', rounded, into LDS ----
-        f32x4 gch[GV ? NKT : 1];                                    // channel decays of this lane's state rows
-        if (!loader) {
+    if (storer) {
+        for (int n = a.n1 - 1; n >= a.n0; --n) {
+            const size_t bhn = ((size_t)bt * a.N + n) * a.H + h;
+            __syncthreads();                                        // barrier 1
+            tile_to_global<RK, VS>(static_cast<char *>(a.dS_ckpt) + (bhn * a.V + vs) * RK, RK, dSb, mt, CS_ * 64);
+            __syncthreads();                                        // barrier 2
+            tile_to_global<RC, VS>(static_cast<char *>(a.dEt) + (bhn * a.V + vs) * RC, RC, dEs, mt, CS_ * 64);
+        }
+        return;
+    }
+    TileFrag<T, RK> fK;
+    TileFrag<T, RC> fC;
+    TileFrag<T, RV> fV;
+    fK.init(lane); fC.init(lane); fV.init(lane);
+    // operands of phase B of one chunk: fragments of K~, P^T dO, rho of this lane's rows; gamma_C and
+    // the scaled fragments of dO, which phase C multiplies
+    Frag kf[NKK], of[TPW][NKC];
+    f32x4 loc = {}, rho = {1.f, 1.f, 1.f, 1.f};
+    float gC = 1.f;
+    auto fetchB = [&](const char *tB) {
+        if (inB) {
+            if (PRE) {
 #pragma unroll
-            for (int vt = 0; vt < NVT; ++vt)
-#pragma unroll
-                for (int q = 0; q < NKT; ++q)
-                    store_tile_t(dSb + vt * 16 * LDK + (wave * NKT + q) * 16, LDK, dSt[vt][q], lane);
-            if (GV) {
-#pragma unroll
-                for (int q = 0; q < NKT; ++q)
-                    gch[GV ? q : 0] = *reinterpret_cast<const f32x4 *>(
-                        a.gamC + bhn * K + (wave * NKT + q) * 16 + acc_row(lane, 0));
+                for (int kk = 0; kk < NKK; ++kk) kf[kk] = fK.kc(tB + B_K, rb * 16, kk * KS);
             }
+            loc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKC; ++kk)
+                if (kk * KS + KS > rb * 16)                     // P[i'][i] = 0 for i' < i
+                    loc = Mfma<T>::mma(fC.tr(tB + B_P, kk * KS, rb * 16), fV.tr(tB + B_O, kk * KS, vtB * 16), loc);
+            if (!GV) rho = *reinterpret_cast<const f32x4 *>(tB + B_G + (rb * 16 + acc_row(lane, 0)) * 4 + C * 4);
+        }
+        if (inC) {
+#pragma unroll
+            for (int q = 0; q < TPW; ++q)
+#pragma unroll
+                for (int kk = 0; kk < NKC; ++kk) {
+                    of[q][kk] = fV.tr(tB + B_O, kk * KS, (vtC + q) * 16);
+                    if (!GV) of[q][kk] = scale_frag(of[q][kk], reinterpret_cast<const float *>(tB + B_G) + kk * KS + (lane >> 4) * (KS / 4));
+                }
+        }
+        if (!GV) gC = *reinterpret_cast<const float *>(tB + B_G + (C - 1) * 4);
+    };
+    if (PRE) fetchB(ringB);
+    for (int n = a.n1 - 1; n >= a.n0; --n) {
+        const char *tB = ringB + sb * B_BYTES, *tC = ringC + sc * C_BYTES;
+        // ---- phase A ----
+        if (inC) {
+#pragma unroll
+            for (int q = 0; q < TPW; ++q) fK.put(dSb, (vtC + q) * 16, fb * 16, dSt[q]);
         }
         __syncthreads();                                            // barrier 1
-        if (loader) {
-            if (NB == 2) {
-                if (lgrp == ((n + 1) & 1)) {                        // this group's chunk (n - 1) comes next
-                    if (n > a.n0) {
-                        OSDN_BC_STORE((n - 1) & 1)
-                        OSDN_BC_LOAD(max(n - 3, a.n0))              // (past the start: a harmless reload)
-                    }
-                } else {
-                    store_tile_global(static_cast<T *>(a.dS_ckpt) + (bhn * a.V + vs) * K, (size_t)K, dSb, LDK, VS, K, lti, LTN);
-                }
-            } else {
-                store_tile_global(static_cast<T *>(a.dS_ckpt) + (bhn * a.V + vs) * K, (size_t)K, dSb, LDK, VS, K, lt, CL_);
-            }
-        } else {
-            // ---- phase B: dE = scale P^T dO + (rho . K~) dS'^T (rows 16*wave ..), kept transposed ----
-            const int k0 = (wave * 16) / KS * KS;                   // P[i'][i] = 0 for i' < i
+        // ---- phase B ----
+        Frag sf[NKK], qf[NKC], wf[NKC];
+        f32x4 dc = {};
+        if (!PRE) fetchB(tB);
+        if (inB) {
 #pragma unroll
-            for (int vt = 0; vt < NVT; ++vt) {
-                f32x4 acc = mma_tile0<T, false, true>(&Krt[buf][wave * 16], LDC, dSb + vt * 16 * LDK, LDK, K, lane);
-                const f32x4 loc = mma_tile0<T, false, false>(&Pn[buf][k0 * LDC + wave * 16], LDC,
-                                                             &dOn[buf][k0 * LDS_ + vt * 16], LDS_, C - k0, lane);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r] = __builtin_fmaf(a.scale, loc[r], acc[r]);
-                store_tile_t(dEt + vt * 16 * LDC + wave * 16, LDC, acc, lane);
-            }
+            for (int kk = 0; kk < NKK; ++kk) sf[kk] = fK.kc(dSb, vtB * 16, kk * KS);
         }
+        if (PRE && inC) {
+#pragma unroll
+            for (int kk = 0; kk < NKC; ++kk) qf[kk] = fK.tr(tC + C_Q, kk * KS, fb * 16);
+#pragma unroll
+            for (int kk = 0; kk < NKC; ++kk) wf[kk] = fK.tr(tC + C_W, kk * KS, fb * 16);
+            if (GV) dc = *reinterpret_cast<const f32x4 *>(tC + C_D + (fb * 16 + acc_row(lane, 0)) * 4);
+        }
+        if (inB) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKK; kk += 2) {
+                acc = Mfma<T>::mma(PRE ? kf[kk] : fK.kc(tB + B_K, rb * 16, kk * KS), sf[kk], acc);
+                acc2 = Mfma<T>::mma(PRE ? kf[kk + 1] : fK.kc(tB + B_K, rb * 16, (kk + 1) * KS), sf[kk + 1], acc2);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] = __builtin_fmaf(rho[r], acc[r] + acc2[r], a.scale * loc[r]);
+            fC.put(dEs, vtB * 16, rb * 16, acc);
+        }
+        auto withoutE = [&] {                   // what does not need dE
+#pragma unroll
+            for (int q = 0; q < TPW; ++q) {
+                f32x4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < NKC; ++kk) part = Mfma<T>::mma(PRE ? qf[kk] : fK.tr(tC + C_Q, kk * KS, fb * 16), of[q][kk], part);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dSt[q][r] = __builtin_fmaf(gC, dSt[q][r], a.scale * part[r]);
+            }
+        };
+        if (PRE && inC) withoutE();
         __syncthreads();                                            // barrier 2
-        if (loader) {
-            if (NB == 2) {
-                if (lgrp == ((n + 1) & 1))                          // the group with no load wait ahead
-                    store_tile_global(static_cast<T *>(a.dEt) + (bhn * a.V + vs) * C, (size_t)C, dEt, LDC, VS, C, lti, LTN);
-            } else {
-                store_tile_global(static_cast<T *>(a.dEt) + (bhn * a.V + vs) * C, (size_t)C, dEt, LDC, VS, C, lt, CL_);
+        // ---- phase C ----
+        if (inC) {
+            Frag fe[TPW][NKC];
+            if (!PRE) {
+                withoutE();
+                if (GV) dc = *reinterpret_cast<const f32x4 *>(tC + C_D + (fb * 16 + acc_row(lane, 0)) * 4);
             }
-        } else {
-            // ---- phase C: dS <- gamma_C dS' + (scale gamma . dO)^T Q - dE^T W, transposed ----
-            const float gC = gCs[buf];
 #pragma unroll
-            for (int vt = 0; vt < NVT; ++vt)
+            for (int q = 0; q < TPW; ++q)
 #pragma unroll
-                for (int q = 0; q < NKT; ++q) {
+                for (int kk = 0; kk < NKC; ++kk) fe[q][kk] = fC.kc(dEs, (vtC + q) * 16, kk * KS);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) dSt[vt][q][r] *= GV ? gch[GV ? q : 0][r] : gC;
-                    const int ct = (wave * NKT + q) * 16;
-                    if (BF) {
-                        mma_tile<T, false, false>(dSt[vt][q], &Qn[buf][ct], LDK, &dOg[BF ? buf : 0][BF ? vt * 16 : 0], LDS_, C, lane);
-                    } else {
-                        // fp32: one value per lane and operand, scaled on the way (no second tile)
-                        for (int kk = 0; kk < C; kk += KS) {
-                            typename Mfma<T>::Frag fa = Mfma<T>::template load<false>(&Qn[buf][kk * LDK + ct], LDK, lane);
-                            typename Mfma<T>::Frag fb = Mfma<T>::template load<false>(&dOn[buf][kk * LDS_ + vt * 16], LDS_, lane);
-                            fb = scale_frag(fb, sgam[buf][kk + (lane >> 4)]);
-                            dSt[vt][q] = Mfma<T>::mma(fa, fb, dSt[vt][q]);
-                        }
-                    }
-                    mma_tile<T, true, true>(dSt[vt][q], &Wtt[buf][ct * LDC], LDC, dEt + vt * 16 * LDC, LDC, C, lane);
+            for (int q = 0; q < TPW; ++q) {
+#pragma unroll
+                for (int kk = 0; kk < NKC; ++kk) dSt[q] = Mfma<T>::mma(PRE ? wf[kk] : fK.tr(tC + C_W, kk * KS, fb * 16), fe[q][kk], dSt[q]);
+                if (GV && n > a.n0) {           // (what leaves the launch is dS itself)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) dSt[q][r] *= dc[r];
                 }
-        }
-        if (NB == 1) __syncthreads();                               // single buffer: everyone is through with it
-        if (n > a.n0) {
-            if (NB == 1 && loader) {
-                OSDN_BC_STORE(0)
-                OSDN_BC_LOAD(max(n - 2, a.n0))
-            }
-            if (!loader) {
-                // the next chunk's small tiles into its buffer (free since barrier 1 of this chunk;
-                // its scale gamma table was written before barrier 2), then the request for the one after
-                OSDN_BC_CSTORE(NB == 2 ? (n - 1) & 1 : 0)
-                OSDN_BC_CLOAD(max(n - 2, a.n0))
             }
         }
+        sb = sb + 1 == NSB ? 0 : sb + 1;
+        sc = sc + 1 == NSC ? 0 : sc + 1;
+        if (PRE && n > a.n0) fetchB(ringB + sb * B_BYTES);
     }
-    if (!loader) {
+    if (inC) {
 #pragma unroll
-        for (int vt = 0; vt < NVT; ++vt)
-#pragma unroll
-            for (int q = 0; q < NKT; ++q) {
-                const int v = vs + vt * 16 + acc_col(lane), c0 = (wave * NKT + q) * 16 + acc_row(lane, 0);
-                *reinterpret_cast<f32x4 *>(a.dS_in + (bh * a.V + v) * K + c0) = dSt[vt][q];
-            }
+        for (int q = 0; q < TPW; ++q) {
+            const int v = vs + (vtC + q) * 16 + acc_col(lane), c0 = fb * 16 + acc_row(lane, 0);
+            *reinterpret_cast<f32x4 *>(a.dS_in + (bh * a.V + v) * K + c0) = dSt[q];
+        }
     }
 }
 
@@ -310,8 +309,8 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
 // PW_ wavefronts per workgroup (a parameter of the work split below; 8 is what is launched).
 
 // GV: one state gate per key channel.  The kernel then runs on the folded operands with no
-// scalar gate (log_alpha null); the write rows carry the chunk's decay per channel instead of
-// rho, and dL/d(that decay) is collected per channel.
+// scalar gate (log_alpha null) and on D in place of dS' (see the top of this file); the gradient of
+// the chunk's decays, times the decays, is collected per channel.
 template <typename T, int K, bool GV, int PW_, bool PAIR>
 __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     constexpr int PT_ = PW_ * 64;
@@ -362,7 +361,7 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     // launcher halves the grid): the first loads of the second chunk (gates, K, T, the first slab)
     // are issued when the walk of the first is over and arrive while its results are finished.
     constexpr int tasks = PAIR ? 2 : 1;
-    const int n_first = a.n0 + blockIdx.x * tasks, h = blockIdx.y, b = blockIdx.z;
+    const int n_first = a.n0 + (int)(blockIdx.x / a.H) * tasks, h = blockIdx.x % a.H, b = blockIdx.y;
     const int ntask = min(tasks, a.n1 - n_first);
     int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t tstride = a.H;
@@ -386,14 +385,14 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     // gates, K and T of a chunk, then its first slab
 #define OSDN_BP_ISSUE(n_)                                                                        \
     {                                                                                            \
-        const size_t bhn_i = ((size_t)b * a.H + h) * a.N + (n_);                                 \
+        const size_t bhn_i = ((size_t)b * a.N + (n_)) * a.H + h;                                 \
         const size_t tok_i = ((size_t)b * a.T + (size_t)(n_) * C) * a.H + h;                     \
         if (wave == 0) {                                                                         \
             const size_t th = tok_i + (size_t)lane * tstride;                                    \
-            r_g = a.log_alpha ? a.log_alpha[th] : 0.f;                                           \
+            r_g = a.log_alpha ? a.gates[bhn_i * 3 * C + lane] : 0.f;                             \
             r_b = a.beta[th];                                                                    \
         }                                                                                        \
-        r_Kn.fetch(static_cast<const T *>(a.k) + tok_i * K, tstride * K, tid);                   \
+        r_Kn.fetch(static_cast<const T *>(a.k) + (GV ? bhn_i * C : tok_i) * K, GV ? (size_t)K : tstride * K, tid); \
         r_Tn.fetch(static_cast<const T *>(a.Tm) + bhn_i * C * C, (size_t)C, tid);                \
         OSDN_BP_FETCH(tok_i, bhn_i, 0)                                                           \
     }
@@ -405,7 +404,7 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     asm volatile("" : "+v"(tid));
     wave = __builtin_amdgcn_readfirstlane(tid >> 6); lane = tid & 63;
     const int n = n_first + task;
-    const size_t bhn = ((size_t)b * a.H + h) * a.N + n;
+    const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
     const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const int ct = (wave % NCT) * 16;   // this wave's column tile of the [64 x K] results ...
     const int ib0 = (wave / NCT) * IBN; // ... and its first row block
@@ -413,7 +412,7 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
 
     if (task > 0) __syncthreads();      // the previous chunk is through with every LDS tile
     if (wave == 0) {
-        const float G = wave_cumsum(r_g, lane);
+        const float G = r_g;
         Gs[lane] = G;
         Egs[lane] = __expf(G);
         Ers[lane] = __expf(lane_bcast63(G) - G);
@@ -446,8 +445,8 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
         if (v0 + VB < a.V) {
             OSDN_BP_FETCH(tok0, bhn, v0 + VB)
         } else {
-            r_Q.fetch(static_cast<const T *>(a.q) + tok0 * K, tstride * K, tid);
-            r_Kt.fetch(static_cast<const T *>(a.kt) + tok0 * K, tstride * K, tid);
+            r_Q.fetch(static_cast<const T *>(a.q) + (GV ? bhn * C : tok0) * K, GV ? (size_t)K : tstride * K, tid);
+            r_Kt.fetch(static_cast<const T *>(a.kt) + bhn * C * K, (size_t)K, tid);
         }
         __syncthreads();
         if (v0 == 0) {
@@ -634,9 +633,8 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) tc[ib][r] = 0.f;
     T *dq_g = static_cast<T *>(a.dq) + tok0 * K;
-    T *dk_g = static_cast<T *>(a.dk_read) + tok0 * K;
-    T *dkt_g = static_cast<T *>(a.dkt) + tok0 * K;
-    const float gcv = (GV && has_ct) ? a.gamC[bhn * K + ct + acc_col(lane)] : 1.f;   // this lane's channel
+    T *dk_g = static_cast<T *>(a.dk_read) + bhn * C * K;
+    T *dkt_g = static_cast<T *>(a.dkt) + bhn * C * K;
     float dgc = 0.f;
     if (has_ct) {
 #pragma unroll
@@ -677,7 +675,7 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
                 const float gam = Egs[i], rho = Ers[i];
                 const float gq = a.scale * gam * dQg[iq][r];         // gamma . d(gamma Q)
                 const float gk = -Bs[i] * gam * dKg[iq][r];           // gamma . d(gamma K)
-                const float gr = (GV ? gcv : rho) * dKr[iq][r];       // rho . d(rho K~)
+                const float gr = (GV ? 1.f : rho) * dKr[iq][r];       // rho . d(rho K~)
                 const float qv = to_f32(Qs[i * LDK + c]), kv = to_f32(Ks[i * LDK + c]),
                             ktv = to_f32(Kts[i * LDK + c]);
                 if (GV) dgc = __builtin_fmaf(ktv, dKr[iq][r], dgc);
@@ -685,8 +683,9 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
                 trs = __builtin_fmaf(gr, ktv, trs);
                 const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * K) + (uint32_t)c) * (uint32_t)sizeof(T);
                 *reinterpret_cast<T *>(reinterpret_cast<char *>(dq_g) + go) = from_f32<T>(aq[r] + gq);
-                *reinterpret_cast<T *>(reinterpret_cast<char *>(dk_g) + go) = from_f32<T>(ak[r] + gk);
-                *reinterpret_cast<T *>(reinterpret_cast<char *>(dkt_g) + go) = from_f32<T>(at[r] + gr);
+                const uint32_t gt = ((uint32_t)i * K + (uint32_t)c) * (uint32_t)sizeof(T);
+                *reinterpret_cast<T *>(reinterpret_cast<char *>(dk_g) + gt) = from_f32<T>(ak[r] + gk);
+                *reinterpret_cast<T *>(reinterpret_cast<char *>(dkt_g) + gt) = from_f32<T>(at[r] + gr);
             }
         }
     }
@@ -708,7 +707,7 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     trs = wave_sum(trs);
     if (lane == 0) trsum_s[wave] = trs;
     __syncthreads();
-    if (GV && tid < K) {                // dL/d(decay of channel tid over the chunk)
+    if (GV && tid < K) {                // gamma_C . dL/d(decay of channel tid over the chunk)
         float sd = 0.f;
 #pragma unroll
         for (int j = 0; j < WPC; ++j) sd += dgam_s[GV ? j * K + tid : 0];
@@ -751,10 +750,12 @@ static int launch_chain_t(const ChunkArgs &a, hipStream_t st) {
     else return -1;
     return 0;
 }
-// Slices of 16 values when the caller asks for them (few chains: see ChunkArgs::narrow_slices).
+// Slices of 16 values when the caller asks for them (few chains: see ChunkArgs::narrow_slices), and
+// always with fp32 I/O, whose operands would not fit the LDS beside slices of 32.
 template <typename T, bool GV>
 static int launch_chain_v(const ChunkArgs &a, hipStream_t st) {
-    return a.narrow_slices ? launch_chain_t<T, GV, 16>(a, st) : launch_chain_t<T, GV, 32>(a, st);
+    if constexpr (sizeof(T) == 2) if (!a.narrow_slices) return launch_chain_t<T, GV, 32>(a, st);
+    return launch_chain_t<T, GV, 16>(a, st);
 }
 int launch_bwd_chain(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
     if (a.gate_vec) return bf16_io ? launch_chain_v<bf16, true>(a, st) : launch_chain_v<float, true>(a, st);
@@ -769,8 +770,8 @@ static int launch_post_t(const ChunkArgs &a, hipStream_t st) {
     const int chunks = a.n1 - a.n0;
     constexpr bool PAIRABLE = sizeof(T) == 2 && !GV;     // elsewhere the prefetch registers would spill
     const bool pairs = PAIRABLE && chunks >= 2 && (long long)chunks * a.H * a.B >= BP_MIN_WGS;
-    dim3 grid(pairs ? (chunks + 1) / 2 : chunks, a.H, a.B), block(PW * 64);
-    if (GV && (!a.gamC || !a.dgamC || a.log_alpha || a.dlog_alpha)) return -1;
+    dim3 grid((pairs ? (chunks + 1) / 2 : chunks) * a.H, a.B), block(PW * 64);
+    if (GV && (!a.dgamC || a.log_alpha || a.dlog_alpha)) return -1;
     if (pairs) {
         if (a.K == 64) hipLaunchKernelGGL((bwd_post_kernel<T, 64, GV, PW, PAIRABLE>), grid, block, 0, st, a);
         else if (a.K == 128) hipLaunchKernelGGL((bwd_post_kernel<T, 128, GV, PW, PAIRABLE>), grid, block, 0, st, a);
@@ -799,8 +800,8 @@ template <typename T, int K>
 __global__ __launch_bounds__(NT) void unfold_kernel(UnfoldArgs a) {
     constexpr int GLD = K + 4, VN = 16 / sizeof(T);
     __shared__ __attribute__((aligned(16))) float Gt[C * GLD];     // G, then dG, then dlog_alpha
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-    const size_t bhn = ((size_t)b * a.H + h) * a.N + n;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y, tid = threadIdx.x;
+    const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
     const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const size_t rs = (size_t)a.H * K;                              // elements between consecutive tokens
     const float *gp = a.log_alpha + tok0 * K;
@@ -819,16 +820,16 @@ __global__ __launch_bounds__(NT) void unfold_kernel(UnfoldArgs a) {
     }
     __syncthreads();
     const T *qp = static_cast<const T *>(a.q) + tok0 * K, *kp = static_cast<const T *>(a.k) + tok0 * K,
-            *tp = static_cast<const T *>(a.kt) + tok0 * K;
-    T *dqp = static_cast<T *>(a.dq) + tok0 * K, *dkp = static_cast<T *>(a.dk_read) + tok0 * K,
-      *dtp = static_cast<T *>(a.dkt) + tok0 * K;
+            *tp = static_cast<const T *>(a.kt) + bhn * C * K;
+    T *dqp = static_cast<T *>(a.dq) + tok0 * K, *dkp = static_cast<T *>(a.dk_read) + bhn * C * K,
+      *dtp = static_cast<T *>(a.dkt) + bhn * C * K;
     for (int v = tid; v < C * K / VN; v += NT) {
         const int i = v / (K / VN), c = (v % (K / VN)) * VN;
-        const size_t o = (size_t)i * rs + c;
+        const size_t o = (size_t)i * rs + c, ot_ = i * K + c;            // caller's tensors, workspace tiles
         const u32x4 qv = *reinterpret_cast<const u32x4 *>(qp + o), kv = *reinterpret_cast<const u32x4 *>(kp + o),
-                    tv = *reinterpret_cast<const u32x4 *>(tp + o);
-        const u32x4 gq = *reinterpret_cast<const u32x4 *>(dqp + o), gk = *reinterpret_cast<const u32x4 *>(dkp + o),
-                    gt = *reinterpret_cast<const u32x4 *>(dtp + o);
+                    tv = *reinterpret_cast<const u32x4 *>(tp + ot_);
+        const u32x4 gq = *reinterpret_cast<const u32x4 *>(dqp + o), gk = *reinterpret_cast<const u32x4 *>(dkp + ot_),
+                    gt = *reinterpret_cast<const u32x4 *>(dtp + ot_);
         float oq[VN], ok[VN], ot[VN];
 #pragma unroll
         for (int e = 0; e < VN; ++e) {
@@ -840,12 +841,12 @@ __global__ __launch_bounds__(NT) void unfold_kernel(UnfoldArgs a) {
             Gt[i * GLD + c + e] = oq[e] * vec_get<T>(qv, e) + ok[e] * vec_get<T>(kv, e) - ot[e] * vec_get<T>(tv, e);
         }
         store_vec_t(dqp + o, oq);
-        store_vec_t(dkp + o, ok);
-        store_vec_t(dtp + o, ot);
+        store_vec_t(dkp + ot_, ok);
+        store_vec_t(dtp + ot_, ot);
     }
     __syncthreads();
     if (tid < K) {
-        float acc = a.gamC[bhn * K + tid] * a.dgamC[bhn * K + tid];
+        float acc = a.dgamC[bhn * K + tid];
 #pragma unroll 16
         for (int i = C - 1; i >= 0; --i) {
             acc += Gt[i * GLD + tid];
@@ -862,14 +863,14 @@ __global__ __launch_bounds__(NT) void unfold_kernel(UnfoldArgs a) {
 
 template <typename T>
 static int launch_unfold_t(const UnfoldArgs &a, hipStream_t st) {
-    dim3 grid(a.n1 - a.n0, a.H, a.B), block(NT);
+    dim3 grid((a.n1 - a.n0) * a.H, a.B), block(NT);
     if (a.K == 64) hipLaunchKernelGGL((unfold_kernel<T, 64>), grid, block, 0, st, a);
     else if (a.K == 128) hipLaunchKernelGGL((unfold_kernel<T, 128>), grid, block, 0, st, a);
     else return -1;
     return 0;
 }
 int launch_unfold(const UnfoldArgs &a, bool bf16_io, hipStream_t st) {
-    if (!a.log_alpha || !a.q || !a.k || !a.kt || !a.dq || !a.dk_read || !a.dkt || !a.gamC || !a.dgamC || !a.dlog_alpha)
+    if (!a.log_alpha || !a.q || !a.k || !a.kt || !a.dq || !a.dk_read || !a.dkt || !a.dgamC || !a.dlog_alpha)
         return -1;
     return bf16_io ? launch_unfold_t<bf16>(a, st) : launch_unfold_t<float>(a, st);
 }

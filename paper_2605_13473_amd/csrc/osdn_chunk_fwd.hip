@@ -5,22 +5,28 @@
 //   chunk_prep   (parallel over chunks):  A = tril(beta_i Gamma_ij <k_i, k~_j>, -1),
 //                T = (I + A)^-1 in fp32,  W = T (beta gamma . K),  U = T (beta . V)
 //   state_fwd    (sequential over chunks, parallel over (b, h, slice of V)):
-//                E = U - W S^T ;  S <- gamma_C S + E^T (rho . K~)      (S fp32 in registers)
+//                E = U - W S^T ;  S <- gamma_C S + (rho . E)^T K~      (S fp32 in registers)
 //   output_fwd   (parallel over chunks):  O = scale [ gamma . (Q S^T) + P E ],  P = tril(Gamma . Q K~^T)
 //                (P is also written out when a backward pass follows)
 //
 // All contractions run on MFMA with fp32 accumulation; operands are staged in LDS in the
 // I/O element type.
 #include "osdn_kernels.h"
+#include "osdn_tile.h"
 
 namespace osdn {
 
 // ------------------------------------------------------------ chunk_prep ----
-// Besides T it leaves the tiles the chain kernels consume in exactly the layout their MFMA
-// operands want, so that those kernels only copy: -W^T, (rho . K~)^T and U^T (transposes come
-// for free from the accumulator layout, or from a 0/1 selector product for K~).
-// The row scalings of the right-hand sides move into T: W = (T diag(beta gamma)) K and
-// U = (T diag(beta)) V, so that K and V enter the products as they come from memory.
+// Leaves per chunk -W (natural layout), T diag(beta), the cumulative log-decay G, and T itself when
+// a backward pass follows.  The row scalings of the right-hand sides move into T: W = (T diag(beta
+// gamma)) K and U = (T diag(beta)) V; U is never formed: the state kernel adds (T diag(beta)) V to
+// its product with the state in one accumulator, and scales E (not K~) for the write.  So V, U and a
+// scaled copy of K~ stay out of this kernel's traffic.
+//
+// Bound by its phases' latency and memory: three workgroups share a CU (52 KB of LDS each at K =
+// 128 in bf16: A, K~'s space reused for (I + A)^-1 and then for the outgoing W, the block products
+// of the inverse in A's empty upper blocks).  4096 chunk-heads, K = V = 128 in bf16: 57 us and 269 MB;
+// writing U^T and (rho K~)^T for the chain as well, two workgroups per CU: 104 us and 446 MB.
 //
 // GV: one state gate per key channel (the chunkwise UT form of online-scaled KDA, appendix
 // section on Kimi Delta Attention with online scaling).  The cumulative channel decays
@@ -30,88 +36,56 @@ namespace osdn {
 // chunk's total decay per channel for the state and output kernels.  1 / Gamma grows like
 // e^{|G|}: the cumulative log-decay of a channel inside a chunk has to stay above about -80.
 constexpr int CP_ = 512;        // threads of a chunk_prep workgroup (8 wavefronts)
-constexpr int CP_TASKS = 2;     // chunks per workgroup of a large launch
-constexpr int CP_MIN_WGS = 2048;  // ... large: at least this many workgroups of one chunk each (four rounds of two per CU)
 template <typename T, int K, bool GV>
 __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
-    // K and K~ are read 16 bytes per lane along k (Gram matrix, transposes): 32 bytes of padding
-    // for bf16 (not with per-channel gates, where two workgroups would no longer fit a CU); the
-    // tiles that are written transposed keep 16
-    constexpr int PAD = Pad<T>::v, LDK = K + (sizeof(T) == 2 && !GV ? 16 : PAD), LDC = C + PAD, LDF = C + 1;
-    constexpr int NW = CP_ / 64;
-    __shared__ __attribute__((aligned(16))) T X1[C * LDK];      // K, then V slabs
-    __shared__ __attribute__((aligned(16))) T X2[C * LDK];      // K~, then W staging
-    __shared__ __attribute__((aligned(16))) T Tu[C * LDC];      // T diag(beta)
-    // scratch: A (fp32) | (I + A)^-1 (fp32).  A's space later holds
-    // T diag(beta gamma); the rest doubles as the staging tile for the transposed outputs.
-    constexpr int STAGE_F = (K * LDC * (int)sizeof(T) + 3) / 4;
-    constexpr int TI_F = C * LDF + C;               // (I + A)^-1 and one row of column scalars
-    constexpr int TW_F = C * LDC * (int)sizeof(T) / 4;
-    constexpr int AF_F = ((C * LDF > TW_F ? C * LDF : TW_F) + 3) & ~3;
-    __shared__ __attribute__((aligned(16))) float scratch[AF_F + (TI_F > STAGE_F ? TI_F : STAGE_F)];
-    float *Af = scratch;                                        // A (fp32)
-    float *Ti = scratch + AF_F;                                 // (I + A)^-1 (fp32), 16-byte aligned
-    float *Xs = reinterpret_cast<float *>(Tu);                  // [3][16][17] block products of the inverse: T diag(beta) comes after it
+    constexpr int PAD = Pad<T>::v, LDK = K + PAD, LDC = C + PAD, LDF = C + 1;
+    constexpr int NW = CP_ / 64, VN = 16 / sizeof(T);
+    constexpr int X2_F = (C * LDK * (int)sizeof(T) / 4 > C * LDF ? C * LDK * (int)sizeof(T) / 4 : C * LDF + 3) & ~3;
+    constexpr int TW_F = C * LDC * (int)sizeof(T) / 4, GLD = K + 4;
+    constexpr int AF_F0 = C * LDF > TW_F ? C * LDF : TW_F;
+    constexpr int AF_F = ((GV && C * GLD > AF_F0 ? C * GLD : AF_F0) + 3) & ~3;
+    __shared__ __attribute__((aligned(16))) T X1[C * LDK];      // K
+    __shared__ __attribute__((aligned(16))) float X2f[X2_F];    // K~, then (I + A)^-1 (fp32), then -W on its way out
+    __shared__ __attribute__((aligned(16))) float Af[AF_F];     // (GV: the channel decays,) A (fp32), then T diag(beta gamma)
+    T *X2 = reinterpret_cast<T *>(X2f);
+    float *Ti = X2f;
     T *Tw = reinterpret_cast<T *>(Af);                          // [64][LDC], once A is dead
-    T *stage = reinterpret_cast<T *>(Ti);                       // [K][LDC] / [64][LDC], while Ti is not live
-    __shared__ float Gs[C], Bs[C];
-    __shared__ float gCs[GV ? K : 1];                           // per-channel decay over the whole chunk
+    __shared__ float Gs[C], Bs[C], BGs[C];
 
-    // A workgroup builds `tasks` adjacent chunks one after the other: while it works on one, the
-    // K, K~ tiles and gates of the next are already on their way (a third of a chunk's time is the
-    // wait for its first loads otherwise).  The launcher asks for two only when the launch still
-    // fills the chip several times over: on a short segment the longer workgroups would only
-    // lengthen the time to its last chunk.
-    const int tasks = (int)gridDim.x < a.n1 - a.n0 ? CP_TASKS : 1;
-    const int n_first = a.n0 + blockIdx.x * tasks, h = blockIdx.y, b = blockIdx.z;
-    const int ntask = min(tasks, a.n1 - n_first);
-    int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const size_t tstride = a.H;                                           // tokens are H rows apart
-    TileRegs<T, C, K, CP_> r_K, r_Kt;
-    TileRegs<T, C, C, CP_> r_V;
-    float r_g = 0.f, r_b = 0.f;
-#define OSDN_CP_ISSUE(n_, with_v_)                                                               \
-    {                                                                                            \
-        const size_t tok_ = ((size_t)b * a.T + (size_t)(n_) * C) * a.H + h;                      \
-        r_K.fetch(static_cast<const T *>(a.k) + tok_ * K, tstride * K, tid);                     \
-        r_Kt.fetch(static_cast<const T *>(a.kt) + tok_ * K, tstride * K, tid);                   \
-        if (with_v_) r_V.fetch(static_cast<const T *>(a.v) + tok_ * a.V, tstride * a.V, tid);    \
-        if (wave == 0) {                                                                         \
-            const size_t th = tok_ + (size_t)lane * tstride;                                     \
-            r_g = (!GV && a.log_alpha) ? a.log_alpha[th] : 0.f;   /* GV: the gates go into the operands */ \
-            r_b = a.beta[th];                                                                    \
-        }                                                                                        \
-    }
-    OSDN_CP_ISSUE(n_first, true)
-#pragma unroll 1
-    for (int task = 0; task < ntask; ++task) {
-    // (the thread index is made opaque once per chunk: otherwise every lane address of the body is
-    // computed ahead of the loop and kept in registers, three times the registers of one chunk)
-    asm volatile("" : "+v"(tid));
-    wave = __builtin_amdgcn_readfirstlane(tid >> 6); lane = tid & 63;
-    const int n = n_first + task;
-    const size_t bhn = ((size_t)b * a.H + h) * a.N + n;
+    const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
     const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;      // (b, first token, h)
-
-    if (task > 0) __syncthreads();      // the previous chunk is through with every LDS tile
-    if (wave == 0) {
-        Gs[lane] = wave_cumsum(r_g, lane);
-        Bs[lane] = r_b;
+    {
+        TileRegs<T, C, K, CP_> r_K, r_Kt;
+        float g = 0.f, bt = 0.f;
+        r_K.fetch(static_cast<const T *>(a.k) + tok0 * K, tstride * K, tid);
+        r_Kt.fetch(static_cast<const T *>(a.kt) + bhn * C * K, (size_t)K, tid);
+        if (wave == 0) {
+            const size_t th = tok0 + (size_t)lane * tstride;
+            if (!GV && a.log_alpha) g = a.log_alpha[th];                  // GV: the gates go into the operands
+            bt = a.beta[th];
+            const float G = wave_cumsum(g, lane);
+            Gs[lane] = G;
+            Bs[lane] = bt;
+            BGs[lane] = bt * __expf(G);
+            if (!GV) {                          // the chunk's gates for everyone else: G, gamma = e^G, rho = e^(G_C - G)
+                float *gr = a.gates + bhn * 3 * C;
+                gr[lane] = G;
+                gr[C + lane] = __expf(G);
+                gr[2 * C + lane] = __expf(lane_bcast63(G) - G);
+            }
+        }
+        r_K.put(X1, LDK, tid);
+        r_Kt.put(X2, LDK, tid);
     }
-    r_K.put(X1, LDK, tid);
-    r_Kt.put(X2, LDK, tid);
-    // the first slab of V stays in registers while the chunk's T is being built
-    const T *vg = static_cast<const T *>(a.v) + tok0 * a.V;
-    if (task + 1 < ntask) OSDN_CP_ISSUE(n + 1, false)
     __syncthreads();
     if (GV) {
-        // cumulative log-decay of every channel, G [64 x K] in fp32, in the scratch space (not
-        // yet in use): loaded with vector reads, summed down the columns by one thread per
-        // channel, then K <- e^{G} K and K~ <- e^{-G} K~ in LDS and Gamma . Q straight to memory,
-        // all threads on 16-byte vectors
-        constexpr int GLD = K + 4, VN = 16 / sizeof(T);
-        static_assert(C * GLD <= AF_F + (TI_F > STAGE_F ? TI_F : STAGE_F), "G must fit the scratch space");
-        float *Gt = scratch;
+        // cumulative log-decay of every channel, G [64 x K] in fp32, in A's space: loaded with vector
+        // reads, summed down the columns by one thread per channel, then K <- e^{G} K and K~ <- e^{-G}
+        // K~ in LDS and Gamma . Q straight to memory, all threads on 16-byte vectors
+        float *Gt = Af;
         const size_t rs = tstride * K;
         const float *gp = a.log_alpha + tok0 * K;
         for (int v = tid; v < C * K / 4; v += CP_) {
@@ -126,12 +100,11 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
                 G += Gt[i * GLD + tid];
                 Gt[i * GLD + tid] = G;
             }
-            gCs[GV ? tid : 0] = __expf(G);
             a.gamC[bhn * K + tid] = __expf(G);
         }
         __syncthreads();
         const T *qp = static_cast<const T *>(a.q) + tok0 * K;
-        T *qg = static_cast<T *>(a.Qg) + tok0 * K;
+        T *qg = static_cast<T *>(a.Qg) + bhn * C * K;
         for (int v = tid; v < C * K / VN; v += CP_) {
             const int i = v / (K / VN), c = (v % (K / VN)) * VN;
             const u32x4 kv = *reinterpret_cast<const u32x4 *>(X1 + i * LDK + c);
@@ -148,12 +121,11 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
             }
             store_vec_t(X1 + i * LDK + c, ko);
             store_vec_t(X2 + i * LDK + c, to);
-            store_vec_t(qg + (size_t)i * rs + c, qo);
+            store_vec_t(qg + i * K + c, qo);
         }
-        __syncthreads();
-        store_tile_global(static_cast<T *>(a.Kg) + tok0 * K, tstride * K, X1, LDK, C, K, tid, CP_);
-        store_tile_global(static_cast<T *>(a.Kd) + tok0 * K, tstride * K, X2, LDK, C, K, tid, CP_);
-        __syncthreads();            // the scratch space is handed over to A
+        __syncthreads();            // (the decays' space is handed over to A)
+        store_tile_global(static_cast<T *>(a.Kg) + bhn * C * K, (size_t)K, X1, LDK, C, K, tid, CP_);
+        store_tile_global(static_cast<T *>(a.Kd) + bhn * C * K, (size_t)K, X2, LDK, C, K, tid, CP_);
     }
 
     // ---- A = tril(beta_i Gamma_ij <k_i, k~_j>, -1): the ten lower 16x16 tiles ----
@@ -167,38 +139,14 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
             Af[i * LDF + j] = (j < i) ? Bs[i] * __expf(Gs[i] - Gs[j]) * acc[r] : 0.f;
         }
     }
-    // ---- (rho . K~)^T: pick 16x16 blocks of K~, scale rows by rho_j, store transposed ----
-    {
-        const float GC = Gs[C - 1];
-        for (int t = wave; t < (K / 16) * 4; t += NW) {
-            const int nb = t >> 2, jb = t & 3;                  // 16 features of K~, 16 tokens
-            {
-                f32x4 acc = pick16<T>(X2 + jb * 16 * LDK, LDK, nb * 16, lane);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r] *= __expf(GC - Gs[jb * 16 + acc_row(lane, r)]);
-                if (GV) {                       // (gamma_C / Gamma) . K~ = gamma_C . (K~ / Gamma), channel by channel
-                    const float gc = gCs[GV ? nb * 16 + acc_col(lane) : 0];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[r] *= gc;
-                }
-                store_tile_t(stage + nb * 16 * LDC + jb * 16, LDC, acc, lane);
-            }
-        }
-    }
-    __syncthreads();
-    store_tile_global(static_cast<T *>(a.Ktr) + bhn * K * C, (size_t)C, stage, LDC, K, C, tid, CP_);
-    __syncthreads();                // the staging tile is free again: (I + A)^-1 is built in its place
-
-    // beta_j gamma_j, once per column (behind (I + A)^-1)
-    float *BGs = Ti + C * LDF;
-    if (wave == NW - 1) BGs[lane] = Bs[lane] * __expf(Gs[lane]);
+    __syncthreads();                // A is complete, K~ is dead: (I + A)^-1 is built in its place
     // ---- T = (I + A)^-1 in fp32, blocked ----
-    ut_inverse64<LDF>(Af, Ti, Xs, wave, lane);
-    // ---- T in the I/O type, three times: as it is (straight to memory), with the columns scaled
-    //      by beta (for U) and by beta gamma (for W); the upper triangle is exactly zero ----
+    ut_inverse64<LDF, LDF>(Af, Ti, Af + 16, 16, wave, lane);
+    // ---- T in the I/O type, up to three times: as it is (for a backward pass), with the columns scaled
+    //      by beta (for E) and by beta gamma (for W); the upper triangle is exactly zero ----
     {
-        constexpr int VN = 16 / sizeof(T);
-        T *tg = a.Tm ? static_cast<T *>(a.Tm) + bhn * C * C : nullptr;      // (kept for the backward pass only)
+        T *tg = a.Tm ? static_cast<T *>(a.Tm) + bhn * C * C : nullptr;
+        T *ug = static_cast<T *>(a.Tu) + bhn * C * C;
         for (int v = tid; v < C * C / VN; v += CP_) {
             const int i = v / (C / VN), j0 = (v % (C / VN)) * VN;
             float plain[VN], tu[VN], tw[VN];
@@ -211,82 +159,70 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
                 tw[e] = t * BGs[j];
             }
             if (tg) store_vec_t(tg + i * C + j0, plain);
-            store_vec_t(Tu + i * LDC + j0, tu);
+            store_vec_t(ug + i * C + j0, tu);
             store_vec_t(Tw + i * LDC + j0, tw);
         }
     }
-    __syncthreads();                // Ti is dead from here on: its space is the staging tile again
-
-    // ---- -W^T, W = (T diag(beta gamma)) K (the chain kernels fetch it with transpose reads) ----
-    {
-        for (int t = wave; t < (K / 16) * 4; t += NW) {
-            const int nb = t >> 2, ib = t & 3;
-            {
-                const int kdim = min(C, ((ib + 1) * 16 + Mfma<T>::KSTEP - 1) / Mfma<T>::KSTEP * Mfma<T>::KSTEP);
-                f32x4 acc = mma_tile0<T, true, false>(Tw + ib * 16 * LDC, LDC, X1 + nb * 16, LDK, kdim, lane);
+    __syncthreads();                // (I + A)^-1 is dead from here on: its space is the staging tile
+    // ---- -W = -(T diag(beta gamma)) K ----
+    for (int t = wave; t < (K / 16) * 4; t += NW) {
+        const int nb = t >> 2, ib = t & 3;
+        const int kdim = min(C, ((ib + 1) * 16 + Mfma<T>::KSTEP - 1) / Mfma<T>::KSTEP * Mfma<T>::KSTEP);
+        f32x4 acc = mma_tile0<T, false, true>(X1 + nb * 16, LDK, Tw + ib * 16 * LDC, LDC, kdim, lane);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r] = -acc[r];
-                store_tile_t(stage + nb * 16 * LDC + ib * 16, LDC, acc, lane);
-            }
-        }
+        for (int r = 0; r < 4; ++r) acc[r] = -acc[r];
+        store_tile_t(X2 + ib * 16 * LDK + nb * 16, LDK, acc, lane);       // rows = tokens
     }
     __syncthreads();
-    store_tile_global(static_cast<T *>(a.Wt) + bhn * K * C, (size_t)C, stage, LDC, K, C, tid, CP_);
-
-    // ---- U^T = ((T diag(beta)) V)^T, 64 columns of V at a time ----
-    for (int v0 = 0; v0 < a.V; v0 += C) {
-        __syncthreads();
-        r_V.put(X1, LDC, tid);
-        if (v0 + C < a.V) r_V.fetch(vg + v0 + C, tstride * a.V, tid);
-        else if (task + 1 < ntask)          // the next chunk's first slab
-            r_V.fetch(static_cast<const T *>(a.v) + (tok0 + (size_t)C * a.H) * a.V, tstride * a.V, tid);
-        __syncthreads();
-#pragma unroll
-        for (int iq = 0; iq < 2; ++iq) {
-            const int ib = (wave >> 2) * 2 + iq, wb = wave & 3;        // 16 columns of V (wb), two row blocks
-            const int kdim = min(C, ((ib + 1) * 16 + Mfma<T>::KSTEP - 1) / Mfma<T>::KSTEP * Mfma<T>::KSTEP);
-            const f32x4 acc = mma_tile0<T, true, false>(Tu + ib * 16 * LDC, LDC, X1 + wb * 16, LDC, kdim, lane);
-            store_tile_t(stage + wb * 16 * LDC + ib * 16, LDC, acc, lane);
-        }
-        __syncthreads();
-        store_tile_global(static_cast<T *>(a.Ut) + (bhn * a.V + v0) * C, (size_t)C, stage, LDC, C, C, tid, CP_);
-    }
-    }   // task
+    store_tile_global(static_cast<T *>(a.Wn) + bhn * C * K, (size_t)K, X2, LDK, C, K, tid, CP_);
 }
 
 // ------------------------------------------------------------- state_fwd ----
-// Sequential over the chunks of one (batch, head), one workgroup per slice of VS rows of S.
-// Wavefronts 0-3 carry the dependent chain  S_n -> E_n -> S_{n+1}: the state slice lives
-// transposed in their MFMA accumulators (fp32), so that its rounding to the I/O type lands in
-// LDS with vector stores.  Wavefronts 4-7 only move data: they bring the next chunk's W,
-// (rho . K~)^T and U^T tiles (already in operand layout) into the other LDS buffer and write
-// the state checkpoint and E^T back, off the chain.  Two barriers per chunk.
-constexpr int CT_ = 512;        // threads of a chain workgroup
-constexpr int CL_ = 256;        // ... of which loaders
+// Sequential over the chunks of one (batch, head), one workgroup per slice of VS rows of S.  Eight
+// wavefronts carry the chain  S_n -> E_n -> S_{n+1}  (two barriers per chunk):
+//   A  S, rounded to the I/O type, into LDS                                   | barrier 1
+//   B  E = (T diag(beta)) V - W S^T, one 16x16 tile per wavefront; E and rho E (the operand of the
+//      write) into LDS                                                        | barrier 2
+//   C  S <- gamma_C S + (rho E)^T K~ in the MFMA accumulators (fp32)
+// Everything a phase needs besides S or E is in registers when its barrier opens: the fragments of
+// -W and the product with V are prepared in phase C of the chunk before, those of K~ in phase B.
+// Four more wavefronts move data.  Two load, directly from global memory into two LDS rings
+// (osdn_tile.h): what phase B multiplies (-W, T diag(beta), the slice of V, the gates) and what phase C
+// does (K~; per-channel gates: the chunk's decays).  Two store the checkpoint of S and E^T.  They are
+// wavefronts of their own because a memory instruction stalls its wavefront until the CU's address
+// unit takes it (64 bytes per clock: 700 cycles for a chunk's tiles), which adds to the chain when the
+// same wavefronts do both, and because a wavefront's accesses retire in order: a load issued behind a
+// store is only known to be there when the store is acknowledged, about 1 us later.
+// Bound by what a CU has in flight from HBM (46 KB in and 12 KB out per chunk with slices of 32): 64
+// chains of 64 chunks, V = 128: 115 us, 3.8 TB/s; without the stores 73 us, without any traffic 52 us.
+constexpr int CW_ = 8;          // wavefronts of a chain workgroup that compute
+constexpr int CM_ = 2;          // ... that load
+constexpr int CS_ = 2;          // ... that store
+constexpr int CT_ = (CW_ + CM_ + CS_) * 64;
+// Ring depths (chunks of operands in LDS).
+template <typename T, int K> constexpr int SF_NSB = sizeof(T) == 2 ? 3 : 2;
+template <typename T, int K> constexpr int SF_NSC = sizeof(T) == 2 ? 2 : (K == 64 ? 2 : 1);
 
-// GV: one state gate per key channel; the chunk's decay per channel comes from chunk_prep.
+// GV: one state gate per key channel: the operands carry the decays inside the chunk, and the state
+// takes the chunk's decay per channel after the write.
 // VS: rows of S (values) owned by one workgroup, 32 or 16.  With few chains the narrow slice
 // gives twice the workgroups, each with half the work on the dependent path per chunk.
 template <typename T, int K, bool GV, int VS>
 __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
-    constexpr int NVT = VS / 16;                // value tiles per compute wave
-    constexpr int PAD = Pad<T>::v, LDK = K + PAD, LDC = C + PAD;
-    constexpr int VN = 16 / sizeof(T);
-    constexpr int NKT = K / 64;                 // state row tiles (features) per compute wave
-    constexpr int NB = sizeof(T) == 2 ? 2 : 1;  // LDS operand buffers (fp32 tiles are too big for two)
-    // With two buffers the loaders work as two groups of two wavefronts, one per chunk parity:
-    // a group fetches chunk c + 2 right after it has put chunk c into LDS, so every global
-    // load has two chunk times to arrive.
-    constexpr int LTN = NB == 2 ? CL_ / 2 : CL_;    // threads that share one chunk's tiles
-    constexpr int NWV = C * K / VN / LTN;       // 16-byte vectors per loader thread, [64 x K] tile
-    constexpr int NUV = VS * C / VN / LTN;
-    static_assert(VS * C / VN % LTN == 0 && C * K / VN % LTN == 0, "tiles must split evenly over the loaders");
-    __shared__ __attribute__((aligned(16))) T Wts[NB][K * LDC];      // -W^T  [kf][i], as chunk_prep left it
-    __shared__ __attribute__((aligned(16))) T Ktr[NB][K * LDC];
-    __shared__ __attribute__((aligned(16))) T Uts[NB][VS * LDC];
-    __shared__ __attribute__((aligned(16))) T Sb[VS * LDK];     // S in the I/O type
-    __shared__ __attribute__((aligned(16))) T Et[VS * LDC];     // E^T
-    __shared__ float gCs[NB];
+    constexpr int ES = sizeof(T), RK = K * ES, RC = C * ES, RV = VS * ES;      // bytes per row of a tile
+    constexpr int NVT = VS / 16, NFB = K / 16;
+    constexpr int NTC = NFB * NVT, TPW = NTC > CW_ ? NTC / CW_ : 1;            // state tiles, ... per wavefront
+    constexpr int KS = Mfma<T>::KSTEP, NKK = K / KS, NKC = C / KS;
+    typedef typename Mfma<T>::Frag Frag;
+    constexpr bool PRE = sizeof(T) == 2;        // operands in registers ahead of their phase (fp32: they would not fit)
+    constexpr int NSB = SF_NSB<T, K>, NSC = SF_NSC<T, K>;
+    constexpr int B_W = 0, B_T = B_W + C * RK, B_V = B_T + C * RC, B_G = B_V + C * RV, B_BYTES = B_G + 2 * C * 4;
+    constexpr int C_K = 0, C_D = C_K + C * RK, C_BYTES = C_D + (GV ? K * 4 : 0);
+    __shared__ __attribute__((aligned(1024))) char ringB[NSB * B_BYTES];
+    __shared__ __attribute__((aligned(1024))) char ringC[NSC * C_BYTES];
+    __shared__ __attribute__((aligned(1024))) char Sb[VS * RK];         // S in the I/O type [v][kf]
+    __shared__ __attribute__((aligned(1024))) char Eo[VS * RC];         // E^T  [v][i]
+    __shared__ __attribute__((aligned(1024))) char Ew[GV ? 16 : VS * RC];   // (rho E)^T
 
     int chain, slice;
     chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
@@ -298,163 +234,184 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
         a.S_in = begins ? a.S_first : a.S_out;
         bt = 0;
     }
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const bool loader = wave >= 4;
-    const int lt = tid - CL_;                   // loader thread index
-    const int lgrp = NB == 2 ? (lt >> 7) & 1 : 0;   // loader group (chunk parity it serves)
-    const int lti = NB == 2 ? lt & 127 : lt;    // index inside the group
-    const bool gwave = NB == 2 ? (wave & 1) == 0 : wave == 4;   // the group's wave that handles the gate
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const bool loader = wave >= CW_ && wave < CW_ + CM_, storer = wave >= CW_ + CM_;
+    const int mw = wave - CW_, mt = tid - (CW_ + CM_) * 64;     // loader wavefront, storer thread
     const size_t bh = (size_t)b * a.H + h;      // the chain: indexes S_in / S_out
-    const size_t bth = (size_t)bt * a.H + h;    // indexes the per-chunk buffers
-    const size_t tstride = a.H;
+    const uint32_t gV = (uint32_t)a.H * (uint32_t)a.V * ES;        // bytes between tokens of v
+    const bool wideV = (reinterpret_cast<uintptr_t>(a.v) & 15) == 0;
 
-    // ---- compute waves: state slice, transposed: St[vt][q] rows = features, cols = values ----
-    f32x4 St[NVT][NKT];
-    if (!loader) {
+    LdsLoad<RK, C, CM_> lK;
+    LdsLoad<RC, C, CM_> lT;
+    LdsLoad<RV, C, CM_> lV;
+    lK.init(RK, mw, lane); lT.init(RC, mw, lane); lV.init(gV, mw, lane);
+    auto loadB = [&](int n, int slot) {
+        const size_t bhn = ((size_t)bt * a.N + n) * a.H + h;
+        char *s = ringB + slot * B_BYTES;
+        lK.issue(s + B_W, static_cast<const char *>(a.Wn) + bhn * C * RK, RK, mw, lane, slice);
+        lT.issue(s + B_T, static_cast<const char *>(a.Tu) + bhn * C * RC, RC, mw, lane, slice);
+        lV.issue(s + B_V, static_cast<const char *>(a.v) + (((size_t)bt * a.T + (size_t)n * C) * a.H + h) * a.V * ES + (size_t)vs * ES,
+                 gV, mw, lane, 0, wideV);
+        if (!GV && mw < 2) {                    // gamma (loader 0) and rho (1)
+            const int w = mw;
+            load_lds4(a.gates + (bhn * 3 + 1 + w) * C, lane * 4, lds_offset(s + B_G + w * C * 4));
+        }
+    };
+    auto loadC = [&](int n, int slot) {
+        char *s = ringC + slot * C_BYTES;
+        lK.issue(s + C_K, static_cast<const char *>(a.kt) + (((size_t)bt * a.N + n) * a.H + h) * C * RK, RK, mw, lane, slice);
+        if (GV && mw < K / 64) load_lds4(a.gamC + (((size_t)bt * a.N + n) * a.H + h) * K, mw * 256 + lane * 4, lds_offset(s + C_D + mw * 256));
+    };
+    // loads of a loader that are newer than the tiles it waits for (at least)
+    constexpr int LB = LdsLoad<RK, C, CM_>::MIN + LdsLoad<RC, C, CM_>::MIN + LdsLoad<RV, C, CM_>::MIN, LC = LdsLoad<RK, C, CM_>::MIN;
+    constexpr int NMAX = NSB > NSC ? NSB : NSC;
+    constexpr int NEWER_B = (NSB - 1) * (LB + LC), NEWER_C = (NSC - 1) * (LB + LC);
+    static_assert(NEWER_B < 64 && NEWER_C < 64, "the counter has six bits");
 #pragma unroll
-        for (int vt = 0; vt < NVT; ++vt)
+    for (int j = 0; j < NMAX; ++j) {
+        if (loader && j < NSB && a.n0 + j < a.n1) loadB(a.n0 + j, j);
+        if (loader && j < (PRE ? NSC : NSC - 1) && a.n0 + j < a.n1) loadC(a.n0 + j, j);
+    }
+
+    // ---- state slice, transposed: St[q] rows = features, cols = values ----
+    // this wavefront's tiles of S (feature block fb, value blocks vtC ..) and of E (row block rb, value block vtB)
+    const bool inC = wave * TPW < NTC, inB = wave < 4 * NVT;
+    const int fb = wave % NFB, vtC = wave / NFB;
+    const int rb = wave & 3, vtB = wave >> 2;
+    f32x4 St[TPW] = {};
+    if (inC) {
 #pragma unroll
-            for (int q = 0; q < NKT; ++q) {
-                const int v = vs + vt * 16 + acc_col(lane), c0 = (wave * NKT + q) * 16 + acc_row(lane, 0);
-                if (a.S_in) St[vt][q] = *reinterpret_cast<const f32x4 *>(a.S_in + (bh * a.V + v) * K + c0);
-                else St[vt][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-    }
-    // ---- loader waves: registers for one chunk ----
-    u32x4 wreg[NWV], kreg[NWV], ureg[NUV];
-    float greg = 0.f;
-#define OSDN_SF_LOAD(n_)                                                                         \
-    {                                                                                            \
-        const size_t bhn_ = bth * a.N + (n_);                                                    \
-        const T *wg = static_cast<const T *>(a.Wt) + bhn_ * K * C;                               \
-        const T *kg = static_cast<const T *>(a.Ktr) + bhn_ * K * C;                              \
-        const T *ug = static_cast<const T *>(a.Ut) + (bhn_ * a.V + vs) * C;                      \
-        _Pragma("unroll") for (int m = 0; m < NWV; ++m) {                                        \
-            const int i = lti + m * LTN;                                                          \
-            wreg[m] = *reinterpret_cast<const u32x4 *>(wg + (size_t)i * VN);                     \
-            kreg[m] = *reinterpret_cast<const u32x4 *>(kg + (size_t)i * VN);                     \
-        }                                                                                        \
-        _Pragma("unroll") for (int m = 0; m < NUV; ++m) {                                        \
-            const int i = lti + m * LTN;                                                          \
-            ureg[m] = *reinterpret_cast<const u32x4 *>(ug + (size_t)i * VN);                     \
-        }                                                                                        \
-        if (gwave)                                                                               \
-            greg = a.log_alpha ? a.log_alpha[((size_t)bt * a.T + (size_t)(n_) * C + lane) * a.H + h] : 0.f; \
-    }
-#define OSDN_SF_STORE(buf_)                                                                      \
-    {                                                                                            \
-        _Pragma("unroll") for (int m = 0; m < NWV; ++m) {                                        \
-            const int i = lti + m * LTN;                                                          \
-            { const int r = i / (C / VN), c = (i % (C / VN)) * VN;                               \
-              *reinterpret_cast<u32x4 *>(&Wts[buf_][r * LDC + c]) = wreg[m];                     \
-              *reinterpret_cast<u32x4 *>(&Ktr[buf_][r * LDC + c]) = kreg[m]; }                   \
-        }                                                                                        \
-        _Pragma("unroll") for (int m = 0; m < NUV; ++m) {                                        \
-            const int i = lti + m * LTN, r = i / (C / VN), c = (i % (C / VN)) * VN;               \
-            *reinterpret_cast<u32x4 *>(&Uts[buf_][r * LDC + c]) = ureg[m];                       \
-        }                                                                                        \
-        if (gwave) {                                                                             \
-            const float G_ = wave_cumsum(greg, lane);                                            \
-            if (lane == 63) gCs[buf_] = __expf(G_);                                              \
-        }                                                                                        \
-    }
-    if (loader) {
-        if (NB == 2) {
-            if (lgrp == (a.n0 & 1)) {
-                OSDN_SF_LOAD(a.n0)
-                OSDN_SF_STORE(a.n0 & 1)
-                OSDN_SF_LOAD(min(a.n0 + 2, a.n1 - 1))
-            } else {
-                OSDN_SF_LOAD(min(a.n0 + 1, a.n1 - 1))
-            }
-        } else {
-            OSDN_SF_LOAD(a.n0)
-            OSDN_SF_STORE(0)
-            OSDN_SF_LOAD(min(a.n0 + 1, a.n1 - 1))
+        for (int q = 0; q < TPW; ++q) {
+            const int v = vs + (vtC + q) * 16 + acc_col(lane), c0 = fb * 16 + acc_row(lane, 0);
+            if (a.S_in) St[q] = *reinterpret_cast<const f32x4 *>(a.S_in + (bh * a.V + v) * K + c0);
         }
     }
-
-    for (int n = a.n0; n < a.n1; ++n) {
-        const int buf = NB == 2 ? (n & 1) : 0;
-        const size_t bhn = bth * a.N + n;
-        // ---- phase A (compute): S, rounded, into LDS ----
-        f32x4 gch[GV ? NKT : 1];                                    // channel decays of this lane's state rows
-        if (!loader) {
+    if (loader) wait_vm<0>();
+    __syncthreads();
+    int sb = 0, sc = 0;                         // ring slots of chunk n
+    if (loader) {
+        for (int n = a.n0; n < a.n1; ++n) {
+            const bool full = n + NMAX < a.n1;  // everything counted as newer has been asked for
+            // a slot is refilled as soon as its operands have been read: ahead of their phase (PRE), or in it
+            if (full) wait_vm<PRE ? NEWER_C : NEWER_B>(); else wait_vm<0>();   // K~ (PRE), phase B's operands of this chunk
+            __syncthreads();                                        // barrier 1
+            if (PRE && n + NSB < a.n1) loadB(n + NSB, sb);
+            if (!PRE && n - 1 + NSC < a.n1) loadC(n - 1 + NSC, sc == 0 ? NSC - 1 : sc - 1);
+            if (full) wait_vm<PRE ? NEWER_B : NEWER_C>(); else wait_vm<0>();   // phase B's operands of the next (PRE), K~
+            __syncthreads();                                        // barrier 2
+            if (PRE && n + NSC < a.n1) loadC(n + NSC, sc);
+            if (!PRE && n + NSB < a.n1) loadB(n + NSB, sb);
+            sb = sb + 1 == NSB ? 0 : sb + 1;
+            sc = sc + 1 == NSC ? 0 : sc + 1;
+        }
+        return;
+    }
+    if (storer) {
+        for (int n = a.n0; n < a.n1; ++n) {
+            const size_t bhn = ((size_t)bt * a.N + n) * a.H + h;
+            __syncthreads();                                        // barrier 1
+            tile_to_global<RK, VS>(static_cast<char *>(a.S_ckpt) + (bhn * a.V + vs) * RK, RK, Sb, mt, CS_ * 64);
+            __syncthreads();                                        // barrier 2
+            tile_to_global<RC, VS>(static_cast<char *>(a.Et) + (bhn * a.V + vs) * RC, RC, Eo, mt, CS_ * 64);
+        }
+        return;
+    }
+    TileFrag<T, RK> fK;
+    TileFrag<T, RC> fT;
+    TileFrag<T, RV> fV;
+    fK.init(lane); fT.init(lane); fV.init(lane);
+    // operands of phase B of one chunk: fragments of -W, the product with V, rho of this lane's rows, gamma_C
+    Frag wf[NKK];
+    f32x4 uacc = {}, rho = {1.f, 1.f, 1.f, 1.f};
+    float gC = 1.f;
+    auto fetchB = [&](const char *tB) {
+        if (inB) {
+            if (PRE) {
 #pragma unroll
-            for (int vt = 0; vt < NVT; ++vt)
-#pragma unroll
-                for (int q = 0; q < NKT; ++q)
-                    store_tile_t(Sb + vt * 16 * LDK + (wave * NKT + q) * 16, LDK, St[vt][q], lane);
-            if (GV) {
-#pragma unroll
-                for (int q = 0; q < NKT; ++q)
-                    gch[GV ? q : 0] = *reinterpret_cast<const f32x4 *>(
-                        a.gamC + bhn * K + (wave * NKT + q) * 16 + acc_row(lane, 0));
+                for (int kk = 0; kk < NKK; ++kk) wf[kk] = fK.kc(tB + B_W, rb * 16, kk * KS);
             }
+            uacc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKC; ++kk)
+                if (kk * KS < (rb + 1) * 16)                    // T is lower triangular
+                    uacc = Mfma<T>::mma(fT.kc(tB + B_T, rb * 16, kk * KS), fV.tr(tB + B_V, kk * KS, vtB * 16), uacc);
+            if (!GV) rho = *reinterpret_cast<const f32x4 *>(tB + B_G + (rb * 16 + acc_row(lane, 0)) * 4 + C * 4);
+        }
+        if (!GV) gC = *reinterpret_cast<const float *>(tB + B_G + (C - 1) * 4);
+    };
+    if (PRE) fetchB(ringB);
+    for (int n = a.n0; n < a.n1; ++n) {
+        const char *tB = ringB + sb * B_BYTES, *tC = ringC + sc * C_BYTES;
+        // ---- phase A ----
+        if (inC) {
+#pragma unroll
+            for (int q = 0; q < TPW; ++q) fK.put(Sb, (vtC + q) * 16, fb * 16, St[q]);
         }
         __syncthreads();                                            // barrier 1
-        if (loader) {
-            if (NB == 2) {
-                if (lgrp == ((n + 1) & 1)) {                        // this group's chunk comes next
-                    if (n + 1 < a.n1) {
-                        OSDN_SF_STORE((n + 1) & 1)                  // free since barrier 1
-                        OSDN_SF_LOAD(min(n + 3, a.n1 - 1))          // (past the end: a harmless reload)
-                    }
-                } else if (a.S_ckpt) {
-                    // checkpoint of the chunk-start state (read between barrier 1 and barrier 2)
-                    store_tile_global(static_cast<T *>(a.S_ckpt) + (bhn * a.V + vs) * K, (size_t)K, Sb, LDK, VS, K, lti, LTN);
-                }
-            } else if (a.S_ckpt) {
-                store_tile_global(static_cast<T *>(a.S_ckpt) + (bhn * a.V + vs) * K, (size_t)K, Sb, LDK, VS, K, lt, CL_);
-            }
-        } else {
-            // ---- phase B: E = U - W S^T (rows 16*wave ..), kept transposed ----
+        // ---- phase B ----
+        Frag sf[NKK], kf[NKC];
+        f32x4 dc = {};
+        if (!PRE) fetchB(tB);
+        if (inB) {
 #pragma unroll
-            for (int vt = 0; vt < NVT; ++vt) {
-                f32x4 acc = mma_tile0<T, false, true>(&Wts[buf][wave * 16], LDC, Sb + vt * 16 * LDK, LDK, K, lane);
-                const T *up = &Uts[buf][(vt * 16 + acc_col(lane)) * LDC + wave * 16 + acc_row(lane, 0)];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) acc[r] += to_f32(up[r]);         // U + (-W) S^T
-                store_tile_t(Et + vt * 16 * LDC + wave * 16, LDC, acc, lane);
-            }
+            for (int kk = 0; kk < NKK; ++kk) sf[kk] = fK.kc(Sb, vtB * 16, kk * KS);
         }
+        if (PRE && inC) {
+#pragma unroll
+            for (int kk = 0; kk < NKC; ++kk) kf[kk] = fK.tr(tC + C_K, kk * KS, fb * 16);
+            if (GV) dc = *reinterpret_cast<const f32x4 *>(tC + C_D + (fb * 16 + acc_row(lane, 0)) * 4);
+        }
+        if (inB) {
+            f32x4 acc = uacc, acc2 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < NKK; kk += 2) {
+                acc = Mfma<T>::mma(PRE ? wf[kk] : fK.kc(tB + B_W, rb * 16, kk * KS), sf[kk], acc);
+                acc2 = Mfma<T>::mma(PRE ? wf[kk + 1] : fK.kc(tB + B_W, rb * 16, (kk + 1) * KS), sf[kk + 1], acc2);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] += acc2[r];
+            if (!GV) {
+                f32x4 ew;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) ew[r] = acc[r] * rho[r];
+                fT.put(Ew, vtB * 16, rb * 16, ew);
+            }
+            fT.put(Eo, vtB * 16, rb * 16, acc);
+        }
+        const float g = gC;
         __syncthreads();                                            // barrier 2
-        if (loader) {
-            if (NB == 2) {
-                if (lgrp == ((n + 1) & 1))                          // the group with no load wait ahead
-                    store_tile_global(static_cast<T *>(a.Et) + (bhn * a.V + vs) * C, (size_t)C, Et, LDC, VS, C, lti, LTN);
-            } else {
-                store_tile_global(static_cast<T *>(a.Et) + (bhn * a.V + vs) * C, (size_t)C, Et, LDC, VS, C, lt, CL_);
-            }
-        } else {
-            // ---- phase C: S <- gamma_C S + E^T (rho . K~), transposed ----
-            const float gC = gCs[buf];
+        // ---- phase C ----
+        if (inC) {
+            Frag fe[TPW][NKC];
+            if (!PRE && GV) dc = *reinterpret_cast<const f32x4 *>(tC + C_D + (fb * 16 + acc_row(lane, 0)) * 4);
 #pragma unroll
-            for (int vt = 0; vt < NVT; ++vt)
+            for (int q = 0; q < TPW; ++q)
 #pragma unroll
-                for (int q = 0; q < NKT; ++q) {
+                for (int kk = 0; kk < NKC; ++kk) fe[q][kk] = fT.kc(GV ? Eo : Ew, (vtC + q) * 16, kk * KS);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) St[vt][q][r] *= GV ? gch[GV ? q : 0][r] : gC;
-                    mma_tile<T, true, true>(St[vt][q], &Ktr[buf][(wave * NKT + q) * 16 * LDC], LDC,
-                                            Et + vt * 16 * LDC, LDC, C, lane);
+            for (int q = 0; q < TPW; ++q) {
+                if (!GV) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) St[q][r] *= g;
                 }
-        }
-        if (NB == 1) {                                              // single buffer: refill it now
-            __syncthreads();
-            if (loader && n + 1 < a.n1) {
-                OSDN_SF_STORE(0)
-                OSDN_SF_LOAD(min(n + 2, a.n1 - 1))
+#pragma unroll
+                for (int kk = 0; kk < NKC; ++kk) St[q] = Mfma<T>::mma(PRE ? kf[kk] : fK.tr(tC + C_K, kk * KS, fb * 16), fe[q][kk], St[q]);
+                if (GV) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) St[q][r] *= dc[r];
+                }
             }
         }
+        sb = sb + 1 == NSB ? 0 : sb + 1;
+        sc = sc + 1 == NSC ? 0 : sc + 1;
+        if (PRE && n + 1 < a.n1) fetchB(ringB + sb * B_BYTES);
     }
-    if (!loader) {
+    if (inC) {
 #pragma unroll
-        for (int vt = 0; vt < NVT; ++vt)
-#pragma unroll
-            for (int q = 0; q < NKT; ++q) {
-                const int v = vs + vt * 16 + acc_col(lane), c0 = (wave * NKT + q) * 16 + acc_row(lane, 0);
-                *reinterpret_cast<f32x4 *>(a.S_out + (bh * a.V + v) * K + c0) = St[vt][q];
-            }
+        for (int q = 0; q < TPW; ++q) {
+            const int v = vs + (vtC + q) * 16 + acc_col(lane), c0 = fb * 16 + acc_row(lane, 0);
+            *reinterpret_cast<f32x4 *>(a.S_out + (bh * a.V + v) * K + c0) = St[q];
+        }
     }
 }
 
@@ -471,18 +428,17 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
     __shared__ __attribute__((aligned(16))) T Ets[C * LDC];     // 64 rows of E^T
     __shared__ float Gs[C];
 
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const size_t bhn = ((size_t)b * a.H + h) * a.N + n;
+    const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
     const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const size_t tstride = a.H;
 
     if (wave == 0) {
-        const float g = a.log_alpha ? a.log_alpha[tok0 + (size_t)lane * tstride] : 0.f;
-        Gs[lane] = wave_cumsum(g, lane);
+        Gs[lane] = a.log_alpha ? a.gates[bhn * 3 * C + lane] : 0.f;
     }
-    load_tile(Qs, LDK, static_cast<const T *>(a.q) + tok0 * K, tstride * K, C, K, tid, OT_);
-    load_tile(Kts, LDK, static_cast<const T *>(a.kt) + tok0 * K, tstride * K, C, K, tid, OT_);
+    load_tile(Qs, LDK, static_cast<const T *>(a.q) + (a.gate_vec ? bhn * C : tok0) * K, a.gate_vec ? (size_t)K : tstride * K, C, K, tid, OT_);
+    load_tile(Kts, LDK, static_cast<const T *>(a.kt) + bhn * C * K, (size_t)K, C, K, tid, OT_);
     // the slabs of S and E^T travel through registers, one slab ahead of the products
     TileRegs<T, C, K, OT_> r_S;
     TileRegs<T, C, C, OT_> r_E;
@@ -536,9 +492,7 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
 // -------------------------------------------------------------- launchers ----
 template <typename T, bool GV>
 static int launch_prep_t(const ChunkArgs &a, hipStream_t st) {
-    const int chunks = a.n1 - a.n0;
-    const bool pairs = chunks >= 2 && (long long)chunks * a.H * a.B >= CP_MIN_WGS;
-    dim3 grid(pairs ? (chunks + CP_TASKS - 1) / CP_TASKS : chunks, a.H, a.B), block(CP_);
+    dim3 grid((a.n1 - a.n0) * a.H, a.B), block(CP_);
     if (GV && (!a.log_alpha || !a.Qg || !a.Kg || !a.Kd || !a.gamC)) return -1;
     if (a.K == 64) hipLaunchKernelGGL((chunk_prep_kernel<T, 64, GV>), grid, block, 0, st, a);
     else if (a.K == 128) hipLaunchKernelGGL((chunk_prep_kernel<T, 128, GV>), grid, block, 0, st, a);
@@ -558,10 +512,12 @@ static int launch_state_t(const ChunkArgs &a, hipStream_t st) {
     else return -1;
     return 0;
 }
-// Slices of 16 values when the caller asks for them (few chains: see ChunkArgs::narrow_slices).
+// Slices of 16 values when the caller asks for them (few chains: see ChunkArgs::narrow_slices), and
+// always with fp32 I/O (whose tiles of 32 values would leave no room for a second buffer).
 template <typename T, bool GV>
 static int launch_state_v(const ChunkArgs &a, hipStream_t st) {
-    return a.narrow_slices ? launch_state_t<T, GV, 16>(a, st) : launch_state_t<T, GV, 32>(a, st);
+    if constexpr (sizeof(T) == 2) if (!a.narrow_slices) return launch_state_t<T, GV, 32>(a, st);
+    return launch_state_t<T, GV, 16>(a, st);
 }
 int launch_state_fwd(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
     if (a.gate_vec) return bf16_io ? launch_state_v<bf16, true>(a, st) : launch_state_v<float, true>(a, st);
@@ -569,7 +525,7 @@ int launch_state_fwd(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
 }
 template <typename T>
 static int launch_output_t(const ChunkArgs &a, hipStream_t st) {
-    dim3 grid(a.n1 - a.n0, a.H, a.B), block(OT_);
+    dim3 grid((a.n1 - a.n0) * a.H, a.B), block(OT_);
     if (a.K == 64) hipLaunchKernelGGL((output_fwd_kernel<T, 64>), grid, block, 0, st, a);
     else if (a.K == 128) hipLaunchKernelGGL((output_fwd_kernel<T, 128>), grid, block, 0, st, a);
     else return -1;

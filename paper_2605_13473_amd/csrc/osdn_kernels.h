@@ -29,7 +29,8 @@ struct PrecondArgs {
     const float *retention;   // [B,T,H] ([B,T,H,K] with ret_vec) or null
     int ret_vec;              // one retention per coordinate
     const float *d_in;        // [B,H,K] or null
-    void *k_tilde;            // [B,T,H,K] io
+    void *k_tilde;            // [B,T,H,K] io, or ...
+    int kt_tiles;             // ... [B,T/64,H,64,K]: one contiguous tile per chunk and head
     float *d_out;             // [B,H,K]
     float *d_ckpt;            // [B,H,T/64,K] or null
     float *tok_scalars;       // [B,T,H,4] or null: per token (step, <d,k^2>, sum k^2, unused), kept for the backward
@@ -58,8 +59,8 @@ struct PrecondBwdArgs {
                               // kernel puts sigma_t into the fourth slot for the post kernel
     uint2 *masks;             // [B,H,T/64,K]: bit i = token i of the chunk stayed inside the box
     float *a_ckpt;            // [B,H,T/64,K]: adjoint of d at the right end of every chunk
-    const void *dkt;          // [B,T,H,K] io: dL/dk~ from phase 2
-    const void *dk_read;      // [B,T,H,K] io: read-side dL/dk from phase 2
+    const void *dkt;          // [B,N,H,64,K] io: dL/dk~ from phase 2
+    const void *dk_read;      // [B,N,H,64,K] io: read-side dL/dk from phase 2
     const float *dd_out;      // [B,H,K] or null
     void *dk;                 // [B,T,H,K] io
     float *dbeta;             // [B,T,H] in/out
@@ -88,8 +89,10 @@ struct StepArgs {
     float *S_out, *d_out;             // S_out may be S_in (a workgroup reads its rows before it writes them)
 };
 
-// Everything the chunkwise (phase 2) kernels need.  Per-chunk tiles live in the workspace
-// in [B,H,N,rows,cols] order (one contiguous tile per chunk and head).
+// Everything the chunkwise (phase 2) kernels need.  Per-chunk tiles live in the workspace in
+// [B,N,H,rows,cols] order, one contiguous tile per chunk and head: what the workgroups of a launch
+// (numbered head first) or the chains of a chain kernel (in step) touch at one time is then
+// contiguous in memory and spreads over all its channels.
 struct ChunkArgs {
     int B, T, H, K, V, N;
     int n0, n1;
@@ -105,32 +108,32 @@ struct ChunkArgs {
     void *o;                          // [B,T,H,V] io
     float *S_out;                     // [B,H,V,K]
     // workspace (forward)
-    void *kt;                         // [B,T,H,K] io      k~
-    void *Tm;                         // [B,H,N,64,64] io  (I + A)^-1
-    void *Wt;                         // [B,H,N,K,64] io   -W^T
-    void *Ktr;                        // [B,H,N,K,64] io   (rho . K~)^T
-    void *Ut;                         // [B,H,N,V,64] io   U^T
-    void *Et;                         // [B,H,N,V,64] io   E transposed
-    void *S_ckpt;                     // [B,H,N,V,K] io    state at the start of each chunk (null: not kept)
-    void *Pm;                         // [B,H,N,64,64] io  P = tril(Gamma . Q K~^T), from output_fwd for the backward
+    void *kt;                         // [B,N,H,64,K] io   k~
+    void *Tm;                         // [B,N,H,64,64] io  (I + A)^-1
+    void *Wn;                         // [B,N,H,64,K] io   -W
+    void *Tu;                         // [B,N,H,64,64] io  (I + A)^-1 diag(beta)
+    float *gates;                     // [B,N,H,3,64] f32  cumulative log-decay G inside the chunk, gamma = e^G, rho = e^(G_C - G)
+    void *Et;                         // [B,N,H,V,64] io   E transposed
+    void *S_ckpt;                     // [B,N,H,V,K] io    state at the start of each chunk (null: not kept)
+    void *Pm;                         // [B,N,H,64,64] io  P = tril(Gamma . Q K~^T), from output_fwd for the backward
                                       //                   chain (null: not kept; Tm may be null likewise)
     int narrow_slices;                // chain kernels: 16 rows of the state per workgroup instead of 32
     // one state gate per key channel (gate_vec: log_alpha is [B,T,H,K]; forward only): chunk_prep
     // folds the cumulative channel decays Gamma into the operands and leaves
     int gate_vec;
-    void *Qg;                         // [B,T,H,K] io      Gamma . Q
-    void *Kg;                         // [B,T,H,K] io      Gamma . K
-    void *Kd;                         // [B,T,H,K] io      K~ / Gamma
-    float *gamC;                      // [B,H,N,K] f32     decay of every channel over the whole chunk
-    float *dgamC;                     // [B,H,N,K] f32     backward: dL/d(that decay)
+    void *Qg;                         // [B,N,H,64,K] io   Gamma . Q   (taking the place of q, k, kt in the kernels that follow)
+    void *Kg;                         // [B,N,H,64,K] io   Gamma . K
+    void *Kd;                         // [B,N,H,64,K] io   K~ / Gamma
+    float *gamC;                      // [B,N,H,K] f32     decay of every channel over the whole chunk
+    float *dgamC;                     // [B,N,H,K] f32     backward: gamC . dL/dgamC
     // backward
     const void *dO;                   // [B,T,H,V] io
     const float *dS_out;              // [B,H,V,K] or null
-    void *dEt;                        // [B,H,N,V,64] io   dE transposed (complete)
-    void *dS_ckpt;                    // [B,H,N,V,K] io    adjoint of the state at the END of each chunk
+    void *dEt;                        // [B,N,H,V,64] io   dE transposed (complete)
+    void *dS_ckpt;                    // [B,N,H,V,K] io    adjoint of the state at the END of each chunk (gate_vec: times gamC)
     float *dS_in;                     // [B,H,V,K]
     void *dq, *dv;                    // io
-    void *dk_read, *dkt;              // [B,T,H,K] io: the two parts of dL/dk that phase 1 combines
+    void *dk_read, *dkt;              // [B,N,H,64,K] io: the two parts of dL/dk that phase 1 combines
     float *dbeta, *dlog_alpha;        // [B,T,H]; dlog_alpha may be null
 };
 
@@ -162,9 +165,9 @@ struct UnfoldArgs {
     int B, T, H, K, N;
     int n0, n1;
     const float *log_alpha;           // [B,T,H,K]
-    const void *q, *k, *kt;           // [B,T,H,K] io: the unfolded operands
-    void *dq, *dk_read, *dkt;         // [B,T,H,K] io: in: w.r.t. the folded operands; out: w.r.t. q, k, k~
-    const float *gamC, *dgamC;        // [B,H,N,K]
+    const void *q, *k, *kt;           // io: the unfolded operands (q, k: [B,T,H,K]; kt: [B,N,H,64,K])
+    void *dq, *dk_read, *dkt;         // io, dq [B,T,H,K], the others [B,N,H,64,K]: in: w.r.t. the folded operands; out: w.r.t. q, k, k~
+    const float *dgamC;               // [B,N,H,K]
     float *dlog_alpha;                // [B,T,H,K]
 };
 int launch_unfold(const UnfoldArgs &a, bool bf16_io, hipStream_t st);

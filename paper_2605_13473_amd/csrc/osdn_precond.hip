@@ -286,7 +286,9 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
         }
         // ---- accepted: (c_cur, p_cur) generated dtr and dend ----
         {
-            T *ktp = static_cast<T *>(a.k_tilde) + (((size_t)bt * a.T + t0) * a.H + h) * K;
+            // (kt_tiles: one contiguous [64 x K] tile per chunk and head)
+            T *ktp = static_cast<T *>(a.k_tilde) + (a.kt_tiles ? (((size_t)bt * N + n) * a.H + h) * C : ((size_t)bt * a.T + t0) * a.H + h) * K;
+            const uint32_t ktstride = a.kt_tiles ? K : kstride;
 #pragma unroll
             for (int u = 0; u < RUN; ++u) {
                 const int i = run * RUN + u;
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
                     float out[CPT];
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) out[e] = dtr[u][e] * kf[u][e];
-                    *reinterpret_cast<typename Pk::Raw *>(ktp + (uint32_t)i * kstride + c0) = Pk::pack(out);
+                    *reinterpret_cast<typename Pk::Raw *>(ktp + (uint32_t)i * ktstride + c0) = Pk::pack(out);
                 }
             }
         }

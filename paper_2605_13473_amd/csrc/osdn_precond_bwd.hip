@@ -40,7 +40,7 @@ __global__ __launch_bounds__(K) void precond_mask_kernel(PrecondBwdArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     __shared__ __attribute__((aligned(16))) float steps[C];
     __shared__ __attribute__((aligned(16))) float rs[C];
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y, tid = threadIdx.x;
     const int N = a.T / C;
     const size_t bh = (size_t)b * a.H + h;
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(P1T) void precond_lin_m_kernel(PrecondBwdArgs a) {
     __shared__ float steps[C];
     float *Ti = Ss, *Xs = Ss + C * LDF;
 
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int N = a.T / C;
     const size_t bhn = ((size_t)b * a.H + h) * N + n;
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(P1T) void precond_lin_m_kernel(PrecondBwdArgs a) {
         }
     }
     __syncthreads();                                             // the s tile is dead: its space takes the inverse
-    ut_inverse64<LDF>(Af, Ti, Xs, wave, lane);
+    ut_inverse64<LDF, 17>(Af, Ti, Xs, 16 * 17, wave, lane);
     // ---- (I + U)^-1, row i: entries j >= i are column i of the lower inverse ----
     // (kept in the I/O type: its diagonal is 1 and the rest is of the size of the step, so with
     // bf16 I/O the rounding is far inside what that I/O type's other operands carry)
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
     constexpr int NSEG = P1T / K, TS = C / NSEG, WPS = K / 64, NPART = K / TS;
     __shared__ float tot[NSEG * K];
     __shared__ float part[P1W * 64];
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int c = tid % K, sg = tid / K;
     const int N = a.T / C;
@@ -203,14 +203,13 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
     if (!a.lin_clean[bhn]) return;                               // (uniform)
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const uint32_t kstride = (uint32_t)a.H * K;
-    const T *kp = static_cast<const T *>(a.k) + tokc * K, *gp = static_cast<const T *>(a.dkt) + tokc * K;
+    const T *kp = static_cast<const T *>(a.k) + tokc * K, *gp = static_cast<const T *>(a.dkt) + (((size_t)b * N + n) * a.H + h) * C * K;
     float sv[TS], lam[TS];
 #pragma unroll
     for (int u = 0; u < TS; ++u) {
-        const uint32_t o = (uint32_t)(sg * TS + u) * kstride + (uint32_t)c;
-        const float kf = to_f32(lane_elem(kp, o));
+        const float kf = to_f32(lane_elem(kp, (uint32_t)(sg * TS + u) * kstride + (uint32_t)c));
         sv[u] = kf * kf;
-        lam[u] = kf * to_f32(lane_elem(gp, o));
+        lam[u] = kf * to_f32(lane_elem(gp, (sg * TS + u) * K + c));
     }
     float acc = 0.f;
 #pragma unroll
@@ -304,10 +303,12 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
     {                                                                                            \
         const size_t tokc_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                    \
         const T *kp_ = static_cast<const T *>(a.k) + tokc_ * K;                                  \
-        const T *gp_ = static_cast<const T *>(a.dkt) + tokc_ * K;                                \
+        const T *gp_ = static_cast<const T *>(a.dkt) + (((size_t)bt * N + (n_)) * a.H + h) * C * K; \
+        uint32_t ok_ = (uint32_t)(sg * TS) * kstride + (uint32_t)c, og_ = (uint32_t)(sg * TS * K + c); \
+        if (LINK) asm volatile("" : "+v"(ok_), "+v"(og_));   /* (seldom run there: no addresses kept for it) */ \
         _Pragma("unroll") for (int u = 0; u < TS; ++u) {                                         \
-            const uint32_t o_ = (uint32_t)(sg * TS + u) * kstride + (uint32_t)c;                 \
-            kreg[u] = lane_elem(kp_, o_); greg[u] = lane_elem(gp_, o_);                          \
+            const uint32_t o_ = ok_ + (uint32_t)u * kstride;                                     \
+            kreg[u] = lane_elem(kp_, o_); greg[u] = lane_elem(gp_, og_ + u * K);                 \
             if (RET_VEC) rreg[RET_VEC ? u : 0] = lane_elem(a.retention + tokc_ * K, o_);         \
         }                                                                                        \
         if (tid < C) {                                                                           \
@@ -558,7 +559,7 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
     // wavefront eight tokens at a time, one partial per wavefront and token here
     __shared__ float rpart[(HAS_RET && !RET_VEC) ? (K / 64) * C : 1];
     static_assert(PB == 8, "the fold takes eight values per lane");
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y, tid = threadIdx.x;
     const int N = a.T / C;
     const size_t bh = (size_t)b * a.H + h;
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
@@ -581,7 +582,8 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
     }
     // uniform bases + 32-bit per-thread offsets (64 rows of H*K elements: below 2^31)
     const T *kp = static_cast<const T *>(a.k) + tokc * K;
-    const T *gp = static_cast<const T *>(a.dkt) + tokc * K, *rp = static_cast<const T *>(a.dk_read) + tokc * K;
+    const size_t tile = (((size_t)b * N + n) * a.H + h) * C * K;        // dkt and dk_read: one tile per chunk and head
+    const T *gp = static_cast<const T *>(a.dkt) + tile, *rp = static_cast<const T *>(a.dk_read) + tile;
     T *op = static_cast<T *>(a.dk) + tokc * K;
     const float *retp = RET_VEC ? a.retention + tokc * K : nullptr;     // per-coordinate retention and its gradient
     float *dretp = (RET_VEC && a.dretention) ? a.dretention + tokc * K : nullptr;
@@ -618,8 +620,9 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
     uint32_t sofs = lofs;
 #define OSDN_PLOAD(buf, ih_)                                                                     \
     _Pragma("unroll") for (int u = 0; u < PB; ++u) {                                             \
-        kb[buf][u] = to_f32(at_byte(kp, lofs)); gb[buf][u] = to_f32(at_byte(gp, lofs));          \
-        rb[buf][u] = to_f32(at_byte(rp, lofs));                                                  \
+        const uint32_t tofs = (uint32_t)(((ih_) - u) * K + tid) * (uint32_t)sizeof(T);           \
+        kb[buf][u] = to_f32(at_byte(kp, lofs)); gb[buf][u] = to_f32(at_byte(gp, tofs));          \
+        rb[buf][u] = to_f32(at_byte(rp, tofs));                                                  \
         if (RET_VEC) rrb[RET_VEC ? buf : 0][RET_VEC ? u : 0] = at_byte(retp, lofs * FS);         \
         lofs -= rowb;                                                                            \
     }
@@ -674,7 +677,7 @@ static void launch_chain_k(const PrecondBwdArgs &a, int nchains, hipStream_t st)
 }
 template <typename T, int RET>
 static int launch_precond_bwd_t(const PrecondBwdArgs &a, int which, hipStream_t st) {
-    const dim3 per_chunk(a.n1 - a.n0, a.H, a.B);
+    const dim3 per_chunk((a.n1 - a.n0) * a.H, a.B);
     const int nchains = (a.seq_chunks ? a.n_seqs : a.B) * a.H;
     if (a.K == 64) {
         if (which == 0) hipLaunchKernelGGL((precond_mask_kernel<T, 64, RET>), per_chunk, dim3(64), 0, st, a);
@@ -699,7 +702,7 @@ static int launch_precond_bwd_any(const PrecondBwdArgs &a, bool bf16_io, int whi
 }
 template <typename T>
 static int launch_precond_lin_t(const PrecondBwdArgs &a, bool m_part, hipStream_t st) {
-    const dim3 per_chunk(a.n1 - a.n0, a.H, a.B);
+    const dim3 per_chunk((a.n1 - a.n0) * a.H, a.B);
     if (a.K == 64) {
         if (m_part) hipLaunchKernelGGL((precond_lin_m_kernel<T, 64>), per_chunk, dim3(P1T), 0, st, a);
         else hipLaunchKernelGGL((precond_lin_r_kernel<T, 64>), per_chunk, dim3(P1T), 0, st, a);

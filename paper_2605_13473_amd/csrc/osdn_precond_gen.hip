@@ -60,7 +60,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_m_kernel(PrecondBwdArgs a) {
     __shared__ unsigned char nzv[NG8][C];
     float *Ti = Ss, *Xs = Ss + C * LDF;
 
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int N = a.T / C;
     const size_t bhn = ((size_t)b * a.H + h) * N + n;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_m_kernel(PrecondBwdArgs a) {
         }
     }
     __syncthreads();                                             // the s tile is dead: its space takes the inverse
-    ut_inverse64<LDF>(Af, Ti, Xs, wave, lane);
+    ut_inverse64<LDF, 17>(Af, Ti, Xs, 16 * 17, wave, lane);
     {
         T *mg = static_cast<T *>(a.lin_M) + bhn * C * C + i * C + part * 8;
         constexpr int VNM = 16 / sizeof(T);
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_r_kernel(PrecondBwdArgs a) {
     __shared__ float segL[NSEG * K], segP[NSEG * K];
     __shared__ float rs[C];
     __shared__ float part[P1W * 64];
-    const int n = a.n0 + blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int c = tid % K, sg = tid / K;
     const int N = a.T / C;
@@ -276,14 +276,14 @@ __global__ __launch_bounds__(P1T) void precond_gen_r_kernel(PrecondBwdArgs a) {
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const uint32_t kstride = (uint32_t)a.H * K;
     const bool project = a.d_min <= a.d_max;
-    const T *kp = static_cast<const T *>(a.k) + tokc * K, *gp = static_cast<const T *>(a.dkt) + tokc * K;
+    const T *kp = static_cast<const T *>(a.k) + tokc * K, *gp = static_cast<const T *>(a.dkt) + (((size_t)b * N + n) * a.H + h) * C * K;
     float sv[TS], lam[TS];
 #pragma unroll
     for (int u = 0; u < TS; ++u) {
         const uint32_t o = (uint32_t)(sg * TS + u) * kstride + (uint32_t)c;
         const float kf = to_f32(lane_elem(kp, o));
         sv[u] = kf * kf;
-        lam[u] = kf * to_f32(lane_elem(gp, o));
+        lam[u] = kf * to_f32(lane_elem(gp, (sg * TS + u) * K + c));
     }
     if (tid < C) rs[tid] = HAS_RET ? a.retention[tokc + (size_t)tid * a.H] : 1.f;
     const uint2 mreg = project ? a.masks[bhn * K + c] : make_uint2(0xffffffffu, 0xffffffffu);
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_chain_kernel(PrecondBwdArgs a
 // -------------------------------------------------------------------- launchers ----
 template <typename T>
 static int launch_gen_t(const PrecondBwdArgs &a, int which, hipStream_t st) {
-    const dim3 per_chunk(a.n1 - a.n0, a.H, a.B);
+    const dim3 per_chunk((a.n1 - a.n0) * a.H, a.B);
     const int nchains = (a.seq_chunks ? a.n_seqs : a.B) * a.H;
     const bool ret = a.retention != nullptr;
 #define OSDN_GEN_LAUNCH(K_)                                                                      \

@@ -1,0 +1,59 @@
+"""GPU parity of the chain kernels where their operand rings can go wrong: sequences shorter than,
+as long as and just longer than the rings are deep, in one launch and cut into segments, with wide and
+narrow slices of the state, and token tensors that do not start on a 16-byte boundary (their tiles
+then take the way through registers)."""
+import pytest
+import torch
+
+from paper_2605_13473_amd import binding as ob
+from paper_2605_13473_amd.inputs import make_stress_inputs
+from tests.gpu_util import compare_backward, compare_forward, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("chunks,segments", [(1, 1), (2, 1), (3, 1), (4, 1), (5, 2), (9, 4)])
+@pytest.mark.parametrize("shape", [(1, 2, 128, 192), (2, 2, 64, 64)])
+def test_short_sequences(shape, chunks, segments, bf16):
+    """Few chains: slices of 16 values."""
+    B, H, K, V = shape
+    x = make_stress_inputs(B, 64 * chunks, H, K, V, seed=131 + chunks, bf16=bf16, retention=0.97)
+    hp = ob.Hyper(eta=0.5, segments=segments)
+    compare_forward(x, hp, bf16)
+    compare_backward(x, hp, bf16)
+
+
+@pytest.mark.parametrize("chunks", [1, 2, 3, 5])
+@pytest.mark.parametrize("K", [64, 128])
+def test_many_chains_wide_slices(K, chunks):
+    """Enough chains for slices of 32 values (bf16)."""
+    x = make_stress_inputs(8, 64 * chunks, 16, K, 64, seed=141 + chunks, bf16=True, retention=0.0)
+    hp = ob.Hyper(eta=0.5, segments=1)
+    compare_forward(x, hp, True)
+    compare_backward(x, hp, True)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+def test_token_tensors_off_a_16_byte_boundary(bf16):
+    """q, k, v and dO four bytes past a 16-byte boundary give exactly what aligned tensors give."""
+    x = make_stress_inputs(1, 64 * 5, 2, 128, 128, seed=151, bf16=bf16, retention=0.97)
+    t = to_dev({n: x[n] for n in ("q", "k", "v", "dO", "beta", "log_alpha", "retention", "d_in", "S_in")}, bf16)
+
+    def shifted(a):
+        skip = 4 // a.element_size()
+        buf = torch.empty(a.numel() + skip, dtype=a.dtype, device=a.device)
+        out = buf[skip:].view(a.shape)
+        out.copy_(a)
+        assert out.data_ptr() % 16 == 4
+        return out
+
+    def run(f):
+        o, S, d, ctx = ob.forward(f(t["q"]), f(t["k"]), f(t["v"]), t["beta"], t["log_alpha"], t["retention"], t["d_in"],
+                                  t["S_in"], ob.Hyper(eta=0.5), for_backward=True)
+        g = ob.backward(ctx, f(t["dO"]))
+        torch.cuda.synchronize()
+        return [o, S, d] + [g[n] for n in sorted(g)]
+
+    for a, b in zip(run(lambda a: a), run(shifted)):
+        assert torch.equal(a, b)
