@@ -207,6 +207,22 @@ template <typename U>
 __device__ __forceinline__ U &lane_elem(U *row, int lane_index) {
     return at_byte(row, (uint32_t)lane_index * (uint32_t)sizeof(U));
 }
+// ... with the row's address (the same in the whole wavefront) kept in scalar registers: unrolled over rows,
+// base + lane offset is otherwise taken for the common part and every row costs a 64-bit vector addition.
+// lane_index has to come out of fresh_lane() in the same stretch of straight code, else its widening to 64
+// bits is hoisted and the scalar form is lost.
+__device__ __forceinline__ int fresh_lane(int lane_index) {
+    asm volatile("" : "+v"(lane_index));
+    return lane_index;
+}
+template <typename U>
+__device__ __forceinline__ __attribute__((address_space(1))) U &row_elem(U *row, int lane_index) {
+    typedef __attribute__((address_space(1))) U G;
+    typedef __attribute__((address_space(1))) typename std::conditional<std::is_const<U>::value, const char, char>::type B;
+    G *g = (G *)row;
+    asm("" : "+s"(g));
+    return *(G *)((B *)g + (uint32_t)lane_index * (uint32_t)sizeof(U));
+}
 
 // copy a [rows x cols] tile of T from global (row stride g_ld elements) into LDS (row
 // stride s_ld), 16 bytes per thread and step; cols must be a multiple of 16/sizeof(T)
@@ -334,6 +350,18 @@ __device__ __forceinline__ float wave_sum(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));
 }
 
+// x + the value of the lane 16 (32) lanes across, in both: one swap of rows (halves) between two copies
+// (two wait states between a vector write and the swap that reads it)
+__device__ __forceinline__ float add_xor16(float x) {
+    float y = x;
+    asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y));
+    return x + y;
+}
+__device__ __forceinline__ float add_xor32(float x) {
+    float y = x;
+    asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y));
+    return x + y;
+}
 // the value of lane 63, in every lane
 __device__ __forceinline__ float lane_bcast63(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 63));

@@ -18,8 +18,23 @@
 //     A' = r A,  B' = r B + c s,  L' = clip(r L + c s),  H' = clip(r H + c s)      (r >= 0),
 // so a thread first composes the map of its run, the runs are chained through LDS (one
 // fma + median-of-three per run), and with its run's starting value known the thread replays
-// its 8 tokens.  The products s d are folded over the lanes of the wavefront and the p of a
-// token is the sum of 8 partials.  All arithmetic is fp32; k~ is rounded once, from fp32 d k.
+// its 8 tokens.  The products s d are folded over the lanes of the wavefront.  All arithmetic is fp32; k~ is
+// rounded once, from fp32 d k.
+//
+// Without retention the box is left out of a sweep as long as it cannot matter: with every c >= 0 the
+// trajectory of a run only rises, so it met no face if it starts at or above the lower one and ends at
+// or below the upper one (checked by every sweep).  The map of a run is then x + B and a replayed
+// token one fma, the same one as in the full form.  A chunk that fails the check is done again with the box;
+// one that begins with a coordinate on a face is not tried without it.
+//
+// One barrier per sweep: a sweep's verdict (did p reproduce itself?) is published together with the run
+// maps of the sweep that would follow, which are dropped if there is none; the value of d at the
+// chunk's end travels with them.  The kernel is bound by the issue of one CU's vector instructions (about
+// 500 a wavefront and chunk, two wavefronts per SIMD) and by these barriers: 64 tokens of 128
+// coordinates take 2.8 us at the paper's step size (two sweeps; 3.9 us with the box always in, separate
+// barriers for maps and verdicts, selects instead of register swaps in the folds and 64-bit row addresses
+// in vector registers: 4 x 16 chains of 4096 tokens 250 -> 179 us).  4 runs of 16 tokens fold with fewer
+// instructions but leave one wavefront per SIMD and nothing to cover latency: 210 us.
 //
 // For few long chains the same composition is taken one level up: the chain is cut into pieces,
 // one workgroup per piece walks its chunks from a start value it is given and also composes the
@@ -34,6 +49,7 @@
 namespace osdn {
 
 constexpr int RUN = 8;                           // tokens per run; C / RUN runs = wavefronts
+constexpr int P1F = C / RUN * 64;                // threads
 
 // CPT adjacent elements of type T <-> floats, as one memory access
 template <typename T, int CPT> struct Pack;
@@ -55,9 +71,9 @@ template <> struct Pack<bf16, 1> {
     static __device__ __forceinline__ Raw pack(const float (&v)[1]) { return (bf16)v[0]; }
 };
 template <> struct Pack<float, 2> {
-    typedef float2 Raw;
+    typedef float Raw __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ void unpack(Raw w, float (&o)[2]) { o[0] = w.x; o[1] = w.y; }
-    static __device__ __forceinline__ Raw pack(const float (&v)[2]) { return make_float2(v[0], v[1]); }
+    static __device__ __forceinline__ Raw pack(const float (&v)[2]) { return Raw{v[0], v[1]}; }
 };
 template <> struct Pack<float, 1> {
     typedef float Raw;
@@ -67,24 +83,31 @@ template <> struct Pack<float, 1> {
 
 // RET: 0 = no retention, 1 = one gate per (token, head), 2 = one per coordinate (diag(r_t))
 // PIECES: one workgroup per piece of a chain (sweeps over the whole sequence) instead of one per chain
-template <typename T, int K, int RET, bool PIECES>
-__global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
+// TILES: part of a forward pass: whole chunks, k~ as one contiguous [64 x K] tile per chunk and head, the
+// checkpoints and token scalars wanted.  Then no access of the loop sits under a branch (lanes without
+// an element of their own repeat another's), and the wait for the next chunk's keys, which the compiler
+// counts in accesses, does not become one for the stores behind them.
+template <typename T, int K, int RET, bool PIECES, bool TILES>
+__global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     constexpr int RE = RET_VEC ? K / 64 : 1;      // retention values a thread keeps per token
     constexpr int CPT = K / 64;                   // coordinates per thread (adjacent)
     constexpr int NRUN = C / RUN;                 // = wavefronts of the workgroup
-    static_assert(NRUN == P1W && RUN == 8, "one wavefront per run of 8 tokens");
+    static_assert(K <= P1F, "one thread per coordinate, for the pieces");
     typedef Pack<T, CPT> Pk;
-    __shared__ float dcur[K];                    // d at the start of the chunk
-    // (A, B, L, H) per run and coordinate, [run][e][lane] for coordinate lane * CPT + e: the 16-byte
-    // accesses of adjacent lanes are then adjacent (a lane's own coordinates 32 bytes apart made
-    // every such access a two-way bank conflict)
-    __shared__ __attribute__((aligned(16))) float4 maps[NRUN * K];
-    __shared__ int okflag[NRUN];
+    constexpr bool FAST = RET == 0 && !PIECES;    // sweeps without the box while it does not matter
+    constexpr int NBUF = PIECES ? 3 : 2;          // map buffers, used in turn (a piece reads the accepted maps once more)
+    __shared__ float dnext[K];                   // d at the end of the chunk
+    // per run and coordinate B, L, H and, with one retention per coordinate, A (else A is one number per
+    // run); without the box B alone
+    constexpr int NCOMP = RET_VEC ? 4 : 3;
+    __shared__ __attribute__((aligned(16))) float maps[NBUF][NCOMP][NRUN * K];
+    __shared__ __attribute__((aligned(16))) float runA[2][NRUN];      // (chunks in turn)
+    __shared__ int flags[2][NRUN];
 
-    const int tid = threadIdx.x, run = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, run = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c0 = lane * CPT;                    // first coordinate of this thread
-    const int u_own = lane & (RUN - 1);           // the token of the run whose scalars this lane keeps
+    const int u_own = fold_token<RUN>(lane);      // the token of the run whose scalars this lane keeps
     const int piece = PIECES ? blockIdx.x % a.pieces : 0;
     const int chain = PIECES ? blockIdx.x / a.pieces : blockIdx.x;
     const int b = chain / a.H, h = chain % a.H;               // b: batch entry, or packed sequence
@@ -109,7 +132,7 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
     const uint32_t kstride = (uint32_t)a.H * K;   // elements between consecutive tokens
 
     if (!PIECES) {
-        if (tid < K) dcur[tid] = a.d_in ? a.d_in[bh * K + tid] : 1.f;
+        if (tid < K) dnext[tid] = a.d_in ? a.d_in[bh * K + tid] : 1.f;
     } else {
         // The start value of this piece: the chain's own start value carried through the maps
         // that the previous sweep left for the pieces before this one (first sweep: the chain's
@@ -136,7 +159,7 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
         if (piece == 0 && tid == 0) a.settled[chain] = any ? 0 : 1;
         if (!any) return;
         if (tid < K) {
-            dcur[tid] = xs;
+            dnext[tid] = xs;
             a.piece_start[cur + (bh * a.pieces + piece) * K + tid] = xs;
         }
         a.piece_map += cur;
@@ -150,22 +173,29 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
 #define OSDN_P1_LOAD(n_)                                                                         \
     {                                                                                            \
         const int t0_ = (n_) * C;                                                                \
+        const int fl_ = fresh_lane(lane);                                                        \
         const T *kp_ = static_cast<const T *>(a.k) + (((size_t)bt * a.T + t0_) * a.H + h) * K;   \
         _Pragma("unroll") for (int u = 0; u < RUN; ++u) {                                        \
-            const int i_ = min(run * RUN + u, a.T - 1 - t0_);    /* rows past the end: reread */ \
-            kreg[u] = *reinterpret_cast<const typename Pk::Raw *>(kp_ + (uint32_t)i_ * kstride + c0); \
+            const int i_ = TILES ? run * RUN + u : min(run * RUN + u, a.T - 1 - t0_);    /* rows past the end: reread */ \
+            kreg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(kp_ + (size_t)i_ * kstride), fl_); \
             if (RET_VEC)                                                                         \
-                rreg[u] = *reinterpret_cast<const typename Pr::Raw *>(                           \
-                    a.retention + (((size_t)bt * a.T + t0_) * a.H + h) * K + (uint32_t)i_ * kstride + c0); \
+                rreg[u] = row_elem(reinterpret_cast<const typename Pr::Raw *>(       \
+                    a.retention + (((size_t)bt * a.T + t0_) * a.H + h) * K + (size_t)i_ * kstride), fl_); \
         }                                                                                        \
-        const int t = min(t0_ + run * RUN + u_own, a.T - 1);                                     \
-        const size_t th = ((size_t)bt * a.T + t) * a.H + h;                                      \
-        betreg = a.beta[th];                                                                     \
-        if (HAS_RET && !RET_VEC) retreg = a.retention[th];                                       \
+        const int i_ = TILES ? run * RUN + u_own : min(run * RUN + u_own, a.T - 1 - t0_);        \
+        const size_t th = ((size_t)bt * a.T + t0_) * a.H + h;                                    \
+        betreg = lane_elem(a.beta + th, i_ * a.H);                                               \
+        if (HAS_RET && !RET_VEC) retreg = lane_elem(a.retention + th, i_ * a.H);                 \
     }
     OSDN_P1_LOAD(a.n0)
-
+    // (waited for here: loads that are pending when the loop is entered would make its head wait for the stores too)
+    __builtin_amdgcn_s_waitcnt(0x0f70);         // vmcnt(0)
     __syncthreads();
+    float dst[CPT];                             // d of this thread's coordinates at the start of the chunk
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) dst[e] = dnext[c0 + e];
+    bool boxed = !FAST;                         // this chunk is swept with the box
+    int pub = 0, fl = 0;                        // map buffer and flag row of the next barrier
     for (int n = a.n0; n < a.n1; ++n) {
         const int t0 = n * C;
         const int nvalid = min(C, a.T - t0);
@@ -176,7 +206,7 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
             Pk::unpack(kreg[u], kf[u]);
 #pragma unroll
             for (int e = 0; e < CPT; ++e) {
-                if (run * RUN + u >= nvalid) kf[u][e] = 0.f;
+                if (!TILES && run * RUN + u >= nvalid) kf[u][e] = 0.f;
                 sv[u][e] = kf[u][e] * kf[u][e];
             }
         }
@@ -184,10 +214,10 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
         // ---- the scalars of token (run, u_own): n_raw = sum s, first guess p = <d_0, s> ----
         float nraw, cb, ca, p_cur, c_cur;
         {
-            float dst[CPT];
-#pragma unroll
-            for (int e = 0; e < CPT; ++e) dst[e] = dcur[c0 + e];
-            if (a.d_ckpt && run == 0) {
+            if (TILES) {                        // every wavefront an equal part
+                const int c = run * (K / NRUN) + lane % (K / NRUN);
+                a.d_ckpt[(bth * N + n) * K + c] = dnext[c];
+            } else if (a.d_ckpt && run == 0) {
 #pragma unroll
                 for (int e = 0; e < CPT; ++e) a.d_ckpt[(bth * N + n) * K + c0 + e] = dst[e];
             }
@@ -198,9 +228,9 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
 #pragma unroll
                 for (int e = 0; e < CPT; ++e) { vn[u] += sv[u][e]; vp[u] = __builtin_fmaf(sv[u][e], dst[e], vp[u]); }
             }
-            nraw = lane_fold8_all(vn, lane);
-            p_cur = lane_fold8_all(vp, lane);
-            const bool valid = run * RUN + u_own < nvalid;
+            nraw = fold_tokens(vn);
+            p_cur = fold_tokens(vp);
+            const bool valid = TILES || run * RUN + u_own < nvalid;
             const float nn = fmaxf(nraw, a.eps);
             const float bp = a.beta_aware ? bet : 1.f;
             cb = valid ? a.eta * bp / nn : 0.f;
@@ -214,127 +244,211 @@ __global__ __launch_bounds__(P1T) void precond_fwd_kernel(PrecondArgs a) {
                 float r2[CPT];
                 Pr::unpack(rreg[RET_VEC ? u : 0], r2);
 #pragma unroll
-                for (int e = 0; e < RE; ++e) rv[u][e] = run * RUN + u < nvalid ? r2[e] : 1.f;
+                for (int e = 0; e < RE; ++e) rv[u][e] = TILES || run * RUN + u < nvalid ? r2[e] : 1.f;
             } else {
-                rv[u][0] = HAS_RET ? lane_bcast(run * RUN + u < nvalid ? ret : 1.f, u) : 1.f;
+                rv[u][0] = HAS_RET ? lane_bcast(TILES || run * RUN + u < nvalid ? ret : 1.f, fold_lane<RUN>(u)) : 1.f;
             }
         }
-        if (n + 1 < a.n1) OSDN_P1_LOAD(n + 1)
+        OSDN_P1_LOAD(min(n + 1, a.n1 - 1))       // (past the end: reloaded in vain)
         // ---- fixed-point sweeps ----
+        // flags of a wavefront: 1: its p did not reproduce themselves, 2: the box matters (a sweep without it is void)
+        if (FAST) {                             // (from d alone: where a call or a launch begins must not show)
+            bool in = true;
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) in = in && dst[e] > lo && dst[e] < hi;
+            boxed = !__all(in);
+        }
         int sweeps_used = 0;
         float dtr[RUN][CPT], dend[CPT];
-        for (int sweep = 0; sweep < P1_MAX_SWEEPS; ++sweep) {
-            ++sweeps_used;
+        float c_acc = c_cur, p_acc = p_cur;     // what generated dtr and dend
+        int verdict = 1;
+        auto put_map = [&](int comp, const float (&v)[CPT]) {
+            *reinterpret_cast<typename Pr::Raw *>(&maps[pub][comp][run * K + c0]) = Pr::pack(v);
+        };
+        auto get_map = [&](int comp, int j, float (&v)[CPT]) {
+            Pr::unpack(*reinterpret_cast<const typename Pr::Raw *>(&maps[pub][comp][j * K + c0]), v);
+        };
+        for (int sweep = 0;; ++sweep) {
             float cv[RUN];
 #pragma unroll
-            for (int u = 0; u < RUN; ++u) cv[u] = lane_bcast(c_cur, u);
+            for (int u = 0; u < RUN; ++u) cv[u] = lane_bcast(c_cur, fold_lane<RUN>(u));
             // the map of this run, x -> clip3(A x + B, L, H), per coordinate
+            if (FAST && !boxed) {
+                float Bv[CPT];
 #pragma unroll
-            for (int e = 0; e < CPT; ++e) {
-                float A = 1.f, B = 0.f, L = -FLT_MAX, H = FLT_MAX;
+                for (int e = 0; e < CPT; ++e) {
+                    Bv[e] = cv[0] * sv[0][e];
 #pragma unroll
-                for (int u = 0; u < RUN; ++u) {
-                    const float bs = cv[u] * sv[u][e];
-                    if (HAS_RET) {
-                        const float r = rv[u][RET_VEC ? e : 0];
-                        A *= r;
-                        B = __builtin_fmaf(r, B, bs);
-                        L = clip3(__builtin_fmaf(r, L, bs), lo, hi);
-                        H = clip3(__builtin_fmaf(r, H, bs), lo, hi);
-                    } else {
-                        B += bs;
-                        L = clip3(L + bs, lo, hi);
-                        H = clip3(H + bs, lo, hi);
-                    }
+                    for (int u = 1; u < RUN; ++u) Bv[e] = __builtin_fmaf(cv[u], sv[u][e], Bv[e]);
                 }
-                maps[(run * CPT + e) * 64 + lane] = make_float4(A, B, L, H);
+                put_map(0, Bv);
+            } else {
+                float Av[CPT], Bv[CPT], Lv[CPT], Hv[CPT];
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) {
+                    float A = 1.f, B = 0.f, L = -FLT_MAX, H = FLT_MAX;
+#pragma unroll
+                    for (int u = 0; u < RUN; ++u) {
+                        const float bs = cv[u] * sv[u][e];
+                        if (HAS_RET) {
+                            const float r = rv[u][RET_VEC ? e : 0];
+                            A *= r;
+                            B = __builtin_fmaf(r, B, bs);
+                            L = clip3(__builtin_fmaf(r, L, bs), lo, hi);
+                            H = clip3(__builtin_fmaf(r, H, bs), lo, hi);
+                        } else {
+                            B += bs;
+                            L = clip3(L + bs, lo, hi);
+                            H = clip3(H + bs, lo, hi);
+                        }
+                    }
+                    Av[e] = A; Bv[e] = B; Lv[e] = L; Hv[e] = H;
+                }
+                put_map(0, Bv); put_map(1, Lv); put_map(2, Hv);
+                if (RET_VEC) put_map(NCOMP - 1, Av);
+                else if (HAS_RET && sweep == 0 && lane == 0) runA[n & 1][run] = Av[0];
+            }
+            // with the maps: the verdict on the sweep before, and d at the end of its last run
+            if (sweep > 0) {
+                if (run == NRUN - 1) {
+#pragma unroll
+                    for (int e = 0; e < CPT; ++e) dnext[c0 + e] = dend[e];
+                }
+                if (lane == 0) flags[fl][run] = verdict;
             }
             __syncthreads();
+            if (sweep > 0) {
+                int all = 0;
+#pragma unroll
+                for (int w = 0; w < NRUN; ++w) all |= flags[fl][w];
+                fl ^= 1;
+                if (FAST && (all & 2)) {        // once more, from where p has got to, with the box
+                    boxed = true;
+                    sweep = -1;
+                    continue;
+                }
+                if (all == 0 || sweep >= P1_MAX_SWEEPS) break;
+            }
+            ++sweeps_used;
             float vp[RUN];
 #pragma unroll
             for (int u = 0; u < RUN; ++u) vp[u] = 0.f;
-#pragma unroll
-            for (int e = 0; e < CPT; ++e) {
+            bool within = true;
+            if (FAST && !boxed) {
                 // d at the start of this run: the runs to its left applied to d at the chunk start
-                float d = dcur[c0 + e];
+                // (all runs are read, so that the reads go out together)
+                float d[CPT], Bm[NRUN - 1][CPT];
 #pragma unroll
-                for (int j = 0; j < NRUN - 1; ++j)
-                    if (j < run) {
-                        const float4 m = maps[(j * CPT + e) * 64 + lane];
-                        d = clip3(__builtin_fmaf(m.x, d, m.y), m.z, m.w);
+                for (int j = 0; j < NRUN - 1; ++j) get_map(0, j, Bm[j]);
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) {
+                    d[e] = dst[e];
+#pragma unroll
+                    for (int j = 0; j < NRUN - 1; ++j) d[e] += j < run ? Bm[j][e] : 0.f;
+                    within = within && d[e] >= lo;
+#pragma unroll
+                    for (int u = 0; u < RUN; ++u) {
+                        dtr[u][e] = d[e];
+                        vp[u] = __builtin_fmaf(sv[u][e], d[e], vp[u]);
+                        d[e] = __builtin_fmaf(cv[u], sv[u][e], d[e]);
                     }
-                // replay of the run's tokens (the same arithmetic as the reverse sweep's replay)
-#pragma unroll
-                for (int u = 0; u < RUN; ++u) {
-                    dtr[u][e] = d;
-                    vp[u] = __builtin_fmaf(sv[u][e], d, vp[u]);
-                    d = clip3(d_bar<HAS_RET>(rv[u][RET_VEC ? e : 0], d, cv[u], sv[u][e]), lo, hi);
+                    within = within && d[e] <= hi;
+                    dend[e] = d[e];
                 }
-                dend[e] = d;
-            }
-            const float p_new = lane_fold8_all(vp, lane);
-            const bool ok = fabsf(p_new - p_cur) <= P1_TOL * fabsf(p_new);
-            const bool wave_ok = __all(ok);
-            if (lane == 0) okflag[run] = wave_ok ? 1 : 0;
-            __syncthreads();
-            bool all_ok = true;
+                within = within && (c_cur >= 0.f || !project);
+            } else {
+                float d[CPT], Av[CPT];
+                float Bm[NRUN - 1][CPT], Lm[NRUN - 1][CPT], Hm[NRUN - 1][CPT];
 #pragma unroll
-            for (int w = 0; w < NRUN; ++w) all_ok = all_ok && okflag[w] != 0;
-            if (all_ok) break;
+                for (int j = 0; j < NRUN - 1; ++j) { get_map(0, j, Bm[j]); get_map(1, j, Lm[j]); get_map(2, j, Hm[j]); }
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) d[e] = dst[e];
+#pragma unroll
+                for (int j = 0; j < NRUN - 1; ++j) {
+                    if (RET_VEC) get_map(NCOMP - 1, j, Av);
+#pragma unroll
+                    for (int e = 0; e < CPT; ++e) {
+                        if (!RET_VEC) Av[e] = HAS_RET ? runA[n & 1][j] : 1.f;
+                        const float x = clip3(HAS_RET ? __builtin_fmaf(Av[e], d[e], Bm[j][e]) : d[e] + Bm[j][e], Lm[j][e], Hm[j][e]);
+                        d[e] = j < run ? x : d[e];
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) {
+                    // replay of the run's tokens (the same arithmetic as the reverse sweep's replay)
+#pragma unroll
+                    for (int u = 0; u < RUN; ++u) {
+                        dtr[u][e] = d[e];
+                        vp[u] = __builtin_fmaf(sv[u][e], d[e], vp[u]);
+                        d[e] = clip3(d_bar<HAS_RET>(rv[u][RET_VEC ? e : 0], d[e], cv[u], sv[u][e]), lo, hi);
+                    }
+                    dend[e] = d[e];
+                }
+            }
+            const float p_new = fold_tokens(vp);
+            const bool ok = fabsf(p_new - p_cur) <= P1_TOL * fabsf(p_new);
+            verdict = (__all(ok) ? 0 : 1) | (__all(within) ? 0 : 2);
+            c_acc = c_cur; p_acc = p_cur;
             p_cur = p_new;
             c_cur = cb - ca * p_new;
+            pub = pub + 1 == NBUF ? 0 : pub + 1;
         }
-        // ---- accepted: (c_cur, p_cur) generated dtr and dend ----
+        // ---- accepted: (c_acc, p_acc) generated dtr and dend ----
         {
-            // (kt_tiles: one contiguous [64 x K] tile per chunk and head)
-            T *ktp = static_cast<T *>(a.k_tilde) + (a.kt_tiles ? (((size_t)bt * N + n) * a.H + h) * C : ((size_t)bt * a.T + t0) * a.H + h) * K;
-            const uint32_t ktstride = a.kt_tiles ? K : kstride;
+            T *ktp = static_cast<T *>(a.k_tilde) + (TILES ? (((size_t)bt * N + n) * a.H + h) * C : ((size_t)bt * a.T + t0) * a.H + h) * K;
+            const uint32_t ktstride = TILES ? K : kstride;
+            const int fl = fresh_lane(lane);
 #pragma unroll
             for (int u = 0; u < RUN; ++u) {
                 const int i = run * RUN + u;
-                if (i < nvalid) {
+                if (TILES || i < nvalid) {
                     float out[CPT];
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) out[e] = dtr[u][e] * kf[u][e];
-                    *reinterpret_cast<typename Pk::Raw *>(ktp + (uint32_t)i * ktstride + c0) = Pk::pack(out);
+                    row_elem(reinterpret_cast<typename Pk::Raw *>(ktp + (size_t)i * ktstride), fl) = Pk::pack(out);
                 }
             }
         }
-        if (a.tok_scalars && lane < RUN && run * RUN + lane < nvalid) {
-            const size_t th = ((size_t)bt * a.T + t0 + run * RUN + lane) * a.H + h;
-            *reinterpret_cast<float4 *>(a.tok_scalars + th * 4) = make_float4(c_cur, p_cur, nraw, (float)sweeps_used);
-        }
-        if (run == NRUN - 1) {
-#pragma unroll
-            for (int e = 0; e < CPT; ++e) dcur[c0 + e] = dend[e];
+        if (TILES || (a.tok_scalars && run * RUN + u_own < nvalid)) {       // (eight lanes store the same)
+            const size_t th = ((size_t)bt * a.T + t0) * a.H + h;
+            lane_elem(reinterpret_cast<float4 *>(a.tok_scalars) + th, (run * RUN + u_own) * a.H) = make_float4(c_acc, p_acc, nraw, (float)sweeps_used);
         }
         if (PIECES && tid < K) {                 // the accepted run maps, applied after the piece so far
+            const int acc = pub == 0 ? NBUF - 1 : pub - 1;       // (the last published ones were dropped)
 #pragma unroll
             for (int j = 0; j < NRUN; ++j) {
-                const float4 m = maps[(j * CPT + tid % CPT) * 64 + tid / CPT];
-                PA *= m.x;
-                PB = __builtin_fmaf(m.x, PB, m.y);
-                PL = clip3(__builtin_fmaf(m.x, PL, m.y), m.z, m.w);
-                PH = clip3(__builtin_fmaf(m.x, PH, m.y), m.z, m.w);
+                const float A = RET_VEC ? maps[acc][NCOMP - 1][j * K + tid] : HAS_RET ? runA[n & 1][j] : 1.f;
+                const float B = maps[acc][0][j * K + tid], L = maps[acc][1][j * K + tid], H = maps[acc][2][j * K + tid];
+                PA *= A;
+                PB = __builtin_fmaf(A, PB, B);
+                PL = clip3(__builtin_fmaf(A, PL, B), L, H);
+                PH = clip3(__builtin_fmaf(A, PH, B), L, H);
             }
         }
-        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) dst[e] = dnext[c0 + e];
+        pub = pub + 1 == NBUF ? 0 : pub + 1;
     }
     if (PIECES && tid < K) a.piece_map[(bh * a.pieces + piece) * K + tid] = make_float4(PA, PB, PL, PH);
-    if (tid < K && (!PIECES || piece == a.pieces - 1)) a.d_out[bh * K + tid] = dcur[tid];
+    if (run == 0 && (!PIECES || piece == a.pieces - 1)) {
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) a.d_out[bh * K + c0 + e] = dst[e];
+    }
 }
 
-template <typename T, int RET, bool PIECES>
+template <typename T, int RET, bool PIECES, bool TILES>
 static int launch_precond_fwd_tp(const PrecondArgs &a, hipStream_t st) {
-    dim3 grid((a.seq_chunks ? a.n_seqs : a.B) * a.H * (PIECES ? a.pieces : 1)), block(P1T);
-    if (a.K == 64) hipLaunchKernelGGL((precond_fwd_kernel<T, 64, RET, PIECES>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((precond_fwd_kernel<T, 128, RET, PIECES>), grid, block, 0, st, a);
+    dim3 grid((a.seq_chunks ? a.n_seqs : a.B) * a.H * (PIECES ? a.pieces : 1)), block(P1F);
+    if (TILES && (a.T % C != 0 || !a.d_ckpt || !a.tok_scalars)) return -1;
+    if (a.K == 64) hipLaunchKernelGGL((precond_fwd_kernel<T, 64, RET, PIECES, TILES>), grid, block, 0, st, a);
+    else if (a.K == 128) hipLaunchKernelGGL((precond_fwd_kernel<T, 128, RET, PIECES, TILES>), grid, block, 0, st, a);
     else return -1;
     return 0;
 }
 template <typename T, int RET>
 static int launch_precond_fwd_t(const PrecondArgs &a, hipStream_t st) {
-    return a.pieces ? launch_precond_fwd_tp<T, RET, true>(a, st) : launch_precond_fwd_tp<T, RET, false>(a, st);
+    if (!a.kt_tiles) return a.pieces ? -1 : launch_precond_fwd_tp<T, RET, false, false>(a, st);
+    return a.pieces ? launch_precond_fwd_tp<T, RET, true, true>(a, st) : launch_precond_fwd_tp<T, RET, false, true>(a, st);
 }
 int launch_precond_fwd(const PrecondArgs &a, bool bf16_io, hipStream_t st) {
     const int ret = a.retention ? (a.ret_vec ? 2 : 1) : 0;
