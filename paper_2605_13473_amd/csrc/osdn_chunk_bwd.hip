@@ -303,19 +303,29 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
 }
 
 // -------------------------------------------------------------- bwd_post ----
-// One workgroup of 8 wavefronts per chunk and head (two per SIMD, so that LDS and MFMA
-// latencies of one overlap with the other's issue).  V is walked in slabs of VB columns; the
-// slab buffers are reused for Q and K~ once the walk is over.
-// PW_ wavefronts per workgroup (a parameter of the work split below; 8 is what is launched).
+// One workgroup of 8 wavefronts per chunk and head.  V is walked in slabs of VB columns; the slab
+// buffers are reused for Q and K~ once the walk is over, and so are the registers that carry the next
+// slab while the workgroup computes on this one.
+//
+// Two workgroups share a CU with bf16 I/O (slabs of 32 columns: 80 KB of LDS; at most 128 registers, which
+// is why the scheduler is fenced in below), so that one computes while the other waits for its tiles or at
+// one of its barriers.  Every product is formed with the features (values, or j of a 64 x 64 matrix)
+// down the rows of the accumulator and the tokens across: a lane then holds four adjacent features of one
+// token, so that results leave as 8-byte stores (dv from the accumulators), operands come as
+// 8-byte reads, gates are one number per lane and sums over features need two lane swaps.
+// 16816 chunk-heads, K = V = 128 in bf16: 900 us (4.1 GB needed); with tokens down the rows, 1019; one workgroup
+// per CU on slabs of 64, two chunks in turn, 1072.
+template <typename T> constexpr int BP_WGS = sizeof(T) == 2 ? 2 : 1;      // workgroups that share a CU
 
 // GV: one state gate per key channel.  The kernel then runs on the folded operands with no
 // scalar gate (log_alpha null) and on D in place of dS' (see the top of this file); the gradient of
 // the chunk's decays, times the decays, is collected per channel.
-template <typename T, int K, bool GV, int PW_, bool PAIR>
-__global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
+template <typename T, int K, bool GV, int PW_>
+__global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kernel(ChunkArgs a) {
     constexpr int PT_ = PW_ * 64;
-    constexpr int PAD = sizeof(T) == 2 ? 16 : Pad<T>::v, LDK = K + PAD, LDC = C + PAD;   // bf16: rows 32 bytes apart modulo 128
-    constexpr int VB = sizeof(T) == 2 ? 64 : 32;        // slab width
+    constexpr int PAD = sizeof(T) == 2 ? 16 : Pad<T>::v, LDK = K + PAD, LDE = C + PAD;   // bf16: rows 32 bytes apart modulo 128
+    constexpr int LDC = C + Pad<T>::v;                  // (T, cA, cP)
+    constexpr int VB = 32;                              // slab width
     constexpr int LDV = VB + PAD;
     constexpr int NVT = VB / 16;                         // column tiles of a slab
     constexpr int WPR = PW_ / 4;                         // wavefronts that share a row block in steps (1), (2)
@@ -330,26 +340,27 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     // persistent
     __shared__ __attribute__((aligned(16))) T Ks[C * LDK];
     __shared__ __attribute__((aligned(16))) T Tt[C * LDC];       // T; after the walk: cA
-    __shared__ float Gs[C], Bs[C];
+    __shared__ __attribute__((aligned(16))) float Gs[C];
+    __shared__ float Bs[C];
     __shared__ float Egs[C], Ers[C];                     // gamma_i = e^{G_i} and rho_i = e^{G_C - G_i}, once per row
     __shared__ float red[4 * C];                         // [4][64] partial sums across tiles
-    __shared__ float red2[4 * C];
-    __shared__ float red3[4 * C];
+    __shared__ float red2[GV ? 1 : 4 * C];               // (with per-channel gates dG is not collected here)
+    __shared__ __attribute__((aligned(16))) float red3[GV ? 1 : 4 * C];
     __shared__ float dbeta_s[WPR * C];
     __shared__ float sdot[PW_], trsum_s[PW_];
     __shared__ float colss[GV ? PT_ : 1];                // <dS', S> column by column (partials)
-    __shared__ float dgam_s[GV ? (PW_ / (K / 16) > 0 ? PW_ / (K / 16) : 1) * K : 1];   // sum_i (K~/Gamma)_ic (E dS')_ic, per row-block group
+    __shared__ __attribute__((aligned(16))) float dgam_s[GV ? (PW_ / (K / 16) > 0 ? PW_ / (K / 16) : 1) * K : 1];   // sum_i (K~/Gamma)_ic (E dS')_ic, per row-block group
     // slab buffers, later Q / K~ / cP and the row-dot partials
-    constexpr int SLAB_ELEMS = 3 * C * LDV + 2 * VB * LDC + 2 * VB * LDK;
-    constexpr int POST_ELEMS = 2 * C * LDK + C * LDC + (PW_ * C * 4) / (int)sizeof(T);
+    constexpr int SLAB_ELEMS = 3 * C * LDV + 2 * VB * LDE + 2 * VB * LDK;
+    constexpr int POST_ELEMS = 2 * C * LDK + C * LDC + (GV ? 0 : (PW_ * C * 4) / (int)sizeof(T));
     constexpr int POOL = SLAB_ELEMS > POST_ELEMS ? SLAB_ELEMS : POST_ELEMS;
     __shared__ __attribute__((aligned(16))) T pool[POOL];
     T *dOs = pool;                      // [64][LDV]  dO slab (natural), later dV staging
     T *Vs = dOs + C * LDV;              // [64][LDV]  V slab
     T *dRs = Vs + C * LDV;              // [64][LDV]  dR slab (natural)
-    T *Ets = dRs + C * LDV;             // [VB][LDC]  E^T slab
-    T *dEts = Ets + VB * LDC;           // [VB][LDC]  dE^T slab
-    T *Ss = dEts + VB * LDC;            // [VB][LDK]  S slab
+    T *Ets = dRs + C * LDV;             // [VB][LDE]  E^T slab
+    T *dEts = Ets + VB * LDE;           // [VB][LDE]  dE^T slab
+    T *Ss = dEts + VB * LDE;            // [VB][LDK]  S slab
     T *dSs = Ss + VB * LDK;             // [VB][LDK]  dS' slab
     T *Qs = pool;                       // after the walk
     T *Kts = Qs + C * LDK;
@@ -357,60 +368,40 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     float *pq = reinterpret_cast<float *>(cPs + C * LDC);        // [PW_][64]
     T *cAs = Tt;                        // [64][LDC]
 
-    // PAIR (large launches, bf16): a workgroup does two adjacent chunks one after the other (the
-    // launcher halves the grid): the first loads of the second chunk (gates, K, T, the first slab)
-    // are issued when the walk of the first is over and arrive while its results are finished.
-    constexpr int tasks = PAIR ? 2 : 1;
-    const int n_first = a.n0 + (int)(blockIdx.x / a.H) * tasks, h = blockIdx.x % a.H, b = blockIdx.y;
-    const int ntask = min(tasks, a.n1 - n_first);
-    int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int n = a.n0 + (int)(blockIdx.x / a.H), h = blockIdx.x % a.H, b = blockIdx.y;
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
+    const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const size_t tstride = a.H;
     // the slab tiles travel through registers: the next slab (after the last one: Q and K~) is
     // fetched while the workgroup computes on the current one
-    TileRegs<T, C, VB, PT_> r_dO, r_V;
-    TileRegs<T, VB, C, PT_> r_Et, r_dEt;
-    TileRegs<T, VB, K, PT_> r_S, r_dS;
-    TileRegs<T, C, K, PT_> r_Q, r_Kt, r_Kn;
+    PairRegs<T, C, VB, PT_> r_dOV;
+    PairRegs<T, VB, C, PT_> r_EdE;
+    TileRegs<T, VB, K, PT_> r_S, r_dS;                  // after the last slab: the two halves of Q (and K~ in r_dOV, r_EdE)
+    static_assert(2 * VB == C, "halves of Q");
+    constexpr int NVP = PairRegs<T, C, VB, PT_>::NVP;
+    TileRegs<T, C, K, PT_> r_Kn;
+    static_assert(TileRegs<T, C, K, PT_>::NV <= 2 * NVP, "K~ fits the registers of the slab");
     TileRegs<T, C, C, PT_> r_Tn;
     float r_g = 0.f, r_b = 0.f;
-#define OSDN_BP_FETCH(tok_, bhn_, v0_)                                                           \
-    {                                                                                            \
-        r_dO.fetch(static_cast<const T *>(a.dO) + (tok_) * a.V + (v0_), tstride * a.V, tid);     \
-        r_V.fetch(static_cast<const T *>(a.v) + (tok_) * a.V + (v0_), tstride * a.V, tid);       \
-        r_Et.fetch(static_cast<const T *>(a.Et) + ((bhn_) * a.V + (v0_)) * C, (size_t)C, tid);   \
-        r_dEt.fetch(static_cast<const T *>(a.dEt) + ((bhn_) * a.V + (v0_)) * C, (size_t)C, tid); \
-        r_S.fetch(static_cast<const T *>(a.S_ckpt) + ((bhn_) * a.V + (v0_)) * K, (size_t)K, tid); \
-        r_dS.fetch(static_cast<const T *>(a.dS_ckpt) + ((bhn_) * a.V + (v0_)) * K, (size_t)K, tid); \
+    auto fetch_slab = [&](int v0) {
+        r_dOV.fetch(static_cast<const T *>(a.dO) + tok0 * a.V + v0, static_cast<const T *>(a.v) + tok0 * a.V + v0, tstride * a.V, tid, wave);
+        r_EdE.fetch(static_cast<const T *>(a.Et) + (bhn * a.V + v0) * C, static_cast<const T *>(a.dEt) + (bhn * a.V + v0) * C, (size_t)C, tid, wave);
+        r_S.fetch(static_cast<const T *>(a.S_ckpt) + (bhn * a.V + v0) * K, (size_t)K, tid);
+        r_dS.fetch(static_cast<const T *>(a.dS_ckpt) + (bhn * a.V + v0) * K, (size_t)K, tid);
+    };
+    if (wave == 0) {
+        r_g = a.log_alpha ? a.gates[bhn * 3 * C + lane] : 0.f;
+        r_b = a.beta[tok0 + (size_t)lane * tstride];
     }
-    // gates, K and T of a chunk, then its first slab
-#define OSDN_BP_ISSUE(n_)                                                                        \
-    {                                                                                            \
-        const size_t bhn_i = ((size_t)b * a.N + (n_)) * a.H + h;                                 \
-        const size_t tok_i = ((size_t)b * a.T + (size_t)(n_) * C) * a.H + h;                     \
-        if (wave == 0) {                                                                         \
-            const size_t th = tok_i + (size_t)lane * tstride;                                    \
-            r_g = a.log_alpha ? a.gates[bhn_i * 3 * C + lane] : 0.f;                             \
-            r_b = a.beta[th];                                                                    \
-        }                                                                                        \
-        r_Kn.fetch(static_cast<const T *>(a.k) + (GV ? bhn_i * C : tok_i) * K, GV ? (size_t)K : tstride * K, tid); \
-        r_Tn.fetch(static_cast<const T *>(a.Tm) + bhn_i * C * C, (size_t)C, tid);                \
-        OSDN_BP_FETCH(tok_i, bhn_i, 0)                                                           \
-    }
-    OSDN_BP_ISSUE(n_first)
-#pragma unroll 1
-    for (int task = 0; task < ntask; ++task) {
-    // (the thread index is made opaque once per chunk, so that the lane addresses of the body
-    // are not all computed ahead of the loop and kept in registers)
-    asm volatile("" : "+v"(tid));
-    wave = __builtin_amdgcn_readfirstlane(tid >> 6); lane = tid & 63;
-    const int n = n_first + task;
-    const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
-    const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    r_Kn.fetch(static_cast<const T *>(a.k) + (GV ? bhn * C : tok0) * K, GV ? (size_t)K : tstride * K, tid);
+    r_Tn.fetch(static_cast<const T *>(a.Tm) + bhn * C * C, (size_t)C, tid);
+    fetch_slab(0);
     const int ct = (wave % NCT) * 16;   // this wave's column tile of the [64 x K] results ...
     const int ib0 = (wave / NCT) * IBN; // ... and its first row block
     const bool has_ct = wave < NCT * WPC;
 
-    if (task > 0) __syncthreads();      // the previous chunk is through with every LDS tile
     if (wave == 0) {
         const float G = r_g;
         Gs[lane] = G;
@@ -424,7 +415,7 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     // accumulators over the walk
     f32x4 dP[NLT], dA[NLT];             // the lower tiles idx = wave, wave + PW_ (< 10)
     f32x4 dQg[IBN], dKg[IBN], dKr[IBN]; // [row block ib0 + .], column tile ct
-    float dbeta_part[4] = {0.f, 0.f, 0.f, 0.f};     // rows 16*(wave/2) + acc_row(lane, r), this wave's columns
+    float dbeta_part = 0.f;             // token 16*rb + acc_col(lane), this lane's values
     float ss_part = 0.f;                // <dS', S>
 #pragma unroll
     for (int t = 0; t < NLT; ++t) { dP[t] = f32x4{0.f, 0.f, 0.f, 0.f}; dA[t] = f32x4{0.f, 0.f, 0.f, 0.f}; }
@@ -435,36 +426,35 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
         dKr[ib] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const int rb = wave / WPR;          // row block of steps (1), (2)
-    float gam_rb[4] = {1.f, 1.f, 1.f, 1.f};   // gamma of this lane's four rows there (set once G is in LDS)
 
+    // (the thread index is made opaque here and there, so that the lane addresses of what follows are not
+    // all computed far ahead and kept in registers; and the scheduler is kept from mixing the row blocks)
+#define OSDN_BP_FRESH() asm volatile("" : "+v"(tid), "+v"(lane))
     for (int v0 = 0; v0 < a.V; v0 += VB) {
+        OSDN_BP_FRESH();
         __syncthreads();
-        r_dO.put(dOs, LDV, tid); r_V.put(Vs, LDV, tid);
-        r_Et.put(Ets, LDC, tid); r_dEt.put(dEts, LDC, tid);
+        r_dOV.put(dOs, Vs, LDV, tid, wave);
+        r_EdE.put(Ets, dEts, LDE, tid, wave);
         r_S.put(Ss, LDK, tid); r_dS.put(dSs, LDK, tid);
+        if (!GV) ss_part = TileRegs<T, VB, K, PT_>::dot(r_S, r_dS, ss_part, tid);      // <dS', S> over this slab
         if (v0 + VB < a.V) {
-            OSDN_BP_FETCH(tok0, bhn, v0 + VB)
+            fetch_slab(v0 + VB);
         } else {
-            r_Q.fetch(static_cast<const T *>(a.q) + (GV ? bhn * C : tok0) * K, GV ? (size_t)K : tstride * K, tid);
+            const size_t ldq = GV ? (size_t)K : tstride * K;
+            const T *qp = static_cast<const T *>(a.q) + (GV ? bhn * C : tok0) * K;
+            r_S.fetch(qp, ldq, tid);
+            r_dS.fetch(qp + VB * ldq, ldq, tid);
+            TileRegs<T, C, K, PT_> r_Kt;
             r_Kt.fetch(static_cast<const T *>(a.kt) + bhn * C * K, (size_t)K, tid);
+#pragma unroll
+            for (int m = 0; m < r_Kt.NV; ++m) (m < NVP ? r_dOV.vec(m) : r_EdE.vec(m - NVP)) = r_Kt.v[m];
         }
         __syncthreads();
-        if (v0 == 0) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) gam_rb[r] = Egs[rb * 16 + acc_row(lane, r)];
-        }
-        // <dS', S> over this slab (with per-channel gates: column by column, thread tid keeps column tid % K)
+        // <dS', S> over this slab with per-channel gates: column by column, thread tid keeps column tid % K
         if (GV) {
             for (int idx = tid; idx < VB * K; idx += PT_) {
                 const int r = idx / K, c = idx % K;
                 ss_part += to_f32(Ss[r * LDK + c]) * to_f32(dSs[r * LDK + c]);
-            }
-        } else {
-            constexpr int VN = 16 / sizeof(T);
-            for (int v = tid; v < VB * K / VN; v += PT_) {
-                const int r = v / (K / VN), c = (v % (K / VN)) * VN;
-                ss_part = dot_vec<T>(*reinterpret_cast<const u32x4 *>(Ss + r * LDK + c),
-                                     *reinterpret_cast<const u32x4 *>(dSs + r * LDK + c), ss_part);
             }
         }
         // (1) dR = T^T dE, rows j = 16*rb.. ; (2) R0 = V - gamma . (K S^T), same rows
@@ -476,8 +466,8 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
 #pragma unroll
                 for (int q = 0; q < NVW; ++q) {
                     const int vt = (wave % WPR) * NVW + q;
-                    typename Mfma<T>::Frag fe = Mfma<T>::template load<true>(dEts + vt * 16 * LDC + k0, LDC, lane);
-                    dr[q] = Mfma<T>::mma(ft, fe, f32x4{0.f, 0.f, 0.f, 0.f});
+                    typename Mfma<T>::Frag fe = Mfma<T>::template load<true>(dEts + vt * 16 * LDE + k0, LDE, lane);
+                    dr[q] = Mfma<T>::mma(fe, ft, f32x4{0.f, 0.f, 0.f, 0.f});
                 }
             }
             for (int kk = k0 + KS; kk < C; kk += KS) {
@@ -485,10 +475,11 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
 #pragma unroll
                 for (int q = 0; q < NVW; ++q) {
                     const int vt = (wave % WPR) * NVW + q;
-                    typename Mfma<T>::Frag fe = Mfma<T>::template load<true>(dEts + vt * 16 * LDC + kk, LDC, lane);
-                    dr[q] = Mfma<T>::mma(ft, fe, dr[q]);
+                    typename Mfma<T>::Frag fe = Mfma<T>::template load<true>(dEts + vt * 16 * LDE + kk, LDE, lane);
+                    dr[q] = Mfma<T>::mma(fe, ft, dr[q]);
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kk = 0; kk < K; kk += KS) {
                 typename Mfma<T>::Frag fk = Mfma<T>::template load<true>(Ks + rb * 16 * LDK + kk, LDK, lane);
@@ -496,22 +487,28 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
                 for (int q = 0; q < NVW; ++q) {
                     const int vt = (wave % WPR) * NVW + q;
                     typename Mfma<T>::Frag fs = Mfma<T>::template load<true>(Ss + vt * 16 * LDK + kk, LDK, lane);
-                    ks[q] = Mfma<T>::mma(fk, fs, kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : ks[q]);
+                    ks[q] = Mfma<T>::mma(fs, fk, kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : ks[q]);
                 }
             }
 #pragma unroll
             for (int q = 0; q < NVW; ++q) {
                 const int vt = (wave % WPR) * NVW + q;
+                const int i = rb * 16 + acc_col(lane), c = vt * 16 + acc_row(lane, 0);
+                const f32x4 vv = load4(Vs + i * LDV + c);
+                const float gam = Egs[i], bet = Bs[i];
+                f32x4 dv;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int i = rb * 16 + acc_row(lane, r), c = vt * 16 + acc_col(lane);
-                    const float r0 = to_f32(Vs[i * LDV + c]) - gam_rb[r] * ks[q][r];
-                    dbeta_part[r] += dr[q][r] * r0;
+                    dbeta_part = __builtin_fmaf(dr[q][r], vv[r] - gam * ks[q][r], dbeta_part);
+                    dv[r] = bet * dr[q][r];
                 }
-                store_tile(dRs + rb * 16 * LDV + vt * 16, LDV, dr[q], lane);
+                store4(dRs + i * LDV + c, dr[q]);
+                const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * a.V) + (uint32_t)(v0 + c)) * (uint32_t)sizeof(T);
+                store4(reinterpret_cast<T *>(reinterpret_cast<char *>(static_cast<T *>(a.dv) + tok0 * a.V) + go), dv);
             }
         }
         __syncthreads();
+        OSDN_BP_FRESH();
         // (3,4) dP += dO E^T, dA -= dR E^T on the lower tiles
 #pragma unroll
         for (int t = 0; t < NLT; ++t) {
@@ -520,11 +517,11 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
                 const int ib = idx < 1 ? 0 : idx < 3 ? 1 : idx < 6 ? 2 : 3;
                 const int jb = idx - (ib * (ib + 1)) / 2;
                 for (int kk = 0; kk < VB; kk += KS) {
-                    typename Mfma<T>::Frag fb = Mfma<T>::template load<false>(Ets + kk * LDC + jb * 16, LDC, lane);
+                    typename Mfma<T>::Frag fb = Mfma<T>::template load<false>(Ets + kk * LDE + jb * 16, LDE, lane);
                     typename Mfma<T>::Frag fo = Mfma<T>::template load<true>(dOs + ib * 16 * LDV + kk, LDV, lane);
                     typename Mfma<T>::Frag fr = Mfma<T>::template load<true>(dRs + ib * 16 * LDV + kk, LDV, lane);
-                    dP[t] = Mfma<T>::mma(fo, fb, dP[t]);
-                    dA[t] = Mfma<T>::mma(fr, fb, dA[t]);
+                    dP[t] = Mfma<T>::mma(fb, fo, dP[t]);
+                    dA[t] = Mfma<T>::mma(fb, fr, dA[t]);
                 }
             }
         }
@@ -538,34 +535,25 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
                     const int ib = ib0 + iq;
                     typename Mfma<T>::Frag fo = Mfma<T>::template load<true>(dOs + ib * 16 * LDV + kk, LDV, lane);
                     typename Mfma<T>::Frag fr = Mfma<T>::template load<true>(dRs + ib * 16 * LDV + kk, LDV, lane);
-                    typename Mfma<T>::Frag fe = Mfma<T>::template load<false>(Ets + kk * LDC + ib * 16, LDC, lane);
-                    dQg[iq] = Mfma<T>::mma(fo, fs, dQg[iq]);
-                    dKg[iq] = Mfma<T>::mma(fr, fs, dKg[iq]);
-                    dKr[iq] = Mfma<T>::mma(fe, fd, dKr[iq]);
+                    typename Mfma<T>::Frag fe = Mfma<T>::template load<false>(Ets + kk * LDE + ib * 16, LDE, lane);
+                    dQg[iq] = Mfma<T>::mma(fs, fo, dQg[iq]);
+                    dKg[iq] = Mfma<T>::mma(fs, fr, dKg[iq]);
+                    dKr[iq] = Mfma<T>::mma(fd, fe, dKr[iq]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
-        __syncthreads();
-        // dV = beta . dR for this slab, staged through the dO buffer
-        {
-            constexpr int VN = 16 / sizeof(T);
-            for (int v = tid; v < C * VB / VN; v += PT_) {
-                const int r = v / (VB / VN), c = (v % (VB / VN)) * VN;
-                const u32x4 in = *reinterpret_cast<const u32x4 *>(dRs + r * LDV + c);
-                float o[VN];
-#pragma unroll
-                for (int e = 0; e < VN; ++e) o[e] = Bs[r] * vec_get<T>(in, e);
-                store_vec_t(dOs + r * LDV + c, o);
-            }
-        }
-        __syncthreads();
-        store_tile_global(static_cast<T *>(a.dv) + tok0 * a.V + v0, tstride * a.V, dOs, LDV, C, VB, tid, PT_);
     }
     __syncthreads();
     // ---- after the walk: Q, K~ into the pool ----
-    r_Q.put(Qs, LDK, tid);
-    r_Kt.put(Kts, LDK, tid);
-    if (task + 1 < ntask) OSDN_BP_ISSUE(n + 1)
+    r_S.put(Qs, LDK, tid);
+    r_dS.put(Qs + VB * LDK, LDK, tid);
+    {
+        TileRegs<T, C, K, PT_> r_Kt;
+#pragma unroll
+        for (int m = 0; m < r_Kt.NV; ++m) r_Kt.v[m] = m < NVP ? r_dOV.vec(m) : r_EdE.vec(m - NVP);
+        r_Kt.put(Kts, LDK, tid);
+    }
     {                                                   // upper triangle of cA, cP is zero
         constexpr int VN = 16 / sizeof(T);
         for (int v = tid; v < C * C / VN; v += PT_) {
@@ -577,15 +565,17 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     if (GV) colss[GV ? tid : 0] = ss_part;               // thread tid summed rows of column tid % K
     ss_part = wave_sum(ss_part);
     if (lane == 0) sdot[wave] = ss_part;
-    for (int idx = tid; idx < 4 * C; idx += PT_) { red[idx] = 0.f; red2[idx] = 0.f; red3[idx] = 0.f; }
-    for (int idx = tid; idx < PW_ * C; idx += PT_) pq[idx] = 0.f;          // row-dot partials: a wavefront fills its own row blocks
-    // dbeta: the walk's part, reduced over the 16 lanes of a row; two waves share a row block
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const float sred = row16_sum(dbeta_part[r]);
-        if (acc_col(lane) == 0) dbeta_s[(wave % WPR) * C + rb * 16 + acc_row(lane, r)] = sred;
+    for (int idx = tid; idx < 4 * C; idx += PT_) {
+        red[idx] = 0.f;
+        if (!GV) { red2[idx] = 0.f; red3[idx] = 0.f; }
     }
+    if (!GV)
+        for (int idx = tid; idx < PW_ * C; idx += PT_) pq[idx] = 0.f;          // row-dot partials: a wavefront fills its own row blocks
+    // dbeta: the walk's part, summed over the four lanes of a token; WPR wavefronts share a row block
+    dbeta_part = add_xor32(add_xor16(dbeta_part));
+    if (lane < 16) dbeta_s[(wave % WPR) * C + rb * 16 + lane] = dbeta_part;
     __syncthreads();
+    OSDN_BP_FRESH();
     // ---- lower tiles: A0, P, X, cA, cP ----
 #pragma unroll
     for (int t = 0; t < NLT; ++t) {
@@ -593,52 +583,55 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
         if (idx < 10) {
             const int ib = idx < 1 ? 0 : idx < 3 ? 1 : idx < 6 ? 2 : 3;
             const int jb = idx - (ib * (ib + 1)) / 2;
-            const f32x4 kk = mma_tile0<T, true, true>(Ks + ib * 16 * LDK, LDK, Kts + jb * 16 * LDK, LDK, K, lane);
-            const f32x4 qk = mma_tile0<T, true, true>(Qs + ib * 16 * LDK, LDK, Kts + jb * 16 * LDK, LDK, K, lane);
-            f32x4 ca, cp;
-            float colx = 0.f;
+            const f32x4 kk = mma_tile0<T, true, true>(Kts + jb * 16 * LDK, LDK, Ks + ib * 16 * LDK, LDK, K, lane);
+            __builtin_amdgcn_sched_barrier(0);
+            const f32x4 qk = mma_tile0<T, true, true>(Kts + jb * 16 * LDK, LDK, Qs + ib * 16 * LDK, LDK, K, lane);
+            f32x4 ca, cp, colx;
+            const int i = ib * 16 + acc_col(lane), j0 = jb * 16 + acc_row(lane, 0);
+            const float Gi = Gs[i], bi = Bs[i];
+            const f32x4 Gj = *reinterpret_cast<const f32x4 *>(Gs + j0);
+            float rs_a = 0.f, rs_x = 0.f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int i = ib * 16 + acc_row(lane, r), j = jb * 16 + acc_col(lane);
-                const float gam = (j <= i) ? __expf(Gs[i] - Gs[j]) : 0.f;
+                const int j = j0 + r;
+                const float gam = (j <= i) ? __expf(Gi - Gj[r]) : 0.f;
                 const float da = (j < i) ? -dA[t][r] : 0.f;             // dA_ij
                 const float dp = (j <= i) ? a.scale * dP[t][r] : 0.f;   // dP_ij
                 const float a0 = gam * kk[r];                            // A_ij / beta_i
-                const float x = da * Bs[i] * a0 + dp * gam * qk[r];      // dA.A + dP.P
-                ca[r] = da * Bs[i] * gam;
+                colx[r] = da * bi * a0 + dp * gam * qk[r];              // dA.A + dP.P
+                ca[r] = da * bi * gam;
                 cp[r] = dp * gam;
-                const float rs_a = row16_sum(da * a0);
-                const float rs_x = row16_sum(x);
-                if (acc_col(lane) == 0) {
-                    red[jb * C + i] = rs_a;          // each (jb, i) is written by exactly one lane
-                    red2[jb * C + i] = rs_x;
-                }
-                colx += x;
+                rs_a = __builtin_fmaf(da, a0, rs_a);
+                rs_x += colx[r];
             }
-            colx += __shfl_xor(colx, 16, 64);
-            colx += __shfl_xor(colx, 32, 64);
-            if (lane < 16) red3[ib * C + jb * 16 + lane] = colx;     // each (ib, j) written once
-            store_tile(cAs + ib * 16 * LDC + jb * 16, LDC, ca, lane);
-            store_tile(cPs + ib * 16 * LDC + jb * 16, LDC, cp, lane);
+            rs_a = add_xor32(add_xor16(rs_a));
+            if (lane < 16) red[jb * C + i] = rs_a;              // each (jb, i) is written by exactly one lane
+            if (!GV) {
+                rs_x = add_xor32(add_xor16(rs_x));
+                if (lane < 16) red2[jb * C + i] = rs_x;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) colx[r] = row16_sum(colx[r]);
+                if (acc_col(lane) == 0) *reinterpret_cast<f32x4 *>(red3 + ib * C + j0) = colx;    // each (ib, j) written once
+            }
+            store_tile_t(cAs + ib * 16 * LDC + jb * 16, LDC, ca, lane);
+            store_tile_t(cPs + ib * 16 * LDC + jb * 16, LDC, cp, lane);
         }
     }
     __syncthreads();
+    OSDN_BP_FRESH();
     // ---- dQ, dK (read side), dK~ and the inner products that enter dG (column tile ct) ----
     // dG_i takes <d(gamma Q)_i, gamma_i Q_i> + <d(gamma K)_i, gamma_i K_i> - <d(rho K~)_i, rho_i K~_i>
     // as one number per row; the last term, summed over all rows, goes to the chunk's last token
-    float tc[IBN][4];                             // [row block][r]: that combination over this wave's columns
     float trs = 0.f;                              // the last term over this lane's elements
-#pragma unroll
-    for (int ib = 0; ib < IBN; ++ib)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) tc[ib][r] = 0.f;
     T *dq_g = static_cast<T *>(a.dq) + tok0 * K;
     T *dk_g = static_cast<T *>(a.dk_read) + bhn * C * K;
     T *dkt_g = static_cast<T *>(a.dkt) + bhn * C * K;
-    float dgc = 0.f;
+    f32x4 dgc = {0.f, 0.f, 0.f, 0.f};
     if (has_ct) {
 #pragma unroll
         for (int iq = 0; iq < IBN; ++iq) {
+            OSDN_BP_FRESH();
+            __builtin_amdgcn_sched_barrier(0);
             const int ib = ib0 + iq;
             f32x4 aq, ak, at;                   // the first product of each takes 0 as its addend
             const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -648,8 +641,8 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
                 typename Mfma<T>::Frag fk = Mfma<T>::template load<false>(Kts + kk * LDK + ct, LDK, lane);
                 typename Mfma<T>::Frag fp = Mfma<T>::template load<true>(cPs + ib * 16 * LDC + kk, LDC, lane);
                 typename Mfma<T>::Frag fa = Mfma<T>::template load<true>(cAs + ib * 16 * LDC + kk, LDC, lane);
-                if (kk == 0) { aq = Mfma<T>::mma(fp, fk, zero); ak = Mfma<T>::mma(fa, fk, zero); }
-                else { aq = Mfma<T>::mma(fp, fk, aq); ak = Mfma<T>::mma(fa, fk, ak); }
+                if (kk == 0) { aq = Mfma<T>::mma(fk, fp, zero); ak = Mfma<T>::mma(fk, fa, zero); }
+                else { aq = Mfma<T>::mma(fk, fp, aq); ak = Mfma<T>::mma(fk, fa, ak); }
             }
             // cA^T K + cP^T Q: rows j = 16*ib.., contraction over i >= j
             const int k0 = (ib * 16) / KS * KS;
@@ -658,51 +651,49 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
                 typename Mfma<T>::Frag fpt = Mfma<T>::template load<false>(cPs + k0 * LDC + ib * 16, LDC, lane);
                 typename Mfma<T>::Frag fkk = Mfma<T>::template load<false>(Ks + k0 * LDK + ct, LDK, lane);
                 typename Mfma<T>::Frag fqq = Mfma<T>::template load<false>(Qs + k0 * LDK + ct, LDK, lane);
-                at = Mfma<T>::mma(fat, fkk, zero);
-                at = Mfma<T>::mma(fpt, fqq, at);
+                at = Mfma<T>::mma(fkk, fat, zero);
+                at = Mfma<T>::mma(fqq, fpt, at);
             }
             for (int kk = k0 + KS; kk < C; kk += KS) {
                 typename Mfma<T>::Frag fat = Mfma<T>::template load<false>(cAs + kk * LDC + ib * 16, LDC, lane);
                 typename Mfma<T>::Frag fpt = Mfma<T>::template load<false>(cPs + kk * LDC + ib * 16, LDC, lane);
                 typename Mfma<T>::Frag fkk = Mfma<T>::template load<false>(Ks + kk * LDK + ct, LDK, lane);
                 typename Mfma<T>::Frag fqq = Mfma<T>::template load<false>(Qs + kk * LDK + ct, LDK, lane);
-                at = Mfma<T>::mma(fat, fkk, at);
-                at = Mfma<T>::mma(fpt, fqq, at);
+                at = Mfma<T>::mma(fkk, fat, at);
+                at = Mfma<T>::mma(fqq, fpt, at);
             }
+            const int i = ib * 16 + acc_col(lane), c = ct + acc_row(lane, 0);
+            const float gam = a.scale * Egs[i], bgam = -Bs[i] * Egs[i], rho = GV ? 1.f : Ers[i];
+            const f32x4 qv = load4(Qs + i * LDK + c), kv = load4(Ks + i * LDK + c), ktv = load4(Kts + i * LDK + c);
+            float sc = 0.f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int i = ib * 16 + acc_row(lane, r), c = ct + acc_col(lane);
-                const float gam = Egs[i], rho = Ers[i];
-                const float gq = a.scale * gam * dQg[iq][r];         // gamma . d(gamma Q)
-                const float gk = -Bs[i] * gam * dKg[iq][r];           // gamma . d(gamma K)
-                const float gr = (GV ? 1.f : rho) * dKr[iq][r];       // rho . d(rho K~)
-                const float qv = to_f32(Qs[i * LDK + c]), kv = to_f32(Ks[i * LDK + c]),
-                            ktv = to_f32(Kts[i * LDK + c]);
-                if (GV) dgc = __builtin_fmaf(ktv, dKr[iq][r], dgc);
-                tc[iq][r] = __builtin_fmaf(gq, qv, __builtin_fmaf(gk, kv, -(gr * ktv)));
-                trs = __builtin_fmaf(gr, ktv, trs);
-                const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * K) + (uint32_t)c) * (uint32_t)sizeof(T);
-                *reinterpret_cast<T *>(reinterpret_cast<char *>(dq_g) + go) = from_f32<T>(aq[r] + gq);
-                const uint32_t gt = ((uint32_t)i * K + (uint32_t)c) * (uint32_t)sizeof(T);
-                *reinterpret_cast<T *>(reinterpret_cast<char *>(dk_g) + gt) = from_f32<T>(ak[r] + gk);
-                *reinterpret_cast<T *>(reinterpret_cast<char *>(dkt_g) + gt) = from_f32<T>(at[r] + gr);
+                const float gq = gam * dQg[iq][r];            // gamma . d(gamma Q)
+                const float gk = bgam * dKg[iq][r];           // gamma . d(gamma K)
+                const float gr = rho * dKr[iq][r];            // rho . d(rho K~)
+                if (GV) {
+                    dgc[r] = __builtin_fmaf(ktv[r], gr, dgc[r]);
+                } else {
+                    sc += __builtin_fmaf(gq, qv[r], __builtin_fmaf(gk, kv[r], -(gr * ktv[r])));
+                    trs = __builtin_fmaf(gr, ktv[r], trs);
+                }
+                aq[r] += gq; ak[r] += gk; at[r] += gr;
             }
+            if (!GV) {              // over the four lanes of a token here, over the column tiles through LDS
+                sc = add_xor32(add_xor16(sc));
+                if (lane < 16) pq[wave * C + i] = sc;
+            }
+            const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * K) + (uint32_t)c) * (uint32_t)sizeof(T);
+            store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dq_g) + go), aq);
+            const uint32_t gt = ((uint32_t)i * K + (uint32_t)c) * (uint32_t)sizeof(T);
+            store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dk_g) + gt), ak);
+            store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dkt_g) + gt), at);
         }
     }
-    if (GV && has_ct) {                 // column sums over the rows: lanes 16 apart share a column
-        dgc += __shfl_xor(dgc, 16, 64);
-        dgc += __shfl_xor(dgc, 32, 64);
-        if (lane < 16) dgam_s[GV ? (wave / NCT) * K + ct + lane : 0] = dgc;
-    }
-    // per-row sums across the 16 lanes of a row, then across waves through LDS
-    if (has_ct) {
+    if (GV && has_ct) {                 // channel sums over the rows: the 16 lanes of a channel group
 #pragma unroll
-        for (int iq = 0; iq < IBN; ++iq)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float sc = row16_sum(tc[iq][r]);
-                if (acc_col(lane) == 0) pq[wave * C + (ib0 + iq) * 16 + acc_row(lane, r)] = sc;
-            }
+        for (int r = 0; r < 4; ++r) dgc[r] = row16_sum(dgc[r]);
+        if (acc_col(lane) == 0) *reinterpret_cast<f32x4 *>(dgam_s + (GV ? (wave / NCT) * K + ct + acc_row(lane, 0) : 0)) = dgc;
     }
     trs = wave_sum(trs);
     if (lane == 0) trsum_s[wave] = trs;
@@ -717,18 +708,18 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
     }
     if (wave == 0) {
         const int i = lane;
-        float t_c = 0.f;
-#pragma unroll
-        for (int w = 0; w < PW_; ++w) t_c += pq[w * C + i];
         const float rowa = red[i] + red[C + i] + red[2 * C + i] + red[3 * C + i];
-        const float rowx = red2[i] + red2[C + i] + red2[2 * C + i] + red2[3 * C + i];
-        const float colx = red3[i] + red3[C + i] + red3[2 * C + i] + red3[3 * C + i];
         const size_t th = tok0 + (size_t)i * tstride;
         float dbw = rowa;
 #pragma unroll
         for (int w = 0; w < WPR; ++w) dbw += dbeta_s[w * C + i];
         a.dbeta[th] = dbw;
-        if (a.dlog_alpha) {
+        if (!GV && a.dlog_alpha) {
+            float t_c = 0.f;
+#pragma unroll
+            for (int w = 0; w < PW_; ++w) t_c += pq[w * C + i];
+            const float rowx = red2[i] + red2[C + i] + red2[2 * C + i] + red2[3 * C + i];
+            const float colx = red3[i] + red3[C + i] + red3[2 * C + i] + red3[3 * C + i];
             float dG = rowx - colx + t_c;
             float ssum = 0.f, tr_sum = 0.f;
 #pragma unroll
@@ -737,7 +728,6 @@ __global__ __launch_bounds__(PW_ * 64) void bwd_post_kernel(ChunkArgs a) {
             a.dlog_alpha[th] = wave_suffix_sum(dG, lane);
         }
     }
-    }   // task
 }
 
 // -------------------------------------------------------------- launchers ----
@@ -761,25 +751,13 @@ int launch_bwd_chain(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
     if (a.gate_vec) return bf16_io ? launch_chain_v<bf16, true>(a, st) : launch_chain_v<float, true>(a, st);
     return bf16_io ? launch_chain_v<bf16, false>(a, st) : launch_chain_v<float, false>(a, st);
 }
-constexpr int BP_MIN_WGS = 2048;
 template <typename T, bool GV>
 static int launch_post_t(const ChunkArgs &a, hipStream_t st) {
-    constexpr int PW = 8;           // wavefronts per workgroup (16 was measured for bf16: the kernel then
-                                    // has to fit 128 registers, spills, and takes twice as long)
-    // two chunks per workgroup when the launch still fills the chip many times over (one workgroup per CU)
-    const int chunks = a.n1 - a.n0;
-    constexpr bool PAIRABLE = sizeof(T) == 2 && !GV;     // elsewhere the prefetch registers would spill
-    const bool pairs = PAIRABLE && chunks >= 2 && (long long)chunks * a.H * a.B >= BP_MIN_WGS;
-    dim3 grid((pairs ? (chunks + 1) / 2 : chunks) * a.H, a.B), block(PW * 64);
+    constexpr int PW = 8;           // wavefronts per workgroup
+    dim3 grid((a.n1 - a.n0) * a.H, a.B), block(PW * 64);
     if (GV && (!a.dgamC || a.log_alpha || a.dlog_alpha)) return -1;
-    if (pairs) {
-        if (a.K == 64) hipLaunchKernelGGL((bwd_post_kernel<T, 64, GV, PW, PAIRABLE>), grid, block, 0, st, a);
-        else if (a.K == 128) hipLaunchKernelGGL((bwd_post_kernel<T, 128, GV, PW, PAIRABLE>), grid, block, 0, st, a);
-        else return -1;
-        return 0;
-    }
-    if (a.K == 64) hipLaunchKernelGGL((bwd_post_kernel<T, 64, GV, PW, false>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((bwd_post_kernel<T, 128, GV, PW, false>), grid, block, 0, st, a);
+    if (a.K == 64) hipLaunchKernelGGL((bwd_post_kernel<T, 64, GV, PW>), grid, block, 0, st, a);
+    else if (a.K == 128) hipLaunchKernelGGL((bwd_post_kernel<T, 128, GV, PW>), grid, block, 0, st, a);
     else return -1;
     return 0;
 }

@@ -146,6 +146,21 @@ __device__ __forceinline__ void store_tile_t<bf16>(bf16 *dst, int ld, f32x4 acc,
     *reinterpret_cast<bf16x4 *>(dst + acc_col(lane) * ld + acc_row(lane, 0)) = v;
 }
 
+// four adjacent elements <-> fp32 (8 or 16 bytes, aligned to that)
+__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+__device__ __forceinline__ f32x4 load4(const bf16 *p) {
+    const u32x2 w = *reinterpret_cast<const u32x2 *>(p);
+    return f32x4{__builtin_bit_cast(float, w[0] << 16), __builtin_bit_cast(float, w[0] & 0xffff0000u),
+                 __builtin_bit_cast(float, w[1] << 16), __builtin_bit_cast(float, w[1] & 0xffff0000u)};
+}
+__device__ __forceinline__ void store4(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
+__device__ __forceinline__ void store4(bf16 *p, f32x4 v) {
+    bf16x4 o;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r] = (bf16)v[r];
+    *reinterpret_cast<bf16x4 *>(p) = o;
+}
+
 // acc(row m, col c) = X[m][c0 + c], a 16x16 block of a row-major LDS tile (X points at its
 // first row), obtained by multiplying with a 0/1 selector on the MFMA unit (exact).  Followed
 // by store_tile_t this transposes a block with vector LDS accesses only.
@@ -294,6 +309,39 @@ struct TileRegs {
         for (int m = 0; m < NV; ++m) {
             const int i = tid + m * NT_, r = i / VPR, c = (i % VPR) * VN;
             if (TOTAL % NT_ == 0 || i < TOTAL) *reinterpret_cast<u32x4 *>(s + r * s_ld + c) = v[m];
+        }
+    }
+    // acc + this thread's part of the inner product of two tiles
+    static __device__ __forceinline__ float dot(const TileRegs &x, const TileRegs &y, float acc, int tid) {
+#pragma unroll
+        for (int m = 0; m < NV; ++m)
+            if (TOTAL % NT_ == 0 || tid + m * NT_ < TOTAL) acc = dot_vec<T>(x.v[m], y.v[m], acc);
+        return acc;
+    }
+};
+
+// Two tiles of the same shape at once: small ones by half of the threads each.
+template <typename T, int ROWS, int COLS, int NT_>
+struct PairRegs {
+    static constexpr bool SPLIT = 2 * ROWS * COLS * (int)sizeof(T) / 16 <= NT_;
+    static constexpr int NTH = SPLIT ? NT_ / 2 : NT_;
+    TileRegs<T, ROWS, COLS, NTH> r[SPLIT ? 1 : 2];
+    static constexpr int NV1 = TileRegs<T, ROWS, COLS, NTH>::NV, NVP = NV1 * (SPLIT ? 1 : 2);
+    __device__ __forceinline__ u32x4 &vec(int m) { return r[m / NV1].v[m % NV1]; }
+    __device__ __forceinline__ void fetch(const T *g0, const T *g1, size_t g_ld, int tid, int wave) {
+        if (SPLIT) {
+            r[0].fetch(wave < NTH / 64 ? g0 : g1, g_ld, tid & (NTH - 1));
+        } else {
+            r[0].fetch(g0, g_ld, tid);
+            r[SPLIT ? 0 : 1].fetch(g1, g_ld, tid);
+        }
+    }
+    __device__ __forceinline__ void put(T *s0, T *s1, int s_ld, int tid, int wave) const {
+        if (SPLIT) {
+            r[0].put(wave < NTH / 64 ? s0 : s1, s_ld, tid & (NTH - 1));
+        } else {
+            r[0].put(s0, s_ld, tid);
+            r[SPLIT ? 0 : 1].put(s1, s_ld, tid);
         }
     }
 };
