@@ -142,3 +142,35 @@ def test_step_argument_errors():
     with pytest.raises(ob.OsdnError):        # d_out must not be d_in
         ob.osdn_step(p, z, z, z, z[..., 0].contiguous(), None, None, d, None, z.clone(),
                      torch.zeros(1, 1, 64, 64, device="cuda"), d)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("retention,gate", [("head", "head"), ("channel", "channel"), (None, None)])
+@pytest.mark.parametrize("B,T,H,K,V", [
+    (1, 4, 1, 128, 64),      # 16 rows per workgroup, one block of tokens
+    (1, 5, 3, 64, 128),      # ... one token left over
+    (2, 63, 1, 128, 64),
+    (1, 2, 17, 64, 512),     # 32 rows per workgroup (more than 512 slices of 16 rows), less than a block
+    (1, 7, 17, 128, 512),
+])
+def test_tokens_of_one_call_equal_single_calls(B, T, H, K, V, retention, gate, bf16):
+    """A call of several tokens gives, bit for bit, what that many calls of one token give: every sum
+    of the several-token kernel is formed in the order of the one-token kernel, which the oracle pins."""
+    g = torch.Generator(device="cuda").manual_seed(B * 1000 + T)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    dt = torch.bfloat16 if bf16 else torch.float32
+    shape = {None: None, "head": (B, T, H), "channel": (B, T, H, K)}
+    sh, sr = shape[gate], shape[retention]
+    x = dict(q=rnd(B, T, H, K).to(dt), k=(rnd(B, T, H, K) / K ** 0.5).to(dt), v=rnd(B, T, H, V).to(dt),
+             beta=torch.sigmoid(rnd(B, T, H)),
+             log_alpha=None if sh is None else -torch.nn.functional.softplus(rnd(*sh)),
+             retention=None if sr is None else torch.sigmoid(4.0 + rnd(*sr)))
+    d0, S0 = (1.0 + 0.1 * rnd(B, H, K)).clamp(0.5, 2.0), 0.1 * rnd(B, H, V, K)
+    hp = ob.Hyper(eta=0.5)
+    o_all, S_all, d_all = ob.step(*x.values(), d0, S0, hp)
+    S, d, outs = S0, d0, []
+    for i in range(T):
+        o, S, d = ob.step(*(None if a is None else a[:, i:i + 1].contiguous() for a in x.values()), d, S, hp)
+        outs.append(o)
+    assert torch.equal(torch.cat(outs, 1), o_all)
+    assert torch.equal(S, S_all) and torch.equal(d, d_all)
