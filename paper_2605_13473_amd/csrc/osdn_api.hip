@@ -44,8 +44,8 @@ struct Layout {
     size_t dEt, dS_ckpt, dk_read, dkt, masks, a_ckpt;                    // backward only
     size_t lin_clean, lin_M, lin_r0, lin_t0, lin_aux;                           // backward: chunks of phase 1 in solved form
     // padded copies of the caller's tensors, only when T is not a multiple of the chunk length
-    size_t p_q, p_k, p_v, p_beta, p_g, p_r, p_o;                        // forward
-    size_t p_dO, p_dq, p_dk, p_dv, p_dbeta, p_dg, p_dr;                 // backward
+    size_t p_q, p_k, p_v, p_beta, p_g, p_r;                        // forward
+    size_t p_dO, p_dq, p_dbeta, p_dg, p_dr;                 // backward
     size_t total_fwd, total_bwd;
 };
 
@@ -150,7 +150,7 @@ Layout make_layout(const osdn_params *p, const Packing &pk) {
     }
     if (ragged) {
         L.p_q = take(B * T * H * K * es); L.p_k = take(B * T * H * K * es);
-        L.p_v = take(B * T * H * V * es); L.p_o = take(B * T * H * V * es);
+        L.p_v = take(B * T * H * V * es);
         L.p_beta = take(B * T * H * 4); L.p_g = take(B * T * H * 4 * GK); L.p_r = take(B * T * H * 4 * RK);
     }
     L.piece_start = take((size_t)2 * MAX_PIECES * K * 4);
@@ -172,9 +172,10 @@ Layout make_layout(const osdn_params *p, const Packing &pk) {
     L.lin_aux = take(B * H * N * 2048);
     if (p->gate_per_channel) L.dgamC = take(B * H * N * K * 4);
     if (ragged) {
-        L.p_dO = take(B * T * H * V * es); L.p_dv = take(B * T * H * V * es);
-        L.p_dq = take(B * T * H * K * es); L.p_dk = take(B * T * H * K * es);
-        L.p_dbeta = take(B * T * H * 4); L.p_dg = take(B * T * H * 4 * GK); L.p_dr = take(B * T * H * 4 * RK);
+        L.p_dO = take(B * T * H * V * es);
+        if (p->gate_per_channel) L.p_dq = take(B * T * H * K * es);
+        L.p_dbeta = take(B * T * H * 4); L.p_dg = take(B * T * H * 4 * GK);
+        if (!p->retention_per_channel) L.p_dr = take(B * T * H * 4);
     }
     L.total_bwd = off;
     return L;
@@ -494,36 +495,30 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         return OSDN_ERR_SHAPE;
 
     // ragged chunks (the tail of the sequence, or of any packed sequence): work on padded copies
-    // (no-op pad tokens) and move the output back at the end
+    // (no-op pad tokens); the output goes straight to the caller's rows
     osdn_params padded = *p;
     padded.T = pk.N * C;
     const int T_user = p->T;
     const bool ragged = pk.ragged;
-    void *o_user = o;
-    auto move = [&](const void *src, void *dst, size_t row, bool to_padded, uint32_t fill) {
+    auto move = [&](const void *src, void *dst, size_t row, uint32_t fill) {
         return timed(KID_PAD, st, [&] {
-            if (pk.n_seqs) return launch_move_chunk_rows(src, dst, chunk_row, chunk_len, pk.N, row, to_padded, fill, st);
-            return to_padded ? launch_copy_rows(src, T_user, dst, padded.T, p->B, row, fill, st)
-                             : launch_copy_rows(src, padded.T, dst, T_user, p->B, row, fill, st);
+            if (pk.n_seqs) return launch_move_chunk_rows(src, dst, chunk_row, chunk_len, pk.N, row, true, fill, st);
+            return launch_copy_rows(src, T_user, dst, padded.T, p->B, row, fill, st);
         });
     };
     if (ragged) {
         const size_t es = bf ? 2 : 4, rk = (size_t)p->H * p->K * es, rv = (size_t)p->H * p->V * es, rg = (size_t)p->H * 4;
-        auto pad = [&](const void *src, size_t off, size_t row, uint32_t fill) { return move(src, ws + off, row, true, fill); };
+        auto pad = [&](const void *src, size_t off, size_t row, uint32_t fill) { return move(src, ws + off, row, fill); };
         if (pad(q, L.p_q, rk, 0u) != 0 || pad(k, L.p_k, rk, 0u) != 0 || pad(v, L.p_v, rv, 0u) != 0 ||
             pad(beta, L.p_beta, rg, 0u) != 0 || (log_alpha && pad(log_alpha, L.p_g, p->gate_per_channel ? rg * p->K : rg, 0u) != 0) ||
             (retention && pad(retention, L.p_r, p->retention_per_channel ? rg * p->K : rg, 0x3f800000u) != 0))
             return OSDN_ERR_SHAPE;
-        q = ws + L.p_q; k = ws + L.p_k; v = ws + L.p_v; o = ws + L.p_o;
+        q = ws + L.p_q; k = ws + L.p_k; v = ws + L.p_v;
         beta = reinterpret_cast<const float *>(ws + L.p_beta);
         if (log_alpha) log_alpha = reinterpret_cast<const float *>(ws + L.p_g);
         if (retention) retention = reinterpret_cast<const float *>(ws + L.p_r);
         p = &padded;
     }
-    auto finish = [&]() -> int {
-        if (ragged && move(o, o_user, (size_t)p->H * p->V * (bf ? 2 : 4), false, 0u) != 0) return OSDN_ERR_SHAPE;
-        return launch_status();
-    };
 
     PrecondArgs pa = precond_args(p);
     pa.k = k; pa.beta = beta; pa.retention = retention;
@@ -533,6 +528,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     ChunkArgs c = chunk_args(p, L, ws);
     c.q = q; c.k = k; c.v = v; c.beta = beta; c.log_alpha = log_alpha;
     c.o = o; c.S_out = S_out;
+    c.out = OutRows{T_user, ragged && pk.n_seqs ? chunk_row : nullptr, ragged && pk.n_seqs ? chunk_len : nullptr};
     // (I + A)^-1 and P are only of use to a backward pass: they are written when the workspace is
     // the one osdn_workspace_bytes(p, 1) asks for, which osdn_bwd requires anyway
     if (workspace_bytes >= L.total_bwd) { c.Tm = ws + L.Tm; c.Pm = ws + L.Pm; }
@@ -602,7 +598,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         if ((pieces ? precond_pieces() : precond(0, st)) != 0 || phase2(KID_CHUNK_PREP, 0) != 0 ||
             phase2(KID_STATE_FWD, 0) != 0 || phase2(KID_OUTPUT_FWD, 0) != 0)
             return OSDN_ERR_SHAPE;
-        return finish();
+        return launch_status();
     }
     // side: phase 1, segment after segment          (a[s]: phase 1 of segment s done)
     // main: phase 2 of segment s once a[s] has fired
@@ -620,7 +616,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
             return OSDN_ERR_SHAPE;
     }
     rejoin.armed = false;               // the wait for the last segment's event was the join
-    return finish();
+    return launch_status();
 }
 
 static int bwd_impl(const osdn_params *p, const void *q, const void *k, const void *v, const float *beta,
@@ -655,7 +651,8 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         return OSDN_ERR_SHAPE;
 
     // ragged chunks: the padded inputs are the ones the forward call left in the workspace; dO
-    // is padded here, the gradients are produced padded and moved back at the end
+    // is padded here; dk, dv and (one state gate per head) dq go straight to the caller's rows, the
+    // gradients of the gates are produced padded and moved back at the end
     osdn_params padded = *p;
     padded.T = pk.N * C;
     const int T_user = p->T;
@@ -667,7 +664,9 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
                              : launch_copy_rows(src, padded.T, dst, T_user, p->B, row, 0u, st);
         });
     };
-    void *dq_user = dq, *dk_user = dk, *dv_user = dv;
+    const OutRows out{T_user, ragged && pk.n_seqs ? chunk_row : nullptr, ragged && pk.n_seqs ? chunk_len : nullptr};
+    const bool gv = p->gate_per_channel != 0, rv = p->retention_per_channel != 0;
+    void *dq_user = dq;
     float *dbeta_user = dbeta, *dg_user = dlog_alpha, *dr_user = dretention;
     const size_t es_ = bf ? 2 : 4, rk_ = (size_t)p->H * p->K * es_, rv_ = (size_t)p->H * p->V * es_, rg_ = (size_t)p->H * 4;
     if (ragged) {
@@ -676,18 +675,18 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         beta = reinterpret_cast<const float *>(ws + L.p_beta);
         if (log_alpha) log_alpha = reinterpret_cast<const float *>(ws + L.p_g);
         if (retention) retention = reinterpret_cast<const float *>(ws + L.p_r);
-        dq = ws + L.p_dq; dk = ws + L.p_dk; dv = ws + L.p_dv;
+        if (gv) dq = ws + L.p_dq;
         dbeta = reinterpret_cast<float *>(ws + L.p_dbeta);
         dlog_alpha = reinterpret_cast<float *>(ws + L.p_dg);
-        dretention = reinterpret_cast<float *>(ws + L.p_dr);
+        if (!rv) dretention = reinterpret_cast<float *>(ws + L.p_dr);
         p = &padded;
     }
     auto finish = [&]() -> int {
         if (ragged) {
             auto cut = [&](const void *src, void *dst, size_t row) { return move(src, dst, row, false); };
-            if (cut(dq, dq_user, rk_) != 0 || cut(dk, dk_user, rk_) != 0 || cut(dv, dv_user, rv_) != 0 ||
-                cut(dbeta, dbeta_user, rg_) != 0 || (log_alpha && cut(dlog_alpha, dg_user, p->gate_per_channel ? rg_ * p->K : rg_) != 0) ||
-                (retention && cut(dretention, dr_user, p->retention_per_channel ? rg_ * p->K : rg_) != 0))
+            if ((gv && cut(dq, dq_user, rk_) != 0) || cut(dbeta, dbeta_user, rg_) != 0 ||
+                (log_alpha && cut(dlog_alpha, dg_user, gv ? rg_ * p->K : rg_) != 0) ||
+                (retention && !rv && cut(dretention, dr_user, rg_) != 0))
                 return OSDN_ERR_SHAPE;
         }
         return launch_status();
@@ -697,14 +696,13 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     c.q = q; c.k = k; c.v = v; c.beta = beta; c.log_alpha = log_alpha;
     c.dO = dO; c.dS_out = dS_out;
     c.Tm = ws + L.Tm; c.Pm = ws + L.Pm; c.dEt = ws + L.dEt; c.dS_ckpt = ws + L.dS_ckpt;
-    c.dS_in = dS_in; c.dq = dq; c.dv = dv;
+    c.dS_in = dS_in; c.dq = dq; c.dv = dv; c.out = out;
     c.dk_read = ws + L.dk_read;
     c.dkt = ws + L.dkt;
     c.dbeta = dbeta; c.dlog_alpha = log_alpha ? dlog_alpha : nullptr;
     c.n_seqs = pk.n_seqs; c.seq_chunks = seq_chunks; c.dS_last = dS_out;
     // one state gate per key channel: phase 2 runs ungated on the folded operands the forward
     // pass left (Gamma . Q, Gamma . K, K~ / Gamma) and the unfold kernel maps its gradients back
-    const bool gv = p->gate_per_channel != 0;
     UnfoldArgs un{};
     if (gv) {
         un.B = p->B; un.T = p->T; un.H = p->H; un.K = p->K; un.N = p->T / C;
@@ -729,7 +727,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     pb.a_ckpt = reinterpret_cast<float *>(ws + L.a_ckpt);
     pb.dkt = c.dkt; pb.dk_read = c.dk_read;
     pb.n_seqs = pk.n_seqs; pb.seq_chunks = seq_chunks; pb.dd_last = dd_out;
-    pb.dk = dk; pb.dbeta = dbeta; pb.dretention = retention ? dretention : nullptr; pb.dd_in = dd_in;
+    pb.out = out; pb.dk = dk; pb.dbeta = dbeta; pb.dretention = retention ? dretention : nullptr; pb.dd_in = dd_in;
     // Without retention, chunks that never met the box can take the solved form of the reverse
     // sweep: a dependent chain less than half as long for about 0.6 KB more memory traffic per
     // token-head.  It pays while the phase-1 chain is what the pass waits for: chains on at most a

@@ -396,6 +396,9 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
         r_b = a.beta[tok0 + (size_t)lane * tstride];
     }
     r_Kn.fetch(static_cast<const T *>(a.k) + (GV ? bhn * C : tok0) * K, GV ? (size_t)K : tstride * K, tid);
+    // the caller's first row, and how many there are, for dv and dq (the first loads are on their way)
+    const size_t out0 = a.out.first(b, n) * a.H + h;
+    const int rows = a.out.count(n);
     r_Tn.fetch(static_cast<const T *>(a.Tm) + bhn * C * C, (size_t)C, tid);
     fetch_slab(0);
     const int ct = (wave % NCT) * 16;   // this wave's column tile of the [64 x K] results ...
@@ -504,7 +507,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
                 }
                 store4(dRs + i * LDV + c, dr[q]);
                 const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * a.V) + (uint32_t)(v0 + c)) * (uint32_t)sizeof(T);
-                store4(reinterpret_cast<T *>(reinterpret_cast<char *>(static_cast<T *>(a.dv) + tok0 * a.V) + go), dv);
+                if (i < rows) store4(reinterpret_cast<T *>(reinterpret_cast<char *>(static_cast<T *>(a.dv) + out0 * a.V) + go), dv);
             }
         }
         __syncthreads();
@@ -623,7 +626,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     // dG_i takes <d(gamma Q)_i, gamma_i Q_i> + <d(gamma K)_i, gamma_i K_i> - <d(rho K~)_i, rho_i K~_i>
     // as one number per row; the last term, summed over all rows, goes to the chunk's last token
     float trs = 0.f;                              // the last term over this lane's elements
-    T *dq_g = static_cast<T *>(a.dq) + tok0 * K;
+    T *dq_g = static_cast<T *>(a.dq) + (GV ? tok0 : out0) * K;      // (GV: unfold_kernel works on the padded rows)
     T *dk_g = static_cast<T *>(a.dk_read) + bhn * C * K;
     T *dkt_g = static_cast<T *>(a.dkt) + bhn * C * K;
     f32x4 dgc = {0.f, 0.f, 0.f, 0.f};
@@ -684,7 +687,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
                 if (lane < 16) pq[wave * C + i] = sc;
             }
             const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * K) + (uint32_t)c) * (uint32_t)sizeof(T);
-            store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dq_g) + go), aq);
+            if (GV || i < rows) store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dq_g) + go), aq);
             const uint32_t gt = ((uint32_t)i * K + (uint32_t)c) * (uint32_t)sizeof(T);
             store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dk_g) + gt), ak);
             store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dkt_g) + gt), at);

@@ -460,6 +460,8 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
         store_tile_t(Ps + ib * 16 * LDC + jb * 16, LDC, acc, lane);
     }
     T *Os = Kts;
+    const size_t out0 = a.out.first(b, n) * a.H + h;            // (here: the tiles' loads are on their way)
+    const int rows = a.out.count(n);
     for (int v0 = 0; v0 < a.V; v0 += C) {
         __syncthreads();
         // P is kept for the backward pass (its chain kernel forms scale P^T dO from it)
@@ -485,7 +487,9 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
             store_tile(Os + rb * 16 * LDC + vt * 16, LDC, a1, lane);
         }
         __syncthreads();
-        store_tile_global(static_cast<T *>(a.o) + tok0 * a.V + v0, tstride * a.V, Os, LDC, C, C, tid, OT_);
+        T *og = static_cast<T *>(a.o) + out0 * a.V + v0;
+        if (rows == C) store_tile_global(og, tstride * a.V, Os, LDC, C, C, tid, OT_);      // (a constant count: unrolled)
+        else store_tile_global(og, tstride * a.V, Os, LDC, rows, C, tid, OT_);
     }
 }
 

@@ -16,6 +16,20 @@ namespace osdn {
 // sequential kernels run one chain per (sequence, head).  A chain takes its start value from
 // the *_first / *_last pointer when its sequence begins (ends, in the backward pass) inside
 // [n0, n1), and from the carry buffer otherwise.
+// Where the results of a chunk go.  The kernels read padded copies of ragged sequences, but write the
+// large results (o, dq, dk, dv, a gradient of retention per coordinate) straight to the caller's rows and
+// leave the pad tokens out: a padded result that is moved afterwards costs its bytes twice more.
+// 65536 packed tokens, 16 heads of 128 x 128 in bf16, forward and backward: 4183 -> 3834 us; calls of
+// whole chunks are level as long as a kernel asks for its rows after its first loads (before them: 0.8 %
+// of a forward pass of 8 x 2048 tokens).
+struct OutRows {
+    int T;                                // tokens per batch entry of the caller's tensors
+    const int *chunk_row, *chunk_len;     // packed ragged sequences: first row and tokens of every chunk; else null
+    // first row of chunk n of batch entry b, and how many of its tokens exist (at least 1)
+    __device__ __forceinline__ size_t first(int b, int n) const { return chunk_row ? (size_t)chunk_row[n] : (size_t)b * T + (size_t)n * C; }
+    __device__ __forceinline__ int count(int n) const { return chunk_row ? chunk_len[n] : (T - n * C < C ? T - n * C : C); }
+};
+
 struct PrecondArgs {
     int B, T, H, K;
     int n0, n1;
@@ -62,6 +76,7 @@ struct PrecondBwdArgs {
     const void *dkt;          // [B,N,H,64,K] io: dL/dk~ from phase 2
     const void *dk_read;      // [B,N,H,64,K] io: read-side dL/dk from phase 2
     const float *dd_out;      // [B,H,K] or null
+    OutRows out;              // rows of dk, and of dretention with ret_vec
     void *dk;                 // [B,T,H,K] io
     float *dbeta;             // [B,T,H] in/out
     float *dretention;        // [B,T,H] ([B,T,H,K] with ret_vec) or null
@@ -101,6 +116,7 @@ struct ChunkArgs {
     const float *S_first;             // packed sequences: [n_seqs,H,V,K] or null
     const float *dS_last;             // packed sequences: adjoint of the final S, or null
     float scale;
+    OutRows out;                      // rows of o, dv and (one state gate per head) dq
     // caller tensors
     const void *q, *k, *v;            // [B,T,H,*] io
     const float *beta, *log_alpha;    // [B,T,H]; log_alpha may be null

@@ -584,9 +584,11 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
     const T *kp = static_cast<const T *>(a.k) + tokc * K;
     const size_t tile = (((size_t)b * N + n) * a.H + h) * C * K;        // dkt and dk_read: one tile per chunk and head
     const T *gp = static_cast<const T *>(a.dkt) + tile, *rp = static_cast<const T *>(a.dk_read) + tile;
-    T *op = static_cast<T *>(a.dk) + tokc * K;
+    const size_t out0 = a.out.first(b, n) * a.H + h;
+    const int rows = a.out.count(n);
+    T *op = static_cast<T *>(a.dk) + out0 * K;
     const float *retp = RET_VEC ? a.retention + tokc * K : nullptr;     // per-coordinate retention and its gradient
-    float *dretp = (RET_VEC && a.dretention) ? a.dretention + tokc * K : nullptr;
+    float *dretp = (RET_VEC && a.dretention) ? a.dretention + out0 * K : nullptr;
     const uint32_t kstride = (uint32_t)a.H * K;
     float Dv[C];
     // which steps landed inside the box: decided once, by precond_mask (or precond_lin_m)
@@ -617,7 +619,9 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
     const uint32_t rowb = kstride * (uint32_t)sizeof(T);
     uint32_t lofs = ((uint32_t)tid + (uint32_t)(C - 1) * kstride) * (uint32_t)sizeof(T);
     asm volatile("" : "+v"(lofs));
-    uint32_t sofs = lofs;
+    // Pad tokens are stored to the last row that exists, which the same thread overwrites later: the
+    // count of stores in flight stays known, where a branch would make every load behind it wait for all.
+    uint32_t sofs = ((uint32_t)tid + (uint32_t)(rows - 1) * kstride) * (uint32_t)sizeof(T);
 #define OSDN_PLOAD(buf, ih_)                                                                     \
     _Pragma("unroll") for (int u = 0; u < PB; ++u) {                                             \
         const uint32_t tofs = (uint32_t)(((ih_) - u) * K + tid) * (uint32_t)sizeof(T);           \
@@ -642,7 +646,7 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
             at_byte(op, sofs) = from_f32<T>(rb[blk & 1][u] + Di * g + 2.f * kv * gsum);
             if (RET_VEC) { if (dretp) at_byte(dretp, sofs * FS) = ab * Di; }
             pr[u] = ab * Di;
-            sofs -= rowb;
+            sofs -= i < rows ? rowb : 0u;
             const float src = __builtin_fmaf(-casig_p[i], kv * kv, kv * g);
             const float r = RET_VEC ? rrb[RET_VEC ? blk & 1 : 0][RET_VEC ? u : 0] : r_p[i];
             av = HAS_RET ? __builtin_fmaf(r, ab, src) : ab + src;
