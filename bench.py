@@ -84,13 +84,14 @@ def kernel_models(cfg, es):
     # solved form of the reverse sweep (only without retention): read k twice and dk~; write the
     # 64 x 64 fp32 inverse, rho0 and the chunk's sum of lambda per chunk
     m["precond_lin"] = ("hbm", th * 3 * K * es + nch * (C * C * 4 + C * 4 + K * 4 + K * 8))
-    # chunk_prep: read k, k~, v, beta, g ; write T, -W^T, (rho k~)^T, U^T
-    m["chunk_prep"] = ("hbm", th * (4 * K * es + 2 * V * es + C * es + 2 * g))
-    # state_fwd: read -W^T, (rho k~)^T, U^T ; write E^T, S checkpoints ; 2 KV-class GEMMs
-    m["state_fwd"] = ("hbm", th * (2 * K * es + 2 * V * es + g) + nch * V * K * es)
+    # chunk_prep: read k, k~, beta, log alpha ; write -W, T diag(beta), the gates (and T when a backward
+    # pass follows)
+    m["chunk_prep"] = ("hbm", th * (3 * K * es + (2 if cfg.backward else 1) * C * es + 5 * g))
+    # state_fwd: read -W, k~, v, T diag(beta), gates ; write E^T, S checkpoints
+    m["state_fwd"] = ("hbm", th * (2 * K * es + 2 * V * es + C * es + 2 * g) + nch * V * K * es)
     # output_fwd: read q, k~, S ckpt, E^T ; write o (and P when a backward pass follows)
     m["output_fwd"] = ("hbm", th * (2 * K * es + 2 * V * es + g + (C * es if cfg.backward else 0)) + nch * V * K * es)
-    # bwd_chain: read -W^T, (rho k~)^T, q, dO, P ; write dE^T, dS' checkpoints
+    # bwd_chain: read -W, k~, q, dO, P ; write dE^T, dS' checkpoints
     m["bwd_chain"] = ("hbm", th * (3 * K * es + 2 * V * es + C * es + g) + nch * V * K * es)
     # bwd_post: read q, k, k~, v, dO, E^T, dE^T, T, S and dS' ckpts ; write dq, dv, dk (read side), dk~, dbeta, dg
     m["bwd_post"] = ("hbm", th * (6 * K * es + 5 * V * es + C * es + 4 * g) + 2 * nch * V * K * es)
