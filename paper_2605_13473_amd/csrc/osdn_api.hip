@@ -36,7 +36,7 @@ template <typename F> int timed(int id, hipStream_t st, F &&launch) {
 }
 
 struct Layout {
-    size_t Qg, Kg, Kd, gamC, dgamC;                                      // per-channel state gate
+    size_t Qg, Kg, Kd, Kw, gamC, dgamC;                                    // per-channel state gate
     size_t tables;                                                       // packed sequences: the index tables
     size_t kt, d_ckpt, tok_scalars, Wn, Tu, gates, Et, S_ckpt;        // forward
     size_t piece_start, piece_map, piece_flags;                          // phase 1 as sweeps over the whole sequence
@@ -141,11 +141,12 @@ Layout make_layout(const osdn_params *p, const Packing &pk) {
     L.tok_scalars = take(B * T * H * 4 * 4);
     L.Wn = take(B * T * H * K * es);
     L.Tu = take(B * H * N * C * C * es);
-    L.gates = take(B * T * H * 3 * 4);
+    if (!p->gate_per_channel) L.gates = take(B * T * H * 3 * 4);
     L.Et = take(B * T * H * V * es);
     L.S_ckpt = take(B * H * N * V * K * es);
     if (p->gate_per_channel) {
         L.Qg = take(B * T * H * K * es); L.Kg = take(B * T * H * K * es); L.Kd = take(B * T * H * K * es);
+        L.Kw = take(B * T * H * K * es);
         L.gamC = take(B * H * N * K * 4);
     }
     if (ragged) {
@@ -203,7 +204,7 @@ ChunkArgs chunk_args(const osdn_params *p, const Layout &L, char *ws) {      // 
     c.B = p->B; c.T = p->T; c.H = p->H; c.K = p->K; c.V = p->V; c.N = p->T / C;
     c.scale = p->scale;
     c.kt = ws + L.kt; c.Wn = ws + L.Wn; c.Tu = ws + L.Tu;
-    c.gates = reinterpret_cast<float *>(ws + L.gates); c.Et = ws + L.Et;
+    c.gates = p->gate_per_channel ? nullptr : reinterpret_cast<float *>(ws + L.gates); c.Et = ws + L.Et;
     c.S_ckpt = ws + L.S_ckpt;
     return c;
 }
@@ -534,14 +535,16 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     if (workspace_bytes >= L.total_bwd) { c.Tm = ws + L.Tm; c.Pm = ws + L.Pm; }
     c.n_seqs = pk.n_seqs; c.seq_chunks = seq_chunks; c.S_first = S_in;
     // one state gate per key channel: chunk_prep folds the channel decays into the operands and
-    // leaves Gamma . Q and K~ / Gamma, on which the state and output kernels run as if ungated
+    // leaves Gamma . Q, K~ / Gamma and gamma_C . K~ / Gamma, on which the output and state kernels run as if ungated
     const bool gv = p->gate_per_channel != 0;
-    ChunkArgs cg = c;                                  // what state_fwd and output_fwd see
+    ChunkArgs cg = c, cs = c;                          // what output_fwd and state_fwd see
     if (gv) {
         c.gate_vec = 1;
-        c.Qg = ws + L.Qg; c.Kg = ws + L.Kg; c.Kd = ws + L.Kd; c.gamC = reinterpret_cast<float *>(ws + L.gamC);
+        c.Qg = ws + L.Qg; c.Kg = ws + L.Kg; c.Kd = ws + L.Kd; c.Kw = ws + L.Kw; c.gamC = reinterpret_cast<float *>(ws + L.gamC);
         cg = c;
         cg.log_alpha = nullptr; cg.q = c.Qg; cg.kt = c.Kd;
+        cs = cg;
+        cs.kt = c.Kw;
     }
 
     const int N = p->T / C;
@@ -556,7 +559,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     // Few chains: the state kernel takes slices of 16 values instead of 32 when its workgroups then
     // still find a CU each (beside those of phase 1, unless phase 1 runs ahead as sweeps over pieces):
     // its time per chunk is latency, not work, and half the work per workgroup shortens it.
-    c.narrow_slices = cg.narrow_slices = chains * (p->V / 16) + (pieces ? 0 : chains) <= NUM_CU;
+    c.narrow_slices = cg.narrow_slices = cs.narrow_slices = chains * (p->V / 16) + (pieces ? 0 : chains) <= NUM_CU;
     auto seg_range = [&](int sidx, int &n0, int &n1) {
         if (crowded) { n0 = seg_begin_grow(N, S, sidx, 1.7); n1 = seg_begin_grow(N, S, sidx + 1, 1.7); return; }
         n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1);
@@ -567,7 +570,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         return timed(KID_PRECOND_FWD, s1, [&] { return launch_precond_fwd(pa, bf, s1); });
     };
     auto phase2 = [&](int kid, int sidx) {
-        ChunkArgs &ck = (gv && kid != KID_CHUNK_PREP) ? cg : c;
+        ChunkArgs &ck = !gv || kid == KID_CHUNK_PREP ? c : kid == KID_STATE_FWD ? cs : cg;
         seg_range(sidx, ck.n0, ck.n1);
         ck.S_in = sidx == 0 ? S_in : S_out;          // S is carried in S_out
         return timed(kid, st, [&] {
@@ -702,7 +705,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     c.dbeta = dbeta; c.dlog_alpha = log_alpha ? dlog_alpha : nullptr;
     c.n_seqs = pk.n_seqs; c.seq_chunks = seq_chunks; c.dS_last = dS_out;
     // one state gate per key channel: phase 2 runs ungated on the folded operands the forward
-    // pass left (Gamma . Q, Gamma . K, K~ / Gamma) and the unfold kernel maps its gradients back
+    // pass left (Gamma . Q, Gamma . K, K~ / Gamma, gamma_C . K~ / Gamma) and the unfold kernel maps its gradients back
     UnfoldArgs un{};
     if (gv) {
         un.B = p->B; un.T = p->T; un.H = p->H; un.K = p->K; un.N = p->T / C;
@@ -711,7 +714,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         un.dgamC = reinterpret_cast<const float *>(ws + L.dgamC);
         un.dlog_alpha = dlog_alpha;
         c.gate_vec = 1;
-        c.q = ws + L.Qg; c.k = ws + L.Kg; c.kt = ws + L.Kd;
+        c.q = ws + L.Qg; c.k = ws + L.Kg;                  // (c.kt: by the kernel, below)
         c.log_alpha = nullptr; c.dlog_alpha = nullptr;
         c.gamC = reinterpret_cast<float *>(ws + L.gamC); c.dgamC = reinterpret_cast<float *>(ws + L.dgamC);
     }
@@ -760,6 +763,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     auto phase2 = [&](int kid, int sidx) {
         seg_range(sidx, c.n0, c.n1);
         c.dS_out = sidx == S - 1 ? dS_out : dS_in;   // dS is carried in dS_in
+        if (gv) c.kt = ws + (kid == KID_BWD_CHAIN ? L.Kw : L.Kd);
         const int rc2 = timed(kid, st, [&] {
             return kid == KID_BWD_CHAIN ? launch_bwd_chain(c, bf, st) : launch_bwd_post(c, bf, st);
         });

@@ -18,10 +18,10 @@
 //             dG from every place G enters; dlog_alpha = suffix sums of dG inside the chunk.
 //
 // With one state gate per key channel (GV) the same kernels run, ungated, on the operands in
-// which the forward pass folded the channel decays (Gamma . Q, Gamma . K, K~ / Gamma); the
-// adjoint at a chunk's end is kept as D = gamma_C . dS' (the chunk's decay per channel; S' =
-// (S + E^T K~/Gamma) Diag(gamma_C)), which takes the place of dS' and rho everywhere, and the unfold
-// kernel at the end of this file maps the gradients back to q, k, k~ and log alpha.
+// which the forward pass folded the channel decays (Gamma . Q, Gamma . K, K~ / Gamma); S' =
+// S Diag(gamma_C) + E^T (gamma_C . K~ / Gamma) with the chunk's decay per channel gamma_C, whose last
+// operand takes the place of rho . K~, and the unfold kernel at the end of this file maps the
+// gradients back to q, k, k~ and log alpha.
 #include "osdn_kernels.h"
 #include "osdn_tile.h"
 
@@ -68,9 +68,10 @@ constexpr int CW_ = 8, CM_ = 2, CS_ = 2, CT_ = (CW_ + CM_ + CS_) * 64;     // wa
 template <typename T, int K> constexpr int BC_NSB = sizeof(T) == 2 ? 2 : (K == 64 ? 2 : 1);
 template <typename T, int K> constexpr int BC_NSC = sizeof(T) == 2 ? 2 : 1;
 
-// GV: one state gate per key channel.  The state adjoint at the end of a chunk then only enters
-// multiplied by the chunk's decay per channel, D = gamma_C . dS': the accumulators carry D at the
-// chunk boundaries, and D is what the checkpoint holds.
+// GV: one state gate per key channel: every coordinate of dS has its own gamma_C, and K~ is
+// gamma_C . K~ / Gamma.  dS' itself is rounded and kept: gamma_C . dS' would lose bits, and then
+// itself, below the smallest normal number (at a decay of e^-79 from |dS'| = 2.4e-4 on), which K~ /
+// Gamma would bring back to the size of dS'.
 // VS: rows of S (values) owned by one workgroup, 32 or 16 (the narrow slice when the chains are few:
 // twice the workgroups, each with half the work on the dependent path per chunk).
 template <typename T, int K, bool GV, int VS>
@@ -121,7 +122,6 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
             load_lds4(a.gates + (bhn * 3 + 1 + w) * C, lane * 4, lds_offset(s + B_G + w * C * 4));
         }
     };
-    // (GV: with the operands of chunk n come the decays of the chunk to its left, whose D follows)
     auto loadC = [&](int n, int slot) {
         const size_t bhn = ((size_t)bt * a.N + n) * a.H + h, tok = ((size_t)bt * a.T + (size_t)n * C) * a.H + h;
         char *s = ringC + slot * C_BYTES;
@@ -129,7 +129,7 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
         if (GV) lK.issue(s + C_Q, static_cast<const char *>(a.q) + bhn * C * RK, RK, mw, lane, slice);
         else lQ.issue(s + C_Q, static_cast<const char *>(a.q) + tok * RK, gK, mw, lane, slice, wideQ);
         if (GV && mw < K / 64)
-            load_lds4(a.gamC + (((size_t)bt * a.N + max(n - 1, 0)) * a.H + h) * K, mw * 256 + lane * 4, lds_offset(s + C_D + mw * 256));
+            load_lds4(a.gamC + bhn * K, mw * 256 + lane * 4, lds_offset(s + C_D + mw * 256));
     };
     // loads of a loader that are newer than the tiles it waits for (at least)
     constexpr int LB = LdsLoad<RK, C, CM_>::MIN + LdsLoad<RC, C, CM_>::MIN + LdsLoad<RV, C, CM_>::MIN, LC = 2 * LdsLoad<RK, C, CM_>::MIN;
@@ -152,11 +152,6 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
         for (int q = 0; q < TPW; ++q) {
             const int v = vs + (vtC + q) * 16 + acc_col(lane), c0 = fb * 16 + acc_row(lane, 0);
             if (a.dS_out) dSt[q] = *reinterpret_cast<const f32x4 *>(a.dS_out + (bh * a.V + v) * K + c0);
-            if (GV) {
-                const f32x4 dc = *reinterpret_cast<const f32x4 *>(a.gamC + (((size_t)bt * a.N + a.n1 - 1) * a.H + h) * K + c0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) dSt[q][r] *= dc[r];
-            }
         }
     }
     if (loader) wait_vm<0>();
@@ -263,7 +258,7 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
 #pragma unroll
                 for (int kk = 0; kk < NKC; ++kk) part = Mfma<T>::mma(PRE ? qf[kk] : fK.tr(tC + C_Q, kk * KS, fb * 16), of[q][kk], part);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) dSt[q][r] = __builtin_fmaf(gC, dSt[q][r], a.scale * part[r]);
+                for (int r = 0; r < 4; ++r) dSt[q][r] = __builtin_fmaf(GV ? dc[r] : gC, dSt[q][r], a.scale * part[r]);
             }
         };
         if (PRE && inC) withoutE();
@@ -272,22 +267,17 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
         if (inC) {
             Frag fe[TPW][NKC];
             if (!PRE) {
-                withoutE();
                 if (GV) dc = *reinterpret_cast<const f32x4 *>(tC + C_D + (fb * 16 + acc_row(lane, 0)) * 4);
+                withoutE();
             }
 #pragma unroll
             for (int q = 0; q < TPW; ++q)
 #pragma unroll
                 for (int kk = 0; kk < NKC; ++kk) fe[q][kk] = fC.kc(dEs, (vtC + q) * 16, kk * KS);
 #pragma unroll
-            for (int q = 0; q < TPW; ++q) {
+            for (int q = 0; q < TPW; ++q)
 #pragma unroll
                 for (int kk = 0; kk < NKC; ++kk) dSt[q] = Mfma<T>::mma(PRE ? wf[kk] : fK.tr(tC + C_W, kk * KS, fb * 16), fe[q][kk], dSt[q]);
-                if (GV && n > a.n0) {           // (what leaves the launch is dS itself)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) dSt[q][r] *= dc[r];
-                }
-            }
         }
         sb = sb + 1 == NSB ? 0 : sb + 1;
         sc = sc + 1 == NSC ? 0 : sc + 1;
@@ -318,8 +308,8 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
 template <typename T> constexpr int BP_WGS = sizeof(T) == 2 ? 2 : 1;      // workgroups that share a CU
 
 // GV: one state gate per key channel.  The kernel then runs on the folded operands with no
-// scalar gate (log_alpha null) and on D in place of dS' (see the top of this file); the gradient of
-// the chunk's decays, times the decays, is collected per channel.
+// scalar gate (log_alpha null) and takes gamma_C, per channel, in place of rho (see the top of this
+// file); the gradient of the chunk's decays, times the decays, is collected per channel.
 template <typename T, int K, bool GV, int PW_>
 __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kernel(ChunkArgs a) {
     constexpr int PT_ = PW_ * 64;
@@ -349,7 +339,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     __shared__ float dbeta_s[WPR * C];
     __shared__ float sdot[PW_], trsum_s[PW_];
     __shared__ float colss[GV ? PT_ : 1];                // <dS', S> column by column (partials)
-    __shared__ __attribute__((aligned(16))) float dgam_s[GV ? (PW_ / (K / 16) > 0 ? PW_ / (K / 16) : 1) * K : 1];   // sum_i (K~/Gamma)_ic (E dS')_ic, per row-block group
+    __shared__ __attribute__((aligned(16))) float dgam_s[GV ? (PW_ / (K / 16) > 0 ? PW_ / (K / 16) : 1) * K : 1];   // gamma_C sum_i (K~/Gamma)_ic (E dS')_ic, per row-block group
     // slab buffers, later Q / K~ / cP and the row-dot partials
     constexpr int SLAB_ELEMS = 3 * C * LDV + 2 * VB * LDE + 2 * VB * LDK;
     constexpr int POST_ELEMS = 2 * C * LDK + C * LDC + (GV ? 0 : (PW_ * C * 4) / (int)sizeof(T));
@@ -629,7 +619,8 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     T *dq_g = static_cast<T *>(a.dq) + (GV ? tok0 : out0) * K;      // (GV: unfold_kernel works on the padded rows)
     T *dk_g = static_cast<T *>(a.dk_read) + bhn * C * K;
     T *dkt_g = static_cast<T *>(a.dkt) + bhn * C * K;
-    f32x4 dgc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 dgc = {0.f, 0.f, 0.f, 0.f}, gcv = {1.f, 1.f, 1.f, 1.f};
+    if (GV && has_ct) gcv = *reinterpret_cast<const f32x4 *>(a.gamC + bhn * K + ct + acc_row(lane, 0));     // this lane's channels
     if (has_ct) {
 #pragma unroll
         for (int iq = 0; iq < IBN; ++iq) {
@@ -666,14 +657,14 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
                 at = Mfma<T>::mma(fqq, fpt, at);
             }
             const int i = ib * 16 + acc_col(lane), c = ct + acc_row(lane, 0);
-            const float gam = a.scale * Egs[i], bgam = -Bs[i] * Egs[i], rho = GV ? 1.f : Ers[i];
+            const float gam = a.scale * Egs[i], bgam = -Bs[i] * Egs[i], rho = Ers[i];
             const f32x4 qv = load4(Qs + i * LDK + c), kv = load4(Ks + i * LDK + c), ktv = load4(Kts + i * LDK + c);
             float sc = 0.f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float gq = gam * dQg[iq][r];            // gamma . d(gamma Q)
                 const float gk = bgam * dKg[iq][r];           // gamma . d(gamma K)
-                const float gr = rho * dKr[iq][r];            // rho . d(rho K~)
+                const float gr = (GV ? gcv[r] : rho) * dKr[iq][r];      // rho . d(rho K~)
                 if (GV) {
                     dgc[r] = __builtin_fmaf(ktv[r], gr, dgc[r]);
                 } else {
@@ -702,12 +693,12 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     if (lane == 0) trsum_s[wave] = trs;
     __syncthreads();
     if (GV && tid < K) {                // gamma_C . dL/d(decay of channel tid over the chunk)
-        float sd = 0.f;
+        float sd = 0.f, ss = 0.f;
 #pragma unroll
         for (int j = 0; j < WPC; ++j) sd += dgam_s[GV ? j * K + tid : 0];
 #pragma unroll
-        for (int j = 0; j < PT_ / K; ++j) sd += colss[GV ? tid + j * K : 0];
-        a.dgamC[bhn * K + tid] = sd;
+        for (int j = 0; j < PT_ / K; ++j) ss += colss[GV ? tid + j * K : 0];
+        a.dgamC[bhn * K + tid] = __builtin_fmaf(a.gamC[bhn * K + tid], ss, sd);
     }
     if (wave == 0) {
         const int i = lane;
@@ -758,7 +749,7 @@ template <typename T, bool GV>
 static int launch_post_t(const ChunkArgs &a, hipStream_t st) {
     constexpr int PW = 8;           // wavefronts per workgroup
     dim3 grid((a.n1 - a.n0) * a.H, a.B), block(PW * 64);
-    if (GV && (!a.dgamC || a.log_alpha || a.dlog_alpha)) return -1;
+    if (GV && (!a.gamC || !a.dgamC || a.log_alpha || a.dlog_alpha)) return -1;
     if (a.K == 64) hipLaunchKernelGGL((bwd_post_kernel<T, 64, GV, PW>), grid, block, 0, st, a);
     else if (a.K == 128) hipLaunchKernelGGL((bwd_post_kernel<T, 128, GV, PW>), grid, block, 0, st, a);
     else return -1;

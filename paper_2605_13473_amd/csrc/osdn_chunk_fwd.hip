@@ -32,9 +32,10 @@ namespace osdn {
 // section on Kimi Delta Attention with online scaling).  The cumulative channel decays
 // Gamma [64 x K] do not factor out of the Gram matrix as a 64 x 64 mask, so they are folded
 // into the operands: K <- Gamma . K and K~ <- K~ / Gamma in LDS before anything else, after
-// which the kernel runs as with no gate at all; it also leaves Gamma . Q, K~ / Gamma and the
-// chunk's total decay per channel for the state and output kernels.  1 / Gamma grows like
-// e^{|G|}: the cumulative log-decay of a channel inside a chunk has to stay above about -80.
+// which the kernel runs as with no gate at all; it also leaves Gamma . Q, K~ / Gamma, the chunk's
+// total decay per channel gamma_C, and gamma_C . K~ / Gamma (from k~, rounded once) for the chain
+// kernels.  1 / Gamma grows like e^{|G|}: the cumulative log-decay of a channel inside a chunk has
+// to stay above about -80.
 constexpr int CP_ = 512;        // threads of a chunk_prep workgroup (8 wavefronts)
 template <typename T, int K, bool GV>
 __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
@@ -104,16 +105,17 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
         }
         __syncthreads();
         const T *qp = static_cast<const T *>(a.q) + tok0 * K;
-        T *qg = static_cast<T *>(a.Qg) + bhn * C * K;
+        T *qg = static_cast<T *>(a.Qg) + bhn * C * K, *kw = static_cast<T *>(a.Kw) + bhn * C * K;
         for (int v = tid; v < C * K / VN; v += CP_) {
             const int i = v / (K / VN), c = (v % (K / VN)) * VN;
             const u32x4 kv = *reinterpret_cast<const u32x4 *>(X1 + i * LDK + c);
             const u32x4 tv = *reinterpret_cast<const u32x4 *>(X2 + i * LDK + c);
             const u32x4 qv = *reinterpret_cast<const u32x4 *>(qp + (size_t)i * rs + c);
-            float ko[VN], to[VN], qo[VN];
+            float ko[VN], to[VN], qo[VN], wo[VN];
 #pragma unroll
             for (int e = 0; e < VN; ++e) {
                 const float G = Gt[i * GLD + c + e];
+                wo[e] = vec_get<T>(tv, e) * __expf(Gt[(C - 1) * GLD + c + e] - G);
                 const float gam = __expf(G), inv = __expf(-G);
                 ko[e] = vec_get<T>(kv, e) * gam;
                 to[e] = vec_get<T>(tv, e) * inv;
@@ -122,6 +124,7 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
             store_vec_t(X1 + i * LDK + c, ko);
             store_vec_t(X2 + i * LDK + c, to);
             store_vec_t(qg + i * K + c, qo);
+            store_vec_t(kw + i * K + c, wo);
         }
         __syncthreads();            // (the decays' space is handed over to A)
         store_tile_global(static_cast<T *>(a.Kg) + bhn * C * K, (size_t)K, X1, LDK, C, K, tid, CP_);
@@ -203,8 +206,8 @@ constexpr int CT_ = (CW_ + CM_ + CS_) * 64;
 template <typename T, int K> constexpr int SF_NSB = sizeof(T) == 2 ? 3 : 2;
 template <typename T, int K> constexpr int SF_NSC = sizeof(T) == 2 ? 2 : (K == 64 ? 2 : 1);
 
-// GV: one state gate per key channel: the operands carry the decays inside the chunk, and the state
-// takes the chunk's decay per channel after the write.
+// GV: one state gate per key channel: the operands carry the decays inside the chunk, and every
+// coordinate of the state its own gamma_C; K~ is gamma_C . K~ / Gamma.
 // VS: rows of S (values) owned by one workgroup, 32 or 16.  With few chains the narrow slice
 // gives twice the workgroups, each with half the work on the dependent path per chunk.
 template <typename T, int K, bool GV, int VS>
@@ -390,16 +393,10 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
                 for (int kk = 0; kk < NKC; ++kk) fe[q][kk] = fT.kc(GV ? Eo : Ew, (vtC + q) * 16, kk * KS);
 #pragma unroll
             for (int q = 0; q < TPW; ++q) {
-                if (!GV) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) St[q][r] *= g;
-                }
+                for (int r = 0; r < 4; ++r) St[q][r] *= GV ? dc[r] : g;
 #pragma unroll
                 for (int kk = 0; kk < NKC; ++kk) St[q] = Mfma<T>::mma(PRE ? kf[kk] : fK.tr(tC + C_K, kk * KS, fb * 16), fe[q][kk], St[q]);
-                if (GV) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) St[q][r] *= dc[r];
-                }
             }
         }
         sb = sb + 1 == NSB ? 0 : sb + 1;
@@ -497,7 +494,7 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
 template <typename T, bool GV>
 static int launch_prep_t(const ChunkArgs &a, hipStream_t st) {
     dim3 grid((a.n1 - a.n0) * a.H, a.B), block(CP_);
-    if (GV && (!a.log_alpha || !a.Qg || !a.Kg || !a.Kd || !a.gamC)) return -1;
+    if (GV && (!a.log_alpha || !a.Qg || !a.Kg || !a.Kd || !a.Kw || !a.gamC)) return -1;
     if (a.K == 64) hipLaunchKernelGGL((chunk_prep_kernel<T, 64, GV>), grid, block, 0, st, a);
     else if (a.K == 128) hipLaunchKernelGGL((chunk_prep_kernel<T, 128, GV>), grid, block, 0, st, a);
     else return -1;

@@ -140,13 +140,16 @@ struct ChunkArgs {
     void *Qg;                         // [B,N,H,64,K] io   Gamma . Q   (taking the place of q, k, kt in the kernels that follow)
     void *Kg;                         // [B,N,H,64,K] io   Gamma . K
     void *Kd;                         // [B,N,H,64,K] io   K~ / Gamma
+    void *Kw;                         // [B,N,H,64,K] io   K~ . gamC / Gamma, what the chain kernels multiply: it stays below
+                                      //                   K~, where K~ / Gamma times a state or its adjoint leaves the range
+                                      //                   of the type (e^79 at the strongest decay a chunk may have)
     float *gamC;                      // [B,N,H,K] f32     decay of every channel over the whole chunk
     float *dgamC;                     // [B,N,H,K] f32     backward: gamC . dL/dgamC
     // backward
     const void *dO;                   // [B,T,H,V] io
     const float *dS_out;              // [B,H,V,K] or null
     void *dEt;                        // [B,N,H,V,64] io   dE transposed (complete)
-    void *dS_ckpt;                    // [B,N,H,V,K] io    adjoint of the state at the END of each chunk (gate_vec: times gamC)
+    void *dS_ckpt;                    // [B,N,H,V,K] io    adjoint of the state at the END of each chunk
     float *dS_in;                     // [B,H,V,K]
     void *dq, *dv;                    // io
     void *dk_read, *dkt;              // [B,N,H,64,K] io: the two parts of dL/dk that phase 1 combines

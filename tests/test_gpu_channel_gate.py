@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2605_13473_amd import binding as ob
 from paper_2605_13473_amd.inputs import make_stress_inputs
-from tests.gpu_util import check, compare_backward, compare_forward, f64, oracle_hp, to_dev
+from tests.gpu_util import check, compare_backward, compare_forward, f64, gpu_forward, oracle_hp, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -50,6 +50,38 @@ def test_decay_near_the_documented_limit(bf16):
     assert -75.0 < worst < -70.0
     compare_forward(x, ob.Hyper(eta=0.3), bf16)
     compare_backward(x, ob.Hyper(eta=0.3), bf16)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("K,B", [(64, 1), (128, 8)])
+def test_strongest_decay_does_not_narrow_the_range(K, B, bf16):
+    """Every channel decays by e^-79 in every chunk, and the adjoints have the size that the mean over a
+    batch leaves them (2^-20): whatever is kept between chunks must stay in the range of its type.
+    The backward pass is linear in its adjoints, so the gradients times 2^20 are those of the adjoints
+    at unit size; the scaling is exact, hence no tolerance of its own.  The gradients that pass through
+    dL/d(K~ / Gamma) (k, log alpha, d, retention) are not looked at: that one is folded with e^-79 by
+    definition.  Forward, the same for values and a carried state of 2^20.  (B = 8: slices of 32 values.)"""
+    H, V, hp = 2, 64 if B == 1 else 512, ob.Hyper(eta=0.3)
+    x = make_stress_inputs(B, 192, H, K, V, seed=95, bf16=bf16, retention=0.95)
+    rng = np.random.default_rng(96)
+    w = rng.uniform(0.5, 1.5, (B, 3, 64, H, K))
+    x["log_alpha"] = (-79.0 * w / w.sum(axis=2, keepdims=True)).reshape(B, 192, H, K).astype(np.float32)
+    dS = rng.standard_normal((B, H, V, K)).astype(np.float32)
+    s = np.float32(2.0 ** 20)
+    y = f64(x)
+    z = dict(x, v=x["v"] * s, S_in=x["S_in"] * s)
+    o, S, _, _, _ = gpu_forward(z, hp, bf16)
+    oo, oS, _ = oracle.fwd(y["q"], y["k"], y["v"], y["beta"], y["log_alpha"], y["retention"], y["d_in"], y["S_in"],
+                           oracle_hp(hp))
+    check("o", o.float() / s, oo, bf16)
+    check("S_out", S / s, oS, bf16)
+    _, _, _, ctx, t = gpu_forward(dict(x, dO=x["dO"] / s), hp, bf16, for_backward=True)
+    g = ob.backward(ctx, t["dO"], torch.from_numpy(dS / s).cuda(), None)
+    torch.cuda.synchronize()
+    og = oracle.bwd(y["q"], y["k"], y["v"], y["beta"], y["dO"], y["log_alpha"], y["retention"], y["d_in"], y["S_in"],
+                    dS_out=dS.astype(np.float64), hp=oracle_hp(hp))
+    for name in ("dq", "dv", "dbeta", "dS_in"):
+        check(name, g[name].float() * s, og[name], bf16)
 
 
 def test_equal_entries_reproduce_the_scalar_gate():
