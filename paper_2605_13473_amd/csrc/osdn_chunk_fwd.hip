@@ -19,8 +19,8 @@ namespace osdn {
 // ------------------------------------------------------------ chunk_prep ----
 // Leaves per chunk -W (natural layout), T diag(beta), the cumulative log-decay G, and T itself when
 // a backward pass follows.  The row scalings of the right-hand sides move into T: W = (T diag(beta
-// gamma)) K and U = (T diag(beta)) V; U is never formed: the state kernel adds (T diag(beta)) V to
-// its product with the state in one accumulator, and scales E (not K~) for the write.  So V, U and a
+// gamma)) K and U = (T diag(beta)) V; U is never stored: the state kernel adds (T diag(beta)) V to
+// its product with the state, and scales E (not K~) for the write.  So V, U and a
 // scaled copy of K~ stay out of this kernel's traffic.
 //
 // Bound by its phases' latency and memory: three workgroups share a CU (52 KB of LDS each at K =
@@ -365,14 +365,14 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
             if (GV) dc = *reinterpret_cast<const f32x4 *>(tC + C_D + (fb * 16 + acc_row(lane, 0)) * 4);
         }
         if (inB) {
-            f32x4 acc = uacc, acc2 = {0.f, 0.f, 0.f, 0.f};
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < NKK; kk += 2) {
                 acc = Mfma<T>::mma(PRE ? wf[kk] : fK.kc(tB + B_W, rb * 16, kk * KS), sf[kk], acc);
                 acc2 = Mfma<T>::mma(PRE ? wf[kk + 1] : fK.kc(tB + B_W, rb * 16, (kk + 1) * KS), sf[kk + 1], acc2);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] += acc2[r];
+            for (int r = 0; r < 4; ++r) acc[r] = uacc[r] + (acc[r] + acc2[r]);     // (last: begun with U, every step would round at its size)
             if (!GV) {
                 f32x4 ew;
 #pragma unroll

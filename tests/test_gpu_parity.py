@@ -164,6 +164,30 @@ def test_large_launches_two_chunks_per_workgroup(bf16):
     compare_backward(x, hp, bf16)
 
 
+@pytest.mark.parametrize("V,H", [(64, 2), (512, 64)])
+def test_fp32_write_is_rounded_at_its_end(V, H):
+    """E = U - W S^T with S small beside U: every product but the dense ones with S is exact (orthogonal
+    keys of +-1/8, so T = I and P = I; beta = 1; d fixed at 1), and q = k gives o = v exactly.  What is
+    left: the products with S, K of them of size |S|/8, rounded to 2^-24 of partial sums below
+    K max|S|/8, twice (W S^T and Q S^T), and one rounding each of the sums with U and with P E, 2^-24 of
+    |v| + K max|S|/8 each.  (An accumulator that begins with U instead rounds at |v| in every step.)"""
+    K = 64
+    h = np.ones((1, 1))
+    while h.shape[0] < K:
+        h = np.block([[h, h], [h, -h]])
+    k = torch.from_numpy(np.broadcast_to((h / 8).astype(np.float32)[None, :, None, :], (1, K, H, K)).copy()).cuda()
+    rng = np.random.default_rng(171)
+    v = torch.from_numpy(rng.uniform(1.0, 2.0, (1, K, H, V)).astype(np.float32)).cuda()
+    S = torch.from_numpy(rng.uniform(-2.0 ** -11, 2.0 ** -11, (1, H, V, K)).astype(np.float32)).cuda()
+    o, _, _, _ = ob.forward(k, k, v, torch.ones(1, K, H, device="cuda"), None, None, None, S,
+                            ob.Hyper(scale=1.0, eta=0.0))
+    torch.cuda.synchronize()
+    s = K * 2.0 ** -11 / 8
+    bound = 2.0 ** -24 * (2 * (v.double() + s) + 2 * K * s)
+    err = (o.double() - v.double()).abs()
+    assert (err <= bound).all(), f"{float((err / bound).max()):.2f} of the bound"
+
+
 @pytest.mark.parametrize("variant", ["ungated", "no_retention", "non_beta_aware", "no_projection",
                                      "eta_one_clamped", "defaults_null"])
 def test_variants_fwd_bwd_fp32(variant):
