@@ -752,11 +752,13 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const int N = p->T / C;
     const long long chains = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
     int S = segment_count(p->segments, N, pk.longest, chains * (p->V / 32) + chains, true, chains);   // chain kernel: 32 rows of the state per workgroup
-    // (the backward chain keeps slices of 32 values: with 16 the kernel itself is a fifth faster on
-    // few chains, but its workgroups then hold twice the CUs and what they take from the phase-1
-    // chain beside them, which bounds the pass there, costs more.  The exception is fp32 I/O at
-    // K = 128, where the wide slice does not fit the registers: 131 spilled against 19.)
-    c.narrow_slices = !bf && p->K == 128;
+    // (Slices of bwd_chain: bf16 keeps 32 values, because with 16 the kernel itself is a fifth faster on
+    // few chains, but its workgroups then hold twice the CUs and what they take from the phase-1 chain
+    // beside them, which bounds the pass there, costs more.  fp32 I/O at K = 64: 16 values while the
+    // workgroups find a CU each (64 chains of 32 chunks, V = 64: training step 705 against 721 us; 16 chains of
+    // 128 chunks, V = 128: 1240 against 1400), above that 32, which read the shared tiles half as often
+    // (256 chains of 16 chunks, V = 64: 1109 against 1155; 128 chains, V = 256: 1330 against 1404).)
+    c.narrow_slices = !bf && (p->K == 128 || chains * (p->V / 16) <= NUM_CU);
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
     auto seg_range = [&](int sidx, int &n0, int &n1) { n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1); };

@@ -72,8 +72,7 @@ template <typename T, int K> constexpr int BC_NSC = sizeof(T) == 2 ? 2 : 1;
 // gamma_C . K~ / Gamma.  dS' itself is rounded and kept: gamma_C . dS' would lose bits, and then
 // itself, below the smallest normal number (at a decay of e^-79 from |dS'| = 2.4e-4 on), which K~ /
 // Gamma would bring back to the size of dS'.
-// VS: rows of S (values) owned by one workgroup, 32 or 16 (the narrow slice when the chains are few:
-// twice the workgroups, each with half the work on the dependent path per chunk).
+// VS: rows of S (values) owned by one workgroup, 32 or 16 (launch_chain_v says which).
 template <typename T, int K, bool GV, int VS>
 __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
     constexpr int ES = sizeof(T), RK = K * ES, RC = C * ES, RV = VS * ES;      // bytes per row of a tile
@@ -725,21 +724,26 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
 }
 
 // -------------------------------------------------------------- launchers ----
-template <typename T, bool GV, int VS>
-static int launch_chain_t(const ChunkArgs &a, hipStream_t st) {
+template <typename T, int K, bool GV, int VS>
+static void launch_chain_t(const ChunkArgs &a, hipStream_t st) {
     dim3 grid((a.V / VS) * a.H * (a.seq_chunks ? a.n_seqs : a.B)), block(CT_);
-    if ((GV && !a.gamC) || !a.Pm || !a.q || !a.dO) return -1;
-    if (a.K == 64) hipLaunchKernelGGL((bwd_chain_kernel<T, 64, GV, VS>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((bwd_chain_kernel<T, 128, GV, VS>), grid, block, 0, st, a);
-    else return -1;
-    return 0;
+    hipLaunchKernelGGL((bwd_chain_kernel<T, K, GV, VS>), grid, block, 0, st, a);
 }
-// Slices of 16 values when the caller asks for them (few chains: see ChunkArgs::narrow_slices), and
-// always with fp32 I/O, whose operands would not fit the LDS beside slices of 32.
+// Slices of 32 values with bf16 I/O, of 16 with fp32 I/O at K = 128 (beside slices of 32 one chunk's operands
+// would fill the LDS, with nothing in flight for the next), either with fp32 I/O at K = 64 (few chains: see osdn_bwd).
 template <typename T, bool GV>
 static int launch_chain_v(const ChunkArgs &a, hipStream_t st) {
-    if constexpr (sizeof(T) == 2) if (!a.narrow_slices) return launch_chain_t<T, GV, 32>(a, st);
-    return launch_chain_t<T, GV, 16>(a, st);
+    if ((GV && !a.gamC) || !a.Pm || !a.q || !a.dO) return -1;
+    if (a.K != 64 && a.K != 128) return -1;
+    if constexpr (sizeof(T) == 2) {
+        if (a.K == 64) launch_chain_t<T, 64, GV, 32>(a, st);
+        else launch_chain_t<T, 128, GV, 32>(a, st);
+    } else {
+        if (a.K == 128) launch_chain_t<T, 128, GV, 16>(a, st);
+        else if (a.narrow_slices) launch_chain_t<T, 64, GV, 16>(a, st);
+        else launch_chain_t<T, 64, GV, 32>(a, st);
+    }
+    return 0;
 }
 int launch_bwd_chain(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
     if (a.gate_vec) return bf16_io ? launch_chain_v<bf16, true>(a, st) : launch_chain_v<float, true>(a, st);

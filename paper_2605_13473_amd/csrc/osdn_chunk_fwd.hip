@@ -187,24 +187,30 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
 //   B  E = (T diag(beta)) V - W S^T, one 16x16 tile per wavefront; E and rho E (the operand of the
 //      write) into LDS                                                        | barrier 2
 //   C  S <- gamma_C S + (rho E)^T K~ in the MFMA accumulators (fp32)
-// Everything a phase needs besides S or E is in registers when its barrier opens: the fragments of
-// -W and the product with V are prepared in phase C of the chunk before, those of K~ in phase B.
-// Four more wavefronts move data.  Two load, directly from global memory into two LDS rings
-// (osdn_tile.h): what phase B multiplies (-W, T diag(beta), the slice of V, the gates) and what phase C
-// does (K~; per-channel gates: the chunk's decays).  Two store the checkpoint of S and E^T.  They are
+// With bf16 I/O everything a phase needs besides S or E is in registers when its barrier opens: the
+// fragments of -W and the product with V are prepared in phase C of the chunk before, those of K~ in phase
+// B.  (fp32 fragments would not fit the registers: there the product with V alone, at K = 64.)
+// Four more wavefronts move data.  Two load, directly from global memory into three LDS rings
+// (osdn_tile.h): -W; X, what the product with V takes (T diag(beta), the slice of V) and the gates; what
+// phase C multiplies (K~; per-channel gates: the chunk's decays).  Two store the checkpoint of S and E^T.  They are
 // wavefronts of their own because a memory instruction stalls its wavefront until the CU's address
 // unit takes it (64 bytes per clock: 700 cycles for a chunk's tiles), which adds to the chain when the
 // same wavefronts do both, and because a wavefront's accesses retire in order: a load issued behind a
 // store is only known to be there when the store is acknowledged, about 1 us later.
 // Bound by what a CU has in flight from HBM (46 KB in and 12 KB out per chunk with slices of 32): 64
 // chains of 64 chunks, V = 128: 115 us, 3.8 TB/s; without the stores 73 us, without any traffic 52 us.
+// With fp32 I/O bound by what the slices of a chain read over again (84 KB in per chunk at K = 128 with
+// slices of 16, 88 with 32): many chains take slices of 32 there too, although -W alone then has a second
+// slot.  256 chains of 16 chunks: K = V = 128 412 -> 314 us (the product with V a phase ahead, X and K~ both in
+// flight during phase B alone: 390; one slot for -W too: 447), V = 256 799 -> 604, K = 64, V = 128 316 -> 222.
 constexpr int CW_ = 8;          // wavefronts of a chain workgroup that compute
 constexpr int CM_ = 2;          // ... that load
 constexpr int CS_ = 2;          // ... that store
 constexpr int CT_ = (CW_ + CM_ + CS_) * 64;
-// Ring depths (chunks of operands in LDS).
-template <typename T, int K> constexpr int SF_NSB = sizeof(T) == 2 ? 3 : 2;
-template <typename T, int K> constexpr int SF_NSC = sizeof(T) == 2 ? 2 : (K == 64 ? 2 : 1);
+// Ring depths (chunks of operands in LDS) of -W, of T diag(beta), V and the gates, and of K~, from what fits.
+template <typename T, int K, int VS> constexpr int SF_NSW = sizeof(T) == 2 ? 3 : 2;
+template <typename T, int K, int VS> constexpr int SF_NSX = sizeof(T) == 2 ? 3 : (K == 64 || VS == 16 ? 2 : 1);
+template <typename T, int K, int VS> constexpr int SF_NSC = sizeof(T) == 2 || K == 64 ? 2 : 1;
 
 // GV: one state gate per key channel: the operands carry the decays inside the chunk, and every
 // coordinate of the state its own gamma_C; K~ is gamma_C . K~ / Gamma.
@@ -218,10 +224,13 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     constexpr int KS = Mfma<T>::KSTEP, NKK = K / KS, NKC = C / KS;
     typedef typename Mfma<T>::Frag Frag;
     constexpr bool PRE = sizeof(T) == 2;        // operands in registers ahead of their phase (fp32: they would not fit)
-    constexpr int NSB = SF_NSB<T, K>, NSC = SF_NSC<T, K>;
-    constexpr int B_W = 0, B_T = B_W + C * RK, B_V = B_T + C * RC, B_G = B_V + C * RV, B_BYTES = B_G + 2 * C * 4;
+    constexpr int NSW = SF_NSW<T, K, VS>, NSX = SF_NSX<T, K, VS>, NSC = SF_NSC<T, K, VS>;
+    constexpr bool AHEAD = NSC > 1;             // the product with V one phase ahead (else phase B has to cover the loads of K~)
+    static_assert(!PRE || (AHEAD && NSW == NSX), "what phase B multiplies comes at once");
+    constexpr int X_T = 0, X_V = X_T + C * RC, X_G = X_V + C * RV, X_BYTES = X_G + 2 * C * 4;
     constexpr int C_K = 0, C_D = C_K + C * RK, C_BYTES = C_D + (GV ? K * 4 : 0);
-    __shared__ __attribute__((aligned(1024))) char ringB[NSB * B_BYTES];
+    __shared__ __attribute__((aligned(1024))) char ringW[NSW * C * RK];
+    __shared__ __attribute__((aligned(1024))) char ringX[NSX * X_BYTES];
     __shared__ __attribute__((aligned(1024))) char ringC[NSC * C_BYTES];
     __shared__ __attribute__((aligned(1024))) char Sb[VS * RK];         // S in the I/O type [v][kf]
     __shared__ __attribute__((aligned(1024))) char Eo[VS * RC];         // E^T  [v][i]
@@ -248,16 +257,18 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     LdsLoad<RC, C, CM_> lT;
     LdsLoad<RV, C, CM_> lV;
     lK.init(RK, mw, lane); lT.init(RC, mw, lane); lV.init(gV, mw, lane);
-    auto loadB = [&](int n, int slot) {
+    auto loadW = [&](int n, int slot) {
+        lK.issue(ringW + slot * C * RK, static_cast<const char *>(a.Wn) + (((size_t)bt * a.N + n) * a.H + h) * C * RK, RK, mw, lane, slice);
+    };
+    auto loadX = [&](int n, int slot) {
         const size_t bhn = ((size_t)bt * a.N + n) * a.H + h;
-        char *s = ringB + slot * B_BYTES;
-        lK.issue(s + B_W, static_cast<const char *>(a.Wn) + bhn * C * RK, RK, mw, lane, slice);
-        lT.issue(s + B_T, static_cast<const char *>(a.Tu) + bhn * C * RC, RC, mw, lane, slice);
-        lV.issue(s + B_V, static_cast<const char *>(a.v) + (((size_t)bt * a.T + (size_t)n * C) * a.H + h) * a.V * ES + (size_t)vs * ES,
+        char *s = ringX + slot * X_BYTES;
+        lT.issue(s + X_T, static_cast<const char *>(a.Tu) + bhn * C * RC, RC, mw, lane, slice);
+        lV.issue(s + X_V, static_cast<const char *>(a.v) + (((size_t)bt * a.T + (size_t)n * C) * a.H + h) * a.V * ES + (size_t)vs * ES,
                  gV, mw, lane, 0, wideV);
         if (!GV && mw < 2) {                    // gamma (loader 0) and rho (1)
             const int w = mw;
-            load_lds4(a.gates + (bhn * 3 + 1 + w) * C, lane * 4, lds_offset(s + B_G + w * C * 4));
+            load_lds4(a.gates + (bhn * 3 + 1 + w) * C, lane * 4, lds_offset(s + X_G + w * C * 4));
         }
     };
     auto loadC = [&](int n, int slot) {
@@ -265,14 +276,18 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
         lK.issue(s + C_K, static_cast<const char *>(a.kt) + (((size_t)bt * a.N + n) * a.H + h) * C * RK, RK, mw, lane, slice);
         if (GV && mw < K / 64) load_lds4(a.gamC + (((size_t)bt * a.N + n) * a.H + h) * K, mw * 256 + lane * 4, lds_offset(s + C_D + mw * 256));
     };
-    // loads of a loader that are newer than the tiles it waits for (at least)
-    constexpr int LB = LdsLoad<RK, C, CM_>::MIN + LdsLoad<RC, C, CM_>::MIN + LdsLoad<RV, C, CM_>::MIN, LC = LdsLoad<RK, C, CM_>::MIN;
-    constexpr int NMAX = NSB > NSC ? NSB : NSC;
-    constexpr int NEWER_B = (NSB - 1) * (LB + LC), NEWER_C = (NSC - 1) * (LB + LC);
-    static_assert(NEWER_B < 64 && NEWER_C < 64, "the counter has six bits");
+    // Loads of a loader that are newer than the tiles it waits for (at least).  A chunk asks behind barrier 1
+    // for -W and X (PRE), for K~ and X (AHEAD), or for K~, and behind barrier 2 for the others in this order.
+    constexpr int LW = LdsLoad<RK, C, CM_>::MIN, LX = LdsLoad<RC, C, CM_>::MIN + LdsLoad<RV, C, CM_>::MIN, LC = LW, LA = LW + LX + LC;
+    constexpr int NMAX = NSW > NSX ? (NSW > NSC ? NSW : NSC) : (NSX > NSC ? NSX : NSC);
+    constexpr int NEWER_W = (NSW - 1) * LA + (AHEAD ? 0 : LX), NEWER_X = (NSX - 1) * LA, NEWER_C = (NSC - 1) * LA + (AHEAD && !PRE ? LX : 0);
+    constexpr int NEWER_1 = PRE ? NEWER_C : AHEAD || NEWER_W < NEWER_X ? NEWER_W : NEWER_X;
+    constexpr int NEWER_2 = PRE ? NEWER_X : !AHEAD || NEWER_C < NEWER_X ? NEWER_C : NEWER_X;
+    static_assert(NEWER_1 < 64 && NEWER_2 < 64, "the counter has six bits");
 #pragma unroll
     for (int j = 0; j < NMAX; ++j) {
-        if (loader && j < NSB && a.n0 + j < a.n1) loadB(a.n0 + j, j);
+        if (loader && j < NSW && a.n0 + j < a.n1) loadW(a.n0 + j, j);
+        if (loader && j < NSX && a.n0 + j < a.n1) loadX(a.n0 + j, j);
         if (loader && j < (PRE ? NSC : NSC - 1) && a.n0 + j < a.n1) loadC(a.n0 + j, j);
     }
 
@@ -291,21 +306,23 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     }
     if (loader) wait_vm<0>();
     __syncthreads();
-    int sb = 0, sc = 0;                         // ring slots of chunk n
+    int sw = 0, sx = 0, sc = 0;                 // ring slots of chunk n
+    auto next = [](int slot, int depth) { return slot + 1 == depth ? 0 : slot + 1; };
     if (loader) {
         for (int n = a.n0; n < a.n1; ++n) {
             const bool full = n + NMAX < a.n1;  // everything counted as newer has been asked for
-            // a slot is refilled as soon as its operands have been read: ahead of their phase (PRE), or in it
-            if (full) wait_vm<PRE ? NEWER_C : NEWER_B>(); else wait_vm<0>();   // K~ (PRE), phase B's operands of this chunk
+            // a slot is refilled as soon as its operands have been read: ahead of their phase (X; PRE: all), or in it
+            if (full) wait_vm<NEWER_1>(); else wait_vm<0>();        // K~ (PRE), -W, X (not AHEAD)
             __syncthreads();                                        // barrier 1
-            if (PRE && n + NSB < a.n1) loadB(n + NSB, sb);
+            if (PRE && n + NSW < a.n1) loadW(n + NSW, sw);
             if (!PRE && n - 1 + NSC < a.n1) loadC(n - 1 + NSC, sc == 0 ? NSC - 1 : sc - 1);
-            if (full) wait_vm<PRE ? NEWER_B : NEWER_C>(); else wait_vm<0>();   // phase B's operands of the next (PRE), K~
+            if (AHEAD && n + NSX < a.n1) loadX(n + NSX, sx);
+            if (full) wait_vm<NEWER_2>(); else wait_vm<0>();        // -W and X of the next chunk (PRE), X of the next chunk (AHEAD) and K~
             __syncthreads();                                        // barrier 2
             if (PRE && n + NSC < a.n1) loadC(n + NSC, sc);
-            if (!PRE && n + NSB < a.n1) loadB(n + NSB, sb);
-            sb = sb + 1 == NSB ? 0 : sb + 1;
-            sc = sc + 1 == NSC ? 0 : sc + 1;
+            if (!PRE && n + NSW < a.n1) loadW(n + NSW, sw);
+            if (!AHEAD && n + NSX < a.n1) loadX(n + NSX, sx);
+            sw = next(sw, NSW); sx = next(sx, NSX); sc = next(sc, NSC);
         }
         return;
     }
@@ -323,28 +340,28 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     TileFrag<T, RC> fT;
     TileFrag<T, RV> fV;
     fK.init(lane); fT.init(lane); fV.init(lane);
-    // operands of phase B of one chunk: fragments of -W, the product with V, rho of this lane's rows, gamma_C
+    // operands of phase B of one chunk: fragments of -W (PRE), the product with V, rho of this lane's rows, gamma_C
     Frag wf[NKK];
     f32x4 uacc = {}, rho = {1.f, 1.f, 1.f, 1.f};
     float gC = 1.f;
-    auto fetchB = [&](const char *tB) {
+    auto fetchB = [&](const char *tW, const char *tX) {
         if (inB) {
             if (PRE) {
 #pragma unroll
-                for (int kk = 0; kk < NKK; ++kk) wf[kk] = fK.kc(tB + B_W, rb * 16, kk * KS);
+                for (int kk = 0; kk < NKK; ++kk) wf[kk] = fK.kc(tW, rb * 16, kk * KS);
             }
             uacc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < NKC; ++kk)
                 if (kk * KS < (rb + 1) * 16)                    // T is lower triangular
-                    uacc = Mfma<T>::mma(fT.kc(tB + B_T, rb * 16, kk * KS), fV.tr(tB + B_V, kk * KS, vtB * 16), uacc);
-            if (!GV) rho = *reinterpret_cast<const f32x4 *>(tB + B_G + (rb * 16 + acc_row(lane, 0)) * 4 + C * 4);
+                    uacc = Mfma<T>::mma(fT.kc(tX + X_T, rb * 16, kk * KS), fV.tr(tX + X_V, kk * KS, vtB * 16), uacc);
+            if (!GV) rho = *reinterpret_cast<const f32x4 *>(tX + X_G + (rb * 16 + acc_row(lane, 0)) * 4 + C * 4);
         }
-        if (!GV) gC = *reinterpret_cast<const float *>(tB + B_G + (C - 1) * 4);
+        if (!GV) gC = *reinterpret_cast<const float *>(tX + X_G + (C - 1) * 4);
     };
-    if (PRE) fetchB(ringB);
+    if (AHEAD) fetchB(ringW, ringX);
     for (int n = a.n0; n < a.n1; ++n) {
-        const char *tB = ringB + sb * B_BYTES, *tC = ringC + sc * C_BYTES;
+        const char *tW = ringW + sw * C * RK, *tC = ringC + sc * C_BYTES;
         // ---- phase A ----
         if (inC) {
 #pragma unroll
@@ -354,7 +371,7 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
         // ---- phase B ----
         Frag sf[NKK], kf[NKC];
         f32x4 dc = {};
-        if (!PRE) fetchB(tB);
+        if (!AHEAD) fetchB(tW, ringX + sx * X_BYTES);
         if (inB) {
 #pragma unroll
             for (int kk = 0; kk < NKK; ++kk) sf[kk] = fK.kc(Sb, vtB * 16, kk * KS);
@@ -368,8 +385,8 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc2 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kk = 0; kk < NKK; kk += 2) {
-                acc = Mfma<T>::mma(PRE ? wf[kk] : fK.kc(tB + B_W, rb * 16, kk * KS), sf[kk], acc);
-                acc2 = Mfma<T>::mma(PRE ? wf[kk + 1] : fK.kc(tB + B_W, rb * 16, (kk + 1) * KS), sf[kk + 1], acc2);
+                acc = Mfma<T>::mma(PRE ? wf[kk] : fK.kc(tW, rb * 16, kk * KS), sf[kk], acc);
+                acc2 = Mfma<T>::mma(PRE ? wf[kk + 1] : fK.kc(tW, rb * 16, (kk + 1) * KS), sf[kk + 1], acc2);
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[r] = uacc[r] + (acc[r] + acc2[r]);     // (last: begun with U, every step would round at its size)
@@ -399,9 +416,8 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
                 for (int kk = 0; kk < NKC; ++kk) St[q] = Mfma<T>::mma(PRE ? kf[kk] : fK.tr(tC + C_K, kk * KS, fb * 16), fe[q][kk], St[q]);
             }
         }
-        sb = sb + 1 == NSB ? 0 : sb + 1;
-        sc = sc + 1 == NSC ? 0 : sc + 1;
-        if (PRE && n + 1 < a.n1) fetchB(ringB + sb * B_BYTES);
+        sw = next(sw, NSW); sx = next(sx, NSX); sc = next(sc, NSC);
+        if (AHEAD && n + 1 < a.n1) fetchB(ringW + sw * C * RK, ringX + sx * X_BYTES);
     }
     if (inC) {
 #pragma unroll
@@ -513,12 +529,10 @@ static int launch_state_t(const ChunkArgs &a, hipStream_t st) {
     else return -1;
     return 0;
 }
-// Slices of 16 values when the caller asks for them (few chains: see ChunkArgs::narrow_slices), and
-// always with fp32 I/O (whose tiles of 32 values would leave no room for a second buffer).
+// Slices of 16 values when the caller asks for them (few chains: see osdn_fwd), else of 32.
 template <typename T, bool GV>
 static int launch_state_v(const ChunkArgs &a, hipStream_t st) {
-    if constexpr (sizeof(T) == 2) if (!a.narrow_slices) return launch_state_t<T, GV, 32>(a, st);
-    return launch_state_t<T, GV, 16>(a, st);
+    return a.narrow_slices ? launch_state_t<T, GV, 16>(a, st) : launch_state_t<T, GV, 32>(a, st);
 }
 int launch_state_fwd(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
     if (a.gate_vec) return bf16_io ? launch_state_v<bf16, true>(a, st) : launch_state_v<float, true>(a, st);

@@ -2,6 +2,7 @@
 as long as and just longer than the rings are deep, in one launch and cut into segments, with wide and
 narrow slices of the state, and token tensors that do not start on a 16-byte boundary (their tiles
 then take the way through registers)."""
+import numpy as np
 import pytest
 import torch
 
@@ -16,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("chunks,segments", [(1, 1), (2, 1), (3, 1), (4, 1), (5, 2), (9, 4)])
 @pytest.mark.parametrize("shape", [(1, 2, 128, 192), (2, 2, 64, 64)])
 def test_short_sequences(shape, chunks, segments, bf16):
-    """Few chains: slices of 16 values."""
+    """Few chains: slices of 16 values (but for the backward pass in bf16, which always takes slices of 32)."""
     B, H, K, V = shape
     x = make_stress_inputs(B, 64 * chunks, H, K, V, seed=131 + chunks, bf16=bf16, retention=0.97)
     hp = ob.Hyper(eta=0.5, segments=segments)
@@ -24,14 +25,27 @@ def test_short_sequences(shape, chunks, segments, bf16):
     compare_backward(x, hp, bf16)
 
 
-@pytest.mark.parametrize("chunks", [1, 2, 3, 5])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("chunks,segments", [(1, 1), (2, 1), (3, 1), (5, 1), (6, 2)])
 @pytest.mark.parametrize("K", [64, 128])
-def test_many_chains_wide_slices(K, chunks):
-    """Enough chains for slices of 32 values (bf16)."""
-    x = make_stress_inputs(8, 64 * chunks, 16, K, 64, seed=141 + chunks, bf16=True, retention=0.0)
-    hp = ob.Hyper(eta=0.5, segments=1)
-    compare_forward(x, hp, True)
-    compare_backward(x, hp, True)
+def test_many_chains_wide_slices(K, chunks, segments, bf16):
+    """Enough chains for slices of 32 values, forward and backward (but for fp32 at K = 128, whose backward
+    pass always takes slices of 16)."""
+    x = make_stress_inputs(8, 64 * chunks, 16, K, 64, seed=141 + chunks, bf16=bf16, retention=0.0)
+    hp = ob.Hyper(eta=0.5, segments=segments)
+    compare_forward(x, hp, bf16)
+    compare_backward(x, hp, bf16)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("K", [64, 128])
+def test_many_chains_wide_slices_channel_gate(K, bf16):
+    """The same with one state gate per key channel, whose decays travel with K~."""
+    x = make_stress_inputs(8, 64 * 4, 16, K, 64, seed=148, bf16=bf16, retention=0.0)
+    rng = np.random.default_rng(149)
+    x["log_alpha"] = (-0.1 * rng.random((8, 64 * 4, 16, K))).astype(np.float32)
+    compare_forward(x, ob.Hyper(eta=0.5, segments=1), bf16)
+    compare_backward(x, ob.Hyper(eta=0.5, segments=1), bf16)
 
 
 @pytest.mark.parametrize("bf16", [False, True])
