@@ -263,29 +263,34 @@ Pipeline *pipeline_for(hipStream_t caller) {
 //    meets a phase-1 chain kernel on the other stream and the two do not fit on one CU together:
 //    when the workgroups of both (chain_wgs) outnumber the CUs, the count that balances the
 //    exposed tail against that cost is about sqrt(N / 15) (2 at 64 chunks, 4 at 256); when they
-//    all fit side by side, about 32 chunks per segment, at most twelve: of that count and the two
+//    all fit side by side, about 32 chunks per segment, at most four: of that count and the two
 //    above it, the one whose segments fill whole rounds of bwd_post workgroups (one per chunk and
-//    chain, one per CU at a time) best.
+//    chain, post_round at a time) best; from 448 chunks on, where a segment is many rounds, seven,
+//    or twelve if phase 1 sweeps (p1_sweeps: it is slower then, and its last segment what is exposed).
+//    16 chains, bf16, backward pass alone: 128 chunks 494, 499, 493, 515, 546, 575 us with 3 to 8 segments
+//    (5 taken); 256 chunks, V = 256 993, 1014, 1057, 1063, 1097, 1023 with 4 to 9 (5); 512 chunks 1648, 1625, 1621,
+//    1619, 1643, 1816 with 4 to 8 and 12, with retention 2284, 2255, 2219, 2198, 2204, 2206; 4 chains of 625
+//    chunks, fp32, with retention 4026 and 3972 with 7 and 12.
 // Segments cut the chunk axis as a whole.  With packed sequences the sequential kernels of a
 // segment only have the sequences that cross it to work on, one after the other segment by
 // segment, so cutting pays only while one sequence makes up most of the axis; otherwise the
 // many independent chains fill the chip by themselves and everything runs in one piece.
 constexpr int NUM_CU = 256;
-int segment_count(int forced, int N, int longest, long long chain_wgs, bool backward, long long chains = 0) {
+int segment_count(int forced, int N, int longest, long long chain_wgs, bool backward, long long chains = 0, int post_round = 0, bool p1_sweeps = false) {
     if (forced <= 0 && (long long)longest * 4 < (long long)N * 3) return 1;
     int S = forced;
     if (forced <= 0) {
         if (!backward) S = N / 16 > 6 ? 6 : N / 16;
         else if (chain_wgs > NUM_CU) S = (int)std::lround(std::sqrt(N / 15.0)) > 6 ? 6 : (int)std::lround(std::sqrt(N / 15.0));
         else {
-            S = N / 32 > 12 ? 12 : N / 32;
+            S = N >= 448 ? (p1_sweeps ? 12 : 7) : N / 32 > 4 ? 4 : N / 32;
             if (S < 2) S = 2;
             double best = 0.0;
             int pick = S;
-            for (int c = S; c <= S + 2 && c <= 12 && c <= N && chains > 0; ++c) {
+            for (int c = S; N < 448 && c <= S + 2 && c <= N; ++c) {
                 const int first = N / (2 * c) > 0 ? N / (2 * c) : 1;
                 const double wgs = (double)(N - first) / (c - 1) * (double)chains;   // bwd_post workgroups of a segment
-                const double fill = wgs / (std::ceil(wgs / NUM_CU) * NUM_CU);
+                const double fill = wgs / (std::ceil(wgs / post_round) * post_round);
                 if (fill > best + 1e-9) { best = fill; pick = c; }
             }
             S = pick;
@@ -751,14 +756,15 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
 
     const int N = p->T / C;
     const long long chains = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
-    int S = segment_count(p->segments, N, pk.longest, chains * (p->V / 32) + chains, true, chains);   // chain kernel: 32 rows of the state per workgroup
-    // (Slices of bwd_chain: bf16 keeps 32 values, because with 16 the kernel itself is a fifth faster on
+    // Slices of bwd_chain: bf16 keeps 32 values, because with 16 the kernel itself is a fifth faster on
     // few chains, but its workgroups then hold twice the CUs and what they take from the phase-1 chain
     // beside them, which bounds the pass there, costs more.  fp32 I/O at K = 64: 16 values while the
     // workgroups find a CU each (64 chains of 32 chunks, V = 64: training step 705 against 721 us; 16 chains of
     // 128 chunks, V = 128: 1240 against 1400), above that 32, which read the shared tiles half as often
-    // (256 chains of 16 chunks, V = 64: 1109 against 1155; 128 chains, V = 256: 1330 against 1404).)
+    // (256 chains of 16 chunks, V = 64: 1109 against 1155; 128 chains, V = 256: 1330 against 1404).
     c.narrow_slices = !bf && (p->K == 128 || chains * (p->V / 16) <= NUM_CU);
+    const long long chain_wgs = chains * (p->V / (c.narrow_slices ? 16 : 32)) + chains;     // of the chain kernels of both phases
+    int S = segment_count(p->segments, N, pk.longest, chain_wgs, true, chains, (bf ? 2 : 1) * NUM_CU, !solved);   // (bwd_post: two workgroups a CU with bf16 I/O)
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
     auto seg_range = [&](int sidx, int &n0, int &n1) { n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1); };
@@ -811,7 +817,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     // Then the inverses of the first segment are built on the side stream at once (beside
     // bwd_post), and everything else runs on the caller's stream behind the segment's bwd_post,
     // where the phase-1 chain of the segment before covers it.
-    const bool lin_on_main = pb.lin_clean && chains * (p->V / 32) + chains > NUM_CU;
+    const bool lin_on_main = pb.lin_clean && chain_wgs > NUM_CU;
     hipStream_t s1 = pl->side;
     OSDN_HIP_OK(hipEventRecord(pl->fork, st));
     OSDN_HIP_OK(hipStreamWaitEvent(s1, pl->fork, 0));
