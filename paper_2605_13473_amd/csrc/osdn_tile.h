@@ -90,11 +90,11 @@ __device__ __forceinline__ uint32_t lds_offset(const void *p) {      // LDS byte
 // 16 (4) bytes per lane from base + voff (base wave-uniform) to LDS address lds + 16 (4) * lane
 __device__ __forceinline__ void load_lds16(const void *base, uint32_t voff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "s"(lds), "v"(voff), "s"(base) : "memory");
+                 :: "s"(lds), "v"(voff), "s"(base) : "m0", "memory");
 }
 __device__ __forceinline__ void load_lds4(const void *base, uint32_t voff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-                 :: "s"(lds), "v"(voff), "s"(base) : "memory");
+                 :: "s"(lds), "v"(voff), "s"(base) : "m0", "memory");
 }
 // all but the newest N vector memory accesses of this wavefront are complete
 template <int N> __device__ __forceinline__ void wait_vm() {
