@@ -161,30 +161,6 @@ __device__ __forceinline__ void store4(bf16 *p, f32x4 v) {
     *reinterpret_cast<bf16x4 *>(p) = o;
 }
 
-// acc(row m, col c) = X[m][c0 + c], a 16x16 block of a row-major LDS tile (X points at its
-// first row), obtained by multiplying with a 0/1 selector on the MFMA unit (exact).  Followed
-// by store_tile_t this transposes a block with vector LDS accesses only.
-template <typename T> __device__ __forceinline__ f32x4 pick16(const T *X, int ld, int c0, int lane);
-template <> __device__ __forceinline__ f32x4 pick16<float>(const float *X, int ld, int c0, int lane) {
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const int n = lane & 15, kq = lane >> 4;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(X[n * ld + c0 + 4 * s + kq], (n == 4 * s + kq) ? 1.f : 0.f,
-                                                   acc, 0, 0, 0);
-    return acc;
-}
-template <> __device__ __forceinline__ f32x4 pick16<bf16>(const bf16 *X, int ld, int c0, int lane) {
-    const int n = lane & 15, k8 = (lane >> 4) * 8;
-    const int kk = c0 & ~31, half = (c0 >> 4) & 1;
-    const bf16x8 a = *reinterpret_cast<const bf16x8 *>(X + n * ld + kk + k8);
-    bf16x8 sel;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) sel[e] = (bf16)((k8 + e == n + 16 * half) ? 1.f : 0.f);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, sel, acc, 0, 0, 0);
-}
-
 // ------------------------------------------------------- global <-> LDS ----
 // element e (compile-time after unrolling) of a 16-byte vector of T held in a u32x4, as fp32
 __device__ __forceinline__ uint32_t vec_word(const u32x4 &v, int w) { return v[w]; }
@@ -431,11 +407,6 @@ __device__ __forceinline__ float wave_suffix_sum(float x, int lane) {
         if (lane + off < 64) x += y;
     }
     return x;
-}
-
-// offsets into the caller's [B,T,H,D] tensors and the library's per-chunk tiles
-__device__ __forceinline__ size_t tok_off(int b, int t, int h, int T, int H, int D) {
-    return (((size_t)b * T + t) * H + h) * (size_t)D;
 }
 
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  The chain kernels

@@ -52,13 +52,6 @@ __device__ __forceinline__ float wave_max(float x) {      // x >= 0
 }
 // One workgroup = 8 wavefronts, two per SIMD.
 constexpr int P1T = 512, P1W = P1T / 64;
-// sum of the per-wave partials of row i (fixed order)
-__device__ __forceinline__ float sumw(const float *part, int i) {
-    float s = 0.f;
-#pragma unroll
-    for (int w = 0; w < P1W; ++w) s += part[w * C + i];
-    return s;
-}
 
 // partner lane ^ 4 inside a row of 16 lanes: two DPP moves (row_shl:4 into lanes 0-3 and 8-11 of
 // every row, row_shr:4 into the others)
@@ -96,43 +89,34 @@ __device__ __forceinline__ float lane_fold8_all(const float (&v)[8], int lane) {
     y += dpp_f32<0x128>(y);
     return add_xor32(add_xor16(y));
 }
-// Every lane holds the TS values v[0..TS) of TS tokens; returns to every lane the sum over the wavefront
-// of the token fold_token<TS>(lane).  The wide steps come first: a swap of halves (rows) between two
+// Every lane holds the values v[0..8) of eight tokens; returns to every lane the sum over the wavefront
+// of the token fold_token(lane).  The wide steps come first: a swap of halves (rows) between two
 // values and one add leave a register with one value in either half (every other row), two
 // instructions where selecting by lane bit takes three; then row rotations and mirrors into half of
-// the banks.  16 values: 32 instructions.
-template <int TS> __device__ __forceinline__ int fold_token(int lane) {
-    const int b2 = lane >> 2 & 1, b3 = lane >> 3 & 1, b4 = lane >> 4 & 1, b5 = lane >> 5;
-    return TS == 16 ? 8 * b2 + 4 * b3 + 2 * b4 + b5 : 4 * b3 + 2 * b4 + b5;
+// the banks.  17 instructions.
+__device__ __forceinline__ int fold_token(int lane) {
+    return 4 * (lane >> 3 & 1) + 2 * (lane >> 4 & 1) + (lane >> 5);
 }
-template <int TS> __device__ __forceinline__ constexpr int fold_lane(int token) {      // a lane that gets this token
-    return TS == 16 ? (token >> 3) * 4 + (token >> 2 & 1) * 8 + (token >> 1 & 1) * 16 + (token & 1) * 32
-                    : (token >> 2) * 8 + (token >> 1 & 1) * 16 + (token & 1) * 32;
+__device__ __forceinline__ constexpr int fold_lane(int token) {      // a lane that gets this token
+    return (token >> 2) * 8 + (token >> 1 & 1) * 16 + (token & 1) * 32;
 }
-template <int TS> __device__ __forceinline__ float fold_tokens(const float (&v)[TS]) {
-    static_assert(TS == 16 || TS == 8, "tokens");
-    float w[TS / 2], y[TS / 4];
+__device__ __forceinline__ float fold_tokens(const float (&v)[8]) {
+    float w[4], y[2];
 #pragma unroll
-    for (int i = 0; i < TS / 2; ++i) {
+    for (int i = 0; i < 4; ++i) {
         float a = v[2 * i], b = v[2 * i + 1];
         asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
         w[i] = a + b;
     }
 #pragma unroll
-    for (int i = 0; i < TS / 4; ++i) {
+    for (int i = 0; i < 2; ++i) {
         float a = w[2 * i], b = w[2 * i + 1];
         asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
         y[i] = a + b;
     }
-    float z[TS / 8];
-#pragma unroll
-    for (int i = 0; i < TS / 8; ++i) {
-        float t = y[2 * i] + dpp_f32<0x128>(y[2 * i]);                                                        // row_ror:8
-        asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc" : "+v"(t) : "v"(y[2 * i + 1]));
-        z[i] = t;
-    }
-    float x = z[0] + dpp_f32<0x141>(z[0]);                                                                    // row_half_mirror
-    if (TS == 16) asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa" : "+v"(x) : "v"(z[TS / 8 - 1]));
+    float x = y[0] + dpp_f32<0x128>(y[0]);                                                                    // row_ror:8
+    asm("s_nop 1\n\tv_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xc" : "+v"(x) : "v"(y[1]));
+    x += dpp_f32<0x141>(x);                                                                                   // row_half_mirror
     x += dpp_f32<0xB1>(x);
     x += dpp_f32<0x4E>(x);
     return x;

@@ -48,7 +48,7 @@
 
 namespace osdn {
 
-constexpr int RUN = 8;                           // tokens per run; C / RUN runs = wavefronts
+constexpr int RUN = 8;                           // tokens per run (fold_tokens takes eight); C / RUN runs = wavefronts
 constexpr int P1F = C / RUN * 64;                // threads
 
 // CPT adjacent elements of type T <-> floats, as one memory access
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
 
     const int tid = threadIdx.x, run = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c0 = lane * CPT;                    // first coordinate of this thread
-    const int u_own = fold_token<RUN>(lane);      // the token of the run whose scalars this lane keeps
+    const int u_own = fold_token(lane);      // the token of the run whose scalars this lane keeps
     const int piece = PIECES ? blockIdx.x % a.pieces : 0;
     const int chain = PIECES ? blockIdx.x / a.pieces : blockIdx.x;
     const int b = chain / a.H, h = chain % a.H;               // b: batch entry, or packed sequence
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
 #pragma unroll
                 for (int e = 0; e < RE; ++e) rv[u][e] = TILES || run * RUN + u < nvalid ? r2[e] : 1.f;
             } else {
-                rv[u][0] = HAS_RET ? lane_bcast(TILES || run * RUN + u < nvalid ? ret : 1.f, fold_lane<RUN>(u)) : 1.f;
+                rv[u][0] = HAS_RET ? lane_bcast(TILES || run * RUN + u < nvalid ? ret : 1.f, fold_lane(u)) : 1.f;
             }
         }
         OSDN_P1_LOAD(min(n + 1, a.n1 - 1))       // (past the end: reloaded in vain)
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
         for (int sweep = 0;; ++sweep) {
             float cv[RUN];
 #pragma unroll
-            for (int u = 0; u < RUN; ++u) cv[u] = lane_bcast(c_cur, fold_lane<RUN>(u));
+            for (int u = 0; u < RUN; ++u) cv[u] = lane_bcast(c_cur, fold_lane(u));
             // the map of this run, x -> clip3(A x + B, L, H), per coordinate
             if (FAST && !boxed) {
                 float Bv[CPT];
