@@ -48,23 +48,26 @@ def test_many_chains_wide_slices_channel_gate(K, bf16):
     compare_backward(x, ob.Hyper(eta=0.5, segments=1), bf16)
 
 
-@pytest.mark.parametrize("bf16", [False, True])
-def test_token_tensors_off_a_16_byte_boundary(bf16):
-    """q, k, v and dO four bytes past a 16-byte boundary give exactly what aligned tensors give."""
-    x = make_stress_inputs(1, 64 * 5, 2, 128, 128, seed=151, bf16=bf16, retention=0.97)
+@pytest.mark.parametrize("bf16,offset", [(False, 4), (True, 2), (True, 4)])
+@pytest.mark.parametrize("B,H,K,V,segments", [(1, 2, 128, 128, 0), (8, 16, 128, 64, 1), (8, 16, 64, 64, 2), (2, 2, 64, 128, 2)])
+def test_token_tensors_off_a_16_byte_boundary(B, H, K, V, segments, bf16, offset):
+    """q, k, v and dO two or four bytes past a 16-byte boundary give exactly what aligned tensors give:
+    few chains and many (slices of 16 and of 32 values), both widths of K, slots refilled within one launch
+    and by a second one."""
+    x = make_stress_inputs(B, 64 * 5, H, K, V, seed=151, bf16=bf16, retention=0.97)
     t = to_dev({n: x[n] for n in ("q", "k", "v", "dO", "beta", "log_alpha", "retention", "d_in", "S_in")}, bf16)
 
     def shifted(a):
-        skip = 4 // a.element_size()
+        skip = offset // a.element_size()
         buf = torch.empty(a.numel() + skip, dtype=a.dtype, device=a.device)
         out = buf[skip:].view(a.shape)
         out.copy_(a)
-        assert out.data_ptr() % 16 == 4
+        assert out.data_ptr() % 16 == offset
         return out
 
     def run(f):
         o, S, d, ctx = ob.forward(f(t["q"]), f(t["k"]), f(t["v"]), t["beta"], t["log_alpha"], t["retention"], t["d_in"],
-                                  t["S_in"], ob.Hyper(eta=0.5), for_backward=True)
+                                  t["S_in"], ob.Hyper(eta=0.5, segments=segments), for_backward=True)
         g = ob.backward(ctx, f(t["dO"]))
         torch.cuda.synchronize()
         return [o, S, d] + [g[n] for n in sorted(g)]

@@ -152,11 +152,10 @@ def test_reverse_sweep_in_solved_form(case, solved):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-def test_large_launches_two_chunks_per_workgroup(bf16):
-    """256 chains and 17 chunks: the second segment of either pass is a launch of more than 2048
-    chunk-heads, where a chunk_prep workgroup (and, for bf16, a bwd_post workgroup) does two
-    chunks in a row with the second one's first loads prefetched; the counts are odd, so the
-    last workgroup of every chain has a single chunk."""
+def test_large_launches_of_one_chunk_workgroups(bf16):
+    """256 chains and 17 chunks: the second segment of either pass is a launch of several thousand
+    chunk-heads, one workgroup each, numbered head first and then chunk (several rounds of the chip, the last
+    one partly filled), that does not begin at the first chunk."""
     B, T, H, K, V = 16, 64 * 17, 16, 64, 64
     x = make_stress_inputs(B, T, H, K, V, seed=62, bf16=bf16, retention=0.0)
     hp = ob.Hyper(eta=0.5)
