@@ -121,6 +121,45 @@ __device__ __forceinline__ float fold_tokens(const float (&v)[8]) {
     x += dpp_f32<0x4E>(x);
     return x;
 }
+__device__ __forceinline__ float lane_bcast(float x, int src_lane) {     // src_lane uniform
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), src_lane));
+}
+// ---- sweeps over a chunk in runs ------------------------------------------------------------
+// The sequential kernels of both directions cut a chunk into 8 runs of 8 tokens, one wavefront per run,
+// K / 64 adjacent coordinates per lane.
+constexpr int RUN = 8;                           // tokens per run (fold_tokens takes eight); C / RUN runs = wavefronts
+constexpr int P1F = C / RUN * 64;                // threads
+
+// CPT adjacent elements of type T <-> floats, as one memory access
+template <typename T, int CPT> struct Pack;
+template <> struct Pack<bf16, 2> {
+    typedef uint32_t Raw;
+    static __device__ __forceinline__ void unpack(Raw w, float (&o)[2]) {
+        o[0] = __builtin_bit_cast(float, w << 16);
+        o[1] = __builtin_bit_cast(float, w & 0xffff0000u);
+    }
+    static __device__ __forceinline__ Raw pack(const float (&v)[2]) {
+        const uint32_t lo = __builtin_bit_cast(unsigned short, (bf16)v[0]);
+        const uint32_t hi = __builtin_bit_cast(unsigned short, (bf16)v[1]);
+        return lo | (hi << 16);
+    }
+};
+template <> struct Pack<bf16, 1> {
+    typedef bf16 Raw;
+    static __device__ __forceinline__ void unpack(Raw w, float (&o)[1]) { o[0] = (float)w; }
+    static __device__ __forceinline__ Raw pack(const float (&v)[1]) { return (bf16)v[0]; }
+};
+template <> struct Pack<float, 2> {
+    typedef float Raw __attribute__((ext_vector_type(2)));
+    static __device__ __forceinline__ void unpack(Raw w, float (&o)[2]) { o[0] = w.x; o[1] = w.y; }
+    static __device__ __forceinline__ Raw pack(const float (&v)[2]) { return Raw{v[0], v[1]}; }
+};
+template <> struct Pack<float, 1> {
+    typedef float Raw;
+    static __device__ __forceinline__ void unpack(Raw w, float (&o)[1]) { o[0] = w; }
+    static __device__ __forceinline__ Raw pack(const float (&v)[1]) { return v[0]; }
+};
+
 // ---- a chunk of the recurrence in solved form ---------------------------------------------
 // Where a chunk of 64 tokens has no retention and no coordinate meets the box, both sweeps are
 // linear in the K-vector they carry (d forward, its adjoint backward) and couple the tokens only
@@ -157,10 +196,6 @@ __device__ __forceinline__ float sum_lanes4(float x) {
     x += dpp_f32<0xB1>(x);
     x += dpp_f32<0x4E>(x);
     return x;
-}
-
-__device__ __forceinline__ float lane_bcast(float x, int src_lane) {     // src_lane uniform
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), src_lane));
 }
 
 }  // namespace osdn

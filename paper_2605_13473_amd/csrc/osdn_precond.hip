@@ -48,39 +48,6 @@
 
 namespace osdn {
 
-constexpr int RUN = 8;                           // tokens per run (fold_tokens takes eight); C / RUN runs = wavefronts
-constexpr int P1F = C / RUN * 64;                // threads
-
-// CPT adjacent elements of type T <-> floats, as one memory access
-template <typename T, int CPT> struct Pack;
-template <> struct Pack<bf16, 2> {
-    typedef uint32_t Raw;
-    static __device__ __forceinline__ void unpack(Raw w, float (&o)[2]) {
-        o[0] = __builtin_bit_cast(float, w << 16);
-        o[1] = __builtin_bit_cast(float, w & 0xffff0000u);
-    }
-    static __device__ __forceinline__ Raw pack(const float (&v)[2]) {
-        const uint32_t lo = __builtin_bit_cast(unsigned short, (bf16)v[0]);
-        const uint32_t hi = __builtin_bit_cast(unsigned short, (bf16)v[1]);
-        return lo | (hi << 16);
-    }
-};
-template <> struct Pack<bf16, 1> {
-    typedef bf16 Raw;
-    static __device__ __forceinline__ void unpack(Raw w, float (&o)[1]) { o[0] = (float)w; }
-    static __device__ __forceinline__ Raw pack(const float (&v)[1]) { return (bf16)v[0]; }
-};
-template <> struct Pack<float, 2> {
-    typedef float Raw __attribute__((ext_vector_type(2)));
-    static __device__ __forceinline__ void unpack(Raw w, float (&o)[2]) { o[0] = w.x; o[1] = w.y; }
-    static __device__ __forceinline__ Raw pack(const float (&v)[2]) { return Raw{v[0], v[1]}; }
-};
-template <> struct Pack<float, 1> {
-    typedef float Raw;
-    static __device__ __forceinline__ void unpack(Raw w, float (&o)[1]) { o[0] = w; }
-    static __device__ __forceinline__ Raw pack(const float (&v)[1]) { return v[0]; }
-};
-
 // RET: 0 = no retention, 1 = one gate per (token, head), 2 = one per coordinate (diag(r_t))
 // PIECES: one workgroup per piece of a chain (sweeps over the whole sequence) instead of one per chain
 // TILES: part of a forward pass: whole chunks, k~ as one contiguous [64 x K] tile per chunk and head, the

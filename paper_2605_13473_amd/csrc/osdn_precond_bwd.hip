@@ -27,7 +27,7 @@
 //                  so, leaves (I + U)^-1 (Gram matrix and blocked inverse on the fp32 MFMA), kept
 //                  in the I/O type;
 //   precond_lin_r  the same grid, once dL/dk~ of the chunk is there: rho0 and sum_j lambda_j;
-// on such a chunk precond_chain only has the three matrix-vector products left (osdn_precond.h,
+// on such a chunk precond_chain_lin only has the three matrix-vector products left (osdn_precond.h,
 // "a chunk of the recurrence in solved form"); on any other chunk it runs its sweeps.
 #include "osdn_precond.h"
 
@@ -240,18 +240,338 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
 }
 
 // --------------------------------------------------------------- precond_chain ----
-// The adjoint recurrence is linear in a (the masks are data of the forward pass), so a chunk
-// is cut into NSEG = 512 / K runs of TS tokens and every thread owns one coordinate of one
-// run, all in registers: it runs the recurrence over its TS tokens from a zero right-hand
-// value, keeping abar_i = L_i + P_i * carry in the two parts L_i, P_i; the runs are chained
-// through LDS (one fma per run); the TS products s_i abar_i of a thread are folded over the
-// lanes of the wavefront (each lane ends with the sum of one token over a group of lanes) and
-// the sigma of a token is the sum of K / TS such partials.  No tile of the chunk is ever in LDS.
-// LINK: chunks that qualify take the solved form (no retention only; see the top of this file)
-template <typename T, int K, int RET, bool LINK>
-__global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
-    static_assert(!LINK || RET == 0, "the solved form has no retention");
+// The adjoint recurrence is linear in a (the masks are data of the forward pass).  A chunk is cut into
+// runs of 8 tokens, one wavefront per run, K / 64 adjacent coordinates per lane, everything in registers,
+// as in the forward kernel.  Per coordinate a run maps the adjoint at its right end to P a + L at its left:
+// P (mask bits and retentions) is a property of the chunk, L depends on the run's sigma.  A sweep
+// composes L from its sigma, publishes it, chains the runs to its right (one fma each), replays its
+// tokens and folds the products s_i abar_i over the lanes of the wavefront: the next sigma.
+//
+// The first sweep takes sigma = 0, the second what the first found; what the second finds is accepted
+// if it moved by so little that the next would move by less than the tolerance (differences shrink by the
+// ratio just seen); the adjoint at the chunk's left end is the one that gave it.  Two barriers a chunk: the
+// verdict on sigma is published together with the first maps of the next chunk (which need no adjoint); a
+// chunk that is then found not to have settled is done again, with a barrier for every verdict, and so are
+// the chunks after it until one settles in two.
+//
+// Bound by the issue of one CU's vector instructions (two wavefronts per SIMD) and the latency of its two
+// barriers.  Chains of 128 chunks of 128 coordinates, us per chunk: no retention 3.55 -> 2.40, one gate per head
+// 3.07 -> 2.60, per coordinate 3.38 -> 3.03, against three barriers a sweep, one coordinate and 16 tokens per thread,
+// and results stored behind the next chunk's loads.
+template <typename T, int K, int RET>
+__global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
+    constexpr int CPT = K / 64;                  // coordinates per thread (adjacent)
+    constexpr int NRUN = C / RUN;                // = wavefronts of the workgroup
+    typedef Pack<T, CPT> Pk;
+    typedef Pack<float, CPT> Pr;
+    __shared__ __attribute__((aligned(16))) float mapP[2][NRUN * K];     // chunks in turn
+    __shared__ __attribute__((aligned(16))) float mapL[3][NRUN * K];     // 0: of sigma = 0; 1, 2: of later sweeps, in turn
+    __shared__ __attribute__((aligned(16))) float wmax[2][2 * NRUN];           // per wavefront: largest change of sigma, largest sigma
+    __shared__ int flags[NRUN];
+
+    const int tid = threadIdx.x, run = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int c0 = lane * CPT;                   // first coordinate of this thread
+    const int u_own = fold_token(lane);          // the token of the run whose scalars this lane keeps
+    const int b = blockIdx.x / a.H, h = blockIdx.x % a.H;     // b: batch entry, or packed sequence
+    const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes dd_out / dd_in
+    int bt = b;                                               // batch entry of the token tensors
+    if (a.seq_chunks) {
+        bool begins, ends;
+        if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
+        a.dd_out = ends ? a.dd_last : a.dd_in;
+        bt = 0;
+    }
+    const size_t bth = (size_t)bt * a.H + h;                  // indexes the per-chunk buffers
+    const bool project = a.d_min <= a.d_max;
+    const int N = a.T / C;
+    const uint32_t kstride = (uint32_t)a.H * K;               // elements between consecutive tokens
+
+    float ga[CPT];                               // adjoint of d at the right end of the chunk (the same in every wavefront)
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) ga[e] = a.dd_out ? a.dd_out[bh * K + c0 + e] : 0.f;
+
+    typename Pk::Raw kreg[RUN], greg[RUN];       // this thread's k and dL/dk~ of the next chunk
+    typename Pr::Raw rreg[RET_VEC ? RUN : 1];    // ... its per-coordinate retention
+    uint32_t mreg[CPT];                          // ... half of its mask bits
+    float nrawreg = 1.f, betreg = 0.f, retreg = 1.f;          // ... and the scalars of token (run, u_own)
+#define OSDN_P1_BLOAD(n_)                                                                        \
+    {                                                                                            \
+        const size_t tokc_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                    \
+        const int fl_ = fresh_lane(lane);                                                        \
+        const T *kp_ = static_cast<const T *>(a.k) + (tokc_ + (size_t)(run * RUN) * a.H) * K;    \
+        const T *gp_ = static_cast<const T *>(a.dkt) + ((((size_t)bt * N + (n_)) * a.H + h) * C + run * RUN) * K; \
+        _Pragma("unroll") for (int u = 0; u < RUN; ++u) {                                        \
+            kreg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(kp_ + (size_t)u * kstride), fl_); \
+            greg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(gp_ + u * K), fl_);    \
+            if (RET_VEC)                                                                         \
+                rreg[RET_VEC ? u : 0] = row_elem(reinterpret_cast<const typename Pr::Raw *>(     \
+                    a.retention + (tokc_ + (size_t)(run * RUN + u) * a.H) * K), fl_);            \
+        }                                                                                        \
+        const uint32_t *mp_ = reinterpret_cast<const uint32_t *>(a.masks + (bth * N + (n_)) * K) + run / (32 / RUN); \
+        _Pragma("unroll") for (int e = 0; e < CPT; ++e) mreg[e] = lane_elem(mp_, (c0 + e) * 2);  \
+        const int i_ = run * RUN + u_own;                                                        \
+        nrawreg = lane_elem(a.tok_scalars + tokc_ * 4 + 2, i_ * a.H * 4);                        \
+        betreg = lane_elem(a.beta + tokc_, i_ * a.H);                                            \
+        if (HAS_RET && !RET_VEC) retreg = lane_elem(a.retention + tokc_, i_ * a.H);              \
+    }
+    auto put_map = [&](float *m, const float (&v)[CPT]) {
+        *reinterpret_cast<typename Pr::Raw *>(m + run * K + c0) = Pr::pack(v);
+    };
+    auto get_map = [&](const float *m, int j, float (&v)[CPT]) {
+        Pr::unpack(*reinterpret_cast<const typename Pr::Raw *>(m + j * K + c0), v);
+    };
+    // The adjoint g of the chunk's right end carried to the right end of this run (returned in at) and, if
+    // OUT, on to the chunk's left end (in g).  The run is the same for the whole wavefront: scalar branches.
+    auto carry = [&](auto out, const float *mP, const float *mL, float (&g)[CPT], float (&at)[CPT]) {
+        constexpr bool OUT = decltype(out)::value;
+        float P[NRUN][CPT], L[NRUN][CPT];
+        int r = run;
+        asm volatile("" : "+s"(r));              // (compared here: eight conditions kept for the whole kernel would spill)
+#pragma unroll
+        for (int j = NRUN - 1; j >= (OUT ? 0 : 1); --j) { get_map(mP, j, P[j]); get_map(mL, j, L[j]); }
+        float x[CPT];
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) x[e] = g[e];
+#pragma unroll
+        for (int j = NRUN - 1; j >= 0; --j) {
+            if (j == r) {
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) at[e] = x[e];
+                if (!OUT) return;
+            }
+            if (!OUT && j == 0) return;
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) x[e] = __builtin_fmaf(P[j][e], x[e], L[j][e]);
+        }
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) g[e] = x[e];
+    };
+    // (largest of values >= 0, compared as their bit patterns)
+    auto max8 = [](const float *v) {
+        typedef __attribute__((__vector_size__(16))) uint32_t U;
+        const U x = *reinterpret_cast<const U *>(v), y = *reinterpret_cast<const U *>(v + 4);
+        uint32_t m = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m = max(m, max(x[i], y[i]));
+        return __builtin_bit_cast(float, m);
+    };
+    // sqrt(P1_TOL_BWD): a second sweep that moved sigma by this share of what the first one did (from zero) settles it
+    constexpr float SECOND_OK = 3.16e-4f;
+
+    OSDN_P1_BLOAD(a.n1 - 1)
+    // what the next pass stores: chunk, adjoint at its right end, sigma (at first nothing to keep: stored again by the second pass)
+    int done = a.n1 - 1;
+    float gdone[CPT], sdone = 0.f;
+#pragma unroll
+    for (int e = 0; e < CPT; ++e) gdone[e] = ga[e];
+    bool pending = false, careful = false, refetch = false;   // the chunk before awaits its verdict; a barrier for every verdict
+    for (int n = a.n1 - 1;; --n) {
+        // ---- this thread's s = k^2, lambda = k . dL/dk~, masks and retention (past the end: of the last chunk, in vain) ----
+        float sv[RUN][CPT], lam[RUN][CPT], rv[RUN][RET_VEC ? CPT : 1];
+        uint32_t mb[CPT];
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) mb[e] = project ? mreg[e] >> (run % (32 / RUN) * RUN) & ((1u << RUN) - 1) : (1u << RUN) - 1;
+#pragma unroll
+        for (int u = 0; u < RUN; ++u) {
+            float kf[CPT], gf[CPT];
+            Pk::unpack(kreg[u], kf);
+            Pk::unpack(greg[u], gf);
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) {
+                sv[u][e] = kf[e] * kf[e];
+                lam[u][e] = kf[e] * gf[e];
+            }
+            if constexpr (RET_VEC) Pr::unpack(rreg[RET_VEC ? u : 0], rv[u]);
+            else rv[u][0] = HAS_RET ? lane_bcast(retreg, fold_lane(u)) : 1.f;
+        }
+        bool in = true;
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) in = in && mb[e] == (1u << RUN) - 1;
+        const bool clean = __all(in);            // no coordinate of this wavefront met the box in its run
+        float ca;
+        {
+            const float nn = fmaxf(nrawreg, a.eps), bp = a.beta_aware ? betreg : 1.f;
+            ca = a.eta * bp / nn * bp;
+        }
+        // (all that was loaded has been used when its registers are refilled: else the loop's end copies them, and waits)
+        asm volatile("" : "+v"(ca));
+        if constexpr (RET == 1) {
+#pragma unroll
+            for (int u = 0; u < RUN; ++u) asm volatile("" : "+s"(rv[u][0]));
+        }
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) {
+            asm volatile("" : "+v"(mb[e]));
+#pragma unroll
+            for (int u = 0; u < RUN; ++u) {
+                asm volatile("" : "+v"(sv[u][e]), "+v"(lam[u][e]));
+                if constexpr (RET_VEC) asm volatile("" : "+v"(rv[u][e]));
+            }
+        }
+        // the results of the chunk before, ahead of the loads: behind them, the wait for the loads would be one for
+        // these stores too (every wavefront stores the same adjoint, eight lanes the same sigma)
+        *reinterpret_cast<typename Pr::Raw *>(a.a_ckpt + (bth * N + done) * K + c0) = Pr::pack(gdone);
+        lane_elem(a.tok_scalars + (((size_t)bt * a.T + (size_t)done * C) * a.H + h) * 4 + 3, (run * RUN + u_own) * a.H * 4) = sdone;
+        OSDN_P1_BLOAD(max(n - 1, a.n0))
+        int mk[RUN][CPT];                        // all ones where the projection of the token lets the coordinate pass
+#pragma unroll
+        for (int u = 0; u < RUN; ++u)
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) {
+                mk[u][e] = (int)(mb[e] << (31 - u)) >> 31;
+                asm volatile("" : "+v"(mk[u][e]));       // (formed once, not at every use)
+            }
+        auto through = [&](float x, int u, int e) { return __builtin_bit_cast(float, __builtin_bit_cast(int, x) & mk[u][e]); };
+        // the run's L for lambda - ca sigma s = src
+        auto compose = [&](const float (&src)[RUN][CPT], float *m) {
+            float L[CPT];
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) {
+                float x = src[RUN - 1][e];
+                if (clean) {
+#pragma unroll
+                    for (int u = RUN - 2; u >= 0; --u) x = HAS_RET ? __builtin_fmaf(rv[u][RET_VEC ? e : 0], x, src[u][e]) : x + src[u][e];
+                } else {
+#pragma unroll
+                    for (int u = RUN - 2; u >= 0; --u) {
+                        const float t = through(x, u, e);
+                        x = HAS_RET ? __builtin_fmaf(rv[u][RET_VEC ? e : 0], t, src[u][e]) : t + src[u][e];
+                    }
+                }
+                L[e] = x;
+            }
+            put_map(m, L);
+        };
+        float P[CPT];
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) {
+            float x = rv[0][0];
+            if (HAS_RET) {
+                x = rv[0][RET_VEC ? e : 0];
+#pragma unroll
+                for (int u = 1; u < RUN; ++u) x *= rv[u][RET_VEC ? e : 0];
+            }
+            P[e] = mb[e] == (1u << RUN) - 1 ? x : 0.f;
+        }
+        float *const mP = mapP[n & 1];
+        put_map(mP, P);
+        compose(lam, mapL[0]);
+        __syncthreads();
+        if (pending) {
+            pending = false;
+            int bad = 0;
+#pragma unroll
+            for (int w = 0; w < NRUN; ++w) bad |= flags[w];
+            if (bad) {                           // (uniform) the chunk before, once more from the same adjoint
+                careful = refetch = true;
+                n += 3;                          // (the next pass only fetches chunk n + 1)
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) ga[e] = gdone[e];
+                continue;
+            }
+        }
+        if (refetch) {
+            refetch = false;
+            continue;
+        }
+        if (n < a.n0) break;
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) gdone[e] = ga[e];
+        // the tokens of the run replayed from the adjoint x at its right end: their sigma
+        auto replay = [&](const float (&at)[CPT], const float (&src)[RUN][CPT]) {
+            float vp[RUN];
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) {
+                float x = at[e];
+                if (clean) {
+#pragma unroll
+                    for (int u = RUN - 1; u >= 0; --u) {
+                        vp[u] = e == 0 ? sv[u][e] * x : __builtin_fmaf(sv[u][e], x, vp[u]);
+                        x = HAS_RET ? __builtin_fmaf(rv[u][RET_VEC ? e : 0], x, src[u][e]) : x + src[u][e];
+                    }
+                } else {
+#pragma unroll
+                    for (int u = RUN - 1; u >= 0; --u) {
+                        const float t = through(x, u, e);
+                        vp[u] = e == 0 ? sv[u][e] * t : __builtin_fmaf(sv[u][e], t, vp[u]);
+                        x = HAS_RET ? __builtin_fmaf(rv[u][RET_VEC ? e : 0], t, src[u][e]) : t + src[u][e];
+                    }
+                }
+            }
+            return fold_tokens(vp);
+        };
+        float src[RUN][CPT];
+        auto sources = [&](float sigma) {
+            const float cs = ca * sigma;
+#pragma unroll
+            for (int u = 0; u < RUN; ++u) {
+                const float c = -lane_bcast(cs, fold_lane(u));
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) src[u][e] = __builtin_fmaf(c, sv[u][e], lam[u][e]);
+            }
+        };
+        float at[CPT];
+        carry(std::false_type{}, mP, mapL[0], ga, at);
+        float sig0 = replay(at, lam);
+        {   // the largest of the wavefront (a lane holds one of eight tokens, by its upper three bits), in lane 63
+            uint32_t m = __builtin_bit_cast(uint32_t, fabsf(sig0));
+            m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x128, 0xF, 0xF, true));       // row_ror:8
+            m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x142, 0xA, 0xF, false));      // row_bcast:15
+            m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x143, 0xC, 0xF, false));      // row_bcast:31
+            if (lane == 63) wmax[0][NRUN + run] = __builtin_bit_cast(float, m);
+        }
+        sources(sig0);
+        compose(src, mapL[1]);
+        __syncthreads();
+        const float first = max8(wmax[0] + NRUN);
+        carry(std::true_type{}, mP, mapL[1], ga, at);
+        float sig = replay(at, src);
+        if (!careful) {
+            const bool settled = __all(!(fabsf(sig - sig0) > SECOND_OK * first));
+            if (lane == 0) flags[run] = settled ? 0 : 1;
+            pending = true;
+        } else {
+            float dprev = first;
+            int sweeps = 2, buf = 2, row = 1;
+            for (;;) {
+                const float d = wave_max(fabsf(sig - sig0)), x = wave_max(fabsf(sig));
+                if (lane == 0) { wmax[row][run] = d; wmax[row][NRUN + run] = x; }
+                sources(sig);
+                compose(src, mapL[buf]);
+                __syncthreads();
+                const float dcur = max8(wmax[row]), mx = max8(wmax[row] + NRUN);
+                // converged, or the observed contraction ratio says that the next difference would be below the tolerance
+                if (dcur <= P1_TOL_BWD * mx || (dcur <= 0.1f * dprev && dcur * dcur <= P1_TOL_BWD * mx * dprev) || sweeps >= P1_MAX_SWEEPS) break;
+                dprev = dcur;
+                sig0 = sig;
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) ga[e] = gdone[e];
+                carry(std::true_type{}, mP, mapL[buf], ga, at);
+                sig = replay(at, src);
+                buf = 3 - buf;
+                row ^= 1;
+                ++sweeps;
+            }
+            careful = sweeps > 2;
+        }
+        sdone = sig;
+        done = n;
+    }
+    if (run == 0) {
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) a.dd_in[bh * K + c0 + e] = ga[e];
+    }
+#undef OSDN_P1_BLOAD
+}
+
+// --------------------------------------------------------------- precond_chain_lin ----
+// The chain where chunks that qualify take the solved form (no retention; see the top of this file).  Any
+// other chunk is swept: NSEG = 512 / K runs of TS tokens, one coordinate of one run per thread, abar_i kept as
+// L_i + P_i * carry; the runs are chained through LDS, the products s_i abar_i folded over the lanes, three
+// barriers a sweep (such chunks are few here: the library takes this form only where d stays inside the box).
+template <typename T, int K>
+__global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a) {
     constexpr int NSEG = P1T / K;                 // runs per chunk
     constexpr int TS = C / NSEG;                  // tokens per run
     constexpr int WPS = K / 64;                   // wavefronts per run
@@ -259,7 +579,6 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
     __shared__ float ga[K];                      // adjoint of d at the right end of the chunk
     __shared__ float segL[NSEG * K], segP[NSEG * K];
     __shared__ float cas[C], sig[C];
-    __shared__ __attribute__((aligned(16))) float rs[C];
     __shared__ __attribute__((aligned(16))) float casig[C];
     __shared__ float part[P1W * 64];
     __shared__ int done;
@@ -296,8 +615,7 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
     }
 
     T kreg[TS], greg[TS];
-    float rreg[RET_VEC ? TS : 1];               // per-coordinate retention of the next chunk
-    float nrawreg = 1.f, betreg = 0.f, retreg = 1.f;
+    float nrawreg = 1.f, betreg = 0.f;
     uint2 mreg = make_uint2(0xffffffffu, 0xffffffffu);
 #define OSDN_P1_BLOAD(n_)                                                                        \
     {                                                                                            \
@@ -305,17 +623,15 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
         const T *kp_ = static_cast<const T *>(a.k) + tokc_ * K;                                  \
         const T *gp_ = static_cast<const T *>(a.dkt) + (((size_t)bt * N + (n_)) * a.H + h) * C * K; \
         uint32_t ok_ = (uint32_t)(sg * TS) * kstride + (uint32_t)c, og_ = (uint32_t)(sg * TS * K + c); \
-        if (LINK) asm volatile("" : "+v"(ok_), "+v"(og_));   /* (seldom run there: no addresses kept for it) */ \
+        asm volatile("" : "+v"(ok_), "+v"(og_));             /* (seldom run: no addresses kept for it) */ \
         _Pragma("unroll") for (int u = 0; u < TS; ++u) {                                         \
             const uint32_t o_ = ok_ + (uint32_t)u * kstride;                                     \
             kreg[u] = lane_elem(kp_, o_); greg[u] = lane_elem(gp_, og_ + u * K);                 \
-            if (RET_VEC) rreg[RET_VEC ? u : 0] = lane_elem(a.retention + tokc_ * K, o_);         \
         }                                                                                        \
         if (tid < C) {                                                                           \
             const size_t th = tokc_ + (size_t)tid * a.H;                                         \
             nrawreg = a.tok_scalars[th * 4 + 2];                                                 \
             betreg = a.beta[th];                                                                 \
-            if (HAS_RET && !RET_VEC) retreg = a.retention[th];                                   \
         }                                                                                        \
         if (project) mreg = a.masks[(bth * N + (n_)) * K + c];                                   \
     }
@@ -403,13 +719,12 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
         }                                                                                        \
     }
     // Which chunks take the solved form: the flags precond_lin left, as bits in LDS (bit n - n0;
-    // chunks past the table's reach sweep).  With LINK only the solved form prefetches (three
+    // chunks past the table's reach sweep).  Only the solved form prefetches (three
     // chunks deep, inside a run of such chunks); a chunk that has to sweep fetches its operands
     // when it starts: keeping both sets of registers alive across the loop would spill.
     constexpr int FLAG_WORDS = 512;
-    __shared__ uint32_t flagw[LINK ? FLAG_WORDS : 1];
-    const bool lin = LINK && a.lin_clean != nullptr;
-    if (lin) {
+    __shared__ uint32_t flagw[FLAG_WORDS];
+    {
         for (int base = 0; base < a.n1 - a.n0 && base < FLAG_WORDS * 32; base += P1T) {
             const int nn = a.n0 + base + tid;
             const int f = nn < a.n1 ? a.lin_clean[bth * N + nn] : 0;
@@ -420,16 +735,15 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
             }
         }
     }
-    if (!LINK) OSDN_P1_BLOAD(a.n1 - 1)
     __syncthreads();
     auto solved = [&](int nn) -> bool {            // uniform
         const int r = nn - a.n0;
-        return lin && r < FLAG_WORDS * 32 && ((flagw[LINK ? r >> 5 : 0] >> (r & 31)) & 1u) != 0;
+        return r < FLAG_WORDS * 32 && ((flagw[r >> 5] >> (r & 31)) & 1u) != 0;
     };
 
     for (int n = a.n1 - 1; n >= a.n0; --n) {
         const size_t tokc = ((size_t)bt * a.T + (size_t)n * C) * a.H + h;
-        if (LINK && solved(n)) {
+        if (solved(n)) {
             // the run [m, n] of chunks in solved form, three chunks in flight
             int m = n;
             while (m > a.n0 && solved(m - 1)) --m;
@@ -445,7 +759,7 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
             continue;
         }
         // ---- this thread's (s, lambda) = (k^2, k . dL/dk~) and mask bits ----
-        if (LINK) OSDN_P1_BLOAD(n)
+        OSDN_P1_BLOAD(n)
         float sv[TS], lam[TS];
 #pragma unroll
         for (int u = 0; u < TS; ++u) {
@@ -458,19 +772,12 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
         if (tid < C) {
             const float nn = fmaxf(nrawreg, a.eps);
             const float bp = a.beta_aware ? betreg : 1.f;
-            rs[tid] = retreg; cas[tid] = a.eta * bp / nn * bp; sig[tid] = 0.f; casig[tid] = 0.f;
+            cas[tid] = a.eta * bp / nn * bp; sig[tid] = 0.f; casig[tid] = 0.f;
         }
         if (tid < K) a.a_ckpt[(bth * N + n) * K + tid] = ga[tid];
         __syncthreads();
-        float rv[TS];                           // retention of this thread's coordinate, token by token
-        if (HAS_RET) {
-#pragma unroll
-            for (int u = 0; u < TS; ++u) rv[u] = RET_VEC ? rreg[RET_VEC ? u : 0] : rs[sg * TS + u];
-        }
-        if (!LINK && n > a.n0) OSDN_P1_BLOAD(n - 1)      // next chunk: in flight during the sweeps
-        // a wavefront whose coordinates never touched the box in this run, without retention:
-        // P stays 1 and L is a plain running sum
-        const bool plain = !HAS_RET && __all(mbits == ((1u << TS) - 1u));
+        // a wavefront whose coordinates never touched the box in this run: P stays 1 and L is a plain running sum
+        const bool plain = __all(mbits == ((1u << TS) - 1u));
         // ---- sweeps for sigma_i = <s_i, abar_i> ----
         float dprev = 0.f, a_left = 0.f;
         for (int sweep = 0; sweep < P1_MAX_SWEEPS; ++sweep) {
@@ -489,8 +796,8 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
                     abL[u] = in ? loc : 0.f;
                     abP[u] = in ? P : 0.f;
                     const float src = __builtin_fmaf(-casig[sg * TS + u], sv[u], lam[u]);
-                    loc = HAS_RET ? __builtin_fmaf(rv[u], abL[u], src) : abL[u] + src;
-                    P = HAS_RET ? rv[u] * abP[u] : abP[u];
+                    loc = abL[u] + src;
+                    P = abP[u];
                 }
             }
             segL[sg * K + c] = loc;
@@ -539,6 +846,7 @@ __global__ __launch_bounds__(P1T) void precond_chain_kernel(PrecondBwdArgs a) {
     }
     if (tid < K) a.dd_in[bh * K + tid] = ga[tid];
 }
+#undef OSDN_P1_BLOAD
 
 // ---------------------------------------------------------------- precond_post ----
 //   in : k, beta, retention, d_ckpt, tok_scalars (step, <d,s>, sum s, sigma per token),
@@ -673,11 +981,11 @@ template <typename T, int K, int RET>
 static void launch_chain_k(const PrecondBwdArgs &a, int nchains, hipStream_t st) {
     if constexpr (RET == 0) {
         if (a.lin_clean) {
-            hipLaunchKernelGGL((precond_chain_kernel<T, K, 0, true>), dim3(nchains), dim3(P1T), 0, st, a);
+            hipLaunchKernelGGL((precond_chain_lin_kernel<T, K>), dim3(nchains), dim3(P1T), 0, st, a);
             return;
         }
     }
-    hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, false>), dim3(nchains), dim3(P1T), 0, st, a);
+    hipLaunchKernelGGL((precond_chain_kernel<T, K, RET>), dim3(nchains), dim3(P1F), 0, st, a);
 }
 template <typename T, int RET>
 static int launch_precond_bwd_t(const PrecondBwdArgs &a, int which, hipStream_t st) {
