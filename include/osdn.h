@@ -39,10 +39,10 @@
  *     capture and leaves it inside the call).  Calls on different streams share nothing; calls
  *     that share one stream must be issued one after the other, as any work on one stream.
  *     params->segments = 1 keeps everything on `stream`.
- *     With at most 32 (batch, head) chains of at least 64 chunks, osdn_fwd computes the
- *     preconditioner as a few sweeps over pieces of the sequence that run side by side, all on
- *     `stream` (same results to the tolerance of the sweeps, 1e-6 relative; params->p1_pieces = -1
- *     keeps the one sequential sweep per chain).
+ *     With at most 32 (batch, head) chains of at least 24 chunks (with a retention gate 64; osdn_bwd: only
+ *     with one) the preconditioner, and its reverse, is computed as a few sweeps over pieces of the
+ *     sequence that run side by side, all on `stream` (same results to the tolerance of the sweeps, 1e-6
+ *     relative; params->p1_pieces = -1 keeps the one sequential sweep per chain).
  *   - retention values are assumed >= 0 (they are sigmoid gates in the paper).  Wherever a
  *     signature says retention / dretention [B,T,H], params->retention_per_channel = 1 makes
  *     it [B,T,H,K]: one value per coordinate.  Likewise params->gate_per_channel = 1 makes
@@ -101,8 +101,9 @@ typedef struct {
        how the work is cut, not what is computed (p1_pieces: to the sweeps' tolerance, see above). */
     int32_t segments;               /* > 0: cut the sequence into this many segments of chunks for the
                                        two-stream pipeline of osdn_fwd / osdn_bwd (1: one stream) */
-    int32_t p1_pieces;              /* > 0: osdn_fwd runs the preconditioner as sweeps over this many
-                                       pieces per chain; -1: never (always the sequential sweep) */
+    int32_t p1_pieces;              /* > 0: the preconditioner runs as sweeps over this many pieces per
+                                       chain (osdn_bwd: unless segments > 1 or it takes the solved form);
+                                       -1: never (always the sequential sweep) */
     int32_t p1_piece_sweeps;        /* > 0: at most this many such sweeps (up to 13) before the sequential
                                        sweep finishes the chains that have not settled */
     int32_t p1_solved;              /* osdn_bwd: 1: the reverse sweep takes chunks in solved form (a 64 x 64

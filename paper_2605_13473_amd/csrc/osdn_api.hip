@@ -324,16 +324,27 @@ inline int seg_begin(int N, int S, int s) {
     return first + (int)((long long)(N - first) * (s - 1) / (S - 1));
 }
 
-// Phase 1 of the forward pass as sweeps over the whole sequence, for few long chains: with
-// chains on at most an eighth of the CUs the sequential kernel leaves most of the chip idle and
-// its walk over the chunks is the whole forward pass.  Every chain is cut into pieces (one
-// workgroup per CU over all chains, at least 8 chunks each); a sweep runs all pieces side by
+// Phase 1 as sweeps over the whole sequence, for few long chains: one workgroup per chain leaves most
+// of the chip idle and its walk over the chunks is most of the pass.  Every chain is cut into pieces
+// (a workgroup per CU over all chains; two where a piece still has eight chunks, which shortens the walk more
+// than two workgroups on a CU slow each other); a sweep runs all pieces side by
 // side, each from its current start value, and leaves every piece as a composed map per
 // coordinate; the next sweep walks those maps for its start values; a chain is settled when none
 // of its start values moves any more.  Plain batches only.  params->p1_pieces forces a number of
 // pieces per chain (-1: never), params->p1_piece_sweeps the sweep limit.
-inline void pieces_plan(const osdn_params *p, int N, long long chains, bool packed, int &pieces, int &piece_chunks,
-                        int &sweeps) {
+//
+// Where the line lies (us per pass, sequential or in segments against pieces; K = V = 128 in bf16):
+//  - forward, chains on an eighth of the CUs or fewer, from 24 chunks on: 16 chains of 24 110 and 96, with a retention
+//    gate 131 and 105, of 32 137 and 107, 167 and 116, of 64 229 and 187 (pieces of 4 chunks; of 8: 229), 32 of
+//    32 166 and 138; 16 chains of 16 79 and 82.  With a retention gate, whose chunk takes half as long again and which needs
+//    two sweeps instead of three to five, on a quarter of the CUs too, from 32 chunks on: 64 chains of 32 247 and 232, of 64
+//    423 and 407, of 24 187 and 211.
+//  - backward, only with a retention gate (without, a piece needs more sweeps, and the solved form has the shorter
+//    chain): 16 chains of 24 chunks 143 and 126, of 32 175 and 138, of 128 579 and 432, of 512 1986 and 1600; 64 chains
+//    of 32 331 and 308, of 128 1126 and 1097, of 256 2136 and 2159; pieces of four chunks at least (16 chains
+//    of 32 chunks: pieces of two 146).
+inline void pieces_plan(const osdn_params *p, int N, long long chains, bool packed, bool retention, bool backward, int &pieces,
+                        int &piece_chunks, int &sweeps) {
     pieces = 0; piece_chunks = 0;
     // sweeps needed without retention, measured: 4 at 64 and 128 chunks, then one more per
     // doubling (7 at 1024); the limit leaves two in hand
@@ -343,8 +354,15 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
     const int forced = p->p1_pieces;              // 0: decide here; -1: never; n > 0: n pieces per chain
     int target, min_chunks;
     if (forced != 0) { target = forced > 0 ? forced : 0; min_chunks = 1; }
-    else if (chains * 8 <= NUM_CU && N >= 64) { target = (int)(NUM_CU / chains); min_chunks = 8; }
-    else return;
+    else {
+        const bool few = chains * 8 <= NUM_CU, some = retention && chains * 4 <= NUM_CU;
+        if (!(few ? N >= 24 : some && N >= (backward ? 24 : 32) && (!backward || N <= 128)) || (backward && !retention)) return;
+        target = (int)(NUM_CU / chains);
+        if (N >= 16 * target) target *= 2;
+        const int most = N <= 64 ? 16 : 32;          // (every workgroup walks the maps of all pieces of its chain)
+        if (target > most) target = most;
+        min_chunks = backward ? 4 : 2;
+    }
     if ((long long)target * chains > MAX_PIECES) target = (int)(MAX_PIECES / chains);
     if (target < 2) return;
     int len = (N + target - 1) / target;
@@ -555,7 +573,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const int N = p->T / C;
     const long long chains = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
     int pieces, piece_chunks, piece_sweeps;
-    pieces_plan(p, N, chains, pk.n_seqs != 0, pieces, piece_chunks, piece_sweeps);
+    pieces_plan(p, N, chains, pk.n_seqs != 0, retention != nullptr, false, pieces, piece_chunks, piece_sweeps);
     int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, 0, false);
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
@@ -764,7 +782,9 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     // (256 chains of 16 chunks, V = 64: 1109 against 1155; 128 chains, V = 256: 1330 against 1404).
     c.narrow_slices = !bf && (p->K == 128 || chains * (p->V / 16) <= NUM_CU);
     const long long chain_wgs = chains * (p->V / (c.narrow_slices ? 16 : 32)) + chains;     // of the chain kernels of both phases
-    int S = segment_count(p->segments, N, pk.longest, chain_wgs, true, chains, (bf ? 2 : 1) * NUM_CU, !solved);   // (bwd_post: two workgroups a CU with bf16 I/O)
+    int pieces = 0, piece_chunks = 0, piece_sweeps = 0;
+    if (!solved && p->segments <= 1) pieces_plan(p, N, chains, pk.n_seqs != 0, retention != nullptr, true, pieces, piece_chunks, piece_sweeps);
+    int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, chain_wgs, true, chains, (bf ? 2 : 1) * NUM_CU, !solved);   // (bwd_post: two workgroups a CU with bf16 I/O)
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
     auto seg_range = [&](int sidx, int &n0, int &n1) { n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1); };
@@ -797,6 +817,20 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         seg_range(sidx, pb.n0, pb.n1);
         return timed(KID_PRECOND_LIN, s1, [&] { return general ? launch_precond_gen(pb, bf, 1, s1) : launch_precond_lin_bwd(pb, bf, false, s1); });
     };
+    auto precond_pieces = [&]() {
+        PrecondBwdArgs pp = pb;
+        pp.n0 = 0; pp.n1 = N; pp.dd_out = dd_out;
+        pp.pieces = pieces; pp.piece_chunks = piece_chunks;
+        pp.piece_map = reinterpret_cast<float4 *>(ws + L.piece_map);
+        pp.settled = reinterpret_cast<int *>(ws + L.piece_flags);
+        for (int i = 0; i < piece_sweeps; ++i) {
+            pp.sweep = i;
+            if (timed(KID_PRECOND_CHAIN, st, [&] { return launch_precond_chain(pp, bf, st); }) != 0) return -1;
+        }
+        pb.n0 = 0; pb.n1 = N; pb.dd_out = dd_out; pb.settled = pp.settled;
+        if (timed(KID_PRECOND_CHAIN, st, [&] { return launch_precond_chain(pb, bf, st); }) != 0) return -1;
+        return timed(KID_PRECOND_POST, st, [&] { return launch_precond_post(pb, bf, st); });
+    };
     auto phase1 = [&](int sidx, hipStream_t s1) {
         seg_range(sidx, pb.n0, pb.n1);
         pb.dd_out = sidx == S - 1 ? dd_out : dd_in;  // the adjoint of d is carried in dd_in
@@ -805,7 +839,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     };
     if (!pl) {
         if (phase2(KID_BWD_CHAIN, 0) != 0 || phase2(KID_BWD_POST, 0) != 0 ||
-            masks(st) != 0 || lin_m(0, N, st) != 0 || lin_r(0, st) != 0 || phase1(0, st) != 0)
+            masks(st) != 0 || lin_m(0, N, st) != 0 || lin_r(0, st) != 0 || (pieces ? precond_pieces() : phase1(0, st)) != 0)
             return OSDN_ERR_SHAPE;
         return finish();
     }

@@ -87,6 +87,11 @@ struct PrecondBwdArgs {
     void *lin_M;              // [B,H,T/64,64,64] io
     float *lin_r0;            // [B,H,T/64,64]
     float *lin_t0;            // [B,H,T/64,K]
+    // Sweeps over the whole sequence (pieces > 0, plain batches only), as in the forward pass: one workgroup per piece of
+    // piece_chunks chunks; sweep number `sweep` reads the records (x, y, P, g) that sweep - 1 left (two buffers in turn)
+    int pieces, piece_chunks, sweep;
+    float4 *piece_map;        // [2][B*H*pieces, K]
+    int *settled;             // [B*H] or null: a chain whose entry is set is left alone
     unsigned char *lin_aux;   // [B,H,T/64,2048]: with a retention gate, the indicators and retention products of the chunk
 };
 

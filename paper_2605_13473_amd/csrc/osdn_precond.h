@@ -7,6 +7,8 @@ namespace osdn {
 constexpr int P1_MAX_SWEEPS = 66;       // 64 guarantee exactness
 constexpr float P1_TOL = 1e-6f;         // relative agreement of the inner products between sweeps (forward)
 constexpr float P1_TOL_BWD = 1e-7f;     // ... of sigma in the reverse sweep, whose errors add up in the adjoint of d
+constexpr float PIECE_TOL = P1_TOL;     // ... of d at the start of a piece between sweeps over a sequence
+constexpr float PIECE_TOL_BWD = 5e-7f;  // ... of its adjoint at the end of a piece (of the largest coordinate; such errors do not add up)
 constexpr int PB = 8;                   // tokens per LDS prefetch block in the sequential loops
 
 // projection onto [lo, hi] as one median-of-three (lo = -inf, hi = +inf when there is none)

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
                     const size_t i = (bh * a.pieces + q) * K + tid;
                     const float old = a.piece_start[prev + i];
                     if (q == piece) xs = x;
-                    if (!(fabsf(x - old) <= P1_TOL * fmaxf(fabsf(x), fabsf(old)))) moved = true;
+                    if (!(fabsf(x - old) <= PIECE_TOL * fmaxf(fabsf(x), fabsf(old)))) moved = true;
                     const float4 m = a.piece_map[prev + i];
                     x = clip3(__builtin_fmaf(m.x, x, m.y), m.z, m.w);
                 }

@@ -258,8 +258,19 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
 // barriers.  Chains of 128 chunks of 128 coordinates, us per chunk: no retention 3.55 -> 2.40, one gate per head
 // 3.07 -> 2.60, per coordinate 3.38 -> 3.03, against three barriers a sweep, one coordinate and 16 tokens per thread,
 // and results stored behind the next chunk's loads.
-template <typename T, int K, int RET>
+//
+// PIECES: for few long chains the chain is cut into pieces, one workgroup each, as in the forward kernel: every
+// piece is swept from a guess of the adjoint at its right end, and the sweeps over all pieces repeat until
+// no such value of the chain moves.  A piece that began at x and ended at y is left as the map
+//     x' -> y + P (x' - x - g <g, x' - x> / <1, g>),
+// P per coordinate, g = sum over the piece's tokens of ca_t <1, s_t> s_t (retention: without the term in
+// g): exact where nothing moved, and as good as the sweeps need it elsewhere.  The term in g is the coupling of the
+// coordinates along (1, .., 1), which is nearly all of it (sum ca_t s_t s_t^T = g g^T / <1, g> for equal keys).
+// With a retention gate two sweeps do and a third finds that nothing moved (16 chains, K = V = 128, backward pass of 128
+// chunks 579 -> 432 us, of 512 1986 -> 1600); without, three to five.
+template <typename T, int K, int RET, bool PIECES>
 __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
+    constexpr bool COUPLED = PIECES && RET == 0;
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     constexpr int CPT = K / 64;                  // coordinates per thread (adjacent)
     constexpr int NRUN = C / RUN;                // = wavefronts of the workgroup
@@ -273,8 +284,16 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     const int tid = threadIdx.x, run = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c0 = lane * CPT;                   // first coordinate of this thread
     const int u_own = fold_token(lane);          // the token of the run whose scalars this lane keeps
-    const int b = blockIdx.x / a.H, h = blockIdx.x % a.H;     // b: batch entry, or packed sequence
+    const int piece = PIECES ? blockIdx.x % a.pieces : 0;
+    const int chain = PIECES ? blockIdx.x / a.pieces : blockIdx.x;
+    const int b = chain / a.H, h = chain % a.H;               // b: batch entry, or packed sequence
     const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes dd_out / dd_in
+    if (a.settled && !(PIECES && a.sweep == 0) && a.settled[chain]) return;
+    if (PIECES) {
+        a.n0 += piece * a.piece_chunks;
+        a.n1 = min(a.n1, a.n0 + a.piece_chunks);
+        if (a.n0 >= a.n1) return;
+    }
     int bt = b;                                               // batch entry of the token tensors
     if (a.seq_chunks) {
         bool begins, ends;
@@ -290,6 +309,67 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     float ga[CPT];                               // adjoint of d at the right end of the chunk (the same in every wavefront)
 #pragma unroll
     for (int e = 0; e < CPT; ++e) ga[e] = a.dd_out ? a.dd_out[bh * K + c0 + e] : 0.f;
+
+    auto put_map = [&](float *m, const float (&v)[CPT]) {
+        *reinterpret_cast<typename Pr::Raw *>(m + run * K + c0) = Pr::pack(v);
+    };
+    auto get_map = [&](const float *m, int j, float (&v)[CPT]) {
+        Pr::unpack(*reinterpret_cast<const typename Pr::Raw *>(m + j * K + c0), v);
+    };
+    float PP[CPT], gacc[COUPLED ? CPT : 1] = {}, start[CPT];  // the piece so far: P, g; where it began
+    if (PIECES) {
+        // The adjoint at this piece's right end: the chain's own carried through the maps that the sweep before left
+        // (first sweep: the chain's own, as a guess).  Every workgroup of a chain walks all its pieces and so sees
+        // whether any of those values moved; if none did, what the sweep before wrote stands.
+        const size_t buf = (size_t)gridDim.x * K;
+        const float4 *prev = a.piece_map + ((a.sweep & 1) ? 0 : buf) + bh * a.pieces * K;
+        if (run == 0) {
+            float x[CPT], xs[CPT];
+            bool moved = a.sweep == 0;
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) x[e] = xs[e] = ga[e];
+            if (a.sweep > 0) {
+#pragma unroll 4
+                for (int q = a.pieces - 1; q >= 0; --q) {
+                    float4 m[CPT];
+                    float dx[CPT], dot = 0.f, sum = 0.f, big = 0.f;
+#pragma unroll
+                    for (int e = 0; e < CPT; ++e) {
+                        m[e] = prev[(size_t)q * K + c0 + e];
+                        if (q == piece) xs[e] = x[e];
+                        dx[e] = x[e] - m[e].x;
+                        big = fmaxf(big, fabsf(x[e]));
+                        dot = __builtin_fmaf(m[e].w, dx[e], dot);
+                        sum += m[e].w;
+                    }
+                    big = wave_max(big);
+#pragma unroll
+                    for (int e = 0; e < CPT; ++e) moved = moved || !(fabsf(dx[e]) <= PIECE_TOL_BWD * big);   // (not a number: moved)
+                    if (COUPLED) {
+                        dot = wave_sum(dot);
+                        sum = wave_sum(sum);
+                        const float r = sum > 0.f ? dot / sum : 0.f;
+#pragma unroll
+                        for (int e = 0; e < CPT; ++e) dx[e] = __builtin_fmaf(-r, m[e].w, dx[e]);
+                    }
+#pragma unroll
+                    for (int e = 0; e < CPT; ++e) x[e] = __builtin_fmaf(m[e].z, dx[e], m[e].y);
+                }
+            }
+            if (__any(moved)) moved = true;
+            if (lane == 0) flags[0] = moved ? 1 : 0;
+            put_map(mapL[0], xs);
+        }
+        __syncthreads();
+        const int any = flags[0];
+        if (piece == 0 && tid == 0) a.settled[chain] = any ? 0 : 1;
+        if (!any) return;
+        get_map(mapL[0], 0, ga);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) { PP[e] = 1.f; start[e] = ga[e]; }
+        a.piece_map += (a.sweep & 1) ? buf : 0;
+    }
 
     typename Pk::Raw kreg[RUN], greg[RUN];       // this thread's k and dL/dk~ of the next chunk
     typename Pr::Raw rreg[RET_VEC ? RUN : 1];    // ... its per-coordinate retention
@@ -315,12 +395,6 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         betreg = lane_elem(a.beta + tokc_, i_ * a.H);                                            \
         if (HAS_RET && !RET_VEC) retreg = lane_elem(a.retention + tokc_, i_ * a.H);              \
     }
-    auto put_map = [&](float *m, const float (&v)[CPT]) {
-        *reinterpret_cast<typename Pr::Raw *>(m + run * K + c0) = Pr::pack(v);
-    };
-    auto get_map = [&](const float *m, int j, float (&v)[CPT]) {
-        Pr::unpack(*reinterpret_cast<const typename Pr::Raw *>(m + j * K + c0), v);
-    };
     // The adjoint g of the chunk's right end carried to the right end of this run (returned in at) and, if
     // OUT, on to the chunk's left end (in g).  The run is the same for the whole wavefront: scalar branches.
     auto carry = [&](auto out, const float *mP, const float *mL, float (&g)[CPT], float (&at)[CPT]) {
@@ -345,7 +419,13 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
             for (int e = 0; e < CPT; ++e) x[e] = __builtin_fmaf(P[j][e], x[e], L[j][e]);
         }
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) g[e] = x[e];
+        for (int e = 0; e < CPT; ++e) {
+            g[e] = x[e];
+            if (PIECES) {
+#pragma unroll
+                for (int j = 0; j < NRUN; ++j) PP[e] *= P[j][e];
+            }
+        }
     };
     // (largest of values >= 0, compared as their bit patterns)
     auto max8 = [](const float *v) {
@@ -362,7 +442,7 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     OSDN_P1_BLOAD(a.n1 - 1)
     // what the next pass stores: chunk, adjoint at its right end, sigma (at first nothing to keep: stored again by the second pass)
     int done = a.n1 - 1;
-    float gdone[CPT], sdone = 0.f;
+    float gdone[CPT], sdone = 0.f, PPdone[PIECES ? CPT : 1] = {};
 #pragma unroll
     for (int e = 0; e < CPT; ++e) gdone[e] = ga[e];
     bool pending = false, careful = false, refetch = false;   // the chunk before awaits its verdict; a barrier for every verdict
@@ -389,13 +469,14 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
 #pragma unroll
         for (int e = 0; e < CPT; ++e) in = in && mb[e] == (1u << RUN) - 1;
         const bool clean = __all(in);            // no coordinate of this wavefront met the box in its run
-        float ca;
+        float ca, cn = 0.f;
         {
             const float nn = fmaxf(nrawreg, a.eps), bp = a.beta_aware ? betreg : 1.f;
             ca = a.eta * bp / nn * bp;
+            if (COUPLED) cn = ca * nrawreg;
         }
         // (all that was loaded has been used when its registers are refilled: else the loop's end copies them, and waits)
-        asm volatile("" : "+v"(ca));
+        asm volatile("" : "+v"(ca), "+v"(cn));
         if constexpr (RET == 1) {
 #pragma unroll
             for (int u = 0; u < RUN; ++u) asm volatile("" : "+s"(rv[u][0]));
@@ -467,7 +548,10 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
                 careful = refetch = true;
                 n += 3;                          // (the next pass only fetches chunk n + 1)
 #pragma unroll
-                for (int e = 0; e < CPT; ++e) ga[e] = gdone[e];
+                for (int e = 0; e < CPT; ++e) {
+                    ga[e] = gdone[e];
+                    if (PIECES) PP[e] = PPdone[PIECES ? e : 0];
+                }
                 continue;
             }
         }
@@ -477,7 +561,18 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         }
         if (n < a.n0) break;
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) gdone[e] = ga[e];
+        for (int e = 0; e < CPT; ++e) {
+            gdone[e] = ga[e];
+            if (PIECES) PPdone[PIECES ? e : 0] = PP[e];
+        }
+        if (COUPLED) {                           // (a chunk that is done again counts twice: the map is an approximation)
+#pragma unroll
+            for (int u = 0; u < RUN; ++u) {
+                const float c = lane_bcast(cn, fold_lane(u));
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) gacc[COUPLED ? e : 0] = __builtin_fmaf(c, sv[u][e], gacc[COUPLED ? e : 0]);
+            }
+        }
         // the tokens of the run replayed from the adjoint x at its right end: their sigma
         auto replay = [&](const float (&at)[CPT], const float (&src)[RUN][CPT]) {
             float vp[RUN];
@@ -546,7 +641,10 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
                 dprev = dcur;
                 sig0 = sig;
 #pragma unroll
-                for (int e = 0; e < CPT; ++e) ga[e] = gdone[e];
+                for (int e = 0; e < CPT; ++e) {
+                    ga[e] = gdone[e];
+                    if (PIECES) PP[e] = PPdone[PIECES ? e : 0];
+                }
                 carry(std::true_type{}, mP, mapL[buf], ga, at);
                 sig = replay(at, src);
                 buf = 3 - buf;
@@ -558,9 +656,28 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         sdone = sig;
         done = n;
     }
+    if (COUPLED) {                               // g of the piece: the sum over its runs
+        float v[CPT];
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) v[e] = gacc[COUPLED ? e : 0];
+        __syncthreads();
+        put_map(mapL[0], v);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) gacc[COUPLED ? e : 0] = 0.f;
+#pragma unroll
+        for (int j = 0; j < NRUN; ++j) {
+            get_map(mapL[0], j, v);
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) gacc[COUPLED ? e : 0] += v[e];
+        }
+    }
     if (run == 0) {
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) a.dd_in[bh * K + c0 + e] = ga[e];
+        for (int e = 0; e < CPT; ++e) {
+            if (!PIECES || piece == 0) a.dd_in[bh * K + c0 + e] = ga[e];
+            if (PIECES) a.piece_map[(bh * a.pieces + piece) * K + c0 + e] = make_float4(start[e], ga[e], PP[e], COUPLED ? gacc[COUPLED ? e : 0] : 0.f);
+        }
     }
 #undef OSDN_P1_BLOAD
 }
@@ -985,7 +1102,8 @@ static void launch_chain_k(const PrecondBwdArgs &a, int nchains, hipStream_t st)
             return;
         }
     }
-    hipLaunchKernelGGL((precond_chain_kernel<T, K, RET>), dim3(nchains), dim3(P1F), 0, st, a);
+    if (a.pieces) hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, true>), dim3(nchains * a.pieces), dim3(P1F), 0, st, a);
+    else hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, false>), dim3(nchains), dim3(P1F), 0, st, a);
 }
 template <typename T, int RET>
 static int launch_precond_bwd_t(const PrecondBwdArgs &a, int which, hipStream_t st) {

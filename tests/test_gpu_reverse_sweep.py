@@ -1,12 +1,14 @@
 """The reverse sweep of phase 1 (precond_chain) in its two courses: a chunk whose sigma settles in two sweeps
 goes on before its verdict is known, one that does not is fetched and done again (the last and the only chunk of a
-launch among them), at every retention form, with clean and mixed masks in one workgroup, over segments."""
+launch among them), at every retention form, with clean and mixed masks in one workgroup, over segments; and
+its sweeps over pieces of the sequence."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_13473_amd import binding as ob
 from paper_2605_13473_amd.inputs import make_stress_inputs
-from tests.gpu_util import compare_backward
+from tests.gpu_util import compare_backward, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +36,64 @@ def test_no_box_and_no_gradient():
     compare_backward(x, ob.Hyper(eta=0.3, d_min=1.0, d_max=0.0, p1_solved=-1, segments=1), True)
     x["dO"][:] = 0
     compare_backward(x, ob.Hyper(eta=0.3, p1_solved=-1, segments=1), True)
+
+
+@pytest.mark.parametrize("retention", ["none", "head", "channel"])
+@pytest.mark.parametrize("pieces", [2, 7, 24])
+def test_pieces_of_uneven_length(pieces, retention):
+    """The last piece shorter than the others, pieces of one chunk, a ragged end, an adjoint from outside."""
+    rng = np.random.Generator(np.random.Philox(9))
+    T = 64 * 23 + 5
+    x = make_stress_inputs(1, T, 2, 64, 64, seed=191, bf16=False, retention=0.97)
+    if retention == "none":
+        x["retention"] = None
+    elif retention == "channel":
+        x["retention"] = rng.uniform(0.9, 1.0, (1, T, 2, 64)).astype(np.float32)
+    dd = rng.standard_normal((1, 2, 64)).astype(np.float32)
+    compare_backward(x, ob.Hyper(eta=0.3, p1_pieces=pieces, p1_solved=-1), False, dd_out=dd)
+
+
+def test_values_that_are_not_finite_reach_what_they_reached_without_pieces():
+    """A gradient that is not finite never settles: the sequential sweep has the last word."""
+    x = to_dev(make_stress_inputs(1, 64 * 12, 2, 64, 64, seed=193, bf16=False, retention=0.97), False)
+    x["dO"][0, 500, 1, 3] = float("inf")
+    got = []
+    for pieces in (-1, 4):
+        o, S, d, ctx = ob.forward(*[x[n] for n in ("q", "k", "v", "beta", "log_alpha", "retention", "d_in", "S_in")],
+                                  ob.Hyper(eta=0.3, p1_pieces=pieces), for_backward=True)
+        got.append(ob.backward(ctx, x["dO"]))
+    torch.cuda.synchronize()
+    assert not torch.isfinite(got[0]["dd_in"][0, 1]).all() and torch.isfinite(got[0]["dd_in"][0, 0]).all()
+    for n, a in got[0].items():
+        assert torch.equal(torch.isfinite(a), torch.isfinite(got[1][n])), n
+
+
+def test_segments_in_a_captured_graph():
+    """Short sequences take one stream by themselves; the side stream's part of a capture, forced here, and
+    replays between eager calls."""
+    t = to_dev(make_stress_inputs(2, 64 * 6, 2, 64, 64, seed=197, bf16=True, retention=0.97), True)
+    p = ob.make_params(2, 384, 2, 64, 64, True, ob.Hyper(eta=0.3, segments=3))
+    ws = ob.alloc_workspace(p, True)
+    names = ("q", "k", "v", "beta", "log_alpha", "retention", "d_in", "S_in")
+    fwd = [torch.empty_like(t["v"]), torch.empty_like(t["S_in"]), torch.empty_like(t["d_in"])]
+    grads = [torch.empty_like(t[n]) for n in names]
+
+    def step():
+        ob.osdn_fwd(p, *[t[n] for n in names], *fwd, ws)
+        ob.osdn_bwd(p, *[t[n] for n in names], t["dO"], None, None, *grads, ws)
+
+    step()
+    torch.cuda.synchronize()
+    ref = [a.clone() for a in fwd + grads]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for _ in range(3):
+        for a in fwd + grads:
+            a.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, r) for a, r in zip(fwd + grads, ref))
+        step()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, r) for a, r in zip(fwd + grads, ref))
