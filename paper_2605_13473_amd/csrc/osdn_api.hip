@@ -254,12 +254,17 @@ Pipeline *pipeline_for(hipStream_t caller) {
 }
 
 // Number of segments for a sequence of N chunks (params->segments > 0 overrides it; 1 = no
-// pipelining).  At least two (any sequence of at least two chunks, so that short
-// sequences take the same path).  A segment more shortens the stretch of phase 1 that runs with
-// nothing beside it (the first segment of the forward pass, the last of the backward pass) and
-// costs launches, cross-stream waits and partly filled rounds of workgroups.
-//  - forward: about 16 chunks per segment, at most six segments (measured flat beyond).
-//  - backward: a segment more costs more there, because every launch of the phase-2 chain kernel
+// pipelining).  A segment more shortens the stretch of phase 1 that runs with nothing beside it (the
+// first segment of the forward pass, the last of the backward pass) and costs launches, cross-stream
+// waits (25 us a call for the first) and partly filled rounds of workgroups.  Times below: one stream against the best
+// of two to six segments, us, K = V = 128 in bf16.
+//  - short sequences take one stream: forward up to 32 chunks (2 chains of 4 chunks 34 and 80, 64 of 16 107 and
+//    129, 64 of 32 221 and 231; 64 of 48 322 and 309), backward up to 48 (2 of 4 49 and 113, 64 of 16
+//    156 and 208, 8 of 32 128 and 158, 64 of 48 463 and 465, 128 of 48 790 and 802; 32 of 64 409 and 380).
+//  - so do many chains, which fill the chip by themselves: 256 of 64 forward 1141 and 1206, backward 1935 and 1997;
+//    from 128 chains on the forward pass takes two at most (128 of 128 1249, with six 1298).
+//  - forward otherwise: about 16 chunks per segment, at most six segments (measured flat beyond).
+//  - backward otherwise: a segment more costs more there, because every launch of the phase-2 chain kernel
 //    meets a phase-1 chain kernel on the other stream and the two do not fit on one CU together:
 //    when the workgroups of both (chain_wgs) outnumber the CUs, the count that balances the
 //    exposed tail against that cost is about sqrt(N / 15) (2 at 64 chunks, 4 at 256); when they
@@ -269,17 +274,17 @@ Pipeline *pipeline_for(hipStream_t caller) {
 //    or twelve if phase 1 sweeps (p1_sweeps: it is slower then, and its last segment what is exposed).
 //    16 chains, bf16, backward pass alone: 128 chunks 494, 499, 493, 515, 546, 575 us with 3 to 8 segments
 //    (5 taken); 256 chunks, V = 256 993, 1014, 1057, 1063, 1097, 1023 with 4 to 9 (5); 512 chunks 1648, 1625, 1621,
-//    1619, 1643, 1816 with 4 to 8 and 12, with retention 2284, 2255, 2219, 2198, 2204, 2206; 4 chains of 625
-//    chunks, fp32, with retention 4026 and 3972 with 7 and 12.
+//    1619, 1643, 1816 with 4 to 8 and 12.
 // Segments cut the chunk axis as a whole.  With packed sequences the sequential kernels of a
 // segment only have the sequences that cross it to work on, one after the other segment by
 // segment, so cutting pays only while one sequence makes up most of the axis; otherwise the
 // many independent chains fill the chip by themselves and everything runs in one piece.
 constexpr int NUM_CU = 256;
-int segment_count(int forced, int N, int longest, long long chain_wgs, bool backward, long long chains = 0, int post_round = 0, bool p1_sweeps = false) {
+int segment_count(int forced, int N, int longest, long long chains, long long chain_wgs, bool backward, int post_round = 0, bool p1_sweeps = false) {
     if (forced <= 0 && (long long)longest * 4 < (long long)N * 3) return 1;
     int S = forced;
     if (forced <= 0) {
+        if (N <= (backward ? 48 : 32) || chains >= NUM_CU) return 1;
         if (!backward) S = N / 16 > 6 ? 6 : N / 16;
         else if (chain_wgs > NUM_CU) S = (int)std::lround(std::sqrt(N / 15.0)) > 6 ? 6 : (int)std::lround(std::sqrt(N / 15.0));
         else {
@@ -295,7 +300,7 @@ int segment_count(int forced, int N, int longest, long long chain_wgs, bool back
             }
             S = pick;
         }
-        if (S < 2 && N >= 2) S = 2;
+        if (S < 2 || (!backward && chains * 2 >= NUM_CU)) S = 2;
     }
     if (S > MAX_SEGMENTS) S = MAX_SEGMENTS;
     if (S > N) S = N;
@@ -574,7 +579,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const long long chains = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
     int pieces, piece_chunks, piece_sweeps;
     pieces_plan(p, N, chains, pk.n_seqs != 0, retention != nullptr, false, pieces, piece_chunks, piece_sweeps);
-    int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, 0, false);
+    int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, chains, 0, false);
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
     // chain workgroups of both phases (32 rows of the state per workgroup in state_fwd) against the CUs
@@ -755,15 +760,14 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     pb.n_seqs = pk.n_seqs; pb.seq_chunks = seq_chunks; pb.dd_last = dd_out;
     pb.out = out; pb.dk = dk; pb.dbeta = dbeta; pb.dretention = retention ? dretention : nullptr; pb.dd_in = dd_in;
     // Without retention, chunks that never met the box can take the solved form of the reverse
-    // sweep: a dependent chain less than half as long for about 0.6 KB more memory traffic per
-    // token-head.  It pays while the phase-1 chain is what the pass waits for: chains on at most a
-    // quarter of the CUs (measured at 64 chains: 3 % of forward + backward; with more chains the
-    // chains fill the chip by themselves and the pass is bound by its memory traffic).  With fp32
-    // I/O the inverses are twice the size and the form stops paying earlier: an eighth of the CUs.
+    // sweep: a dependent chain about half as long for 0.6 KB more memory traffic per
+    // token-head.  It pays while the phase-1 chain is what the pass waits for: chains on at most an eighth
+    // of the CUs (K = V = 128 in bf16, us, sweeps and solved: 16 chains of 32 chunks 168 and 145, of 128 543 and 491; 32 of 64
+    // 393 and 380; 64 of 32 317 and 327, of 64 603 and 632).
     const long long chains_all = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
     const bool general = retention && !p->retention_per_channel;      // the form with a retention gate and any masks
     const bool solved = general ? p->p1_solved > 0
-                                : !retention && (p->p1_solved > 0 || (p->p1_solved == 0 && chains_all * (bf ? 4 : 8) <= NUM_CU));
+                                : !retention && (p->p1_solved > 0 || (p->p1_solved == 0 && chains_all * 8 <= NUM_CU));
     if (solved) {
         pb.lin_clean = reinterpret_cast<int *>(ws + L.lin_clean);
         pb.lin_M = ws + L.lin_M;
@@ -784,7 +788,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const long long chain_wgs = chains * (p->V / (c.narrow_slices ? 16 : 32)) + chains;     // of the chain kernels of both phases
     int pieces = 0, piece_chunks = 0, piece_sweeps = 0;
     if (!solved && p->segments <= 1) pieces_plan(p, N, chains, pk.n_seqs != 0, retention != nullptr, true, pieces, piece_chunks, piece_sweeps);
-    int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, chain_wgs, true, chains, (bf ? 2 : 1) * NUM_CU, !solved);   // (bwd_post: two workgroups a CU with bf16 I/O)
+    int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, chains, chain_wgs, true, (bf ? 2 : 1) * NUM_CU, !solved);   // (bwd_post: two workgroups a CU with bf16 I/O)
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
     auto seg_range = [&](int sidx, int &n0, int &n1) { n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1); };
