@@ -48,8 +48,8 @@
  *     it [B,T,H,K]: one value per coordinate.  Likewise params->gate_per_channel = 1 makes
  *     log_alpha / dlog_alpha [B,T,H,K]: one state gate per key channel, S <- S Diag(alpha_t)
  *     (online-scaled KDA, appendix section on Kimi Delta Attention with online scaling).
- *   - Supported shapes: chunk == 64; any T >= 1 (osdn_fwd/osdn_bwd pad a ragged last chunk
- *     inside the workspace with tokens that change nothing; osdn_precond_update needs
+ *   - Supported shapes: chunk == 64; any T >= 1 (in a ragged last chunk, osdn_fwd/osdn_bwd
+ *     treat the tokens that do not exist as ones that change nothing; osdn_precond_update needs
  *     T % 64 == 0 only when d_ckpt is asked for; 1 <= T <= 64 for osdn_step); K in {64, 128}
  *     (K = 256 is not built: the [64 x K] operand tiles of the chain and backward kernels would
  *     no longer fit the 160 KB of LDS next to each other); V a multiple of 64 up to 512; B, H >= 1 with H * max(K, V) < 2^24 (the 64 token rows of
@@ -226,9 +226,9 @@ int osdn_bwd(const osdn_params *p, const void *q, const void *k, const void *v, 
  *               S_in, S_out, dS_out, dS_in are [n_seqs,H,V,K].  Every sequence starts from its own
  *               d_in / S_in entry (NULL => ones / zeros: the reset) and leaves its own final
  *               d and S; no state crosses a boundary.
- * Sequences need not be whole chunks: inside the workspace each sequence is moved to start on
- * a chunk boundary and padded with tokens that change nothing (no copies are made when every
- * length is a multiple of 64).  The sequential kernels run one chain per (sequence, head).
+ * Sequences need not be whole chunks: the token tensors are read and written where they are, and
+ * inside the workspace each sequence starts on a chunk boundary.  The sequential kernels run one
+ * chain per (sequence, head).
  * osdn_workspace_bytes_packed sizes the workspace for exactly this cu_seqlens (0 on invalid
  * arguments); osdn_bwd_packed takes the same cu_seqlens and the workspace osdn_fwd_packed filled.
  */

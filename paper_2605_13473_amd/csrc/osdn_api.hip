@@ -39,13 +39,11 @@ struct Layout {
     size_t Qg, Kg, Kd, Kw, gamC, dgamC;                                    // per-channel state gate
     size_t tables;                                                       // packed sequences: the index tables
     size_t kt, d_ckpt, tok_scalars, Wn, Tu, gates, Et, S_ckpt;        // forward
+    size_t k_tail, beta_tail, ret_tail;                                  // ragged last chunks, whole
     size_t piece_start, piece_map, piece_flags;                          // phase 1 as sweeps over the whole sequence
     size_t Tm, Pm;                                                       // written by the forward pass for the backward pass only
     size_t dEt, dS_ckpt, dk_read, dkt, masks, a_ckpt;                    // backward only
     size_t lin_clean, lin_M, lin_r0, lin_t0, lin_aux;                           // backward: chunks of phase 1 in solved form
-    // padded copies of the caller's tensors, only when T is not a multiple of the chunk length
-    size_t p_q, p_k, p_v, p_beta, p_g, p_r;                        // forward
-    size_t p_dO, p_dq, p_dbeta, p_dg, p_dr;                 // backward
     size_t total_fwd, total_bwd;
 };
 
@@ -85,8 +83,10 @@ struct Packing {
     int n_seqs = 0;
     int N = 0;                   // chunks of the padded token axis (per batch entry)
     int longest = 0;             // chunks of the longest sequence
-    bool ragged = false;         // some sequence is not a whole number of chunks: work on padded copies
-    std::vector<int> tables;     // seq_chunks [n_seqs + 1], chunk_row [N], chunk_len [N]
+    bool ragged = false;         // some sequence is not a whole number of chunks
+    const int32_t *cu = nullptr; // the caller's offsets, n_seqs + 1
+    std::vector<int> seq_chunks; // first chunk of every sequence, n_seqs + 1
+    size_t table_ints() const { return n_seqs ? (size_t)n_seqs + 1 + 2 * (size_t)N : 0; }   // seq_chunks, chunk_row [N], chunk_seq [N] on the device
 };
 
 // cu_seqlens: n_seqs + 1 ascending token offsets, from 0 to T, on the host
@@ -105,17 +105,14 @@ int make_packing(const osdn_params *p, const int32_t *cu, int n_seqs, Packing &p
     if (N * C > 0x7fffffffLL) return OSDN_ERR_SHAPE;
     pk.n_seqs = n_seqs;
     pk.N = (int)N;
-    pk.tables.assign((size_t)n_seqs + 1 + 2 * (size_t)N, 0);
-    int *seq_chunks = pk.tables.data(), *chunk_row = seq_chunks + n_seqs + 1, *chunk_len = chunk_row + N;
+    pk.cu = cu;
+    pk.seq_chunks.resize((size_t)n_seqs + 1);
     int c = 0;
     for (int s = 0; s < n_seqs; ++s) {
-        seq_chunks[s] = c;
-        for (int t = cu[s]; t < cu[s + 1]; t += C, ++c) {
-            chunk_row[c] = t;
-            chunk_len[c] = cu[s + 1] - t < C ? cu[s + 1] - t : C;
-        }
+        pk.seq_chunks[s] = c;
+        c += (cu[s + 1] - cu[s] + C - 1) / C;
     }
-    seq_chunks[n_seqs] = c;
+    pk.seq_chunks[n_seqs] = c;
     return OSDN_OK;
 }
 
@@ -125,17 +122,14 @@ void plain_packing(const osdn_params *p, Packing &pk) {
     pk.ragged = pk.N * C != p->T;
 }
 
-// every buffer is sized for the padded token axis of pk.N whole chunks
+// every buffer is sized for a token axis of pk.N whole chunks
 Layout make_layout(const osdn_params *p, const Packing &pk) {
     const size_t es = p->io_dtype == OSDN_BF16 ? 2 : 4;
     const size_t B = p->B, H = p->H, K = p->K, V = p->V, N = (size_t)pk.N, T = N * C;
-    const size_t RK = p->retention_per_channel ? K : 1;    // retention values per (token, head)
-    const size_t GK = p->gate_per_channel ? K : 1;         // state gates per (token, head)
-    const bool ragged = pk.ragged;
     Layout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
-    L.tables = take(pk.tables.size() * sizeof(int));
+    L.tables = take(pk.table_ints() * sizeof(int));
     L.kt = take(B * T * H * K * es);
     L.d_ckpt = take(B * H * N * K * 4);
     L.tok_scalars = take(B * T * H * 4 * 4);
@@ -149,10 +143,11 @@ Layout make_layout(const osdn_params *p, const Packing &pk) {
         L.Kw = take(B * T * H * K * es);
         L.gamC = take(B * H * N * K * 4);
     }
-    if (ragged) {
-        L.p_q = take(B * T * H * K * es); L.p_k = take(B * T * H * K * es);
-        L.p_v = take(B * T * H * V * es);
-        L.p_beta = take(B * T * H * 4); L.p_g = take(B * T * H * 4 * GK); L.p_r = take(B * T * H * 4 * RK);
+    if (pk.ragged) {
+        const size_t tails = pk.n_seqs ? (size_t)pk.n_seqs : B;
+        L.k_tail = take(tails * C * H * K * es);
+        L.beta_tail = take(tails * C * H * 4);
+        L.ret_tail = take(tails * C * H * 4 * (p->retention_per_channel ? K : 1));
     }
     L.piece_start = take((size_t)2 * MAX_PIECES * K * 4);
     L.piece_map = take((size_t)2 * MAX_PIECES * K * 16);
@@ -172,12 +167,6 @@ Layout make_layout(const osdn_params *p, const Packing &pk) {
     L.lin_t0 = take(B * H * N * K * 4);
     L.lin_aux = take(B * H * N * 2048);
     if (p->gate_per_channel) L.dgamC = take(B * H * N * K * 4);
-    if (ragged) {
-        L.p_dO = take(B * T * H * V * es);
-        if (p->gate_per_channel) L.p_dq = take(B * T * H * K * es);
-        L.p_dbeta = take(B * T * H * 4); L.p_dg = take(B * T * H * 4 * GK);
-        if (!p->retention_per_channel) L.p_dr = take(B * T * H * 4);
-    }
     L.total_bwd = off;
     return L;
 }
@@ -199,7 +188,7 @@ PrecondArgs precond_args(const osdn_params *p) {
     return a;
 }
 
-ChunkArgs chunk_args(const osdn_params *p, const Layout &L, char *ws) {      // p: the padded problem
+ChunkArgs chunk_args(const osdn_params *p, const Layout &L, char *ws) {      // p: T in whole chunks
     ChunkArgs c{};
     c.B = p->B; c.T = p->T; c.H = p->H; c.K = p->K; c.V = p->V; c.N = p->T / C;
     c.scale = p->scale;
@@ -466,6 +455,7 @@ int osdn_precond_update(const osdn_params *p, const void *k, const float *beta,
     PrecondArgs a = precond_args(p);
     a.k = k; a.beta = beta; a.retention = retention; a.d_in = d_in;
     a.k_tilde = k_tilde; a.d_out = d_out; a.d_ckpt = d_ckpt; a.tok_scalars = nullptr;
+    a.rows = Rows{p->T, nullptr, nullptr};
     a.n0 = 0; a.n1 = (p->T + C - 1) / C;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool bf = p->io_dtype == OSDN_BF16;
@@ -519,45 +509,27 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const bool bf = p->io_dtype == OSDN_BF16;
     int *tables = reinterpret_cast<int *>(ws + L.tables);
     const int *seq_chunks = pk.n_seqs ? tables : nullptr;
-    const int *chunk_row = tables + pk.n_seqs + 1, *chunk_len = chunk_row + pk.N;
-    if (pk.n_seqs && timed(KID_PAD, st, [&] { return launch_upload_ints(pk.tables.data(), pk.tables.size(), tables, st); }) != 0)
+    const int *chunk_row = tables + pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
+    if (pk.n_seqs && timed(KID_PAD, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
         return OSDN_ERR_SHAPE;
 
-    // ragged chunks (the tail of the sequence, or of any packed sequence): work on padded copies
-    // (no-op pad tokens); the output goes straight to the caller's rows
-    osdn_params padded = *p;
-    padded.T = pk.N * C;
-    const int T_user = p->T;
-    const bool ragged = pk.ragged;
-    auto move = [&](const void *src, void *dst, size_t row, uint32_t fill) {
-        return timed(KID_PAD, st, [&] {
-            if (pk.n_seqs) return launch_move_chunk_rows(src, dst, chunk_row, chunk_len, pk.N, row, true, fill, st);
-            return launch_copy_rows(src, T_user, dst, padded.T, p->B, row, fill, st);
-        });
-    };
-    if (ragged) {
-        const size_t es = bf ? 2 : 4, rk = (size_t)p->H * p->K * es, rv = (size_t)p->H * p->V * es, rg = (size_t)p->H * 4;
-        auto pad = [&](const void *src, size_t off, size_t row, uint32_t fill) { return move(src, ws + off, row, fill); };
-        if (pad(q, L.p_q, rk, 0u) != 0 || pad(k, L.p_k, rk, 0u) != 0 || pad(v, L.p_v, rv, 0u) != 0 ||
-            pad(beta, L.p_beta, rg, 0u) != 0 || (log_alpha && pad(log_alpha, L.p_g, p->gate_per_channel ? rg * p->K : rg, 0u) != 0) ||
-            (retention && pad(retention, L.p_r, p->retention_per_channel ? rg * p->K : rg, 0x3f800000u) != 0))
-            return OSDN_ERR_SHAPE;
-        q = ws + L.p_q; k = ws + L.p_k; v = ws + L.p_v;
-        beta = reinterpret_cast<const float *>(ws + L.p_beta);
-        if (log_alpha) log_alpha = reinterpret_cast<const float *>(ws + L.p_g);
-        if (retention) retention = reinterpret_cast<const float *>(ws + L.p_r);
-        p = &padded;
-    }
+    // the workspace is laid out for whole chunks; the caller's tensors are read where they are
+    osdn_params whole = *p;
+    whole.T = pk.N * C;
+    const Rows rows{p->T, pk.ragged && pk.n_seqs ? chunk_row : nullptr, pk.ragged && pk.n_seqs ? chunk_seq : nullptr};
+    p = &whole;
 
     PrecondArgs pa = precond_args(p);
+    pa.rows = rows;
     pa.k = k; pa.beta = beta; pa.retention = retention;
     pa.k_tilde = ws + L.kt; pa.kt_tiles = 1; pa.d_out = d_out; pa.d_ckpt = reinterpret_cast<float *>(ws + L.d_ckpt);
     pa.tok_scalars = reinterpret_cast<float *>(ws + L.tok_scalars);
+    pa.k_tail = ws + L.k_tail; pa.beta_tail = reinterpret_cast<float *>(ws + L.beta_tail); pa.ret_tail = reinterpret_cast<float *>(ws + L.ret_tail);
     pa.n_seqs = pk.n_seqs; pa.seq_chunks = seq_chunks; pa.d_first = d_in;
     ChunkArgs c = chunk_args(p, L, ws);
     c.q = q; c.k = k; c.v = v; c.beta = beta; c.log_alpha = log_alpha;
     c.o = o; c.S_out = S_out;
-    c.out = OutRows{T_user, ragged && pk.n_seqs ? chunk_row : nullptr, ragged && pk.n_seqs ? chunk_len : nullptr};
+    c.rows = rows;
     // (I + A)^-1 and P are only of use to a backward pass: they are written when the workspace is
     // the one osdn_workspace_bytes(p, 1) asks for, which osdn_bwd requires anyway
     if (workspace_bytes >= L.total_bwd) { c.Tm = ws + L.Tm; c.Pm = ws + L.Pm; }
@@ -677,57 +649,21 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const bool bf = p->io_dtype == OSDN_BF16;
     int *tables = reinterpret_cast<int *>(ws + L.tables);
     const int *seq_chunks = pk.n_seqs ? tables : nullptr;
-    const int *chunk_row = tables + pk.n_seqs + 1, *chunk_len = chunk_row + pk.N;
-    if (pk.n_seqs && timed(KID_PAD, st, [&] { return launch_upload_ints(pk.tables.data(), pk.tables.size(), tables, st); }) != 0)
+    const int *chunk_row = tables + pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
+    if (pk.n_seqs && timed(KID_PAD, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
         return OSDN_ERR_SHAPE;
 
-    // ragged chunks: the padded inputs are the ones the forward call left in the workspace; dO
-    // is padded here; dk, dv and (one state gate per head) dq go straight to the caller's rows, the
-    // gradients of the gates are produced padded and moved back at the end
-    osdn_params padded = *p;
-    padded.T = pk.N * C;
-    const int T_user = p->T;
-    const bool ragged = pk.ragged;
-    auto move = [&](const void *src, void *dst, size_t row, bool to_padded) {
-        return timed(KID_PAD, st, [&] {
-            if (pk.n_seqs) return launch_move_chunk_rows(src, dst, chunk_row, chunk_len, pk.N, row, to_padded, 0u, st);
-            return to_padded ? launch_copy_rows(src, T_user, dst, padded.T, p->B, row, 0u, st)
-                             : launch_copy_rows(src, padded.T, dst, T_user, p->B, row, 0u, st);
-        });
-    };
-    const OutRows out{T_user, ragged && pk.n_seqs ? chunk_row : nullptr, ragged && pk.n_seqs ? chunk_len : nullptr};
-    const bool gv = p->gate_per_channel != 0, rv = p->retention_per_channel != 0;
-    void *dq_user = dq;
-    float *dbeta_user = dbeta, *dg_user = dlog_alpha, *dr_user = dretention;
-    const size_t es_ = bf ? 2 : 4, rk_ = (size_t)p->H * p->K * es_, rv_ = (size_t)p->H * p->V * es_, rg_ = (size_t)p->H * 4;
-    if (ragged) {
-        if (move(dO, ws + L.p_dO, rv_, true) != 0) return OSDN_ERR_SHAPE;
-        q = ws + L.p_q; k = ws + L.p_k; v = ws + L.p_v; dO = ws + L.p_dO;
-        beta = reinterpret_cast<const float *>(ws + L.p_beta);
-        if (log_alpha) log_alpha = reinterpret_cast<const float *>(ws + L.p_g);
-        if (retention) retention = reinterpret_cast<const float *>(ws + L.p_r);
-        if (gv) dq = ws + L.p_dq;
-        dbeta = reinterpret_cast<float *>(ws + L.p_dbeta);
-        dlog_alpha = reinterpret_cast<float *>(ws + L.p_dg);
-        if (!rv) dretention = reinterpret_cast<float *>(ws + L.p_dr);
-        p = &padded;
-    }
-    auto finish = [&]() -> int {
-        if (ragged) {
-            auto cut = [&](const void *src, void *dst, size_t row) { return move(src, dst, row, false); };
-            if ((gv && cut(dq, dq_user, rk_) != 0) || cut(dbeta, dbeta_user, rg_) != 0 ||
-                (log_alpha && cut(dlog_alpha, dg_user, gv ? rg_ * p->K : rg_) != 0) ||
-                (retention && !rv && cut(dretention, dr_user, rg_) != 0))
-                return OSDN_ERR_SHAPE;
-        }
-        return launch_status();
-    };
+    osdn_params whole = *p;                              // (as in the forward pass)
+    whole.T = pk.N * C;
+    const Rows rows{p->T, pk.ragged && pk.n_seqs ? chunk_row : nullptr, pk.ragged && pk.n_seqs ? chunk_seq : nullptr};
+    const bool gv = p->gate_per_channel != 0;
+    p = &whole;
 
     ChunkArgs c = chunk_args(p, L, ws);
     c.q = q; c.k = k; c.v = v; c.beta = beta; c.log_alpha = log_alpha;
     c.dO = dO; c.dS_out = dS_out;
     c.Tm = ws + L.Tm; c.Pm = ws + L.Pm; c.dEt = ws + L.dEt; c.dS_ckpt = ws + L.dS_ckpt;
-    c.dS_in = dS_in; c.dq = dq; c.dv = dv; c.out = out;
+    c.dS_in = dS_in; c.dq = dq; c.dv = dv; c.rows = rows;
     c.dk_read = ws + L.dk_read;
     c.dkt = ws + L.dkt;
     c.dbeta = dbeta; c.dlog_alpha = log_alpha ? dlog_alpha : nullptr;
@@ -736,7 +672,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     // pass left (Gamma . Q, Gamma . K, K~ / Gamma, gamma_C . K~ / Gamma) and the unfold kernel maps its gradients back
     UnfoldArgs un{};
     if (gv) {
-        un.B = p->B; un.T = p->T; un.H = p->H; un.K = p->K; un.N = p->T / C;
+        un.B = p->B; un.T = p->T; un.H = p->H; un.K = p->K; un.N = p->T / C; un.rows = rows;
         un.log_alpha = log_alpha; un.q = q; un.k = k; un.kt = c.kt;
         un.dq = dq; un.dk_read = c.dk_read; un.dkt = c.dkt;
         un.dgamC = reinterpret_cast<const float *>(ws + L.dgamC);
@@ -752,13 +688,14 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     pb.beta_aware = p->beta_aware;
     pb.ret_vec = p->retention_per_channel;
     pb.k = k; pb.beta = beta; pb.retention = retention;
+    pb.k_tail = ws + L.k_tail; pb.beta_tail = reinterpret_cast<const float *>(ws + L.beta_tail); pb.ret_tail = reinterpret_cast<const float *>(ws + L.ret_tail);
     pb.d_ckpt = reinterpret_cast<const float *>(ws + L.d_ckpt);
     pb.tok_scalars = reinterpret_cast<float *>(ws + L.tok_scalars);
     pb.masks = reinterpret_cast<uint2 *>(ws + L.masks);
     pb.a_ckpt = reinterpret_cast<float *>(ws + L.a_ckpt);
     pb.dkt = c.dkt; pb.dk_read = c.dk_read;
     pb.n_seqs = pk.n_seqs; pb.seq_chunks = seq_chunks; pb.dd_last = dd_out;
-    pb.out = out; pb.dk = dk; pb.dbeta = dbeta; pb.dretention = retention ? dretention : nullptr; pb.dd_in = dd_in;
+    pb.rows = rows; pb.dk = dk; pb.dbeta = dbeta; pb.dretention = retention ? dretention : nullptr; pb.dd_in = dd_in;
     // Without retention, chunks that never met the box can take the solved form of the reverse
     // sweep: a dependent chain about half as long for 0.6 KB more memory traffic per
     // token-head.  It pays while the phase-1 chain is what the pass waits for: chains on at most an eighth
@@ -845,7 +782,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
         if (phase2(KID_BWD_CHAIN, 0) != 0 || phase2(KID_BWD_POST, 0) != 0 ||
             masks(st) != 0 || lin_m(0, N, st) != 0 || lin_r(0, st) != 0 || (pieces ? precond_pieces() : phase1(0, st)) != 0)
             return OSDN_ERR_SHAPE;
-        return finish();
+        return launch_status();
     }
     // main: phase 2, segments right to left          (a[s]: phase 2 of segment s done)
     // side: the masks at once, then phase 1 of segment s once a[s] has fired; joined back at the end
@@ -886,7 +823,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     OSDN_HIP_OK(hipEventRecord(pl->join, s1));
     OSDN_HIP_OK(hipStreamWaitEvent(st, pl->join, 0));
     rejoin.armed = false;
-    return finish();
+    return launch_status();
 }
 
 int osdn_fwd(const osdn_params *p, const void *q, const void *k, const void *v, const float *beta,

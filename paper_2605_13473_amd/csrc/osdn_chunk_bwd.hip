@@ -73,7 +73,7 @@ template <typename T, int K> constexpr int BC_NSC = sizeof(T) == 2 ? 2 : 1;
 // itself, below the smallest normal number (at a decay of e^-79 from |dS'| = 2.4e-4 on), which K~ /
 // Gamma would bring back to the size of dS'.
 // VS: rows of S (values) owned by one workgroup, 32 or 16 (launch_chain_v says which).
-template <typename T, int K, bool GV, int VS>
+template <typename T, int K, bool GV, int VS, bool RAG>
 __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
     constexpr int ES = sizeof(T), RK = K * ES, RC = C * ES, RV = VS * ES;      // bytes per row of a tile
     constexpr int NVT = VS / 16, NFB = K / 16;
@@ -110,23 +110,24 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
     LdsLoad<RC, C, CM_> lP;
     LdsLoad<RV, C, CM_> lO;
     lK.init(RK, mw, lane); lQ.init(gK, mw, lane); lP.init(RC, mw, lane); lO.init(gV, mw, lane);
+    const ChainRows<RAG> rows(a.rows, a.seq_chunks, b, a.n0);
     auto loadB = [&](int n, int slot) {
-        const size_t bhn = ((size_t)bt * a.N + n) * a.H + h, tok = ((size_t)bt * a.T + (size_t)n * C) * a.H + h;
+        const size_t bhn = ((size_t)bt * a.N + n) * a.H + h, tok = rows.first(n) * a.H + h;
         char *s = ringB + slot * B_BYTES;
         lK.issue(s + B_K, static_cast<const char *>(a.kt) + bhn * C * RK, RK, mw, lane, slice);
         lP.issue(s + B_P, static_cast<const char *>(a.Pm) + bhn * C * RC, RC, mw, lane, slice);
-        lO.issue(s + B_O, static_cast<const char *>(a.dO) + tok * a.V * ES + (size_t)vs * ES, gV, mw, lane, 0, wideO);
+        lO.issue(s + B_O, static_cast<const char *>(a.dO) + tok * a.V * ES + (size_t)vs * ES, gV, mw, lane, 0, wideO, rows.count(n) - 1);
         if (!GV && mw < 2) {                    // gamma (loader 0) and rho (1)
             const int w = mw;
             load_lds4(a.gates + (bhn * 3 + 1 + w) * C, lane * 4, lds_offset(s + B_G + w * C * 4));
         }
     };
     auto loadC = [&](int n, int slot) {
-        const size_t bhn = ((size_t)bt * a.N + n) * a.H + h, tok = ((size_t)bt * a.T + (size_t)n * C) * a.H + h;
+        const size_t bhn = ((size_t)bt * a.N + n) * a.H + h, tok = rows.first(n) * a.H + h;
         char *s = ringC + slot * C_BYTES;
         lK.issue(s + C_W, static_cast<const char *>(a.Wn) + bhn * C * RK, RK, mw, lane, slice);
         if (GV) lK.issue(s + C_Q, static_cast<const char *>(a.q) + bhn * C * RK, RK, mw, lane, slice);
-        else lQ.issue(s + C_Q, static_cast<const char *>(a.q) + tok * RK, gK, mw, lane, slice, wideQ);
+        else lQ.issue(s + C_Q, static_cast<const char *>(a.q) + tok * RK, gK, mw, lane, slice, wideQ, rows.count(n) - 1);
         if (GV && mw < K / 64)
             load_lds4(a.gamC + bhn * K, mw * 256 + lane * 4, lds_offset(s + C_D + mw * 256));
     };
@@ -155,8 +156,16 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
     }
     if (loader) wait_vm<0>();
     __syncthreads();
+    if (const int cnt = rows.count(a.n1 - 1); cnt < C) {        // (only the first chunk here can have missing tokens) their dO is zero
+        for (int i = tid; i < (C - cnt) * (RV / 16); i += CT_)
+            *reinterpret_cast<u32x4 *>(ringB + B_O + cnt * RV + i * 16) = u32x4{0u, 0u, 0u, 0u};
+        __syncthreads();
+    }
     int sb = 0, sc = 0;                         // ring slots of chunk n
     if (loader) {
+        // (all is there; said to the compiler too, which does not count wait_vm: it would wait for the state's loads where
+        // their registers are used again in the loop, and with them for every tile on its way: 122 -> 142 us)
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
         for (int n = a.n1 - 1; n >= a.n0; --n) {
             const bool full = n - NMAX >= a.n0; // everything counted as newer has been asked for
             if (full) wait_vm<PRE ? NEWER_C : NEWER_B>(); else wait_vm<0>();   // (as in state_fwd)
@@ -309,7 +318,7 @@ template <typename T> constexpr int BP_WGS = sizeof(T) == 2 ? 2 : 1;      // wor
 // GV: one state gate per key channel.  The kernel then runs on the folded operands with no
 // scalar gate (log_alpha null) and takes gamma_C, per channel, in place of rho (see the top of this
 // file); the gradient of the chunk's decays, times the decays, is collected per channel.
-template <typename T, int K, bool GV, int PW_>
+template <typename T, int K, bool GV, int PW_, bool RAG>
 __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kernel(ChunkArgs a) {
     constexpr int PT_ = PW_ * 64;
     constexpr int PAD = sizeof(T) == 2 ? 16 : Pad<T>::v, LDK = K + PAD, LDE = C + PAD;   // bf16: rows 32 bytes apart modulo 128
@@ -361,7 +370,8 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
-    const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    const size_t tok0 = a.rows.first<RAG>(b, n) * a.H + h;
+    const int rows = a.rows.count<RAG>(n);           // tokens that exist; the others: dO and v zero, beta zero, the rest repeats the last one
     const size_t tstride = a.H;
     // the slab tiles travel through registers: the next slab (after the last one: Q and K~) is
     // fetched while the workgroup computes on the current one
@@ -375,19 +385,16 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     TileRegs<T, C, C, PT_> r_Tn;
     float r_g = 0.f, r_b = 0.f;
     auto fetch_slab = [&](int v0) {
-        r_dOV.fetch(static_cast<const T *>(a.dO) + tok0 * a.V + v0, static_cast<const T *>(a.v) + tok0 * a.V + v0, tstride * a.V, tid, wave);
         r_EdE.fetch(static_cast<const T *>(a.Et) + (bhn * a.V + v0) * C, static_cast<const T *>(a.dEt) + (bhn * a.V + v0) * C, (size_t)C, tid, wave);
         r_S.fetch(static_cast<const T *>(a.S_ckpt) + (bhn * a.V + v0) * K, (size_t)K, tid);
         r_dS.fetch(static_cast<const T *>(a.dS_ckpt) + (bhn * a.V + v0) * K, (size_t)K, tid);
+        r_dOV.fetch(static_cast<const T *>(a.dO) + tok0 * a.V + v0, static_cast<const T *>(a.v) + tok0 * a.V + v0, tstride * a.V, tid, wave, rows - 1);
     };
     if (wave == 0) {
         r_g = a.log_alpha ? a.gates[bhn * 3 * C + lane] : 0.f;
-        r_b = a.beta[tok0 + (size_t)lane * tstride];
+        r_b = lane < rows ? a.beta[tok0 + (size_t)lane * tstride] : 0.f;
     }
-    r_Kn.fetch(static_cast<const T *>(a.k) + (GV ? bhn * C : tok0) * K, GV ? (size_t)K : tstride * K, tid);
-    // the caller's first row, and how many there are, for dv and dq (the first loads are on their way)
-    const size_t out0 = a.out.first(b, n) * a.H + h;
-    const int rows = a.out.count(n);
+    r_Kn.fetch(static_cast<const T *>(a.k) + (GV ? bhn * C : tok0) * K, GV ? (size_t)K : tstride * K, tid, GV ? C - 1 : rows - 1);
     r_Tn.fetch(static_cast<const T *>(a.Tm) + bhn * C * C, (size_t)C, tid);
     fetch_slab(0);
     const int ct = (wave % NCT) * 16;   // this wave's column tile of the [64 x K] results ...
@@ -425,6 +432,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     for (int v0 = 0; v0 < a.V; v0 += VB) {
         OSDN_BP_FRESH();
         __syncthreads();
+        if (rows < C) r_dOV.cut(tid, rows - 1);
         r_dOV.put(dOs, Vs, LDV, tid, wave);
         r_EdE.put(Ets, dEts, LDE, tid, wave);
         r_S.put(Ss, LDK, tid); r_dS.put(dSs, LDK, tid);
@@ -434,8 +442,10 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
         } else {
             const size_t ldq = GV ? (size_t)K : tstride * K;
             const T *qp = static_cast<const T *>(a.q) + (GV ? bhn * C : tok0) * K;
-            r_S.fetch(qp, ldq, tid);
-            r_dS.fetch(qp + VB * ldq, ldq, tid);
+            const int lastq = GV ? C - 1 : rows - 1;
+            r_S.fetch(qp, ldq, tid, lastq);
+            if (lastq >= VB) r_dS.fetch(qp + VB * ldq, ldq, tid, lastq - VB);
+            else r_dS.fetch(qp, ldq, tid, 0);            // (of no consequence: cP and dq have no such rows)
             TileRegs<T, C, K, PT_> r_Kt;
             r_Kt.fetch(static_cast<const T *>(a.kt) + bhn * C * K, (size_t)K, tid);
 #pragma unroll
@@ -496,7 +506,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
                 }
                 store4(dRs + i * LDV + c, dr[q]);
                 const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * a.V) + (uint32_t)(v0 + c)) * (uint32_t)sizeof(T);
-                if (i < rows) store4(reinterpret_cast<T *>(reinterpret_cast<char *>(static_cast<T *>(a.dv) + out0 * a.V) + go), dv);
+                if (i < rows) store4(reinterpret_cast<T *>(reinterpret_cast<char *>(static_cast<T *>(a.dv) + tok0 * a.V) + go), dv);
             }
         }
         __syncthreads();
@@ -615,7 +625,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
     // dG_i takes <d(gamma Q)_i, gamma_i Q_i> + <d(gamma K)_i, gamma_i K_i> - <d(rho K~)_i, rho_i K~_i>
     // as one number per row; the last term, summed over all rows, goes to the chunk's last token
     float trs = 0.f;                              // the last term over this lane's elements
-    T *dq_g = static_cast<T *>(a.dq) + (GV ? tok0 : out0) * K;      // (GV: unfold_kernel works on the padded rows)
+    T *dq_g = static_cast<T *>(a.dq) + tok0 * K;
     T *dk_g = static_cast<T *>(a.dk_read) + bhn * C * K;
     T *dkt_g = static_cast<T *>(a.dkt) + bhn * C * K;
     f32x4 dgc = {0.f, 0.f, 0.f, 0.f}, gcv = {1.f, 1.f, 1.f, 1.f};
@@ -670,14 +680,16 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
                     sc += __builtin_fmaf(gq, qv[r], __builtin_fmaf(gk, kv[r], -(gr * ktv[r])));
                     trs = __builtin_fmaf(gr, ktv[r], trs);
                 }
-                aq[r] += gq; ak[r] += gk; at[r] += gr;
+                aq[r] = __builtin_fmaf(gam, dQg[iq][r], aq[r]);
+                ak[r] = __builtin_fmaf(bgam, dKg[iq][r], ak[r]);
+                at[r] = __builtin_fmaf(GV ? gcv[r] : rho, dKr[iq][r], at[r]);
             }
             if (!GV) {              // over the four lanes of a token here, over the column tiles through LDS
                 sc = add_xor32(add_xor16(sc));
                 if (lane < 16) pq[wave * C + i] = sc;
             }
             const uint32_t go = ((uint32_t)i * (uint32_t)(tstride * K) + (uint32_t)c) * (uint32_t)sizeof(T);
-            if (GV || i < rows) store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dq_g) + go), aq);
+            if (i < rows) store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dq_g) + go), aq);
             const uint32_t gt = ((uint32_t)i * K + (uint32_t)c) * (uint32_t)sizeof(T);
             store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dk_g) + gt), ak);
             store4(reinterpret_cast<T *>(reinterpret_cast<char *>(dkt_g) + gt), at);
@@ -706,7 +718,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
         float dbw = rowa;
 #pragma unroll
         for (int w = 0; w < WPR; ++w) dbw += dbeta_s[w * C + i];
-        a.dbeta[th] = dbw;
+        if (i < rows) a.dbeta[th] = dbw;
         if (!GV && a.dlog_alpha) {
             float t_c = 0.f;
 #pragma unroll
@@ -718,7 +730,8 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
 #pragma unroll
             for (int w = 0; w < PW_; ++w) { ssum += sdot[w]; tr_sum += trsum_s[w]; }
             if (i == C - 1) dG += tr_sum + __expf(Gs[C - 1]) * ssum;
-            a.dlog_alpha[th] = wave_suffix_sum(dG, lane);
+            const float dg = wave_suffix_sum(dG, lane);
+            if (i < rows) a.dlog_alpha[th] = dg;
         }
     }
 }
@@ -727,7 +740,7 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
 template <typename T, int K, bool GV, int VS>
 static void launch_chain_t(const ChunkArgs &a, hipStream_t st) {
     dim3 grid((a.V / VS) * a.H * (a.seq_chunks ? a.n_seqs : a.B)), block(CT_);
-    hipLaunchKernelGGL((bwd_chain_kernel<T, K, GV, VS>), grid, block, 0, st, a);
+    with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((bwd_chain_kernel<T, K, GV, VS, decltype(rag)::value>), grid, block, 0, st, a); });
 }
 // Slices of 32 values with bf16 I/O, of 16 with fp32 I/O at K = 128 (beside slices of 32 one chunk's operands
 // would fill the LDS, with nothing in flight for the next), either with fp32 I/O at K = 64 (few chains: see osdn_bwd).
@@ -754,8 +767,8 @@ static int launch_post_t(const ChunkArgs &a, hipStream_t st) {
     constexpr int PW = 8;           // wavefronts per workgroup
     dim3 grid((a.n1 - a.n0) * a.H, a.B), block(PW * 64);
     if (GV && (!a.gamC || !a.dgamC || a.log_alpha || a.dlog_alpha)) return -1;
-    if (a.K == 64) hipLaunchKernelGGL((bwd_post_kernel<T, 64, GV, PW>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((bwd_post_kernel<T, 128, GV, PW>), grid, block, 0, st, a);
+    if (a.K == 64) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((bwd_post_kernel<T, 64, GV, PW, decltype(rag)::value>), grid, block, 0, st, a); });
+    else if (a.K == 128) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((bwd_post_kernel<T, 128, GV, PW, decltype(rag)::value>), grid, block, 0, st, a); });
     else return -1;
     return 0;
 }
@@ -772,18 +785,20 @@ int launch_bwd_post(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
 //     dG = dq . q + dk_read . k - dk~ . k~   (elementwise: G reaches the loss through the three
 //          folded operands only),  dG[last token] += gamma_C . dgamma_C,
 //     dlog_alpha = suffix sum of dG over the tokens of the chunk, channel by channel.
-template <typename T, int K>
+template <typename T, int K, bool RAG>
 __global__ __launch_bounds__(NT) void unfold_kernel(UnfoldArgs a) {
     constexpr int GLD = K + 4, VN = 16 / sizeof(T);
     __shared__ __attribute__((aligned(16))) float Gt[C * GLD];     // G, then dG, then dlog_alpha
     const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y, tid = threadIdx.x;
     const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
-    const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    const size_t tok0 = a.rows.first<RAG>(b, n) * a.H + h;
+    const int rows = a.rows.count<RAG>(n);                               // (tokens that do not exist: gate 1, every gradient zero)
     const size_t rs = (size_t)a.H * K;                              // elements between consecutive tokens
     const float *gp = a.log_alpha + tok0 * K;
     for (int v = tid; v < C * K / 4; v += NT) {
         const int i = v / (K / 4), c = (v % (K / 4)) * 4;
-        *reinterpret_cast<f32x4 *>(Gt + i * GLD + c) = *reinterpret_cast<const f32x4 *>(gp + (size_t)i * rs + c);
+        const f32x4 g4 = *reinterpret_cast<const f32x4 *>(gp + (size_t)min(i, rows - 1) * rs + c);
+        *reinterpret_cast<f32x4 *>(Gt + i * GLD + c) = i < rows ? g4 : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     __syncthreads();
     if (tid < K) {
@@ -801,6 +816,11 @@ __global__ __launch_bounds__(NT) void unfold_kernel(UnfoldArgs a) {
       *dtp = static_cast<T *>(a.dkt) + bhn * C * K;
     for (int v = tid; v < C * K / VN; v += NT) {
         const int i = v / (K / VN), c = (v % (K / VN)) * VN;
+        if (i >= rows) {                                                // (dk~ and dk of the tile are not read there)
+#pragma unroll
+            for (int e = 0; e < VN; ++e) Gt[i * GLD + c + e] = 0.f;
+            continue;
+        }
         const size_t o = (size_t)i * rs + c, ot_ = i * K + c;            // caller's tensors, workspace tiles
         const u32x4 qv = *reinterpret_cast<const u32x4 *>(qp + o), kv = *reinterpret_cast<const u32x4 *>(kp + o),
                     tv = *reinterpret_cast<const u32x4 *>(tp + ot_);
@@ -833,15 +853,15 @@ __global__ __launch_bounds__(NT) void unfold_kernel(UnfoldArgs a) {
     float *dg = a.dlog_alpha + tok0 * K;
     for (int v = tid; v < C * K / 4; v += NT) {
         const int i = v / (K / 4), c = (v % (K / 4)) * 4;
-        *reinterpret_cast<f32x4 *>(dg + (size_t)i * rs + c) = *reinterpret_cast<const f32x4 *>(Gt + i * GLD + c);
+        if (i < rows) *reinterpret_cast<f32x4 *>(dg + (size_t)i * rs + c) = *reinterpret_cast<const f32x4 *>(Gt + i * GLD + c);
     }
 }
 
 template <typename T>
 static int launch_unfold_t(const UnfoldArgs &a, hipStream_t st) {
     dim3 grid((a.n1 - a.n0) * a.H, a.B), block(NT);
-    if (a.K == 64) hipLaunchKernelGGL((unfold_kernel<T, 64>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((unfold_kernel<T, 128>), grid, block, 0, st, a);
+    if (a.K == 64) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((unfold_kernel<T, 64, decltype(rag)::value>), grid, block, 0, st, a); });
+    else if (a.K == 128) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((unfold_kernel<T, 128, decltype(rag)::value>), grid, block, 0, st, a); });
     else return -1;
     return 0;
 }

@@ -37,7 +37,7 @@ namespace osdn {
 // kernels.  1 / Gamma grows like e^{|G|}: the cumulative log-decay of a channel inside a chunk has
 // to stay above about -80.
 constexpr int CP_ = 512;        // threads of a chunk_prep workgroup (8 wavefronts)
-template <typename T, int K, bool GV>
+template <typename T, int K, bool GV, bool RAG>
 __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
     constexpr int PAD = Pad<T>::v, LDK = K + PAD, LDC = C + PAD, LDF = C + 1;
     constexpr int NW = CP_ / 64, VN = 16 / sizeof(T);
@@ -57,16 +57,17 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const size_t tstride = a.H;                                           // tokens are H rows apart
     const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
-    const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;      // (b, first token, h)
+    const size_t tok0 = a.rows.first<RAG>(b, n) * a.H + h;                     // (b, first token, h)
+    const int last = a.rows.count<RAG>(n) - 1;                                 // (rows of K behind it: their columns of T diag(beta) are zero)
     {
         TileRegs<T, C, K, CP_> r_K, r_Kt;
         float g = 0.f, bt = 0.f;
-        r_K.fetch(static_cast<const T *>(a.k) + tok0 * K, tstride * K, tid);
+        r_K.fetch(static_cast<const T *>(a.k) + tok0 * K, tstride * K, tid, last);
         r_Kt.fetch(static_cast<const T *>(a.kt) + bhn * C * K, (size_t)K, tid);
         if (wave == 0) {
-            const size_t th = tok0 + (size_t)lane * tstride;
-            if (!GV && a.log_alpha) g = a.log_alpha[th];                  // GV: the gates go into the operands
-            bt = a.beta[th];
+            const size_t th = tok0 + (size_t)min(lane, last) * tstride;
+            if (!GV && a.log_alpha) g = lane <= last ? a.log_alpha[th] : 0.f;      // GV: the gates go into the operands
+            bt = lane <= last ? a.beta[th] : 0.f;
             const float G = wave_cumsum(g, lane);
             Gs[lane] = G;
             Bs[lane] = bt;
@@ -91,7 +92,8 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
         const float *gp = a.log_alpha + tok0 * K;
         for (int v = tid; v < C * K / 4; v += CP_) {
             const int i = v / (K / 4), c = (v % (K / 4)) * 4;
-            *reinterpret_cast<f32x4 *>(Gt + i * GLD + c) = *reinterpret_cast<const f32x4 *>(gp + (size_t)i * rs + c);
+            const f32x4 g4 = *reinterpret_cast<const f32x4 *>(gp + (size_t)min(i, last) * rs + c);
+            *reinterpret_cast<f32x4 *>(Gt + i * GLD + c) = i <= last ? g4 : f32x4{0.f, 0.f, 0.f, 0.f};
         }
         __syncthreads();
         if (tid < K) {
@@ -110,7 +112,8 @@ __global__ __launch_bounds__(CP_) void chunk_prep_kernel(ChunkArgs a) {
             const int i = v / (K / VN), c = (v % (K / VN)) * VN;
             const u32x4 kv = *reinterpret_cast<const u32x4 *>(X1 + i * LDK + c);
             const u32x4 tv = *reinterpret_cast<const u32x4 *>(X2 + i * LDK + c);
-            const u32x4 qv = *reinterpret_cast<const u32x4 *>(qp + (size_t)i * rs + c);
+            u32x4 qv = *reinterpret_cast<const u32x4 *>(qp + (size_t)min(i, last) * rs + c);
+            if (i > last) qv = u32x4{0u, 0u, 0u, 0u};
             float ko[VN], to[VN], qo[VN], wo[VN];
 #pragma unroll
             for (int e = 0; e < VN; ++e) {
@@ -216,7 +219,7 @@ template <typename T, int K, int VS> constexpr int SF_NSC = sizeof(T) == 2 || K 
 // coordinate of the state its own gamma_C; K~ is gamma_C . K~ / Gamma.
 // VS: rows of S (values) owned by one workgroup, 32 or 16.  With few chains the narrow slice
 // gives twice the workgroups, each with half the work on the dependent path per chunk.
-template <typename T, int K, bool GV, int VS>
+template <typename T, int K, bool GV, int VS, bool RAG>
 __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     constexpr int ES = sizeof(T), RK = K * ES, RC = C * ES, RV = VS * ES;      // bytes per row of a tile
     constexpr int NVT = VS / 16, NFB = K / 16;
@@ -251,6 +254,7 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     const int mw = wave - CW_, mt = tid - (CW_ + CM_) * 64;     // loader wavefront, storer thread
     const size_t bh = (size_t)b * a.H + h;      // the chain: indexes S_in / S_out
     const uint32_t gV = (uint32_t)a.H * (uint32_t)a.V * ES;        // bytes between tokens of v
+    const ChainRows<RAG> rows(a.rows, a.seq_chunks, b, a.n0);
     const bool wideV = (reinterpret_cast<uintptr_t>(a.v) & 15) == 0;
 
     LdsLoad<RK, C, CM_> lK;
@@ -264,8 +268,8 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
         const size_t bhn = ((size_t)bt * a.N + n) * a.H + h;
         char *s = ringX + slot * X_BYTES;
         lT.issue(s + X_T, static_cast<const char *>(a.Tu) + bhn * C * RC, RC, mw, lane, slice);
-        lV.issue(s + X_V, static_cast<const char *>(a.v) + (((size_t)bt * a.T + (size_t)n * C) * a.H + h) * a.V * ES + (size_t)vs * ES,
-                 gV, mw, lane, 0, wideV);
+        lV.issue(s + X_V, static_cast<const char *>(a.v) + (rows.first(n) * a.H + h) * a.V * ES + (size_t)vs * ES,
+                 gV, mw, lane, 0, wideV, rows.count(n) - 1);      // (rows behind the last: their columns of T diag(beta) are zero)
         if (!GV && mw < 2) {                    // gamma (loader 0) and rho (1)
             const int w = mw;
             load_lds4(a.gates + (bhn * 3 + 1 + w) * C, lane * 4, lds_offset(s + X_G + w * C * 4));
@@ -309,6 +313,9 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     int sw = 0, sx = 0, sc = 0;                 // ring slots of chunk n
     auto next = [](int slot, int depth) { return slot + 1 == depth ? 0 : slot + 1; };
     if (loader) {
+        // (all is there; said to the compiler too, which does not count wait_vm: it would wait for the state's loads where
+        // their registers are used again in the loop, and with them for every tile on its way: 122 -> 142 us)
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
         for (int n = a.n0; n < a.n1; ++n) {
             const bool full = n + NMAX < a.n1;  // everything counted as newer has been asked for
             // a slot is refilled as soon as its operands have been read: ahead of their phase (X; PRE: all), or in it
@@ -430,7 +437,7 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
 
 // ------------------------------------------------------------ output_fwd ----
 constexpr int OT_ = 512;        // threads of an output_fwd workgroup: 8 wavefronts, (row block, half of the value tiles)
-template <typename T, int K>
+template <typename T, int K, bool RAG>
 __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
     constexpr int PAD = sizeof(T) == 2 ? 16 : Pad<T>::v, LDK = K + PAD, LDC = C + PAD;   // bf16: rows 32 bytes apart modulo 128 (every operand read here is 16 bytes per lane along k)
     constexpr int NW = OT_ / 64;
@@ -444,13 +451,15 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
     const int n = a.n0 + blockIdx.x / a.H, h = blockIdx.x % a.H, b = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t bhn = ((size_t)b * a.N + n) * a.H + h;
-    const size_t tok0 = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    const size_t tok0 = a.rows.first<RAG>(b, n) * a.H + h;
+    const int rows = a.rows.count<RAG>(n);
     const size_t tstride = a.H;
 
     if (wave == 0) {
         Gs[lane] = a.log_alpha ? a.gates[bhn * 3 * C + lane] : 0.f;
     }
-    load_tile(Qs, LDK, static_cast<const T *>(a.q) + (a.gate_vec ? bhn * C : tok0) * K, a.gate_vec ? (size_t)K : tstride * K, C, K, tid, OT_);
+    load_tile(Qs, LDK, static_cast<const T *>(a.q) + (a.gate_vec ? bhn * C : tok0) * K, a.gate_vec ? (size_t)K : tstride * K, C, K, tid, OT_,
+              a.gate_vec ? C - 1 : rows - 1);
     load_tile(Kts, LDK, static_cast<const T *>(a.kt) + bhn * C * K, (size_t)K, C, K, tid, OT_);
     // the slabs of S and E^T travel through registers, one slab ahead of the products
     TileRegs<T, C, K, OT_> r_S;
@@ -473,8 +482,6 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
         store_tile_t(Ps + ib * 16 * LDC + jb * 16, LDC, acc, lane);
     }
     T *Os = Kts;
-    const size_t out0 = a.out.first(b, n) * a.H + h;            // (here: the tiles' loads are on their way)
-    const int rows = a.out.count(n);
     for (int v0 = 0; v0 < a.V; v0 += C) {
         __syncthreads();
         // P is kept for the backward pass (its chain kernel forms scale P^T dO from it)
@@ -500,7 +507,7 @@ __global__ __launch_bounds__(OT_) void output_fwd_kernel(ChunkArgs a) {
             store_tile(Os + rb * 16 * LDC + vt * 16, LDC, a1, lane);
         }
         __syncthreads();
-        T *og = static_cast<T *>(a.o) + out0 * a.V + v0;
+        T *og = static_cast<T *>(a.o) + tok0 * a.V + v0;
         if (rows == C) store_tile_global(og, tstride * a.V, Os, LDC, C, C, tid, OT_);      // (a constant count: unrolled)
         else store_tile_global(og, tstride * a.V, Os, LDC, rows, C, tid, OT_);
     }
@@ -511,8 +518,8 @@ template <typename T, bool GV>
 static int launch_prep_t(const ChunkArgs &a, hipStream_t st) {
     dim3 grid((a.n1 - a.n0) * a.H, a.B), block(CP_);
     if (GV && (!a.log_alpha || !a.Qg || !a.Kg || !a.Kd || !a.Kw || !a.gamC)) return -1;
-    if (a.K == 64) hipLaunchKernelGGL((chunk_prep_kernel<T, 64, GV>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((chunk_prep_kernel<T, 128, GV>), grid, block, 0, st, a);
+    if (a.K == 64) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((chunk_prep_kernel<T, 64, GV, decltype(rag)::value>), grid, block, 0, st, a); });
+    else if (a.K == 128) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((chunk_prep_kernel<T, 128, GV, decltype(rag)::value>), grid, block, 0, st, a); });
     else return -1;
     return 0;
 }
@@ -524,8 +531,8 @@ template <typename T, bool GV, int VS>
 static int launch_state_t(const ChunkArgs &a, hipStream_t st) {
     dim3 grid((a.V / VS) * a.H * (a.seq_chunks ? a.n_seqs : a.B)), block(CT_);
     if (GV && !a.gamC) return -1;
-    if (a.K == 64) hipLaunchKernelGGL((state_fwd_kernel<T, 64, GV, VS>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((state_fwd_kernel<T, 128, GV, VS>), grid, block, 0, st, a);
+    if (a.K == 64) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((state_fwd_kernel<T, 64, GV, VS, decltype(rag)::value>), grid, block, 0, st, a); });
+    else if (a.K == 128) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((state_fwd_kernel<T, 128, GV, VS, decltype(rag)::value>), grid, block, 0, st, a); });
     else return -1;
     return 0;
 }
@@ -541,8 +548,8 @@ int launch_state_fwd(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
 template <typename T>
 static int launch_output_t(const ChunkArgs &a, hipStream_t st) {
     dim3 grid((a.n1 - a.n0) * a.H, a.B), block(OT_);
-    if (a.K == 64) hipLaunchKernelGGL((output_fwd_kernel<T, 64>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((output_fwd_kernel<T, 128>), grid, block, 0, st, a);
+    if (a.K == 64) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((output_fwd_kernel<T, 64, decltype(rag)::value>), grid, block, 0, st, a); });
+    else if (a.K == 128) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((output_fwd_kernel<T, 128, decltype(rag)::value>), grid, block, 0, st, a); });
     else return -1;
     return 0;
 }

@@ -217,14 +217,15 @@ __device__ __forceinline__ __attribute__((address_space(1))) U &row_elem(U *row,
 
 // copy a [rows x cols] tile of T from global (row stride g_ld elements) into LDS (row
 // stride s_ld), 16 bytes per thread and step; cols must be a multiple of 16/sizeof(T)
+// (last: the last row that exists; rows behind it repeat it)
 template <typename T>
 __device__ __forceinline__ void load_tile(T *s, int s_ld, const T *g, size_t g_ld, int rows,
-                                          int cols, int tid, int nthreads) {
+                                          int cols, int tid, int nthreads, int last = C - 1) {
     constexpr int VN = 16 / sizeof(T);
     const int vpr = cols / VN;
     for (int i = tid; i < rows * vpr; i += nthreads) {
         const int r = i / vpr, c = (i % vpr) * VN;
-        *reinterpret_cast<u32x4 *>(s + r * s_ld + c) = *tile_vec(g, g_ld, r, c);
+        *reinterpret_cast<u32x4 *>(s + r * s_ld + c) = *tile_vec(g, g_ld, min(r, last), c);
     }
 }
 template <typename T>
@@ -273,12 +274,19 @@ struct TileRegs {
     static constexpr int VN = 16 / sizeof(T), VPR = COLS / VN, TOTAL = ROWS * VPR, NV = (TOTAL + NT_ - 1) / NT_;
     static_assert(TOTAL % NT_ == 0 || NT_ % TOTAL == 0, "tile must split evenly over (some of) the threads");
     u32x4 v[NV];
-    __device__ __forceinline__ void fetch(const T *g, size_t g_ld, int tid) {
+    // last: the last row that exists; rows behind it repeat it
+    __device__ __forceinline__ void fetch(const T *g, size_t g_ld, int tid, int last = ROWS - 1) {
 #pragma unroll
         for (int m = 0; m < NV; ++m) {
             const int i = tid + m * NT_, r = i / VPR, c = (i % VPR) * VN;
-            if (TOTAL % NT_ == 0 || i < TOTAL) v[m] = *tile_vec(g, g_ld, r, c);
+            if (TOTAL % NT_ == 0 || i < TOTAL) v[m] = *tile_vec(g, g_ld, min(r, last), c);
         }
+    }
+    // rows behind `last` become zero
+    __device__ __forceinline__ void cut(int tid, int last) {
+#pragma unroll
+        for (int m = 0; m < NV; ++m)
+            if ((tid + m * NT_) / VPR > last) v[m] = u32x4{0u, 0u, 0u, 0u};
     }
     __device__ __forceinline__ void put(T *s, int s_ld, int tid) const {
 #pragma unroll
@@ -304,13 +312,17 @@ struct PairRegs {
     TileRegs<T, ROWS, COLS, NTH> r[SPLIT ? 1 : 2];
     static constexpr int NV1 = TileRegs<T, ROWS, COLS, NTH>::NV, NVP = NV1 * (SPLIT ? 1 : 2);
     __device__ __forceinline__ u32x4 &vec(int m) { return r[m / NV1].v[m % NV1]; }
-    __device__ __forceinline__ void fetch(const T *g0, const T *g1, size_t g_ld, int tid, int wave) {
+    __device__ __forceinline__ void fetch(const T *g0, const T *g1, size_t g_ld, int tid, int wave, int last = ROWS - 1) {
         if (SPLIT) {
-            r[0].fetch(wave < NTH / 64 ? g0 : g1, g_ld, tid & (NTH - 1));
+            r[0].fetch(wave < NTH / 64 ? g0 : g1, g_ld, tid & (NTH - 1), last);
         } else {
-            r[0].fetch(g0, g_ld, tid);
-            r[SPLIT ? 0 : 1].fetch(g1, g_ld, tid);
+            r[0].fetch(g0, g_ld, tid, last);
+            r[SPLIT ? 0 : 1].fetch(g1, g_ld, tid, last);
         }
+    }
+    __device__ __forceinline__ void cut(int tid, int last) {
+#pragma unroll
+        for (int j = 0; j < (SPLIT ? 1 : 2); ++j) r[j].cut(tid & (NTH - 1), last);
     }
     __device__ __forceinline__ void put(T *s0, T *s1, int s_ld, int tid, int wave) const {
         if (SPLIT) {

@@ -16,18 +16,52 @@ namespace osdn {
 // sequential kernels run one chain per (sequence, head).  A chain takes its start value from
 // the *_first / *_last pointer when its sequence begins (ends, in the backward pass) inside
 // [n0, n1), and from the carry buffer otherwise.
-// Where the results of a chunk go.  The kernels read padded copies of ragged sequences, but write the
-// large results (o, dq, dk, dv, a gradient of retention per coordinate) straight to the caller's rows and
-// leave the pad tokens out: a padded result that is moved afterwards costs its bytes twice more.
-// 65536 packed tokens, 16 heads of 128 x 128 in bf16, forward and backward: 4183 -> 3834 us; calls of
-// whole chunks are level as long as a kernel asks for its rows after its first loads (before them: 0.8 %
-// of a forward pass of 8 x 2048 tokens).
-struct OutRows {
+// The caller's rows of the token tensors.  Sequences need not be whole chunks: the kernels read and write the caller's
+// tensors where they are, clamp the row of a token that does not exist to the last one that does, and give
+// such tokens the values that change nothing (k = dO = 0, beta = 0, log alpha = 0, retention = 1).  The workspace is
+// laid out for whole chunks.  The many kernels of phase 1's backward pass take k, beta and retention of a sequence's
+// ragged last chunk from a whole tile that the forward sweep leaves (`tail`): clamped rows cost the chain 8 %.
+// 65536 packed tokens, 16 heads of 128 x 128 in bf16, forward and backward: 3737 us with padded copies of
+// the inputs, 3371 without; one prompt of 1531 tokens 121 and 108.
+struct Rows {
     int T;                                // tokens per batch entry of the caller's tensors
-    const int *chunk_row, *chunk_len;     // packed ragged sequences: first row and tokens of every chunk; else null
-    // first row of chunk n of batch entry b, and how many of its tokens exist (at least 1)
-    __device__ __forceinline__ size_t first(int b, int n) const { return chunk_row ? (size_t)chunk_row[n] : (size_t)b * T + (size_t)n * C; }
-    __device__ __forceinline__ int count(int n) const { return chunk_row ? chunk_len[n] : (T - n * C < C ? T - n * C : C); }
+    // packed ragged sequences, else null: per chunk, its first row; its tokens - 1, and (from bit 6) its sequence
+    const int *chunk_row, *chunk_seq;
+    bool ragged() const { return chunk_row || T % C != 0; }
+    // first row of chunk n of batch entry b, and how many of its tokens exist (at least 1); RAG: some chunk is not whole
+    // (a template parameter of every kernel: the code for the others costs calls of whole chunks up to 4 %)
+    template <bool RAG> __device__ __forceinline__ size_t first(int b, int n) const { return RAG && chunk_row ? (size_t)chunk_row[n] : (size_t)b * T + (size_t)n * C; }
+    template <bool RAG> __device__ __forceinline__ int count(int n) const { return !RAG ? C : chunk_row ? (chunk_seq[n] & 63) + 1 : (T - n * C < C ? T - n * C : C); }
+    // the tile that holds the chunk if it is not whole, else -1
+    template <bool RAG> __device__ __forceinline__ int tail(int b, int n) const {
+        if (!RAG) return -1;
+        const int s = chunk_row ? chunk_seq[n] : 0;
+        return chunk_row ? ((s & 63) == 63 ? -1 : s >> 6) : T - n * C < C ? b : -1;
+    }
+};
+// launches with the kernel instance for whole or ragged chunks: f(std::true_type or std::false_type).  Both are to give the
+// same bits (a call padded by its caller against a ragged one): sums of two products are written as the fma they are
+template <typename F> inline void with_rows(const Rows &r, F &&f) {
+    if (r.ragged()) f(std::true_type{});
+    else f(std::false_type{});
+}
+// The same for a kernel that walks the chunks of one chain (b: batch entry, or packed sequence; n0: a chunk of it).
+template <bool RAG> struct ChainRows {
+    int base, end;                        // row of (the sequence's) chunk 0; one past its last row
+    __device__ __forceinline__ ChainRows(const Rows &r, const int *seq_chunks, int b, int n0) {
+        if (RAG && r.chunk_row) {
+            const int last = seq_chunks[b + 1] - 1;
+            base = r.chunk_row[n0] - n0 * C;
+            end = r.chunk_row[last] + (r.chunk_seq[last] & 63) + 1;
+        } else {
+            base = 0;
+            end = r.T;
+            batch = seq_chunks ? 0 : (size_t)b * r.T;
+        }
+    }
+    __device__ __forceinline__ size_t first(int n) const { return batch + (size_t)(base + n * C); }
+    __device__ __forceinline__ int count(int n) const { const int c = end - (base + n * C); return RAG && c < C ? c : C; }
+    size_t batch = 0;
 };
 
 struct PrecondArgs {
@@ -38,6 +72,7 @@ struct PrecondArgs {
     const float *d_first;     // packed sequences: d before the first token, [n_seqs,H,K] or null
     float eta, d_min, d_max, eps;
     int beta_aware;
+    Rows rows;                // of k, beta, retention
     const void *k;            // [B,T,H,K] io
     const float *beta;        // [B,T,H]
     const float *retention;   // [B,T,H] ([B,T,H,K] with ret_vec) or null
@@ -48,6 +83,8 @@ struct PrecondArgs {
     float *d_out;             // [B,H,K]
     float *d_ckpt;            // [B,H,T/64,K] or null
     float *tok_scalars;       // [B,T,H,4] or null: per token (step, <d,k^2>, sum k^2, unused), kept for the backward
+    void *k_tail;             // [sequences,64,H,K] io: k of ragged last chunks, whole, kept for the backward
+    float *beta_tail, *ret_tail;      // [sequences,64,H], as retention
     // Sweeps over the whole sequence (pieces > 0, plain batches only): a chain is cut into
     // pieces of piece_chunks chunks, one workgroup per piece.  Sweep number `sweep` reads the
     // start values and piece maps x -> clip3(A x + B, L, H) that sweep - 1 left (two buffers
@@ -66,8 +103,12 @@ struct PrecondBwdArgs {
     const float *dd_last;     // packed sequences: adjoint of the final d, [n_seqs,H,K] or null
     float eta, d_min, d_max, eps;
     int beta_aware;
+    Rows rows;                // of k, beta, retention and their gradients
     const void *k;
-    const float *beta, *retention, *d_ckpt;     // retention [B,T,H], or [B,T,H,K] with ret_vec
+    const float *beta, *retention;
+    const void *k_tail;       // ragged last chunks, from the forward sweep
+    const float *beta_tail, *ret_tail;
+    const float *d_ckpt;     // retention [B,T,H], or [B,T,H,K] with ret_vec
     int ret_vec;
     float *tok_scalars;       // [B,T,H,4] from the forward sweep: (step, <d,k^2>, sum k^2, -); the chain
                               // kernel puts sigma_t into the fourth slot for the post kernel
@@ -76,7 +117,6 @@ struct PrecondBwdArgs {
     const void *dkt;          // [B,N,H,64,K] io: dL/dk~ from phase 2
     const void *dk_read;      // [B,N,H,64,K] io: read-side dL/dk from phase 2
     const float *dd_out;      // [B,H,K] or null
-    OutRows out;              // rows of dk, and of dretention with ret_vec
     void *dk;                 // [B,T,H,K] io
     float *dbeta;             // [B,T,H] in/out
     float *dretention;        // [B,T,H] ([B,T,H,K] with ret_vec) or null
@@ -121,7 +161,7 @@ struct ChunkArgs {
     const float *S_first;             // packed sequences: [n_seqs,H,V,K] or null
     const float *dS_last;             // packed sequences: adjoint of the final S, or null
     float scale;
-    OutRows out;                      // rows of o, dv and (one state gate per head) dq
+    Rows rows;                        // of q, k, v, beta, log_alpha, o, dO and the gradients
     // caller tensors
     const void *q, *k, *v;            // [B,T,H,*] io
     const float *beta, *log_alpha;    // [B,T,H]; log_alpha may be null
@@ -163,11 +203,7 @@ struct ChunkArgs {
 
 int launch_precond_fwd(const PrecondArgs &a, bool bf16_io, hipStream_t st);
 int launch_step(const StepArgs &a, bool bf16_io, hipStream_t st);
-int launch_copy_rows(const void *src, int Ts, void *dst, int Td, int B, size_t row_bytes, uint32_t fill,
-                     hipStream_t st);
-int launch_upload_ints(const int *host, size_t count, int *dst, hipStream_t st);
-int launch_move_chunk_rows(const void *src, void *dst, const int *chunk_row, const int *chunk_len, int n_chunks,
-                           size_t row_bytes, bool to_padded, uint32_t fill, hipStream_t st);
+int launch_seq_tables(const int *cu, const int *seq_chunks, int n_seqs, int N, int *tables, hipStream_t st);
 int launch_precond_mask(const PrecondBwdArgs &a, bool bf16_io, hipStream_t st);
 // solved form with a retention gate per (token, head): which = 0 masks, inverse and indicators (forward
 // data only), 1 rho0 and t0 (needs dL/dk~), 2 the chain; chunks [n0, n1)
@@ -188,6 +224,7 @@ int launch_bwd_post(const ChunkArgs &a, bool bf16_io, hipStream_t st);
 struct UnfoldArgs {
     int B, T, H, K, N;
     int n0, n1;
+    Rows rows;                        // of log_alpha, q, k, dq and dlog_alpha
     const float *log_alpha;           // [B,T,H,K]
     const void *q, *k, *kt;           // io: the unfolded operands (q, k: [B,T,H,K]; kt: [B,N,H,64,K])
     void *dq, *dk_read, *dkt;         // io, dq [B,T,H,K], the others [B,N,H,64,K]: in: w.r.t. the folded operands; out: w.r.t. q, k, k~

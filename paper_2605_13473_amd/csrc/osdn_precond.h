@@ -200,4 +200,38 @@ __device__ __forceinline__ float sum_lanes4(float x) {
     return x;
 }
 
+// ---- where the backward kernels of phase 1 read ---------------------------------------------
+// k, beta and retention of chunk n, head h: the caller's rows, or the tile of a ragged last chunk; tokens are H rows apart
+template <typename T, int K, int RET, bool RAG> struct ChunkIn {
+    const T *k;
+    const float *beta, *ret;
+    __device__ __forceinline__ ChunkIn(const PrecondBwdArgs &a, int b, int n, int h) {
+        const int tile = a.rows.tail<RAG>(b, n);
+        const size_t row = (tile < 0 ? a.rows.first<RAG>(b, n) : (size_t)tile * C) * a.H + h;
+        k = static_cast<const T *>(tile < 0 ? a.k : a.k_tail) + row * K;
+        beta = (tile < 0 ? a.beta : a.beta_tail) + row;
+        ret = RET ? (tile < 0 ? a.retention : a.ret_tail) + row * (RET == 2 ? K : 1) : nullptr;
+    }
+};
+// The same for a kernel that walks the chunks of one chain: base(n) as above, without a table.
+template <typename T, int K, int RET, bool RAG> struct ChainIn {
+    const T *k, *k_tail;
+    const float *beta, *beta_tail, *ret, *ret_tail;
+    size_t chunk_rows;
+    int tail;                                    // the ragged chunk, or one that does not exist
+    __device__ __forceinline__ ChainIn(const PrecondBwdArgs &a, int b, int n0, int h) {
+        const ChainRows<RAG> rows(a.rows, a.seq_chunks, b, n0);
+        const size_t u0 = (rows.batch + (size_t)(long long)rows.base) * a.H + h, t0 = (size_t)b * C * a.H + h;
+        constexpr int RK = RET == 2 ? K : 1;
+        chunk_rows = (size_t)C * a.H;
+        tail = (rows.end - rows.base) % C ? (rows.end - rows.base) / C : -1;
+        k = static_cast<const T *>(a.k) + u0 * K; k_tail = static_cast<const T *>(a.k_tail) + t0 * K;
+        beta = a.beta + u0; beta_tail = a.beta_tail + t0;
+        ret = RET ? a.retention + u0 * RK : nullptr; ret_tail = RET ? a.ret_tail + t0 * RK : nullptr;
+    }
+    __device__ __forceinline__ const T *k_of(int n) const { return RAG && n == tail ? k_tail : k + (size_t)n * chunk_rows * K; }
+    __device__ __forceinline__ const float *beta_of(int n) const { return RAG && n == tail ? beta_tail : beta + (size_t)n * chunk_rows; }
+    __device__ __forceinline__ const float *ret_of(int n) const { return RAG && n == tail ? ret_tail : ret + (size_t)n * chunk_rows * (RET == 2 ? K : 1); }
+};
+
 }  // namespace osdn

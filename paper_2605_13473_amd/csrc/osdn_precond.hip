@@ -54,7 +54,7 @@ namespace osdn {
 // checkpoints and token scalars wanted.  Then no access of the loop sits under a branch (lanes without
 // an element of their own repeat another's), and the wait for the next chunk's keys, which the compiler
 // counts in accesses, does not become one for the stores behind them.
-template <typename T, int K, int RET, bool PIECES, bool TILES>
+template <typename T, int K, int RET, bool PIECES, bool TILES, bool RAG>
 __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     constexpr int RE = RET_VEC ? K / 64 : 1;      // retention values a thread keeps per token
@@ -97,6 +97,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
     const float lo = project ? a.d_min : -INFINITY, hi = project ? a.d_max : INFINITY;
     const int N = (a.T + C - 1) / C;
     const uint32_t kstride = (uint32_t)a.H * K;   // elements between consecutive tokens
+    const ChainRows<RAG> rows(a.rows, a.seq_chunks, b, a.n0);
 
     if (!PIECES) {
         if (tid < K) dnext[tid] = a.d_in ? a.d_in[bh * K + tid] : 1.f;
@@ -137,22 +138,47 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
     typename Pk::Raw kreg[RUN];                  // this thread's k of the next chunk
     typename Pr::Raw rreg[RET_VEC ? RUN : 1];    // ... and its per-coordinate retention
     float betreg = 0.f, retreg = 1.f;            // gates of token (run, u_own) of the next chunk
+    // (rows past the end: reread; a row's address is the one before, a row further if there is one)
+    const size_t u0 = (rows.batch + (size_t)(long long)rows.base) * a.H + h, chunk_rows = (size_t)C * a.H;
+    const T *const kc = static_cast<const T *>(a.k) + u0 * K;
+    const float *const bc = a.beta + u0, *const rc = HAS_RET ? a.retention + u0 * (RET_VEC ? K : 1) : nullptr;
 #define OSDN_P1_LOAD(n_)                                                                         \
     {                                                                                            \
-        const int t0_ = (n_) * C;                                                                \
+        const size_t off_ = (size_t)(n_) * chunk_rows;                                           \
+        const int last_ = rows.count(n_) - 1, r0_ = min(run * RUN, last_);                       \
         const int fl_ = fresh_lane(lane);                                                        \
-        const T *kp_ = static_cast<const T *>(a.k) + (((size_t)bt * a.T + t0_) * a.H + h) * K;   \
+        const T *kp_ = kc + (off_ * K + (uint32_t)r0_ * kstride);                                \
+        const float *rp_ = RET_VEC ? rc + (off_ * K + (uint32_t)r0_ * kstride) : nullptr;        \
         _Pragma("unroll") for (int u = 0; u < RUN; ++u) {                                        \
-            const int i_ = TILES ? run * RUN + u : min(run * RUN + u, a.T - 1 - t0_);    /* rows past the end: reread */ \
-            kreg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(kp_ + (size_t)i_ * kstride), fl_); \
-            if (RET_VEC)                                                                         \
-                rreg[u] = row_elem(reinterpret_cast<const typename Pr::Raw *>(       \
-                    a.retention + (((size_t)bt * a.T + t0_) * a.H + h) * K + (size_t)i_ * kstride), fl_); \
+            kreg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(kp_), fl_);            \
+            if (RET_VEC) rreg[u] = row_elem(reinterpret_cast<const typename Pr::Raw *>(rp_), fl_); \
+            const uint32_t st_ = u < last_ - r0_ ? kstride : 0u;                                 \
+            kp_ += st_;                                                                          \
+            if (RET_VEC) rp_ += st_;                                                             \
         }                                                                                        \
-        const int i_ = TILES ? run * RUN + u_own : min(run * RUN + u_own, a.T - 1 - t0_);        \
-        const size_t th = ((size_t)bt * a.T + t0_) * a.H + h;                                    \
-        betreg = lane_elem(a.beta + th, i_ * a.H);                                               \
-        if (HAS_RET && !RET_VEC) retreg = lane_elem(a.retention + th, i_ * a.H);                 \
+        const int i_ = min(run * RUN + u_own, last_);                                            \
+        betreg = lane_elem(bc + off_, i_ * a.H);                                                 \
+        if (HAS_RET && !RET_VEC) retreg = lane_elem(rc + off_, i_ * a.H);                        \
+    }
+    if (RAG && TILES && rows.count(a.n1 - 1) < C) {      // the last chunk as a whole tile, for the backward pass
+        const int there = rows.count(a.n1 - 1);
+        const size_t off = (size_t)(a.n1 - 1) * chunk_rows, tl = (size_t)b * C * a.H + h;
+        for (int u = 0; u < RUN; ++u) {
+            const int i = run * RUN + u, from = min(i, there - 1);
+            typedef typename Pk::Raw R;
+            const R x = reinterpret_cast<const R *>(kc + (off + (size_t)from * a.H) * K)[lane];
+            reinterpret_cast<R *>(static_cast<T *>(a.k_tail) + (tl + (size_t)i * a.H) * K)[lane] = i < there ? x : R{};
+            if (RET_VEC)
+                for (int e = 0; e < CPT; ++e) {
+                    const float r = rc[(off + (size_t)from * a.H) * K + c0 + e];
+                    a.ret_tail[(tl + (size_t)i * a.H) * K + c0 + e] = i < there ? r : 1.f;
+                }
+        }
+        if (tid < C) {
+            const size_t from = off + (size_t)min(tid, there - 1) * a.H, to = tl + (size_t)tid * a.H;
+            a.beta_tail[to] = tid < there ? bc[from] : 0.f;
+            if (HAS_RET && !RET_VEC) a.ret_tail[to] = tid < there ? rc[from] : 1.f;
+        }
     }
     OSDN_P1_LOAD(a.n0)
     // (waited for here: loads that are pending when the loop is entered would make its head wait for the stores too)
@@ -165,19 +191,24 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
     int pub = 0, fl = 0;                        // map buffer and flag row of the next barrier
     for (int n = a.n0; n < a.n1; ++n) {
         const int t0 = n * C;
-        const int nvalid = min(C, a.T - t0);
+        const int nvalid = rows.count(n);
         // ---- this thread's k and s = k^2 (rows past the end of the sequence: no-op tokens) ----
         float kf[RUN][CPT], sv[RUN][CPT];
+        if (nvalid < C) {
+#pragma unroll
+            for (int u = 0; u < RUN; ++u)
+                if (run * RUN + u >= nvalid) kreg[u] = typename Pk::Raw{};
+        }
 #pragma unroll
         for (int u = 0; u < RUN; ++u) {
             Pk::unpack(kreg[u], kf[u]);
 #pragma unroll
             for (int e = 0; e < CPT; ++e) {
-                if (!TILES && run * RUN + u >= nvalid) kf[u][e] = 0.f;
                 sv[u][e] = kf[u][e] * kf[u][e];
             }
         }
-        const float bet = betreg, ret = retreg;
+        const bool valid = run * RUN + u_own < nvalid;
+        const float bet = betreg, ret = valid ? retreg : 1.f;
         // ---- the scalars of token (run, u_own): n_raw = sum s, first guess p = <d_0, s> ----
         float nraw, cb, ca, p_cur, c_cur;
         {
@@ -193,11 +224,10 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
             for (int u = 0; u < RUN; ++u) {
                 vn[u] = 0.f; vp[u] = 0.f;
 #pragma unroll
-                for (int e = 0; e < CPT; ++e) { vn[u] += sv[u][e]; vp[u] = __builtin_fmaf(sv[u][e], dst[e], vp[u]); }
+                for (int e = 0; e < CPT; ++e) { vn[u] = __builtin_fmaf(kf[u][e], kf[u][e], vn[u]); vp[u] = __builtin_fmaf(sv[u][e], dst[e], vp[u]); }
             }
             nraw = fold_tokens(vn);
             p_cur = fold_tokens(vp);
-            const bool valid = TILES || run * RUN + u_own < nvalid;
             const float nn = fmaxf(nraw, a.eps);
             const float bp = a.beta_aware ? bet : 1.f;
             cb = valid ? a.eta * bp / nn : 0.f;
@@ -211,9 +241,9 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
                 float r2[CPT];
                 Pr::unpack(rreg[RET_VEC ? u : 0], r2);
 #pragma unroll
-                for (int e = 0; e < RE; ++e) rv[u][e] = TILES || run * RUN + u < nvalid ? r2[e] : 1.f;
+                for (int e = 0; e < RE; ++e) rv[u][e] = run * RUN + u < nvalid ? r2[e] : 1.f;
             } else {
-                rv[u][0] = HAS_RET ? lane_bcast(TILES || run * RUN + u < nvalid ? ret : 1.f, fold_lane(u)) : 1.f;
+                rv[u][0] = HAS_RET ? lane_bcast(ret, fold_lane(u)) : 1.f;
             }
         }
         OSDN_P1_LOAD(min(n + 1, a.n1 - 1))       // (past the end: reloaded in vain)
@@ -376,7 +406,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
                 }
             }
         }
-        if (TILES || (a.tok_scalars && run * RUN + u_own < nvalid)) {       // (eight lanes store the same)
+        if (TILES || (a.tok_scalars && valid)) {       // (eight lanes store the same)
             const size_t th = ((size_t)bt * a.T + t0) * a.H + h;
             lane_elem(reinterpret_cast<float4 *>(a.tok_scalars) + th, (run * RUN + u_own) * a.H) = make_float4(c_acc, p_acc, nraw, (float)sweeps_used);
         }
@@ -407,8 +437,8 @@ template <typename T, int RET, bool PIECES, bool TILES>
 static int launch_precond_fwd_tp(const PrecondArgs &a, hipStream_t st) {
     dim3 grid((a.seq_chunks ? a.n_seqs : a.B) * a.H * (PIECES ? a.pieces : 1)), block(P1F);
     if (TILES && (a.T % C != 0 || !a.d_ckpt || !a.tok_scalars)) return -1;
-    if (a.K == 64) hipLaunchKernelGGL((precond_fwd_kernel<T, 64, RET, PIECES, TILES>), grid, block, 0, st, a);
-    else if (a.K == 128) hipLaunchKernelGGL((precond_fwd_kernel<T, 128, RET, PIECES, TILES>), grid, block, 0, st, a);
+    if (a.K == 64) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_fwd_kernel<T, 64, RET, PIECES, TILES, decltype(rag)::value>), grid, block, 0, st, a); });
+    else if (a.K == 128) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_fwd_kernel<T, 128, RET, PIECES, TILES, decltype(rag)::value>), grid, block, 0, st, a); });
     else return -1;
     return 0;
 }

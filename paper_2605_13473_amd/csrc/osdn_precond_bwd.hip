@@ -35,7 +35,7 @@ namespace osdn {
 
 // ---------------------------------------------------------------- precond_mask ----
 // RET (all three kernels): 0 = no retention, 1 = one gate per (token, head), 2 = one per coordinate
-template <typename T, int K, int RET>
+template <typename T, int K, int RET, bool RAG>
 __global__ __launch_bounds__(K) void precond_mask_kernel(PrecondBwdArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     __shared__ __attribute__((aligned(16))) float steps[C];
@@ -44,15 +44,16 @@ __global__ __launch_bounds__(K) void precond_mask_kernel(PrecondBwdArgs a) {
     const int N = a.T / C;
     const size_t bh = (size_t)b * a.H + h;
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    const ChunkIn<T, K, RET, RAG> in(a, b, n, h);
     const bool project = a.d_min <= a.d_max;
     const float lo = project ? a.d_min : -INFINITY, hi = project ? a.d_max : INFINITY;
     if (tid < C) {
         const size_t th = tokc + (size_t)tid * a.H;
         steps[tid] = a.tok_scalars[th * 4];
-        rs[tid] = (HAS_RET && !RET_VEC) ? a.retention[th] : 1.f;
+        rs[tid] = (HAS_RET && !RET_VEC) ? in.ret[(size_t)tid * a.H] : 1.f;
     }
-    const T *kp = static_cast<const T *>(a.k) + tokc * K;
-    const float *rp = RET_VEC ? a.retention + tokc * K : nullptr;
+    const T *kp = in.k;
+    const float *rp = in.ret;
     const uint32_t kstride = (uint32_t)a.H * K;
     float kv[C], rvv[RET_VEC ? C : 1];
 #pragma unroll
@@ -67,9 +68,9 @@ __global__ __launch_bounds__(K) void precond_mask_kernel(PrecondBwdArgs a) {
     for (int i = 0; i < C; ++i) {
         const float sq = kv[i] * kv[i];
         const float r = RET_VEC ? rvv[RET_VEC ? i : 0] : rs[i];
-        const uint32_t in = lands_inside<HAS_RET>(r, d, steps[i], sq, lo, hi) ? (1u << (i & 31)) : 0u;
+        const uint32_t bit = lands_inside<HAS_RET>(r, d, steps[i], sq, lo, hi) ? (1u << (i & 31)) : 0u;
         d = clip3(d_bar<HAS_RET>(r, d, steps[i], sq), lo, hi);
-        if (i < 32) mlo |= in; else mhi |= in;
+        if (i < 32) mlo |= bit; else mhi |= bit;
     }
     a.masks[(bh * N + n) * K + tid] = make_uint2(mlo, mhi);
 }
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(K) void precond_mask_kernel(PrecondBwdArgs a) {
 // precond_mask does when this form is off: the same arithmetic, from the s tile it builds anyway),
 // decides from them whether the chunk qualifies, and inverts the system.
 // precond_lin_r needs dL/dk~ of the chunk as well: rho0 and the sum of lambda.
-template <typename T, int K>
+template <typename T, int K, bool RAG>
 __global__ __launch_bounds__(P1T) void precond_lin_m_kernel(PrecondBwdArgs a) {
     typedef Lin<K> LN;
     constexpr int EPT = LN::EPT, VN = 16 / sizeof(T), NVK = EPT / VN;
@@ -99,12 +100,13 @@ __global__ __launch_bounds__(P1T) void precond_lin_m_kernel(PrecondBwdArgs a) {
     const int N = a.T / C;
     const size_t bhn = ((size_t)b * a.H + h) * N + n;
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    const ChunkIn<T, K, 0, RAG> src(a, b, n, h);
     const int i = tid >> 3, part = tid & 7;
     const uint32_t kstride = (uint32_t)a.H * K;
     u32x4 kv[NVK];
     {
         const uint32_t off = ((uint32_t)i * kstride + (uint32_t)(part * EPT)) * (uint32_t)sizeof(T);
-        const u32x4 *kp = reinterpret_cast<const u32x4 *>(static_cast<const T *>(a.k) + tokc * K);
+        const u32x4 *kp = reinterpret_cast<const u32x4 *>(src.k);
 #pragma unroll
         for (int m = 0; m < NVK; ++m) kv[m] = at_byte(kp, off + 16 * m);
     }
@@ -115,7 +117,7 @@ __global__ __launch_bounds__(P1T) void precond_lin_m_kernel(PrecondBwdArgs a) {
         const float4 sc = *reinterpret_cast<const float4 *>(a.tok_scalars + th * 4);
         steps[tid] = sc.x;
         nraw = sc.z;
-        bet = a.beta[th];
+        bet = src.beta[(size_t)tid * a.H];
     }
     if (project && tid < K) d = a.d_ckpt[bhn * K + tid];
 #pragma unroll
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(P1T) void precond_lin_m_kernel(PrecondBwdArgs a) {
 // (c = tid % K, tg = tid / K) keeps TS consecutive tokens of coordinate c in registers; the suffix
 // sums run down its tokens and across the runs through LDS; the row dots are folded over the lanes
 // as in the sweeps of precond_chain.
-template <typename T, int K>
+template <typename T, int K, bool RAG>
 __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
     constexpr int NSEG = P1T / K, TS = C / NSEG, WPS = K / 64, NPART = K / TS;
     __shared__ float tot[NSEG * K];
@@ -201,9 +203,9 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
     const int N = a.T / C;
     const size_t bhn = ((size_t)b * a.H + h) * N + n;
     if (!a.lin_clean[bhn]) return;                               // (uniform)
-    const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const uint32_t kstride = (uint32_t)a.H * K;
-    const T *kp = static_cast<const T *>(a.k) + tokc * K, *gp = static_cast<const T *>(a.dkt) + (((size_t)b * N + n) * a.H + h) * C * K;
+    const ChunkIn<T, K, 0, RAG> src(a, b, n, h);
+    const T *kp = src.k, *gp = static_cast<const T *>(a.dkt) + (((size_t)b * N + n) * a.H + h) * C * K;
     float sv[TS], lam[TS];
 #pragma unroll
     for (int u = 0; u < TS; ++u) {
@@ -268,7 +270,7 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
 // coordinates along (1, .., 1), which is nearly all of it (sum ca_t s_t s_t^T = g g^T / <1, g> for equal keys).
 // With a retention gate two sweeps do and a third finds that nothing moved (16 chains, K = V = 128, backward pass of 128
 // chunks 579 -> 432 us, of 512 1986 -> 1600); without, three to five.
-template <typename T, int K, int RET, bool PIECES>
+template <typename T, int K, int RET, bool PIECES, bool RAG>
 __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     constexpr bool COUPLED = PIECES && RET == 0;
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
@@ -305,6 +307,7 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     const bool project = a.d_min <= a.d_max;
     const int N = a.T / C;
     const uint32_t kstride = (uint32_t)a.H * K;               // elements between consecutive tokens
+    const ChainIn<T, K, RET, RAG> in(a, b, a.n0, h);
 
     float ga[CPT];                               // adjoint of d at the right end of the chunk (the same in every wavefront)
 #pragma unroll
@@ -375,25 +378,29 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     typename Pr::Raw rreg[RET_VEC ? RUN : 1];    // ... its per-coordinate retention
     uint32_t mreg[CPT];                          // ... half of its mask bits
     float nrawreg = 1.f, betreg = 0.f, retreg = 1.f;          // ... and the scalars of token (run, u_own)
+    // (per-chunk buffers, like the caller's rows, lie a constant step apart from chunk to chunk)
+    const T *const gc = static_cast<const T *>(a.dkt) + (((size_t)bt * N * a.H + h) * C + run * RUN) * K;
+    float *const tc = a.tok_scalars + ((size_t)bt * a.T * a.H + h) * 4;
+    const uint32_t *const mc = reinterpret_cast<const uint32_t *>(a.masks + bth * N * K) + run / (32 / RUN);
+    float *const ac = a.a_ckpt + bth * N * K;
 #define OSDN_P1_BLOAD(n_)                                                                        \
     {                                                                                            \
-        const size_t tokc_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                    \
+        const size_t off_ = (size_t)(n_) * in.chunk_rows;                                        \
         const int fl_ = fresh_lane(lane);                                                        \
-        const T *kp_ = static_cast<const T *>(a.k) + (tokc_ + (size_t)(run * RUN) * a.H) * K;    \
-        const T *gp_ = static_cast<const T *>(a.dkt) + ((((size_t)bt * N + (n_)) * a.H + h) * C + run * RUN) * K; \
+        const T *kp_ = in.k_of(n_) + (uint32_t)(run * RUN) * kstride, *gp_ = gc + off_ * K;      \
+        const float *rp_ = HAS_RET ? in.ret_of(n_) : nullptr;                                    \
         _Pragma("unroll") for (int u = 0; u < RUN; ++u) {                                        \
             kreg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(kp_ + (size_t)u * kstride), fl_); \
             greg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(gp_ + u * K), fl_);    \
             if (RET_VEC)                                                                         \
                 rreg[RET_VEC ? u : 0] = row_elem(reinterpret_cast<const typename Pr::Raw *>(     \
-                    a.retention + (tokc_ + (size_t)(run * RUN + u) * a.H) * K), fl_);            \
+                    rp_ + (size_t)(run * RUN + u) * kstride), fl_);                              \
         }                                                                                        \
-        const uint32_t *mp_ = reinterpret_cast<const uint32_t *>(a.masks + (bth * N + (n_)) * K) + run / (32 / RUN); \
-        _Pragma("unroll") for (int e = 0; e < CPT; ++e) mreg[e] = lane_elem(mp_, (c0 + e) * 2);  \
-        const int i_ = run * RUN + u_own;                                                        \
-        nrawreg = lane_elem(a.tok_scalars + tokc_ * 4 + 2, i_ * a.H * 4);                        \
-        betreg = lane_elem(a.beta + tokc_, i_ * a.H);                                            \
-        if (HAS_RET && !RET_VEC) retreg = lane_elem(a.retention + tokc_, i_ * a.H);              \
+        _Pragma("unroll") for (int e = 0; e < CPT; ++e) mreg[e] = lane_elem(mc + (size_t)(n_) * K * 2, (c0 + e) * 2); \
+        const int i_ = (run * RUN + u_own) * a.H;                                                \
+        nrawreg = lane_elem(tc + off_ * 4 + 2, i_ * 4);                                          \
+        betreg = lane_elem(in.beta_of(n_), i_);                                                  \
+        if (HAS_RET && !RET_VEC) retreg = lane_elem(rp_, i_);                                    \
     }
     // The adjoint g of the chunk's right end carried to the right end of this run (returned in at) and, if
     // OUT, on to the chunk's left end (in g).  The run is the same for the whole wavefront: scalar branches.
@@ -465,10 +472,10 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
             if constexpr (RET_VEC) Pr::unpack(rreg[RET_VEC ? u : 0], rv[u]);
             else rv[u][0] = HAS_RET ? lane_bcast(retreg, fold_lane(u)) : 1.f;
         }
-        bool in = true;
+        bool whole = true;
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) in = in && mb[e] == (1u << RUN) - 1;
-        const bool clean = __all(in);            // no coordinate of this wavefront met the box in its run
+        for (int e = 0; e < CPT; ++e) whole = whole && mb[e] == (1u << RUN) - 1;
+        const bool clean = __all(whole);            // no coordinate of this wavefront met the box in its run
         float ca, cn = 0.f;
         {
             const float nn = fmaxf(nrawreg, a.eps), bp = a.beta_aware ? betreg : 1.f;
@@ -492,8 +499,8 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         }
         // the results of the chunk before, ahead of the loads: behind them, the wait for the loads would be one for
         // these stores too (every wavefront stores the same adjoint, eight lanes the same sigma)
-        *reinterpret_cast<typename Pr::Raw *>(a.a_ckpt + (bth * N + done) * K + c0) = Pr::pack(gdone);
-        lane_elem(a.tok_scalars + (((size_t)bt * a.T + (size_t)done * C) * a.H + h) * 4 + 3, (run * RUN + u_own) * a.H * 4) = sdone;
+        lane_elem(reinterpret_cast<typename Pr::Raw *>(ac + (size_t)done * K), lane) = Pr::pack(gdone);
+        lane_elem(tc + (size_t)done * in.chunk_rows * 4 + 3, (run * RUN + u_own) * a.H * 4) = sdone;
         OSDN_P1_BLOAD(max(n - 1, a.n0))
         int mk[RUN][CPT];                        // all ones where the projection of the token lets the coordinate pass
 #pragma unroll
@@ -687,7 +694,7 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
 // other chunk is swept: NSEG = 512 / K runs of TS tokens, one coordinate of one run per thread, abar_i kept as
 // L_i + P_i * carry; the runs are chained through LDS, the products s_i abar_i folded over the lanes, three
 // barriers a sweep (such chunks are few here: the library takes this form only where d stays inside the box).
-template <typename T, int K>
+template <typename T, int K, bool RAG>
 __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a) {
     constexpr int NSEG = P1T / K;                 // runs per chunk
     constexpr int TS = C / NSEG;                  // tokens per run
@@ -724,6 +731,7 @@ __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a
     const bool project = a.d_min <= a.d_max;
     const int N = a.T / C;
     const uint32_t kstride = (uint32_t)a.H * K;   // elements between consecutive tokens
+    const ChainIn<T, K, 0, RAG> src(a, b, a.n0, h);
 
     if (tid < K) {
         const float g0 = a.dd_out ? a.dd_out[bh * K + tid] : 0.f;
@@ -737,7 +745,7 @@ __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a
 #define OSDN_P1_BLOAD(n_)                                                                        \
     {                                                                                            \
         const size_t tokc_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                    \
-        const T *kp_ = static_cast<const T *>(a.k) + tokc_ * K;                                  \
+        const T *kp_ = src.k_of(n_);                                                             \
         const T *gp_ = static_cast<const T *>(a.dkt) + (((size_t)bt * N + (n_)) * a.H + h) * C * K; \
         uint32_t ok_ = (uint32_t)(sg * TS) * kstride + (uint32_t)c, og_ = (uint32_t)(sg * TS * K + c); \
         asm volatile("" : "+v"(ok_), "+v"(og_));             /* (seldom run: no addresses kept for it) */ \
@@ -748,7 +756,7 @@ __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a
         if (tid < C) {                                                                           \
             const size_t th = tokc_ + (size_t)tid * a.H;                                         \
             nrawreg = a.tok_scalars[th * 4 + 2];                                                 \
-            betreg = a.beta[th];                                                                 \
+            betreg = src.beta_of(n_)[(size_t)tid * a.H];                                         \
         }                                                                                        \
         if (project) mreg = a.masks[(bth * N + (n_)) * K + c];                                   \
     }
@@ -765,13 +773,13 @@ __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a
         const size_t tokc_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                    \
         const size_t bhn_ = bth * N + (n_);                                                      \
         const uint32_t off_ = ((uint32_t)li * kstride + (uint32_t)(lpart * EPT)) * (uint32_t)sizeof(T); \
-        const u32x4 *kp_ = reinterpret_cast<const u32x4 *>(static_cast<const T *>(a.k) + tokc_ * K); \
+        const u32x4 *kp_ = reinterpret_cast<const u32x4 *>(src.k_of(n_));                        \
         _Pragma("unroll") for (int m_ = 0; m_ < NVK; ++m_) R.kq[m_] = at_byte(kp_, off_ + 16 * m_); \
         const u32x4 *mp_ = reinterpret_cast<const u32x4 *>(static_cast<const T *>(a.lin_M) + bhn_ * C * C + li * C + lpart * 8); \
         _Pragma("unroll") for (int m_ = 0; m_ < (int)(8 * sizeof(T) / 16); ++m_) R.mq[m_] = mp_[m_]; \
         const size_t th = tokc_ + (size_t)li * a.H;      /* (every lane of a token loads its scalars) */ \
         R.nraw = a.tok_scalars[th * 4 + 2];                                                      \
-        R.beta = a.beta[th];                                                                     \
+        R.beta = src.beta_of(n_)[(size_t)li * a.H];                                              \
         R.rho = a.lin_r0[bhn_ * C + li];                                                         \
         R.t0 = a.lin_t0[bhn_ * K + lc];                                                          \
         __builtin_amdgcn_sched_barrier(0);                                                       \
@@ -971,7 +979,7 @@ __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a
 //        dk_read (read-side dL/dk), dbeta (partial, from phase 2)
 //   out: dk (io type) = dk_read + d_t . dkt + 2 k_t (step_t abar_t + g_p d_t + g_nraw),
 //        dbeta += sigma_t eta (1 - 2 b' p_t)/n_t,  dretention_t = <abar_t, d_t>
-template <typename T, int K, int RET>
+template <typename T, int K, int RET, bool RAG>
 __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void precond_post_kernel(PrecondBwdArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     constexpr int LD = K + 1;
@@ -988,31 +996,32 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
     const int N = a.T / C;
     const size_t bh = (size_t)b * a.H + h;
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    const ChunkIn<T, K, RET, RAG> in(a, b, n, h);
+    const size_t out0 = a.rows.first<RAG>(b, n) * a.H + h;
+    const int rows = a.rows.count<RAG>(n);
     const bool project = a.d_min <= a.d_max;
     const float lo = project ? a.d_min : -INFINITY, hi = project ? a.d_max : INFINITY;
     if (tid < C) {
         const size_t th = tokc + (size_t)tid * a.H;
         const float4 sc = *reinterpret_cast<const float4 *>(a.tok_scalars + th * 4);
         const float step = sc.x, p = sc.y, n_raw = sc.z, sg = sc.w;
-        const float bet = a.beta[th];
+        const float bet = in.beta[(size_t)tid * a.H];
         const float nn = fmaxf(n_raw, a.eps);
         const float bp = a.beta_aware ? bet : 1.f;
         const float ca = a.eta * bp / nn * bp;
         st_s[tid] = step;
-        r_s[tid] = (HAS_RET && !RET_VEC) ? a.retention[th] : 1.f;
+        r_s[tid] = (HAS_RET && !RET_VEC) ? in.ret[(size_t)tid * a.H] : 1.f;
         casig_s[tid] = ca * sg;
         gp_s[tid] = -sg * ca;
         gn_s[tid] = (n_raw >= a.eps) ? -sg * step / nn : 0.f;
-        if (a.beta_aware) a.dbeta[th] += sg * a.eta * (1.f - 2.f * bp * p) / nn;
+        if (a.beta_aware && tid < rows) a.dbeta[out0 + (size_t)tid * a.H] += sg * a.eta * (1.f - 2.f * bp * p) / nn;
     }
     // uniform bases + 32-bit per-thread offsets (64 rows of H*K elements: below 2^31)
-    const T *kp = static_cast<const T *>(a.k) + tokc * K;
+    const T *kp = in.k;
     const size_t tile = (((size_t)b * N + n) * a.H + h) * C * K;        // dkt and dk_read: one tile per chunk and head
     const T *gp = static_cast<const T *>(a.dkt) + tile, *rp = static_cast<const T *>(a.dk_read) + tile;
-    const size_t out0 = a.out.first(b, n) * a.H + h;
-    const int rows = a.out.count(n);
     T *op = static_cast<T *>(a.dk) + out0 * K;
-    const float *retp = RET_VEC ? a.retention + tokc * K : nullptr;     // per-coordinate retention and its gradient
+    const float *retp = RET_VEC ? in.ret : nullptr;     // per-coordinate retention and its gradient
     float *dretp = (RET_VEC && a.dretention) ? a.dretention + out0 * K : nullptr;
     const uint32_t kstride = (uint32_t)a.H * K;
     float Dv[C];
@@ -1084,11 +1093,11 @@ __global__ __launch_bounds__(K) __attribute__((amdgpu_waves_per_eu(2, 8))) void 
     }
     if (HAS_RET && !RET_VEC) {
         __syncthreads();
-        if (tid < C && a.dretention) {
+        if (tid < rows && a.dretention) {
             float s = 0.f;
 #pragma unroll
             for (int w = 0; w < K / 64; ++w) s += rpart[(HAS_RET && !RET_VEC) ? w * C + tid : 0];
-            a.dretention[tokc + (size_t)tid * a.H] = s;
+            a.dretention[out0 + (size_t)tid * a.H] = s;
         }
     }
 }
@@ -1098,25 +1107,25 @@ template <typename T, int K, int RET>
 static void launch_chain_k(const PrecondBwdArgs &a, int nchains, hipStream_t st) {
     if constexpr (RET == 0) {
         if (a.lin_clean) {
-            hipLaunchKernelGGL((precond_chain_lin_kernel<T, K>), dim3(nchains), dim3(P1T), 0, st, a);
+            with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_chain_lin_kernel<T, K, decltype(rag)::value>), dim3(nchains), dim3(P1T), 0, st, a); });
             return;
         }
     }
-    if (a.pieces) hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, true>), dim3(nchains * a.pieces), dim3(P1F), 0, st, a);
-    else hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, false>), dim3(nchains), dim3(P1F), 0, st, a);
+    if (a.pieces) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, true, decltype(rag)::value>), dim3(nchains * a.pieces), dim3(P1F), 0, st, a); });
+    else with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, false, decltype(rag)::value>), dim3(nchains), dim3(P1F), 0, st, a); });
 }
 template <typename T, int RET>
 static int launch_precond_bwd_t(const PrecondBwdArgs &a, int which, hipStream_t st) {
     const dim3 per_chunk((a.n1 - a.n0) * a.H, a.B);
     const int nchains = (a.seq_chunks ? a.n_seqs : a.B) * a.H;
     if (a.K == 64) {
-        if (which == 0) hipLaunchKernelGGL((precond_mask_kernel<T, 64, RET>), per_chunk, dim3(64), 0, st, a);
+        if (which == 0) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_mask_kernel<T, 64, RET, decltype(rag)::value>), per_chunk, dim3(64), 0, st, a); });
         else if (which == 1) launch_chain_k<T, 64, RET>(a, nchains, st);
-        else hipLaunchKernelGGL((precond_post_kernel<T, 64, RET>), per_chunk, dim3(64), 0, st, a);
+        else with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_post_kernel<T, 64, RET, decltype(rag)::value>), per_chunk, dim3(64), 0, st, a); });
     } else if (a.K == 128) {
-        if (which == 0) hipLaunchKernelGGL((precond_mask_kernel<T, 128, RET>), per_chunk, dim3(128), 0, st, a);
+        if (which == 0) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_mask_kernel<T, 128, RET, decltype(rag)::value>), per_chunk, dim3(128), 0, st, a); });
         else if (which == 1) launch_chain_k<T, 128, RET>(a, nchains, st);
-        else hipLaunchKernelGGL((precond_post_kernel<T, 128, RET>), per_chunk, dim3(128), 0, st, a);
+        else with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_post_kernel<T, 128, RET, decltype(rag)::value>), per_chunk, dim3(128), 0, st, a); });
     } else {
         return -1;
     }
@@ -1134,11 +1143,11 @@ template <typename T>
 static int launch_precond_lin_t(const PrecondBwdArgs &a, bool m_part, hipStream_t st) {
     const dim3 per_chunk((a.n1 - a.n0) * a.H, a.B);
     if (a.K == 64) {
-        if (m_part) hipLaunchKernelGGL((precond_lin_m_kernel<T, 64>), per_chunk, dim3(P1T), 0, st, a);
-        else hipLaunchKernelGGL((precond_lin_r_kernel<T, 64>), per_chunk, dim3(P1T), 0, st, a);
+        if (m_part) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_lin_m_kernel<T, 64, decltype(rag)::value>), per_chunk, dim3(P1T), 0, st, a); });
+        else with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_lin_r_kernel<T, 64, decltype(rag)::value>), per_chunk, dim3(P1T), 0, st, a); });
     } else if (a.K == 128) {
-        if (m_part) hipLaunchKernelGGL((precond_lin_m_kernel<T, 128>), per_chunk, dim3(P1T), 0, st, a);
-        else hipLaunchKernelGGL((precond_lin_r_kernel<T, 128>), per_chunk, dim3(P1T), 0, st, a);
+        if (m_part) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_lin_m_kernel<T, 128, decltype(rag)::value>), per_chunk, dim3(P1T), 0, st, a); });
+        else with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_lin_r_kernel<T, 128, decltype(rag)::value>), per_chunk, dim3(P1T), 0, st, a); });
     } else {
         return -1;
     }

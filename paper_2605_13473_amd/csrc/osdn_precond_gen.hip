@@ -67,6 +67,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_m_kernel(PrecondBwdArgs a) {
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
     const int i = tid >> 3, part = tid & 7;
     const uint32_t kstride = (uint32_t)a.H * K;
+    const ChunkIn<T, K, HAS_RET ? 1 : 0, true> src(a, b, n, h);
     unsigned char *aux = a.lin_aux + bhn * GEN_AUX;
     const bool project = a.d_min <= a.d_max;
     const float lo = project ? a.d_min : -INFINITY, hi = project ? a.d_max : INFINITY;
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_m_kernel(PrecondBwdArgs a) {
     u32x4 kv[NVK];
     {
         const uint32_t off = ((uint32_t)i * kstride + (uint32_t)(part * EPT)) * (uint32_t)sizeof(T);
-        const u32x4 *kp = reinterpret_cast<const u32x4 *>(static_cast<const T *>(a.k) + tokc * K);
+        const u32x4 *kp = reinterpret_cast<const u32x4 *>(src.k);
 #pragma unroll
         for (int m = 0; m < NVK; ++m) kv[m] = at_byte(kp, off + 16 * m);
     }
@@ -82,12 +83,12 @@ __global__ __launch_bounds__(P1T) void precond_gen_m_kernel(PrecondBwdArgs a) {
     if (tid < C) {
         const size_t th = tokc + (size_t)tid * a.H;
         const float4 sc = *reinterpret_cast<const float4 *>(a.tok_scalars + th * 4);
-        const float bet = a.beta[th];
+        const float bet = src.beta[(size_t)tid * a.H];
         const float nn = fmaxf(sc.z, a.eps);
         const float bp = a.beta_aware ? bet : 1.f;
         steps[tid] = sc.x;
         cas[tid] = a.eta * bp / nn * bp;
-        rs[tid] = HAS_RET ? a.retention[th] : 1.f;
+        rs[tid] = HAS_RET ? src.ret[(size_t)tid * a.H] : 1.f;
     }
     if (project && tid < K) d = a.d_ckpt[bhn * K + tid];
     if (tid < K / 32) cleanw[tid] = 0u;
@@ -273,10 +274,10 @@ __global__ __launch_bounds__(P1T) void precond_gen_r_kernel(PrecondBwdArgs a) {
     const int c = tid % K, sg = tid / K;
     const int N = a.T / C;
     const size_t bhn = ((size_t)b * a.H + h) * N + n;
-    const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
+    const ChunkIn<T, K, HAS_RET ? 1 : 0, true> src(a, b, n, h);
     const uint32_t kstride = (uint32_t)a.H * K;
     const bool project = a.d_min <= a.d_max;
-    const T *kp = static_cast<const T *>(a.k) + tokc * K, *gp = static_cast<const T *>(a.dkt) + (((size_t)b * N + n) * a.H + h) * C * K;
+    const T *kp = src.k, *gp = static_cast<const T *>(a.dkt) + (((size_t)b * N + n) * a.H + h) * C * K;
     float sv[TS], lam[TS];
 #pragma unroll
     for (int u = 0; u < TS; ++u) {
@@ -285,7 +286,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_r_kernel(PrecondBwdArgs a) {
         sv[u] = kf * kf;
         lam[u] = kf * to_f32(lane_elem(gp, (sg * TS + u) * K + c));
     }
-    if (tid < C) rs[tid] = HAS_RET ? a.retention[tokc + (size_t)tid * a.H] : 1.f;
+    if (tid < C) rs[tid] = HAS_RET ? src.ret[(size_t)tid * a.H] : 1.f;
     const uint2 mreg = project ? a.masks[bhn * K + c] : make_uint2(0xffffffffu, 0xffffffffu);
     const uint32_t mword = (sg * TS) < 32 ? mreg.x : mreg.y;
     const uint32_t mbits = (mword >> ((sg * TS) & 31)) & ((1u << TS) - 1u);
@@ -355,6 +356,7 @@ __global__ __launch_bounds__(P1T) void precond_gen_chain_kernel(PrecondBwdArgs a
     const size_t bth = (size_t)bt * a.H + h;
     const int N = a.T / C;
     const uint32_t kstride = (uint32_t)a.H * K;
+    const ChainIn<T, K, 0, true> src(a, b, a.n0, h);
 
     if (tid < K) {
         const float g0 = a.dd_out ? a.dd_out[bh * K + tid] : 0.f;
@@ -373,13 +375,13 @@ __global__ __launch_bounds__(P1T) void precond_gen_chain_kernel(PrecondBwdArgs a
         const size_t tokc_ = ((size_t)bt * a.T + (size_t)(n_) * C) * a.H + h;                    \
         const size_t bhn_ = bth * N + (n_);                                                      \
         const uint32_t off_ = ((uint32_t)li * kstride + (uint32_t)(lpart * EPT)) * (uint32_t)sizeof(T); \
-        const u32x4 *kp_ = reinterpret_cast<const u32x4 *>(static_cast<const T *>(a.k) + tokc_ * K); \
+        const u32x4 *kp_ = reinterpret_cast<const u32x4 *>(src.k_of(n_));                        \
         _Pragma("unroll") for (int m_ = 0; m_ < NVK; ++m_) R.kq[m_] = at_byte(kp_, off_ + 16 * m_); \
         const u32x4 *mp_ = reinterpret_cast<const u32x4 *>(static_cast<const T *>(a.lin_M) + bhn_ * C * C + li * C + lpart * 8); \
         _Pragma("unroll") for (int m_ = 0; m_ < MQ; ++m_) R.mq[m_] = mp_[m_];                    \
         const size_t th = tokc_ + (size_t)li * a.H;                                              \
         const float nraw_ = a.tok_scalars[th * 4 + 2];                                           \
-        const float bet_ = a.beta[th];                                                           \
+        const float bet_ = src.beta_of(n_)[(size_t)li * a.H];                                                           \
         const unsigned char *aux_ = a.lin_aux + bhn_ * GEN_AUX;                                  \
         R.rho = a.lin_r0[bhn_ * C + li];                                                         \
         R.rsuf = *reinterpret_cast<const float *>(aux_ + GA_RSUF + 4 * li);                      \

@@ -121,7 +121,7 @@ template <int ROWB, int ROWS, int NW> struct LdsLoad {
     // rot: the wavefront starts with its rot-th load.  Workgroups that read the same tile at the same time
     // start in different places, so that together they have more of it in flight and find the rest in the
     // L2 (8 workgroups per tile, 40 KB a step from HBM beside stores of 8 KB: 1.05 -> 0.83 us per step).
-    __device__ __forceinline__ void issue(char *tile, const char *g, uint32_t gstride, int wave, int lane, int rot = 0, bool wide = true) const {
+    __device__ __forceinline__ void issue(char *tile, const char *g, uint32_t gstride, int wave, int lane, int rot = 0, bool wide = true, int last = ROWS - 1) const {
         const uint32_t lds = lds_offset(tile);
         constexpr int M = (NI + NW - 1) / NW;
         static_assert((M & (M - 1)) == 0, "loads per wavefront");
@@ -130,7 +130,12 @@ template <int ROWB, int ROWS, int NW> struct LdsLoad {
             const int m = (j + rot) & (M - 1), i = wave + m * NW;
             if (NI % NW == 0 || i < NI) {
                 const char *gm = g + (size_t)m * NW * RPI * gstride;
-                const uint32_t vo = voff ^ (uint32_t)(((m * STEP) & 15 & (STEP % 16 ? 15 : 0)) << 4);
+                uint32_t vo = voff ^ (uint32_t)(((m * STEP) & 15 & (STEP % 16 ? 15 : 0)) << 4);
+                if (last < ROWS - 1) {              // (uniform) rows behind the last one that exists repeat it
+                    const uint32_t r = i * RPI + lane / (ROWB / 16), ph = lane % (ROWB / 16);
+                    gm = g;
+                    vo = min(r, (uint32_t)last) * gstride + ((ph ^ Swz<ROWB>::f(r)) << 4);
+                }
                 if (wide) load_lds16(gm, vo, lds + i * 1024);
                 else *reinterpret_cast<u32x4 *>(tile + i * 1024 + lane * 16) = *reinterpret_cast<const u32x4 *>(gm + vo);
             }
