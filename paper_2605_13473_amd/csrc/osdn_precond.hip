@@ -145,18 +145,21 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
 #define OSDN_P1_LOAD(n_)                                                                         \
     {                                                                                            \
         const size_t off_ = (size_t)(n_) * chunk_rows;                                           \
-        const int last_ = rows.count(n_) - 1, r0_ = min(run * RUN, last_);                       \
+        const int last_ = rows.count(n_) - 1, r0_ = RAG ? min(run * RUN, last_) : run * RUN;     \
         const int fl_ = fresh_lane(lane);                                                        \
         const T *kp_ = kc + (off_ * K + (uint32_t)r0_ * kstride);                                \
         const float *rp_ = RET_VEC ? rc + (off_ * K + (uint32_t)r0_ * kstride) : nullptr;        \
         _Pragma("unroll") for (int u = 0; u < RUN; ++u) {                                        \
-            kreg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(kp_), fl_);            \
-            if (RET_VEC) rreg[u] = row_elem(reinterpret_cast<const typename Pr::Raw *>(rp_), fl_); \
-            const uint32_t st_ = u < last_ - r0_ ? kstride : 0u;                                 \
-            kp_ += st_;                                                                          \
-            if (RET_VEC) rp_ += st_;                                                             \
+            const size_t at_ = RAG ? 0 : (size_t)u * kstride;                                    \
+            kreg[u] = row_elem(reinterpret_cast<const typename Pk::Raw *>(kp_ + at_), fl_);      \
+            if (RET_VEC) rreg[u] = row_elem(reinterpret_cast<const typename Pr::Raw *>(rp_ + at_), fl_); \
+            if (RAG) {                                                                           \
+                const uint32_t st_ = u < last_ - r0_ ? kstride : 0u;                             \
+                kp_ += st_;                                                                      \
+                if (RET_VEC) rp_ += st_;                                                         \
+            }                                                                                    \
         }                                                                                        \
-        const int i_ = min(run * RUN + u_own, last_);                                            \
+        const int i_ = RAG ? min(run * RUN + u_own, last_) : run * RUN + u_own;                  \
         betreg = lane_elem(bc + off_, i_ * a.H);                                                 \
         if (HAS_RET && !RET_VEC) retreg = lane_elem(rc + off_, i_ * a.H);                        \
     }
