@@ -9,7 +9,10 @@
 // separates into K independent scalar recurrences; from the resulting trajectory the 64 inner
 // products are recomputed; the sweep repeats until they reproduce themselves.  Sweep m fixes
 // at least the first m tokens exactly, so 64 sweeps always suffice; because the coupling is
-// O(eta) two do in practice, also when coordinates sit on a face of the box.
+// O(eta) two do in practice, also when coordinates sit on a face of the box.  With one retention per
+// token the first guess takes what the gates of the tokens before leave of d_0 (a prefix product over
+// the chunk, every wavefront its own: 25 instructions): without it a third sweep is needed where the gates
+// leave 0.9 of d over a chunk (2 x 384 tokens, 8 heads of 128 x 128, retention about 0.999: 52.8 -> 46.9 us).
 //
 // A sweep does not walk the 64 tokens one after the other.  The chunk is cut into 8 runs of
 // 8 tokens, one wavefront per run, a lane per coordinate (pair): everything a thread needs of
@@ -137,7 +140,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
     typedef Pack<float, CPT> Pr;
     typename Pk::Raw kreg[RUN];                  // this thread's k of the next chunk
     typename Pr::Raw rreg[RET_VEC ? RUN : 1];    // ... and its per-coordinate retention
-    float betreg = 0.f, retreg = 1.f;            // gates of token (run, u_own) of the next chunk
+    float betreg = 0.f, retreg = 1.f;            // next chunk: beta of token (run, u_own), retention of token `lane`
     // (rows past the end: reread; a row's address is the one before, a row further if there is one)
     const size_t u0 = (rows.batch + (size_t)(long long)rows.base) * a.H + h, chunk_rows = (size_t)C * a.H;
     const T *const kc = static_cast<const T *>(a.k) + u0 * K;
@@ -147,6 +150,9 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
         const size_t off_ = (size_t)(n_) * chunk_rows;                                           \
         const int last_ = rows.count(n_) - 1, r0_ = RAG ? min(run * RUN, last_) : run * RUN;     \
         const int fl_ = fresh_lane(lane);                                                        \
+        const int i_ = RAG ? min(run * RUN + u_own, last_) : run * RUN + u_own;                  \
+        betreg = lane_elem(bc + off_, i_ * a.H);                                                 \
+        if (RET == 1) retreg = lane_elem(rc + off_, (RAG ? min(lane, last_) : lane) * a.H);      \
         const T *kp_ = kc + (off_ * K + (uint32_t)r0_ * kstride);                                \
         const float *rp_ = RET_VEC ? rc + (off_ * K + (uint32_t)r0_ * kstride) : nullptr;        \
         _Pragma("unroll") for (int u = 0; u < RUN; ++u) {                                        \
@@ -159,9 +165,6 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
                 if (RET_VEC) rp_ += st_;                                                         \
             }                                                                                    \
         }                                                                                        \
-        const int i_ = RAG ? min(run * RUN + u_own, last_) : run * RUN + u_own;                  \
-        betreg = lane_elem(bc + off_, i_ * a.H);                                                 \
-        if (HAS_RET && !RET_VEC) retreg = lane_elem(rc + off_, i_ * a.H);                        \
     }
     if (RAG && TILES && rows.count(a.n1 - 1) < C) {      // the last chunk as a whole tile, for the backward pass
         const int there = rows.count(a.n1 - 1);
@@ -211,8 +214,19 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
             }
         }
         const bool valid = run * RUN + u_own < nvalid;
-        const float bet = betreg, ret = valid ? retreg : 1.f;
-        // ---- the scalars of token (run, u_own): n_raw = sum s, first guess p = <d_0, s> ----
+        const float bet = betreg, ret = !RAG || lane < nvalid ? retreg : 1.f;
+        float left = 1.f;                       // what the retention of the tokens before (run, u_own) leaves of d_0
+        if (RET == 1) {
+            float x = ret;
+#define OSDN_P1_SCAN(ctrl_, rows_) x *= __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0x3f800000, __builtin_bit_cast(int, x), ctrl_, rows_, 0xF, false));
+            OSDN_P1_SCAN(0x111, 0xF) OSDN_P1_SCAN(0x112, 0xF) OSDN_P1_SCAN(0x114, 0xF) OSDN_P1_SCAN(0x118, 0xF)      // row_shr:1, 2, 4, 8
+            OSDN_P1_SCAN(0x142, 0xA) OSDN_P1_SCAN(0x143, 0xC)                                                        // row_bcast:15, 31
+#undef OSDN_P1_SCAN
+            const int t = run * RUN + u_own;
+            x = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((t - 1) * 4, __builtin_bit_cast(int, x)));
+            left = t > 0 ? x : 1.f;
+        }
+        // ---- the scalars of token (run, u_own): n_raw = sum s, first guess p = <d_0, s> times what retention leaves ----
         float nraw, cb, ca, p_cur, c_cur;
         {
             if (TILES) {                        // every wavefront an equal part
@@ -225,12 +239,12 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
             float vn[RUN], vp[RUN];
 #pragma unroll
             for (int u = 0; u < RUN; ++u) {
-                vn[u] = 0.f; vp[u] = 0.f;
+                vn[u] = sv[u][0]; vp[u] = sv[u][0] * dst[0];
 #pragma unroll
-                for (int e = 0; e < CPT; ++e) { vn[u] = __builtin_fmaf(kf[u][e], kf[u][e], vn[u]); vp[u] = __builtin_fmaf(sv[u][e], dst[e], vp[u]); }
+                for (int e = 1; e < CPT; ++e) { vn[u] = __builtin_fmaf(kf[u][e], kf[u][e], vn[u]); vp[u] = __builtin_fmaf(sv[u][e], dst[e], vp[u]); }
             }
             nraw = fold_tokens(vn);
-            p_cur = fold_tokens(vp);
+            p_cur = fold_tokens(vp) * left;
             const float nn = fmaxf(nraw, a.eps);
             const float bp = a.beta_aware ? bet : 1.f;
             cb = valid ? a.eta * bp / nn : 0.f;
@@ -246,7 +260,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
 #pragma unroll
                 for (int e = 0; e < RE; ++e) rv[u][e] = run * RUN + u < nvalid ? r2[e] : 1.f;
             } else {
-                rv[u][0] = HAS_RET ? lane_bcast(ret, fold_lane(u)) : 1.f;
+                rv[u][0] = HAS_RET ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ret), run * RUN + u)) : 1.f;
             }
         }
         OSDN_P1_LOAD(min(n + 1, a.n1 - 1))       // (past the end: reloaded in vain)
@@ -331,8 +345,6 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
             }
             ++sweeps_used;
             float vp[RUN];
-#pragma unroll
-            for (int u = 0; u < RUN; ++u) vp[u] = 0.f;
             bool within = true;
             if (FAST && !boxed) {
                 // d at the start of this run: the runs to its left applied to d at the chunk start
@@ -349,7 +361,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
 #pragma unroll
                     for (int u = 0; u < RUN; ++u) {
                         dtr[u][e] = d[e];
-                        vp[u] = __builtin_fmaf(sv[u][e], d[e], vp[u]);
+                        vp[u] = e == 0 ? sv[u][e] * d[e] : __builtin_fmaf(sv[u][e], d[e], vp[u]);
                         d[e] = __builtin_fmaf(cv[u], sv[u][e], d[e]);
                     }
                     within = within && d[e] <= hi;
@@ -379,7 +391,7 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
 #pragma unroll
                     for (int u = 0; u < RUN; ++u) {
                         dtr[u][e] = d[e];
-                        vp[u] = __builtin_fmaf(sv[u][e], d[e], vp[u]);
+                        vp[u] = e == 0 ? sv[u][e] * d[e] : __builtin_fmaf(sv[u][e], d[e], vp[u]);
                         d[e] = clip3(d_bar<HAS_RET>(rv[u][RET_VEC ? e : 0], d[e], cv[u], sv[u][e]), lo, hi);
                     }
                     dend[e] = d[e];
