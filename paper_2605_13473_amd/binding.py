@@ -13,6 +13,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 
 import torch
@@ -123,6 +124,10 @@ def _io_torch_dtype(params: OsdnParams):
 def _ptr(t, dtype, shape=None, name="tensor"):
     if t is None:
         return None
+    # what every good call takes, as one expression; the checks one by one below say what is wrong with a bad one
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous() and (
+            shape is None or t.shape == shape):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name}: expected a CUDA/HIP torch tensor")
     if t.dtype != dtype:
@@ -131,13 +136,13 @@ def _ptr(t, dtype, shape=None, name="tensor"):
         raise ValueError(f"{name}: must be contiguous")
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream_ptr(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is None:      # the handle of torch.cuda.current_stream(), without the Stream object
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _check(rc):
@@ -157,16 +162,18 @@ def osdn_precond_update(params, k, beta, retention, d_in, k_tilde, d_out, d_ckpt
 
 
 def osdn_step(params, q, k, v, beta, log_alpha, retention, d_in, S_in, o, S_out, d_out, stream=None):
+    # A decode step of few sequences takes the device 4 us: the time of a call is that of this function and of `step`.
+    # 16 heads of 128 x 128, one token, through `step`: 16.5 -> 11.7 us a call.
     p = params
+    B, T, H, K, V = p.B, p.T, p.H, p.K, p.V
     io, f32 = _io_torch_dtype(p), torch.float32
-    bth, bthk, bthv = (p.B, p.T, p.H), (p.B, p.T, p.H, p.K), (p.B, p.T, p.H, p.V)
+    bth, bthk, bthv, bhk, bhvk = (B, T, H), (B, T, H, K), (B, T, H, V), (B, H, K), (B, H, V, K)
     _check(lib().osdn_step(
         ctypes.byref(p), _ptr(q, io, bthk, "q"), _ptr(k, io, bthk, "k"), _ptr(v, io, bthv, "v"),
-        _ptr(beta, f32, bth, "beta"), _ptr(log_alpha, f32, _gate_shape(p), "log_alpha"),
-        _ptr(retention, f32, _ret_shape(p), "retention"), _ptr(d_in, f32, (p.B, p.H, p.K), "d_in"),
-        _ptr(S_in, f32, (p.B, p.H, p.V, p.K), "S_in"), _ptr(o, io, bthv, "o"),
-        _ptr(S_out, f32, (p.B, p.H, p.V, p.K), "S_out"), _ptr(d_out, f32, (p.B, p.H, p.K), "d_out"),
-        _stream_ptr(stream)))
+        _ptr(beta, f32, bth, "beta"), _ptr(log_alpha, f32, bthk if p.gate_per_channel else bth, "log_alpha"),
+        _ptr(retention, f32, bthk if p.retention_per_channel else bth, "retention"), _ptr(d_in, f32, bhk, "d_in"),
+        _ptr(S_in, f32, bhvk, "S_in"), _ptr(o, io, bthv, "o"), _ptr(S_out, f32, bhvk, "S_out"),
+        _ptr(d_out, f32, bhk, "d_out"), _stream_ptr(stream)))
 
 
 def osdn_fwd(params, q, k, v, beta, log_alpha, retention, d_in, S_in, o, S_out, d_out, workspace,
@@ -288,6 +295,22 @@ def make_params(B, T, H, K, V, bf16: bool, hp: Hyper = Hyper(), retention_per_ch
                       int(hp.p1_solved))
 
 
+_PARAMS = struct.Struct("=7i5f7i")
+assert _PARAMS.size == ctypes.sizeof(OsdnParams)
+
+
+def _shape_params(B, T, H, K, V, bf16, hp, retention_per_channel, gate_per_channel) -> OsdnParams:
+    """make_params for sizes that come from a tensor's shape: the same fields, packed at once (1.5 -> 0.9 us)."""
+    try:
+        return OsdnParams.from_buffer_copy(_PARAMS.pack(
+            B, T, H, K, V, 64, OSDN_BF16 if bf16 else OSDN_F32,
+            float(K) ** -0.5 if hp.scale is None else float(hp.scale), hp.eta, hp.d_min, hp.d_max, hp.eps,
+            int(hp.beta_aware), retention_per_channel, gate_per_channel, int(hp.segments), int(hp.p1_pieces),
+            int(hp.p1_piece_sweeps), int(hp.p1_solved)))
+    except (struct.error, OverflowError):       # (a value outside its field: what ctypes makes of it)
+        return make_params(B, T, H, K, V, bf16, hp, retention_per_channel, gate_per_channel)
+
+
 def _ret_shape(p: OsdnParams):
     return (p.B, p.T, p.H, p.K) if p.retention_per_channel else (p.B, p.T, p.H)
 
@@ -313,7 +336,7 @@ def forward(q, k, v, beta, log_alpha=None, retention=None, d_in=None, S_in=None,
     given: B == 1, one carried entry per sequence).  Returns (o, S_out, d_out, ctx)."""
     B, T, H, K = k.shape
     V = v.shape[-1]
-    p = make_params(B, T, H, K, V, k.dtype == torch.bfloat16, hp, _per_channel(retention), _per_channel(log_alpha))
+    p = _shape_params(B, T, H, K, V, k.dtype == torch.bfloat16, hp, _per_channel(retention), _per_channel(log_alpha))
     if cu_seqlens is not None:
         cu_seqlens = [int(x) for x in cu_seqlens]
     if workspace is None:
@@ -368,7 +391,7 @@ def step(q, k, v, beta, log_alpha=None, retention=None, d_in=None, S_in=None, hp
     is updated where it is (and returned)."""
     B, T, H, K = k.shape
     V = v.shape[-1]
-    p = make_params(B, T, H, K, V, k.dtype == torch.bfloat16, hp, _per_channel(retention), _per_channel(log_alpha))
+    p = _shape_params(B, T, H, K, V, k.dtype == torch.bfloat16, hp, _per_channel(retention), _per_channel(log_alpha))
     f32 = dict(dtype=torch.float32, device=k.device)
     o = torch.empty_like(v)
     S_out = S_in if (in_place and S_in is not None) else torch.empty(B, H, V, K, **f32)
