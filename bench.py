@@ -296,7 +296,7 @@ def main():
     # a kernel may be launched once per segment of the sequence: durations and work are
     # summed over the launches of one step (= launch-weighted average rate)
     per_kernel = {k: ms / args.steps for k, (ms, n) in prof.items() if n > 0}
-    copies_ms = per_kernel.pop("pad", None)         # moving ragged / packed sequences onto chunk boundaries
+    tables_ms = per_kernel.pop("pad", None)         # index tables of packed sequences
     unfold_ms = per_kernel.pop("unfold", None)      # per-channel gates: gradients of the folded operands mapped back
     launches = {k: n // args.steps for k, (ms, n) in prof.items() if n > 0}
     dominant = max(per_kernel, key=per_kernel.get)
@@ -318,8 +318,8 @@ def main():
                              "note": "the kernel's own inputs and outputs once each, intermediates included"},
             "mfma_frac_of_kernel": flops.get(dominant, 0.0) / dur / PEAK_BF16_FLOPS if cfg.bf16 else None,
             "per_kernel_ms": {k: round(v, 4) for k, v in per_kernel.items()}}
-    if copies_ms is not None:
-        roof["per_kernel_ms"]["pad (copies)"] = round(copies_ms, 4)
+    if tables_ms is not None:
+        roof["per_kernel_ms"]["pad (tables)"] = round(tables_ms, 4)
     if unfold_ms is not None:
         roof["per_kernel_ms"]["unfold"] = round(unfold_ms, 4)
 
