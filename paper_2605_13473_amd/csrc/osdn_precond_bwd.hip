@@ -616,12 +616,18 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         float at[CPT];
         carry(std::false_type{}, mP, mapL[0], ga, at);
         float sig0 = replay(at, lam);
-        {   // the largest of the wavefront (a lane holds one of eight tokens, by its upper three bits), in lane 63
-            uint32_t m = __builtin_bit_cast(uint32_t, fabsf(sig0));
+        // in lane 63, the largest |x| of the wavefront (a lane holds one of eight tokens, by its upper three bits; what is not a
+        // number is left out: it has no say in whether the others have settled)
+        auto largest = [](float x) {
+            uint32_t m = __builtin_bit_cast(uint32_t, fmaxf(fabsf(x), 0.f));
             m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x128, 0xF, 0xF, true));       // row_ror:8
             m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x142, 0xA, 0xF, false));      // row_bcast:15
             m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x143, 0xC, 0xF, false));      // row_bcast:31
-            if (lane == 63) wmax[0][NRUN + run] = __builtin_bit_cast(float, m);
+            return __builtin_bit_cast(float, m);
+        };
+        {
+            const float m = largest(sig0);
+            if (lane == 63) wmax[0][NRUN + run] = m;
         }
         sources(sig0);
         compose(src, mapL[1]);
@@ -637,8 +643,8 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
             float dprev = first;
             int sweeps = 2, buf = 2, row = 1;
             for (;;) {
-                const float d = wave_max(fabsf(sig - sig0)), x = wave_max(fabsf(sig));
-                if (lane == 0) { wmax[row][run] = d; wmax[row][NRUN + run] = x; }
+                const float d = largest(sig - sig0), x = largest(sig);
+                if (lane == 63) { wmax[row][run] = d; wmax[row][NRUN + run] = x; }
                 sources(sig);
                 compose(src, mapL[buf]);
                 __syncthreads();

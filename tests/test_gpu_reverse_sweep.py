@@ -68,6 +68,26 @@ def test_values_that_are_not_finite_reach_what_they_reached_without_pieces():
         assert torch.equal(torch.isfinite(a), torch.isfinite(got[1][n])), n
 
 
+def test_a_sigma_that_is_not_a_number_has_no_say_in_the_verdict():
+    """Retention inf at one token: the box takes d to its upper face there, as any large retention would, and what lies left of it
+    gets gradients that are not numbers.  The seven tokens right of it have the ones they have with 1e6, to ten times the sweeps'
+    tolerance (the large eta makes two sweeps far too few for them: 1e-4 off; the chunk behind settles in two)."""
+    x = to_dev(make_stress_inputs(1, 128, 1, 64, 64, seed=199, bf16=False, retention=0.97), False)
+    x["beta"][0, 64:] = 1e-4
+    got = []
+    for big in (1e6, float("inf")):
+        x["retention"][0, 56, 0] = big
+        o, S, d, ctx = ob.forward(*[x[n] for n in ("q", "k", "v", "beta", "log_alpha", "retention", "d_in", "S_in")],
+                                  ob.Hyper(eta=64.0, p1_solved=-1, segments=1), for_backward=True)
+        got.append((o, ob.backward(ctx, x["dO"])))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0])
+    assert not torch.isfinite(got[1][1]["dbeta"][0, :56]).all()
+    for n in ("dk", "dbeta"):
+        a, b = (g[n][0, 57:64] for _, g in got)
+        assert (a - b).abs().max() <= 1e-6 * a.abs().max(), n
+
+
 def test_segments_in_a_captured_graph():
     """Short sequences take one stream by themselves; the side stream's part of a capture, forced here, and
     replays between eager calls."""
