@@ -697,14 +697,19 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     pb.n_seqs = pk.n_seqs; pb.seq_chunks = seq_chunks; pb.dd_last = dd_out;
     pb.rows = rows; pb.dk = dk; pb.dbeta = dbeta; pb.dretention = retention ? dretention : nullptr; pb.dd_in = dd_in;
     // Without retention, chunks that never met the box can take the solved form of the reverse
-    // sweep: a dependent chain about half as long for 0.6 KB more memory traffic per
-    // token-head.  It pays while the phase-1 chain is what the pass waits for: chains on at most an eighth
-    // of the CUs (K = V = 128 in bf16, us, sweeps and solved: 16 chains of 32 chunks 168 and 145, of 128 543 and 491; 32 of 64
-    // 393 and 380; 64 of 32 317 and 327, of 64 603 and 632).
+    // sweep: a dependent chain shorter than the sweeps' for 0.6 KB more memory traffic per
+    // token-head.  It pays while the phase-1 chain is what the pass waits for (us of the backward pass, sweeps and solved, V = K
+    // unless said; beta = sigmoid(N(0, 1)), then about 0.95, where a chunk takes three sweeps; the solved form knows neither):
+    //  - chains on at most an eighth of the CUs (K = 128, bf16: 32 of 64 chunks 420 and 377, 560 and 379; K = 64: 352 and 248);
+    //  - with bf16 I/O on a quarter (K = 64: 40 of 64 405 and 290, 64 of 64 447 and 351, of 128 801 and 702; K = 128: 40 of 64
+    //    471 and 442, 599 and 442; V = 64: 64 of 64 644 and 507), but for K = 128 with V >= 128 beyond 48 chains, where the
+    //    traffic of phase 2 fills the chip (48 of 64 499 and 501; 64 of 32 318 and 327, 378 and 327; 64 of 64 608 and 637, 732 and
+    //    637; 64 of 128 1097 and 1199, 1317 and 1198).
     const long long chains_all = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
+    const bool solved_quarter = bf && !(p->K == 128 && p->V >= 128 && chains_all > 48);
     const bool general = retention && !p->retention_per_channel;      // the form with a retention gate and any masks
     const bool solved = general ? p->p1_solved > 0
-                                : !retention && (p->p1_solved > 0 || (p->p1_solved == 0 && chains_all * 8 <= NUM_CU));
+                                : !retention && (p->p1_solved > 0 || (p->p1_solved == 0 && chains_all * (solved_quarter ? 4 : 8) <= NUM_CU));
     if (solved) {
         pb.lin_clean = reinterpret_cast<int *>(ws + L.lin_clean);
         pb.lin_M = ws + L.lin_M;
