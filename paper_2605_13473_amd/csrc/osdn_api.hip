@@ -700,11 +700,11 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     // sweep: a dependent chain shorter than the sweeps' for 0.6 KB more memory traffic per
     // token-head.  It pays while the phase-1 chain is what the pass waits for (us of the backward pass, sweeps and solved, V = K
     // unless said; beta = sigmoid(N(0, 1)), then about 0.95, where a chunk takes three sweeps; the solved form knows neither):
-    //  - chains on at most an eighth of the CUs (K = 128, bf16: 32 of 64 chunks 420 and 377, 560 and 379; K = 64: 352 and 248);
-    //  - with bf16 I/O on a quarter (K = 64: 40 of 64 405 and 290, 64 of 64 447 and 351, of 128 801 and 702; K = 128: 40 of 64
-    //    471 and 442, 599 and 442; V = 64: 64 of 64 644 and 507), but for K = 128 with V >= 128 beyond 48 chains, where the
-    //    traffic of phase 2 fills the chip (48 of 64 499 and 501; 64 of 32 318 and 327, 378 and 327; 64 of 64 608 and 637, 732 and
-    //    637; 64 of 128 1097 and 1199, 1317 and 1198).
+    //  - chains on at most an eighth of the CUs (K = 128, bf16: 32 of 64 chunks 430 and 380, 485 and 380; K = 64: 302 and 250);
+    //  - with bf16 I/O on a quarter (K = 64: 40 of 64 339 and 288, 64 of 32 201 and 191, of 64 395 and 352, of 128 639 and 701; K = 128:
+    //    40 of 64 476 and 443, 527 and 443; V = 64: 64 of 64 514 and 510, 569 and 508, of 128 916 and 1014), but for K = 128 with
+    //    V >= 128 beyond 48 chains, where the traffic of phase 2 fills the chip (48 of 64 507 and 500, 559 and 501; 64 of 32 319 and
+    //    328, 350 and 327; 64 of 64 611 and 636, 668 and 637; 64 of 128 1102 and 1200, 1163 and 1200).
     const long long chains_all = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
     const bool solved_quarter = bf && !(p->K == 128 && p->V >= 128 && chains_all > 48);
     const bool general = retention && !p->retention_per_channel;      // the form with a retention gate and any masks

@@ -253,13 +253,17 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
 // if it moved by so little that the next would move by less than the tolerance (differences shrink by the
 // ratio just seen); the adjoint at the chunk's left end is the one that gave it.  Two barriers a chunk: the
 // verdict on sigma is published together with the first maps of the next chunk (which need no adjoint); a
-// chunk that is then found not to have settled is done again, with a barrier for every verdict, and so are
-// the chunks after it until one settles in two.
+// chunk that is then found not to have settled is done again with three sweeps before the verdict, and so are
+// the chunks after it, until eight in a row would have settled in two.  One that does not settle in three either is
+// done again with a barrier for every verdict, and so are those after it until eight in a row take no more than three.
+// (One chunk that needs three sweeps among others that need two costs more than all of them with three: back after one chunk,
+// beta about 0.95 without retention took 4.22 us a chunk, with every verdict waited for 3.75, as it is 3.24.)  With retention a
+// chunk whose coordinates the box holds at every token has sigma = 0: no sweep (gates of 0.97: 2.5 -> 1.7).
 //
 // Bound by the issue of one CU's vector instructions (two wavefronts per SIMD) and the latency of its two
-// barriers.  Chains of 128 chunks of 128 coordinates, us per chunk: no retention 3.55 -> 2.40, one gate per head
-// 3.07 -> 2.60, per coordinate 3.38 -> 3.03, against three barriers a sweep, one coordinate and 16 tokens per thread,
-// and results stored behind the next chunk's loads.
+// barriers.  Chains of 64 chunks of 128 coordinates, bf16, us per chunk: no retention 3.43 -> 2.43, one gate per head
+// 2.97 -> 2.45, per coordinate 3.26 -> 2.99 against three barriers a sweep, one coordinate and 16 tokens per thread,
+// and results stored behind the next chunk's loads; with three sweeps 4.19 -> 3.24, 3.70 -> 3.29, 3.89 -> 3.75.
 //
 // PIECES: for few long chains the chain is cut into pieces, one workgroup each, as in the forward kernel: every
 // piece is swept from a guess of the adjoint at its right end, and the sweeps over all pieces repeat until
@@ -281,7 +285,9 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     __shared__ __attribute__((aligned(16))) float mapP[2][NRUN * K];     // chunks in turn
     __shared__ __attribute__((aligned(16))) float mapL[3][NRUN * K];     // 0: of sigma = 0; 1, 2: of later sweeps, in turn
     __shared__ __attribute__((aligned(16))) float wmax[2][2 * NRUN];           // per wavefront: largest change of sigma, largest sigma
-    __shared__ int flags[NRUN];
+    // per wavefront: 1: the chunk before has not settled, 2: nor would it have in two sweeps; 4: some coordinate of this chunk is
+    // not held by the box throughout
+    __shared__ __attribute__((aligned(16))) int flags[NRUN];
 
     const int tid = threadIdx.x, run = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c0 = lane * CPT;                   // first coordinate of this thread
@@ -443,8 +449,10 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         for (int i = 0; i < 4; ++i) m = max(m, max(x[i], y[i]));
         return __builtin_bit_cast(float, m);
     };
-    // sqrt(P1_TOL_BWD): a second sweep that moved sigma by this share of what the first one did (from zero) settles it
-    constexpr float SECOND_OK = 3.16e-4f;
+    // P1_TOL_BWD to the 1/2 and 2/3: a second (third) sweep that moved sigma by this share of what the first one did (from
+    // zero) settles it, with differences that shrink by one ratio
+    constexpr float SECOND_OK = 3.16e-4f, THIRD_OK = 2.15e-5f;
+    constexpr int CALM = 8;                      // chunks in a row that needed less before less is tried again
 
     OSDN_P1_BLOAD(a.n1 - 1)
     // what the next pass stores: chunk, adjoint at its right end, sigma (at first nothing to keep: stored again by the second pass)
@@ -452,7 +460,10 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     float gdone[CPT], sdone = 0.f, PPdone[PIECES ? CPT : 1] = {};
 #pragma unroll
     for (int e = 0; e < CPT; ++e) gdone[e] = ga[e];
-    bool pending = false, careful = false, refetch = false;   // the chunk before awaits its verdict; a barrier for every verdict
+    // Sweeps of a chunk whose verdict waits for the next chunk's maps: two (three: deep).  Careful: as many as it takes, with a
+    // barrier for every verdict.  pending: the chunk before awaits its verdict; again: it is done once more
+    bool deep = false, careful = false, pending = false, refetch = false, again = false;
+    int calm = 0, verdict = 0;
     for (int n = a.n1 - 1;; --n) {
         // ---- this thread's s = k^2, lambda = k . dL/dk~, masks and retention (past the end: of the last chunk, in vain) ----
         float sv[RUN][CPT], lam[RUN][CPT], rv[RUN][RET_VEC ? CPT : 1];
@@ -544,23 +555,39 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         }
         float *const mP = mapP[n & 1];
         put_map(mP, P);
+        {
+            uint32_t some = mb[0];
+#pragma unroll
+            for (int e = 1; e < CPT; ++e) some |= mb[e];
+            if (!HAS_RET || __any(some != 0u)) verdict |= 4;
+            if (lane == 0) flags[run] = verdict;
+        }
         compose(lam, mapL[0]);
         __syncthreads();
+        int all;
+        {
+            typedef __attribute__((__vector_size__(16))) int I;
+            const I x = *reinterpret_cast<const I *>(flags) | *reinterpret_cast<const I *>(flags + 4);
+            all = __builtin_amdgcn_readfirstlane(x[0] | x[1] | x[2] | x[3]);
+        }
+        verdict = 0;
         if (pending) {
             pending = false;
-            int bad = 0;
-#pragma unroll
-            for (int w = 0; w < NRUN; ++w) bad |= flags[w];
-            if (bad) {                           // (uniform) the chunk before, once more from the same adjoint
-                careful = refetch = true;
+            calm = all & 2 ? 0 : calm + 1;
+            if (all & 1) {                       // (uniform) the chunk before, once more from the same adjoint
+                careful = deep;
+                deep = refetch = again = true;
+                calm = 0;
                 n += 3;                          // (the next pass only fetches chunk n + 1)
 #pragma unroll
                 for (int e = 0; e < CPT; ++e) {
                     ga[e] = gdone[e];
                     if (PIECES) PP[e] = PPdone[PIECES ? e : 0];
                 }
+                __syncthreads();                 // (the flags have been read)
                 continue;
             }
+            if (calm >= CALM) deep = false;
         }
         if (refetch) {
             refetch = false;
@@ -572,13 +599,22 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
             gdone[e] = ga[e];
             if (PIECES) PPdone[PIECES ? e : 0] = PP[e];
         }
-        if (COUPLED) {                           // (a chunk that is done again counts twice: the map is an approximation)
+        if (COUPLED && !again) {
 #pragma unroll
             for (int u = 0; u < RUN; ++u) {
                 const float c = lane_bcast(cn, fold_lane(u));
 #pragma unroll
                 for (int e = 0; e < CPT; ++e) gacc[COUPLED ? e : 0] = __builtin_fmaf(c, sv[u][e], gacc[COUPLED ? e : 0]);
             }
+        }
+        again = false;
+        if (HAS_RET && !(all & 4)) {                 // the box holds every coordinate at every token: sigma is zero
+            float at[CPT];
+            carry(std::true_type{}, mP, mapL[0], ga, at);
+            sdone = 0.f;
+            done = n;
+            __syncthreads();                     // (maps and flags have been read)
+            continue;
         }
         // the tokens of the run replayed from the adjoint x at its right end: their sigma
         auto replay = [&](const float (&at)[CPT], const float (&src)[RUN][CPT]) {
@@ -636,8 +672,21 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         carry(std::true_type{}, mP, mapL[1], ga, at);
         float sig = replay(at, src);
         if (!careful) {
-            const bool settled = __all(!(fabsf(sig - sig0) > SECOND_OK * first));
-            if (lane == 0) flags[run] = settled ? 0 : 1;
+            verdict = __any(fabsf(sig - sig0) > SECOND_OK * first) ? 3 : 0;
+            if (deep) {
+                sources(sig);
+                compose(src, mapL[2]);
+                __syncthreads();
+                sig0 = sig;
+#pragma unroll
+                for (int e = 0; e < CPT; ++e) {
+                    ga[e] = gdone[e];
+                    if (PIECES) PP[e] = PPdone[PIECES ? e : 0];
+                }
+                carry(std::true_type{}, mP, mapL[2], ga, at);
+                sig = replay(at, src);
+                verdict = (verdict & 2) | (__any(fabsf(sig - sig0) > THIRD_OK * first) ? 1 : 0);
+            }
             pending = true;
         } else {
             float dprev = first;
@@ -664,7 +713,11 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
                 row ^= 1;
                 ++sweeps;
             }
-            careful = sweeps > 2;
+            calm = sweeps > 3 ? 0 : calm + 1;
+            if (calm >= CALM) {
+                careful = false;
+                calm = 0;
+            }
         }
         sdone = sig;
         done = n;

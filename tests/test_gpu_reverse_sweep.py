@@ -30,6 +30,43 @@ def test_chunks_that_settle_and_chunks_that_do_not(K, retention, eta):
         compare_backward(x, ob.Hyper(eta=eta, p1_solved=-1, segments=segments), False, dd_out=dd)
 
 
+# chunk by chunk (0: nothing couples, one sweep; 1: two; 2: three; 3: more): runs of either kind, single ones among others
+COURSES = {"three_and_back": [1] * 3 + [2] + [1] * 10 + [2] * 3 + [1] * 2, "waited_for_and_back": [2, 3] + [1] * 19 + [3] + [2] * 9,
+           "alternating": [1, 2, 0, 3] * 4}
+
+
+@pytest.mark.parametrize("retention", ["none", "head", "channel"])
+@pytest.mark.parametrize("course", COURSES)
+def test_chunks_of_every_course_in_turn(course, retention):
+    rng = np.random.Generator(np.random.Philox(11))
+    kinds = COURSES[course]
+    T = 64 * len(kinds)
+    x = make_stress_inputs(1, T, 2, 64, 64, seed=173, bf16=False, retention=0.97)
+    x["retention"] = {"none": None, "head": np.ones((1, T, 2), np.float32) * np.float32(0.9999),
+                      "channel": rng.uniform(0.9998, 1.0, (1, T, 2, 64)).astype(np.float32)}[retention]
+    # (the coupling goes with beta^2: eta = 1 alone would need more than three sweeps)
+    x["beta"] = np.repeat(np.array([0.0, 0.01, 0.05, 0.9], np.float32)[kinds], 64)[None, :, None].repeat(2, axis=2)
+    compare_backward(x, ob.Hyper(eta=1.0, p1_solved=-1, segments=1), False)
+
+
+@pytest.mark.parametrize("K", [64, 128])
+@pytest.mark.parametrize("retention", ["head", "channel"])
+def test_chunks_that_the_box_holds_throughout(retention, K):
+    """Retention 0.5: every coordinate lies on the lower face at every token, but in chunks whose gates are 1."""
+    T = 64 * 9
+    x = make_stress_inputs(1, T, 2, K, 64, seed=175, bf16=False, retention=0.97)
+    r = np.full((1, T, 2) + ((K,) if retention == "channel" else ()), 0.5, np.float32)
+    r[:, 128:192] = 1.0
+    r[:, 384:448] = 1.0
+    if retention == "channel":
+        r[:, 256:320, :, K - 1] = 1.0            # (one coordinate is let go)
+    x["retention"] = r
+    x["d_in"] = np.full((1, 2, K), 0.5, np.float32)
+    dd = np.random.Generator(np.random.Philox(12)).standard_normal((1, 2, K)).astype(np.float32)
+    for segments in (1, 2):
+        compare_backward(x, ob.Hyper(eta=0.3, p1_solved=-1, segments=segments), False, dd_out=dd)
+
+
 def test_no_box_and_no_gradient():
     """No masks are written without a box; a zero adjoint (sigma = 0 throughout) settles at once."""
     x = make_stress_inputs(1, 192, 2, 128, 64, seed=181, bf16=True, retention=0.97)
