@@ -11,8 +11,10 @@
 // at least the first m tokens exactly, so 64 sweeps always suffice; because the coupling is
 // O(eta) two do in practice, also when coordinates sit on a face of the box.  With one retention per
 // token the first guess takes what the gates of the tokens before leave of d_0 (a prefix product over
-// the chunk, every wavefront its own: 25 instructions): without it a third sweep is needed where the gates
-// leave 0.9 of d over a chunk (2 x 384 tokens, 8 heads of 128 x 128, retention about 0.999: 52.8 -> 46.9 us).
+// the chunk, every wavefront its own): without it a third sweep is needed where d still fades, as it does over the first ten
+// chunks of a sequence with gates of 0.999 (2 x 384 tokens, 8 heads of 128 x 128: 52.8 -> 46.9 us).  Once d lies on the lower face
+// the gates change nothing, and a guess that fades is what needs one sweep more (16 heads of 64 chunks of 128 coordinates, bf16, us
+// a chunk, without a fading guess, with one throughout, and as it is: gates of 0.97 2.71, 3.84, 2.72, of 0.999 3.39, 3.86, 3.30).
 //
 // A sweep does not walk the 64 tokens one after the other.  The chunk is cut into 8 runs of
 // 8 tokens, one wavefront per run, a lane per coordinate (pair): everything a thread needs of
@@ -57,8 +59,10 @@ namespace osdn {
 // checkpoints and token scalars wanted.  Then no access of the loop sits under a branch (lanes without
 // an element of their own repeat another's), and the wait for the next chunk's keys, which the compiler
 // counts in accesses, does not become one for the stores behind them.
+// Registers: with one gate per token, K = 128 in bf16 the compiler is held to 128, which it would pass by four: two workgroups
+// to a CU, which the pieces are laid out for (16 chains of 256 chunks, forward pass: 873 us with 132 registers, 753 with 128).
 template <typename T, int K, int RET, bool PIECES, bool TILES, bool RAG>
-__global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
+__global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 2) void precond_fwd_kernel(PrecondArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     constexpr int RE = RET_VEC ? K / 64 : 1;      // retention values a thread keeps per token
     constexpr int CPT = K / 64;                   // coordinates per thread (adjacent)
@@ -215,16 +219,29 @@ __global__ __launch_bounds__(P1F) void precond_fwd_kernel(PrecondArgs a) {
         }
         const bool valid = run * RUN + u_own < nvalid;
         const float bet = betreg, ret = !RAG || lane < nvalid ? retreg : 1.f;
-        float left = 1.f;                       // what the retention of the tokens before (run, u_own) leaves of d_0
-        if (RET == 1) {
+        // what the retention of the tokens before (run, u_own) leaves of d_0, unless that is nearly all of it or the lower face holds
+        // it up (from this chunk's d and gates alone: where a call or a launch begins must not show)
+        float left = 1.f;
+        bool fades = RET == 1 && !__all(ret > 0.99995f);
+        if (fades) {
+            bool near = true;
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) near = near && dst[e] <= 1.02f * lo;
+            fades = !__all(near);
+        }
+        if (fades) {
             float x = ret;
 #define OSDN_P1_SCAN(ctrl_, rows_) x *= __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0x3f800000, __builtin_bit_cast(int, x), ctrl_, rows_, 0xF, false));
             OSDN_P1_SCAN(0x111, 0xF) OSDN_P1_SCAN(0x112, 0xF) OSDN_P1_SCAN(0x114, 0xF) OSDN_P1_SCAN(0x118, 0xF)      // row_shr:1, 2, 4, 8
             OSDN_P1_SCAN(0x142, 0xA) OSDN_P1_SCAN(0x143, 0xC)                                                        // row_bcast:15, 31
 #undef OSDN_P1_SCAN
             const int t = run * RUN + u_own;
+            const float all = lane_bcast(x, 63);
             x = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((t - 1) * 4, __builtin_bit_cast(int, x)));
-            left = t > 0 ? x : 1.f;
+            bool faced = true;                  // every coordinate comes to the lower face within this chunk
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) faced = faced && dst[e] * all <= lo;
+            left = t > 0 && !__all(faced) ? x : 1.f;
         }
         // ---- the scalars of token (run, u_own): n_raw = sum s, first guess p = <d_0, s> times what retention leaves ----
         float nraw, cb, ca, p_cur, c_cur;

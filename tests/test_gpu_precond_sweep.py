@@ -65,3 +65,51 @@ def test_carried_d_is_bit_for_bit_across_calls(case):
         k1, d = ob.precond_update(t["k"][:, cut:cut + 64].contiguous(), t["beta"][:, cut:cut + 64].contiguous(), None, d, hp)
         parts.append(k1)
     assert torch.equal(torch.cat(parts, 1), kt) and torch.equal(d, d_out)
+
+
+def _sweeps(x, hp):
+    """Sweeps that each chunk of a forward pass took, [chains, chunks] (fourth scalar that is kept per token)."""
+    t = to_dev(x, False)
+    B, T, H, K = x["k"].shape
+    p = ob.make_params(B, T, H, K, x["v"].shape[-1], False, hp)
+    ws = torch.empty(ob.osdn_workspace_bytes(p, True), dtype=torch.uint8, device="cuda")
+    ob.forward(*[t[n] for n in ("q", "k", "v", "beta", "log_alpha", "retention", "d_in", "S_in")], hp, workspace=ws, for_backward=True)
+    torch.cuda.synchronize()
+    at = B * T * H * K * 4 + B * H * T // 64 * K * 4         # behind k~ and the checkpoints of d
+    sc = ws[at:at + B * T * H * 16].view(torch.float32).view(B, T // 64, 64, H, 4)[..., 3]
+    assert torch.equal(sc, sc[:, :, :1].expand_as(sc)) and int(sc.min()) >= 1
+    return sc[:, :, 0].permute(0, 2, 1).reshape(B * H, T // 64).cpu().numpy()
+
+
+@pytest.mark.parametrize("K", [64, 128])
+def test_first_guess_where_d_fades_and_where_the_face_holds_it(K):
+    """d = 1 fades with gates of 0.999 (two sweeps: the guess knows the gates), reaches the lower face, and lies there (one)."""
+    T = 64 * 16
+    x = make_stress_inputs(1, T, 2, K, 64, seed=163, bf16=False, retention=0.97)
+    x["retention"] = np.full((1, T, 2), 0.999, np.float32)
+    x["d_in"] = np.ones((1, 2, K), np.float32)
+    hp = ob.Hyper(eta=1e-4, p1_pieces=-1, segments=1)
+    n = _sweeps(x, hp)
+    assert (n[:, :10] <= 2).all() and (n[:, 12:] == 1).all(), n
+    x["retention"][:] = 0.97                                 # on the face within a chunk
+    n = _sweeps(x, hp)
+    assert (n[:, 1:] == 1).all(), n
+    compare_forward(x, hp, False)
+
+
+def test_carried_d_is_bit_for_bit_across_calls_with_retention():
+    """Which first guess a chunk takes must follow from its own d and gates."""
+    rng = np.random.Generator(np.random.Philox(13))
+    x = make_stress_inputs(1, 64 * 18, 2, 128, 64, seed=167, bf16=True, retention=0.97)
+    x["retention"] = (1 - 0.003 * rng.random((1, 64 * 18, 2))).astype(np.float32)
+    x["retention"][:, 64 * 14:] = 1.0
+    t = to_dev(x, True)
+    hp = ob.Hyper(eta=0.003)
+    kt, d = ob.precond_update(t["k"], t["beta"], t["retention"], t["d_in"], hp)[:2]
+    parts, dd = [], t["d_in"]
+    for a, b in ((0, 1), (1, 2), (2, 9), (9, 15), (15, 18)):
+        sl = slice(64 * a, 64 * b)
+        k2, dd = ob.precond_update(t["k"][:, sl].contiguous(), t["beta"][:, sl].contiguous(), t["retention"][:, sl].contiguous(), dd, hp)[:2]
+        parts.append(k2)
+    torch.cuda.synchronize()
+    assert torch.equal(kt, torch.cat(parts, dim=1)) and torch.equal(d, dd)
