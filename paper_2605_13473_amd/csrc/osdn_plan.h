@@ -1,0 +1,152 @@
+// The rules by which osdn_fwd and osdn_bwd cut the work: segments of the sequence, pieces of a chain, the solved form of the
+// reverse sweep.  Plain host code without a device in it, so that the rules can be tested by themselves.
+#pragma once
+#include "../../include/osdn.h"
+
+#include <cmath>
+
+namespace osdn {
+
+constexpr int NUM_CU = 256;
+constexpr int MAX_SEGMENTS = 16, MAX_PIECES = 512, MAX_PIECE_SWEEPS = 13;
+
+// Number of segments for a sequence of N chunks (params->segments > 0 overrides it; 1 = no
+// pipelining).  A segment more shortens the stretch of phase 1 that runs with nothing beside it (the
+// first segment of the forward pass, the last of the backward pass) and costs launches, cross-stream
+// waits (25 us a call for the first) and partly filled rounds of workgroups.  Times below: one stream against the best
+// of two to six segments, us, K = V = 128 in bf16.
+//  - short sequences take one stream: forward up to 32 chunks (2 chains of 4 chunks 34 and 80, 64 of 16 107 and
+//    129, 64 of 32 221 and 231; 64 of 48 322 and 309), backward up to 48 (2 of 4 49 and 113, 64 of 16
+//    156 and 208, 8 of 32 128 and 158, 64 of 48 463 and 465, 128 of 48 790 and 802; 32 of 64 409 and 380).
+//  - so do many chains, which fill the chip by themselves: 256 of 64 forward 1141 and 1206, backward 1935 and 1997;
+//    from 128 chains on the forward pass takes two at most (128 of 128 1249, with six 1298).
+//  - forward otherwise: about 16 chunks per segment, at most six segments (measured flat beyond).
+//  - backward otherwise: a segment more costs more there, because every launch of the phase-2 chain kernel
+//    meets a phase-1 chain kernel on the other stream and the two do not fit on one CU together:
+//    when the workgroups of both (chain_wgs) outnumber the CUs, the count that balances the
+//    exposed tail against that cost is about sqrt(N / 15) (2 at 64 chunks, 4 at 256); when they
+//    all fit side by side, about 32 chunks per segment, at most four: of that count and the two
+//    above it, the one whose segments fill whole rounds of bwd_post workgroups (one per chunk and
+//    chain, post_round at a time) best; from 448 chunks on, where a segment is many rounds, seven,
+//    or twelve if phase 1 sweeps (p1_sweeps: it is slower then, and its last segment what is exposed).
+//    16 chains, bf16, backward pass alone: 128 chunks 494, 499, 493, 515, 546, 575 us with 3 to 8 segments
+//    (5 taken); 256 chunks, V = 256 993, 1014, 1057, 1063, 1097, 1023 with 4 to 9 (5); 512 chunks 1648, 1625, 1621,
+//    1619, 1643, 1816 with 4 to 8 and 12.
+// Segments cut the chunk axis as a whole.  With packed sequences the sequential kernels of a
+// segment only have the sequences that cross it to work on, one after the other segment by
+// segment, so cutting pays only while one sequence makes up most of the axis; otherwise the
+// many independent chains fill the chip by themselves and everything runs in one piece.
+inline int segment_count(int forced, int N, int longest, long long chains, long long chain_wgs, bool backward, int post_round = 0, bool p1_sweeps = false) {
+    if (forced <= 0 && (long long)longest * 4 < (long long)N * 3) return 1;
+    int S = forced;
+    if (forced <= 0) {
+        if (N <= (backward ? 48 : 32) || chains >= NUM_CU) return 1;
+        if (!backward) S = N / 16 > 6 ? 6 : N / 16;
+        else if (chain_wgs > NUM_CU) S = (int)std::lround(std::sqrt(N / 15.0)) > 6 ? 6 : (int)std::lround(std::sqrt(N / 15.0));
+        else {
+            S = N >= 448 ? (p1_sweeps ? 12 : 7) : N / 32 > 4 ? 4 : N / 32;
+            if (S < 2) S = 2;
+            double best = 0.0;
+            int pick = S;
+            for (int c = S; N < 448 && c <= S + 2 && c <= N; ++c) {
+                const int first = N / (2 * c) > 0 ? N / (2 * c) : 1;
+                const double wgs = (double)(N - first) / (c - 1) * (double)chains;   // bwd_post workgroups of a segment
+                const double fill = wgs / (std::ceil(wgs / post_round) * post_round);
+                if (fill > best + 1e-9) { best = fill; pick = c; }
+            }
+            S = pick;
+        }
+        if (S < 2 || (!backward && chains * 2 >= NUM_CU)) S = 2;
+    }
+    if (S > MAX_SEGMENTS) S = MAX_SEGMENTS;
+    if (S > N) S = N;
+    return S < 1 ? 1 : S;
+}
+// first chunk of segment s.  Segment 0 is half as long as the others: it is the one that runs
+// without a partner (phase 1 of it before anything of phase 2 can start in the forward pass,
+// and after everything else in the backward pass).
+// First chunk of segment s when every segment is r times as long as the one before.  Used by
+// the forward pass when phase 2 is the slower of the two phases (many chains): phase 2 then
+// starts early on a short segment and is never left waiting for phase 1, and the long last
+// segment runs when phase 1 is already out of the way.
+inline int seg_begin_grow(int N, int S, int s, double r) {
+    if (s <= 0) return 0;
+    if (s >= S) return N;
+    const double f = (std::pow(r, s) - 1.0) / (std::pow(r, S) - 1.0);
+    int b = (int)std::lround(N * f);
+    if (b < s) b = s;                       // at least one chunk per segment
+    if (b > N - (S - s)) b = N - (S - s);
+    return b;
+}
+inline int seg_begin(int N, int S, int s) {
+    if (s <= 0) return 0;
+    if (s >= S) return N;
+    const int first = N / (2 * S) > 0 ? N / (2 * S) : 1;
+    return first + (int)((long long)(N - first) * (s - 1) / (S - 1));
+}
+
+// Phase 1 as sweeps over the whole sequence, for few long chains: one workgroup per chain leaves most
+// of the chip idle and its walk over the chunks is most of the pass.  Every chain is cut into pieces
+// (a workgroup per CU over all chains; two where a piece still has eight chunks, which shortens the walk more
+// than two workgroups on a CU slow each other); a sweep runs all pieces side by
+// side, each from its current start value, and leaves every piece as a composed map per
+// coordinate; the next sweep walks those maps for its start values; a chain is settled when none
+// of its start values moves any more.  Plain batches only.  params->p1_pieces forces a number of
+// pieces per chain (-1: never), params->p1_piece_sweeps the sweep limit.
+//
+// Where the line lies (us per pass, sequential or in segments against pieces; K = V = 128 in bf16):
+//  - forward, chains on an eighth of the CUs or fewer, from 24 chunks on: 16 chains of 24 110 and 96, with a retention
+//    gate 131 and 105, of 32 137 and 107, 167 and 116, of 64 229 and 187 (pieces of 4 chunks; of 8: 229), 32 of
+//    32 166 and 138; 16 chains of 16 79 and 82.  With a retention gate, whose chunk takes half as long again and which needs
+//    two sweeps instead of three to five, on a quarter of the CUs too, from 32 chunks on: 64 chains of 32 247 and 232, of 64
+//    423 and 407, of 24 187 and 211.
+//  - backward, only with a retention gate (without, a piece needs more sweeps, and the solved form has the shorter
+//    chain): 16 chains of 24 chunks 143 and 126, of 32 175 and 138, of 128 579 and 432, of 512 1986 and 1600; 64 chains
+//    of 32 331 and 308, of 128 1126 and 1097, of 256 2136 and 2159; pieces of four chunks at least (16 chains
+//    of 32 chunks: pieces of two 146).
+inline void pieces_plan(const osdn_params *p, int N, long long chains, bool packed, bool retention, bool backward, int &pieces,
+                        int &piece_chunks, int &sweeps) {
+    pieces = 0; piece_chunks = 0;
+    // sweeps needed without retention, measured: 4 at 64 and 128 chunks, then one more per
+    // doubling (7 at 1024); the limit leaves two in hand
+    sweeps = 7;                                  // (the last one only finds that nothing moved)
+    for (int n = 128; n < N && sweeps < MAX_PIECE_SWEEPS; n *= 2) ++sweeps;
+    if (packed || chains > MAX_PIECES / 2) return;
+    const int forced = p->p1_pieces;              // 0: decide here; -1: never; n > 0: n pieces per chain
+    int target, min_chunks;
+    if (forced != 0) { target = forced > 0 ? forced : 0; min_chunks = 1; }
+    else {
+        const bool few = chains * 8 <= NUM_CU, some = retention && chains * 4 <= NUM_CU;
+        if (!(few ? N >= 24 : some && N >= (backward ? 24 : 32) && (!backward || N <= 128)) || (backward && !retention)) return;
+        target = (int)(NUM_CU / chains);
+        if (N >= 16 * target) target *= 2;
+        const int most = N <= 64 ? 16 : 32;          // (every workgroup walks the maps of all pieces of its chain)
+        if (target > most) target = most;
+        min_chunks = backward ? 4 : 2;
+    }
+    if ((long long)target * chains > MAX_PIECES) target = (int)(MAX_PIECES / chains);
+    if (target < 2) return;
+    int len = (N + target - 1) / target;
+    if (len < min_chunks) len = min_chunks;
+    const int P = (N + len - 1) / len;
+    if (P < 2) return;
+    pieces = P; piece_chunks = len;
+    if (p->p1_piece_sweeps >= 1) sweeps = p->p1_piece_sweeps;
+}
+
+// Without retention, chunks that never met the box can take the solved form of the reverse
+// sweep: a dependent chain shorter than the sweeps' for 0.6 KB more memory traffic per
+// token-head.  It pays while the phase-1 chain is what the pass waits for (us of the backward pass, sweeps and solved, V = K
+// unless said; beta = sigmoid(N(0, 1)), then about 0.95, where a chunk takes three sweeps; the solved form knows neither):
+//  - chains on at most an eighth of the CUs (K = 128, bf16: 32 of 64 chunks 430 and 380, 485 and 380; K = 64: 302 and 250);
+//  - with bf16 I/O on a quarter (K = 64: 40 of 64 339 and 288, 64 of 32 201 and 191, of 64 395 and 352, of 128 639 and 701; K = 128:
+//    40 of 64 476 and 443, 527 and 443; V = 64: 64 of 64 514 and 510, 569 and 508, of 128 916 and 1014), but for K = 128 with
+//    V >= 128 beyond 48 chains, where the traffic of phase 2 fills the chip (48 of 64 507 and 500, 559 and 501; 64 of 32 319 and
+//    328, 350 and 327; 64 of 64 611 and 636, 668 and 637; 64 of 128 1102 and 1200, 1163 and 1200).
+inline bool solved_plan(const osdn_params *p, long long chains, bool retention) {
+    const bool bf = p->io_dtype == OSDN_BF16, quarter = bf && !(p->K == 128 && p->V >= 128 && chains > 48);
+    if (retention) return !p->retention_per_channel && p->p1_solved > 0;       // (the form with a retention gate and any masks)
+    return p->p1_solved > 0 || (p->p1_solved == 0 && chains * (quarter ? 4 : 8) <= NUM_CU);
+}
+
+}  // namespace osdn

@@ -1,0 +1,59 @@
+"""The rules that cut the work (csrc/osdn_plan.h), compiled for the CPU and asked over sizes: every plan covers the sequence and stays
+inside the buffers that are laid out for it, and the calls that measurements put on one course take it."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_13473_amd", "csrc")
+MAIN = r"""
+#include "osdn_plan.h"
+#include <cstdio>
+using namespace osdn;
+// in: chains chunks K V bf16 retention(0, 1, 2) eta forced_pieces backward; out: pieces, chunks of one, sweeps, solved, segments, begins
+int main() {
+    long long ch; int N, K, V, bf, ret, forced, back; float eta;
+    while (std::scanf("%lld %d %d %d %d %d %f %d %d", &ch, &N, &K, &V, &bf, &ret, &eta, &forced, &back) == 9) {
+        osdn_params p{};
+        p.K = K; p.V = V; p.io_dtype = bf ? OSDN_BF16 : OSDN_F32; p.eta = eta; p.retention_per_channel = ret == 2; p.p1_pieces = forced;
+        int pieces, len, sweeps;
+        const bool solved = back && solved_plan(&p, ch, ret != 0);
+        pieces_plan(&p, N, ch, false, ret != 0, back != 0, pieces, len, sweeps);
+        if (solved) pieces = 0;
+        const int S = pieces ? 1 : segment_count(0, N, N, ch, ch * (V / 32) + ch, back != 0, 512);
+        std::printf("%d %d %d %d %d", pieces, len, sweeps, (int)solved, S);
+        for (int s = 0; s <= S; ++s) std::printf(" %d", back || ch * (V / 32) + ch <= NUM_CU ? seg_begin(N, S, s) : seg_begin_grow(N, S, s, 1.7));
+        std::printf("\n");
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "main.cpp").write_text(MAIN)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, "-o", str(d / "plan"), str(d / "main.cpp")])
+
+    def ask(calls):
+        """calls: (chains, chunks, K, V, bf16, retention, eta, forced, backward) each."""
+        text = "\n".join(" ".join(str(x) for x in c) for c in calls) + "\n"
+        r = subprocess.run([str(d / "plan")], input=text, capture_output=True, text=True, check=True)
+        return [[int(x) for x in line.split()] for line in r.stdout.splitlines()]
+    return ask
+
+
+def test_every_plan_covers_the_sequence(plan):
+    calls = [(ch, N, K, V, bf, ret, eta, forced, back)
+             for ch in (1, 2, 3, 5, 8, 16, 17, 32, 33, 64, 100, 255, 256, 300, 1000)
+             for N in (1, 2, 23, 24, 25, 31, 47, 63, 64, 65, 127, 200, 448, 513, 1024, 4001)
+             for K, V in ((64, 64), (128, 512)) for bf in (0, 1) for ret in (0, 1, 2) for eta in (0.003, 1.0)
+             for forced in (-1, 0, 1, 7, 600) for back in (0, 1)]
+    for c, (P, length, sweeps, solved, S, *cuts) in zip(calls, plan(calls)):
+        ch, N = c[:2]
+        assert 1 <= sweeps <= 13
+        if P:
+            assert P >= 2 and (P - 1) * length < N <= P * length and P * ch <= 512 and ch <= 256, c
+        assert 1 <= S <= min(N, 16) and cuts[0] == 0 and cuts[-1] == N and all(a < b for a, b in zip(cuts, cuts[1:])), c
+        if c[7] == -1:
+            assert not P, c
