@@ -100,6 +100,9 @@ inline int seg_begin(int N, int S, int s) {
 //    32 166 and 138; 16 chains of 16 79 and 82.  With a retention gate, whose chunk takes half as long again and which needs
 //    two sweeps instead of three to five, on a quarter of the CUs too, from 32 chunks on: 64 chains of 32 247 and 232, of 64
 //    423 and 407, of 24 187 and 211.
+//  - how many pieces, forward without retention: 4 chains of 64 chunks 205 with 8 pieces, 159 with 16, 148 with 32; of 256 410 with
+//    32, 390 with 64, 469 with 128; of 512 883, 783, 852; 2 of 1024 1649, 1346, 1298 and with 256 1516; 1 of 1024 1192 with 64, 1141
+//    with 128, 1317 with 256.
 //  - backward, only with a retention gate (without, a piece needs more sweeps, and the solved form has the shorter
 //    chain): 16 chains of 24 chunks 143 and 126, of 32 175 and 138, of 128 579 and 432, of 512 1986 and 1600; 64 chains
 //    of 32 331 and 308, of 128 1126 and 1097, of 256 2136 and 2159; pieces of four chunks at least (16 chains
@@ -120,7 +123,8 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
         if (!(few ? N >= 24 : some && N >= (backward ? 24 : 32) && (!backward || N <= 128)) || (backward && !retention)) return;
         target = (int)(NUM_CU / chains);
         if (N >= 16 * target) target *= 2;
-        const int most = N <= 64 ? 16 : 32;          // (every workgroup walks the maps of all pieces of its chain)
+        // (every workgroup walks the maps of all pieces of its chain; but pieces of more than eight chunks cost more than that walk)
+        const int most = N <= 64 ? 16 : N <= 256 ? 32 : (N + 7) / 8;
         if (target > most) target = most;
         min_chunks = backward ? 4 : 2;
     }

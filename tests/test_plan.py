@@ -57,3 +57,10 @@ def test_every_plan_covers_the_sequence(plan):
         assert 1 <= S <= min(N, 16) and cuts[0] == 0 and cuts[-1] == N and all(a < b for a, b in zip(cuts, cuts[1:])), c
         if c[7] == -1:
             assert not P, c
+
+
+@pytest.mark.parametrize("ret", [0, 1])
+@pytest.mark.parametrize("chains,chunks,pieces", [(1, 1024, 128), (2, 1024, 128), (4, 512, 64), (2, 296, 37), (4, 300, 38), (4, 64, 16),
+                                                  (8, 128, 32), (4, 256, 32)])
+def test_long_sequences_of_few_chains_are_cut_into_pieces_of_eight(plan, chains, chunks, pieces, ret):
+    assert plan([(chains, chunks, 128, 128, 1, ret, 0.003, 0, 0)])[0][0] == pieces
