@@ -59,7 +59,9 @@ template <bool RAG> struct ChainRows {
             batch = seq_chunks ? 0 : (size_t)b * r.T;
         }
     }
-    __device__ __forceinline__ size_t first(int n) const { return batch + (size_t)(base + n * C); }
+    // (in 64 bits throughout: from a 32-bit sum the compiler forms a loader's addresses anew for every chunk, eight products; one
+    // chain of 1024 chunks, state_fwd: 618 us, so 599)
+    __device__ __forceinline__ size_t first(int n) const { return batch + (size_t)(long long)base + (size_t)n * C; }
     __device__ __forceinline__ int count(int n) const { const int c = end - (base + n * C); return RAG && c < C ? c : C; }
     size_t batch = 0;
 };
