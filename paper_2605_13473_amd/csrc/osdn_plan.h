@@ -97,9 +97,11 @@ inline int seg_begin(int N, int S, int s) {
 // Where the line lies (us per pass, sequential or in segments against pieces; K = V = 128 in bf16):
 //  - forward, chains on an eighth of the CUs or fewer, from 24 chunks on: 16 chains of 24 110 and 96, with a retention
 //    gate 131 and 105, of 32 137 and 107, 167 and 116, of 64 229 and 187 (pieces of 4 chunks; of 8: 229), 32 of
-//    32 166 and 138; 16 chains of 16 79 and 82.  With a retention gate, whose chunk takes half as long again and which needs
-//    two sweeps instead of three to five, on a quarter of the CUs too, from 32 chunks on: 64 chains of 32 247 and 232, of 64
-//    423 and 407, of 24 187 and 211.
+//    32 166 and 138; 16 chains of 16 79 and 82.
+//  - not for more chains: how many sweeps the pieces need with a retention gate goes by how much it fades, two with gates of 0.999,
+//    three to five with 0.9999 or 1, and with 33 to 64 chains only two pay (64 chains, gates of 0.999, then of 1: forward of 32
+//    chunks 252 and 217, 252 and 253, of 128 797 and 708, 792 and 919, of 256 1487 and 1351, 1482 and 1974; backward of 64 623 and 590, 620
+//    and 692, of 128 1115 and 1106, 1108 and 1334).
 //  - how many pieces, forward without retention: 4 chains of 64 chunks 205 with 8 pieces, 159 with 16, 148 with 32; of 256 410 with
 //    32, 390 with 64, 469 with 128; of 512 883, 783, 852; 2 of 1024 1649, 1346, 1298 and with 256 1516; 1 of 1024 1192 with 64, 1141
 //    with 128, 1317 with 256.
@@ -119,8 +121,7 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
     int target, min_chunks;
     if (forced != 0) { target = forced > 0 ? forced : 0; min_chunks = 1; }
     else {
-        const bool few = chains * 8 <= NUM_CU, some = retention && chains * 4 <= NUM_CU;
-        if (!(few ? N >= 24 : some && N >= (backward ? 24 : 32) && (!backward || N <= 128)) || (backward && !retention)) return;
+        if (chains * 8 > NUM_CU || N < 24 || (backward && !retention)) return;
         target = (int)(NUM_CU / chains);
         if (N >= 16 * target) target *= 2;
         // (every workgroup walks the maps of all pieces of its chain; but pieces of more than eight chunks cost more than that walk)

@@ -64,3 +64,12 @@ def test_every_plan_covers_the_sequence(plan):
                                                   (8, 128, 32), (4, 256, 32)])
 def test_long_sequences_of_few_chains_are_cut_into_pieces_of_eight(plan, chains, chunks, pieces, ret):
     assert plan([(chains, chunks, 128, 128, 1, ret, 0.003, 0, 0)])[0][0] == pieces
+
+
+@pytest.mark.parametrize("back", [0, 1])
+def test_no_pieces_beyond_an_eighth_of_the_cus(plan, back):
+    """With a retention gate pieces win there only if it fades much, which the rule does not know."""
+    calls = [(ch, N, K, 128, bf, ret, 0.003, 0, back) for ch in (33, 48, 64) for N in (24, 32, 64, 128, 256) for K in (64, 128)
+             for bf in (0, 1) for ret in (0, 1, 2)]
+    assert not any(r[0] for r in plan(calls))
+    assert all(r[0] for r in plan([(32, N, 128, 128, 1, 1, 0.003, 0, back) for N in (24, 32, 64)]))
