@@ -87,8 +87,8 @@ inline int seg_begin(int N, int S, int s) {
 
 // Phase 1 as sweeps over the whole sequence, for few long chains: one workgroup per chain leaves most
 // of the chip idle and its walk over the chunks is most of the pass.  Every chain is cut into pieces
-// (a workgroup per CU over all chains; two where a piece still has eight chunks, which shortens the walk more
-// than two workgroups on a CU slow each other); a sweep runs all pieces side by
+// (a workgroup per CU over all chains; two where a piece still has eight chunks and the kernel's registers let two onto a CU, at
+// most 128: that shortens the walk more than two workgroups on a CU slow each other); a sweep runs all pieces side by
 // side, each from its current start value, and leaves every piece as a composed map per
 // coordinate; the next sweep walks those maps for its start values; a chain is settled when none
 // of its start values moves any more.  Plain batches only.  params->p1_pieces forces a number of
@@ -105,6 +105,9 @@ inline int seg_begin(int N, int S, int s) {
 //  - how many pieces, forward without retention: 4 chains of 64 chunks 205 with 8 pieces, 159 with 16, 148 with 32; of 256 410 with
 //    32, 390 with 64, 469 with 128; of 512 883, 783, 852; 2 of 1024 1649, 1346, 1298 and with 256 1516; 1 of 1024 1192 with 64, 1141
 //    with 128, 1317 with 256.
+//  - two workgroups a CU where they fit (us, one and two): forward, K = 128, one gate in bf16 (127 registers) 16 chains of 256 chunks
+//    581 and 567, with gates of 1 790 and 754; where they do not, the pieces run in two rounds: one gate in fp32 (136) 1302 and 1347,
+//    1537 and 1645; a gate per coordinate (159) 597 and 668, 826 and 939; backward (153 and more) 826 and 863, 972 and 1090.
 //  - backward, only with a retention gate (without, a piece needs more sweeps, and the solved form has the shorter
 //    chain): 16 chains of 24 chunks 143 and 126, of 32 175 and 138, of 128 579 and 432, of 512 1986 and 1600; 64 chains
 //    of 32 331 and 308, of 128 1126 and 1097, of 256 2136 and 2159; pieces of four chunks at least (16 chains
@@ -123,7 +126,8 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
     else {
         if (chains * 8 > NUM_CU || N < 24 || (backward && !retention)) return;
         target = (int)(NUM_CU / chains);
-        if (N >= 16 * target) target *= 2;
+        const bool two = p->K == 64 || (!backward && (!retention || (p->io_dtype == OSDN_BF16 && !p->retention_per_channel)));
+        if (two && N >= 16 * target) target *= 2;
         // (every workgroup walks the maps of all pieces of its chain; but pieces of more than eight chunks cost more than that walk)
         const int most = N <= 64 ? 16 : N <= 256 ? 32 : (N + 7) / 8;
         if (target > most) target = most;

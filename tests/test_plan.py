@@ -73,3 +73,9 @@ def test_no_pieces_beyond_an_eighth_of_the_cus(plan, back):
              for bf in (0, 1) for ret in (0, 1, 2)]
     assert not any(r[0] for r in plan(calls))
     assert all(r[0] for r in plan([(32, N, 128, 128, 1, 1, 0.003, 0, back) for N in (24, 32, 64)]))
+
+
+@pytest.mark.parametrize("K,bf16,ret,back,pieces", [(128, 1, 0, 0, 32), (128, 0, 0, 0, 32), (128, 1, 1, 0, 32), (128, 0, 1, 0, 16), (128, 1, 2, 0, 16),
+                                                    (128, 0, 2, 0, 16), (128, 1, 1, 1, 16), (128, 1, 2, 1, 16), (64, 1, 1, 1, 32), (64, 0, 2, 0, 32)])
+def test_two_workgroups_a_cu_only_where_the_kernel_fits_twice(plan, K, bf16, ret, back, pieces):
+    assert plan([(16, 256, K, 128, bf16, ret, 0.003, 0, back)])[0][0] == pieces
