@@ -102,8 +102,8 @@ typedef struct {
     int32_t segments;               /* > 0: cut the sequence into this many segments of chunks for the
                                        two-stream pipeline of osdn_fwd / osdn_bwd (1: one stream) */
     int32_t p1_pieces;              /* > 0: the preconditioner runs as sweeps over this many pieces per
-                                       chain (osdn_bwd: unless segments > 1 or it takes the solved form);
-                                       -1: never (always the sequential sweep) */
+                                       chain (osdn_bwd: with a retention gate, unless segments > 1 or it takes
+                                       the solved form); -1: never (always the sequential sweep) */
     int32_t p1_piece_sweeps;        /* > 0: at most this many such sweeps (up to 13) before the sequential
                                        sweep finishes the chains that have not settled */
     int32_t p1_solved;              /* osdn_bwd: 1: the reverse sweep takes chunks in solved form (a 64 x 64

@@ -99,19 +99,18 @@ inline int seg_begin(int N, int S, int s) {
 //    gate 131 and 105, of 32 137 and 107, 167 and 116, of 64 229 and 187 (pieces of 4 chunks; of 8: 229), 32 of
 //    32 166 and 138; 16 chains of 16 79 and 82.
 //  - not for more chains: how many sweeps the pieces need with a retention gate goes by how much it fades, two with gates of 0.999,
-//    three to five with 0.9999 or 1, and with 33 to 64 chains only two pay (64 chains, gates of 0.999, then of 1: forward of 32
-//    chunks 252 and 217, 252 and 253, of 128 797 and 708, 792 and 919, of 256 1487 and 1351, 1482 and 1974; backward of 64 623 and 590, 620
-//    and 692, of 128 1115 and 1106, 1108 and 1334).
+//    three to five with 0.9999 or 1, and with 33 to 64 chains only two pay (64 chains, segments and pieces, gates of 0.999, then of
+//    1: forward of 32 chunks 240 and 219, 250 and 252, of 64 427 and 389, 435 and 471, of 128 770 and 695, 834 and 915, of 256 1354 and
+//    1312, 1476 and 1947; backward of 64 625 and 583, 629 and 632, of 128 1115 and 1093, 1118 and 1193).
 //  - how many pieces, forward without retention: 4 chains of 64 chunks 205 with 8 pieces, 159 with 16, 148 with 32; of 256 410 with
 //    32, 390 with 64, 469 with 128; of 512 883, 783, 852; 2 of 1024 1649, 1346, 1298 and with 256 1516; 1 of 1024 1192 with 64, 1141
 //    with 128, 1317 with 256.
 //  - two workgroups a CU where they fit (us, one and two): forward, K = 128, one gate in bf16 (127 registers) 16 chains of 256 chunks
 //    581 and 567, with gates of 1 790 and 754; where they do not, the pieces run in two rounds: one gate in fp32 (136) 1302 and 1347,
 //    1537 and 1645; a gate per coordinate (159) 597 and 668, 826 and 939; backward (153 and more) 826 and 863, 972 and 1090.
-//  - backward, only with a retention gate (without, a piece needs more sweeps, and the solved form has the shorter
-//    chain): 16 chains of 24 chunks 143 and 126, of 32 175 and 138, of 128 579 and 432, of 512 1986 and 1600; 64 chains
-//    of 32 331 and 308, of 128 1126 and 1097, of 256 2136 and 2159; pieces of four chunks at least (16 chains
-//    of 32 chunks: pieces of two 146).
+//  - backward, only with a retention gate (without, the solved form has the shorter chain), gates of 0.999, then of 1: 16 chains of
+//    24 chunks 142 and 130, 141 and 146, of 32 173 and 142, 183 and 173, of 128 567 and 437, 571 and 503, of 512 1927 and 1602, 1954
+//    and 1802; pieces of four chunks at least (16 chains of 32 chunks: pieces of two 146).
 inline void pieces_plan(const osdn_params *p, int N, long long chains, bool packed, bool retention, bool backward, int &pieces,
                         int &piece_chunks, int &sweeps) {
     pieces = 0; piece_chunks = 0;
@@ -119,12 +118,12 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
     // doubling (7 at 1024); the limit leaves two in hand
     sweeps = 7;                                  // (the last one only finds that nothing moved)
     for (int n = 128; n < N && sweeps < MAX_PIECE_SWEEPS; n *= 2) ++sweeps;
-    if (packed || chains > MAX_PIECES / 2) return;
+    if (packed || chains > MAX_PIECES / 2 || (backward && !retention)) return;
     const int forced = p->p1_pieces;              // 0: decide here; -1: never; n > 0: n pieces per chain
     int target, min_chunks;
     if (forced != 0) { target = forced > 0 ? forced : 0; min_chunks = 1; }
     else {
-        if (chains * 8 > NUM_CU || N < 24 || (backward && !retention)) return;
+        if (chains * 8 > NUM_CU || N < 24) return;
         target = (int)(NUM_CU / chains);
         const bool two = p->K == 64 || (!backward && (!retention || (p->io_dtype == OSDN_BF16 && !p->retention_per_channel)));
         if (two && N >= 16 * target) target *= 2;

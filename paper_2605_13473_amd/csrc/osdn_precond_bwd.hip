@@ -269,14 +269,16 @@ __global__ __launch_bounds__(P1T) void precond_lin_r_kernel(PrecondBwdArgs a) {
 // piece is swept from a guess of the adjoint at its right end, and the sweeps over all pieces repeat until
 // no such value of the chain moves.  A piece that began at x and ended at y is left as the map
 //     x' -> y + P (x' - x - g <g, x' - x> / <1, g>),
-// P per coordinate, g = sum over the piece's tokens of ca_t <1, s_t> s_t (retention: without the term in
-// g): exact where nothing moved, and as good as the sweeps need it elsewhere.  The term in g is the coupling of the
-// coordinates along (1, .., 1), which is nearly all of it (sum ca_t s_t s_t^T = g g^T / <1, g> for equal keys).
-// With a retention gate two sweeps do and a third finds that nothing moved (16 chains, K = V = 128, backward pass of 128
-// chunks 579 -> 432 us, of 512 1986 -> 1600); without, three to five.
+// P per coordinate, g = sum over the piece's tokens of ca_t <1, s_t> s_t:
+// exact where nothing moved, and as good as the sweeps need it elsewhere.  The term in g is the coupling of the
+// coordinates along (1, .., 1), which is nearly all of it (sum ca_t s_t s_t^T = g g^T / <1, g> for equal keys); one gate per token
+// multiplies it as it does the rest.  How many sweeps it takes goes by how much the gates fade, and without the term in g also by
+// eta and beta (16 chains of 128 chunks, K = 64, gates of 1, beta about 0.95: more than the limit, 900 us; 350 with it).
+// With gates of 0.999 two sweeps do and a third finds that nothing moved, with 0.9999 or 1 three to five (16 chains, K = V = 128,
+// backward pass against segments: 128 chunks 567 and 437 us, with gates of 1 571 and 503; 512 1927 and 1602, 1954 and 1802).
 template <typename T, int K, int RET, bool PIECES, bool RAG>
 __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
-    constexpr bool COUPLED = PIECES && RET == 0;
+    static_assert(!PIECES || RET != 0, "without retention a chain is not cut");
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     constexpr int CPT = K / 64;                  // coordinates per thread (adjacent)
     constexpr int NRUN = C / RUN;                // = wavefronts of the workgroup
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     auto get_map = [&](const float *m, int j, float (&v)[CPT]) {
         Pr::unpack(*reinterpret_cast<const typename Pr::Raw *>(m + j * K + c0), v);
     };
-    float PP[CPT], gacc[COUPLED ? CPT : 1] = {}, start[CPT];  // the piece so far: P, g; where it began
+    float PP[CPT], gacc[PIECES ? CPT : 1] = {}, start[CPT];  // the piece so far: P, g; where it began
     if (PIECES) {
         // The adjoint at this piece's right end: the chain's own carried through the maps that the sweep before left
         // (first sweep: the chain's own, as a guess).  Every workgroup of a chain walks all its pieces and so sees
@@ -354,13 +356,11 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
                     big = wave_max(big);
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) moved = moved || !(fabsf(dx[e]) <= PIECE_TOL_BWD * big);   // (not a number: moved)
-                    if (COUPLED) {
-                        dot = wave_sum(dot);
-                        sum = wave_sum(sum);
-                        const float r = sum > 0.f ? dot / sum : 0.f;
+                    dot = wave_sum(dot);
+                    sum = wave_sum(sum);
+                    const float r = sum > 0.f ? dot / sum : 0.f;
 #pragma unroll
-                        for (int e = 0; e < CPT; ++e) dx[e] = __builtin_fmaf(-r, m[e].w, dx[e]);
-                    }
+                    for (int e = 0; e < CPT; ++e) dx[e] = __builtin_fmaf(-r, m[e].w, dx[e]);
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) x[e] = __builtin_fmaf(m[e].z, dx[e], m[e].y);
                 }
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         {
             const float nn = fmaxf(nrawreg, a.eps), bp = a.beta_aware ? betreg : 1.f;
             ca = a.eta * bp / nn * bp;
-            if (COUPLED) cn = ca * nrawreg;
+            if (PIECES) cn = ca * nrawreg;
         }
         // (all that was loaded has been used when its registers are refilled: else the loop's end copies them, and waits)
         asm volatile("" : "+v"(ca), "+v"(cn));
@@ -599,12 +599,12 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
             gdone[e] = ga[e];
             if (PIECES) PPdone[PIECES ? e : 0] = PP[e];
         }
-        if (COUPLED && !again) {
+        if (PIECES && !again) {
 #pragma unroll
             for (int u = 0; u < RUN; ++u) {
                 const float c = lane_bcast(cn, fold_lane(u));
 #pragma unroll
-                for (int e = 0; e < CPT; ++e) gacc[COUPLED ? e : 0] = __builtin_fmaf(c, sv[u][e], gacc[COUPLED ? e : 0]);
+                for (int e = 0; e < CPT; ++e) gacc[PIECES ? e : 0] = __builtin_fmaf(c, sv[u][e], gacc[PIECES ? e : 0]);
             }
         }
         again = false;
@@ -722,27 +722,27 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         sdone = sig;
         done = n;
     }
-    if (COUPLED) {                               // g of the piece: the sum over its runs
+    if (PIECES) {                                // g of the piece: the sum over its runs
         float v[CPT];
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) v[e] = gacc[COUPLED ? e : 0];
+        for (int e = 0; e < CPT; ++e) v[e] = gacc[PIECES ? e : 0];
         __syncthreads();
         put_map(mapL[0], v);
         __syncthreads();
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) gacc[COUPLED ? e : 0] = 0.f;
+        for (int e = 0; e < CPT; ++e) gacc[PIECES ? e : 0] = 0.f;
 #pragma unroll
         for (int j = 0; j < NRUN; ++j) {
             get_map(mapL[0], j, v);
 #pragma unroll
-            for (int e = 0; e < CPT; ++e) gacc[COUPLED ? e : 0] += v[e];
+            for (int e = 0; e < CPT; ++e) gacc[PIECES ? e : 0] += v[e];
         }
     }
     if (run == 0) {
 #pragma unroll
         for (int e = 0; e < CPT; ++e) {
             if (!PIECES || piece == 0) a.dd_in[bh * K + c0 + e] = ga[e];
-            if (PIECES) a.piece_map[(bh * a.pieces + piece) * K + c0 + e] = make_float4(start[e], ga[e], PP[e], COUPLED ? gacc[COUPLED ? e : 0] : 0.f);
+            if (PIECES) a.piece_map[(bh * a.pieces + piece) * K + c0 + e] = make_float4(start[e], ga[e], PP[e], gacc[PIECES ? e : 0]);
         }
     }
 #undef OSDN_P1_BLOAD
@@ -1170,8 +1170,13 @@ static void launch_chain_k(const PrecondBwdArgs &a, int nchains, hipStream_t st)
             return;
         }
     }
-    if (a.pieces) with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, true, decltype(rag)::value>), dim3(nchains * a.pieces), dim3(P1F), 0, st, a); });
-    else with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, false, decltype(rag)::value>), dim3(nchains), dim3(P1F), 0, st, a); });
+    if constexpr (RET != 0) {
+        if (a.pieces) {
+            with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, true, decltype(rag)::value>), dim3(nchains * a.pieces), dim3(P1F), 0, st, a); });
+            return;
+        }
+    }
+    with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((precond_chain_kernel<T, K, RET, false, decltype(rag)::value>), dim3(nchains), dim3(P1F), 0, st, a); });
 }
 template <typename T, int RET>
 static int launch_precond_bwd_t(const PrecondBwdArgs &a, int which, hipStream_t st) {

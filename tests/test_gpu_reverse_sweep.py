@@ -90,6 +90,28 @@ def test_pieces_of_uneven_length(pieces, retention):
     compare_backward(x, ob.Hyper(eta=0.3, p1_pieces=pieces, p1_solved=-1), False, dd_out=dd)
 
 
+@pytest.mark.parametrize("retention", ["head", "channel"])
+def test_pieces_settle_where_the_gates_hardly_fade(retention):
+    """Gates of 1, large beta, K = 64: the coupling of the coordinates is what moves from piece to piece.  Chains that settle within six
+    sweeps have the same bits with any higher limit (those that do not are done by the sequential sweep, with others)."""
+    T = 64 * 64
+    x = make_stress_inputs(1, T, 4, 64, 64, seed=195, bf16=True, retention=0.97)
+    x["retention"] = np.ones((1, T, 4) + ((64,) if retention == "channel" else ()), np.float32)
+    x["beta"] = (0.9 + 0.1 * np.random.Generator(np.random.Philox(14)).random((1, T, 4))).astype(np.float32)
+    t, got = to_dev(x, True), []
+    for pieces, limit in ((-1, 0), (16, 6), (16, 13)):
+        *_, ctx = ob.forward(*[t[n] for n in ("q", "k", "v", "beta", "log_alpha", "retention", "d_in", "S_in")],
+                             ob.Hyper(p1_pieces=-1), for_backward=True)
+        ctx["params"].p1_pieces, ctx["params"].p1_piece_sweeps = pieces, limit
+        got.append(ob.backward(ctx, t["dO"]))
+    torch.cuda.synchronize()
+    seq, six, many = got
+    assert all(torch.equal(six[n], many[n]) for n in six)
+    assert not torch.equal(six["dd_in"], seq["dd_in"])
+    for n in ("dretention", "dd_in", "dbeta"):
+        assert (six[n] - seq[n]).abs().max() <= 1e-5 * seq[n].abs().max(), n
+
+
 def test_values_that_are_not_finite_reach_what_they_reached_without_pieces():
     """A gradient that is not finite never settles: the sequential sweep has the last word."""
     x = to_dev(make_stress_inputs(1, 64 * 12, 2, 64, 64, seed=193, bf16=False, retention=0.97), False)
