@@ -111,6 +111,12 @@ inline int seg_begin(int N, int S, int s) {
 //  - backward, only with a retention gate (without, the solved form has the shorter chain), gates of 0.999, then of 1: 16 chains of
 //    24 chunks 142 and 130, 141 and 146, of 32 173 and 142, 183 and 173, of 128 567 and 437, 571 and 503, of 512 1927 and 1602, 1954
 //    and 1802; pieces of four chunks at least (16 chains of 32 chunks: pieces of two 146).
+//  - all this for eta up to what K allows (the sweeps over the pieces need the more the larger eta / K is, and beyond a limit do not
+//    settle: 0.003 is within it by a factor of 2.1 and 1.07 for the forward pass, K = 128 and 64, of 11 and 5 for the
+//    backward pass).  16 chains of 48 chunks, gates of 1, segments and pieces: forward, K = 128, eta 0.01 256 and 160, 0.03 310 and 219,
+//    0.1 310 and 471; K = 64, 0.003 199 and 132, 0.01 233 and 157, 0.03 233 and 354; backward, K = 128, 0.03 283 and 249, 1 433 and
+//    768, K = 64, 16 chains of 128 chunks 0.01 500 and 382, 0.1 676 and 1000.  Beyond it only the forward pass of 64 chunks and more is
+//    cut, into pieces of eight chunks.
 inline void pieces_plan(const osdn_params *p, int N, long long chains, bool packed, bool retention, bool backward, int &pieces,
                         int &piece_chunks, int &sweeps) {
     pieces = 0; piece_chunks = 0;
@@ -125,12 +131,18 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
     else {
         if (chains * 8 > NUM_CU || N < 24) return;
         target = (int)(NUM_CU / chains);
-        const bool two = p->K == 64 || (!backward && (!retention || (p->io_dtype == OSDN_BF16 && !p->retention_per_channel)));
-        if (two && N >= 16 * target) target *= 2;
-        // (every workgroup walks the maps of all pieces of its chain; but pieces of more than eight chunks cost more than that walk)
-        const int most = N <= 64 ? 16 : N <= 256 ? 32 : (N + 7) / 8;
-        if (target > most) target = most;
-        min_chunks = backward ? 4 : 2;
+        const bool gentle = p->eta <= (backward ? 2.5e-4f : 5e-5f) * p->K;
+        if (!gentle) {
+            if (backward || N < 64) return;
+            min_chunks = 8;
+        } else {
+            const bool two = p->K == 64 || (!backward && (!retention || (p->io_dtype == OSDN_BF16 && !p->retention_per_channel)));
+            if (two && N >= 16 * target) target *= 2;
+            // (every workgroup walks the maps of all pieces of its chain; but pieces of more than eight chunks cost more than that walk)
+            const int most = N <= 64 ? 16 : N <= 256 ? 32 : (N + 7) / 8;
+            if (target > most) target = most;
+            min_chunks = backward ? 4 : 2;
+        }
     }
     if ((long long)target * chains > MAX_PIECES) target = (int)(MAX_PIECES / chains);
     if (target < 2) return;

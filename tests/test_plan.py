@@ -79,3 +79,15 @@ def test_no_pieces_beyond_an_eighth_of_the_cus(plan, back):
                                                     (128, 0, 2, 0, 16), (128, 1, 1, 1, 16), (128, 1, 2, 1, 16), (64, 1, 1, 1, 32), (64, 0, 2, 0, 32)])
 def test_two_workgroups_a_cu_only_where_the_kernel_fits_twice(plan, K, bf16, ret, back, pieces):
     assert plan([(16, 256, K, 128, bf16, ret, 0.003, 0, back)])[0][0] == pieces
+
+
+def test_pieces_by_eta(plan):
+    """A large eta, where the sweeps over pieces need many rounds or never settle: backward none, forward pieces of eight chunks."""
+    for K, fwd_most, bwd_most in ((64, 0.0032, 0.016), (128, 0.0064, 0.032)):
+        ask = lambda N, eta, back: plan([(16, N, K, 128, 1, 1, eta, 0, back)])[0][:2]
+        for eta in (1e-4, 0.003, 0.99 * fwd_most):
+            assert ask(24, eta, 0)[0] and ask(128, eta, 0)[0] == 16 and ask(64, eta, 0) == [16, 4]
+        for eta in (1.01 * fwd_most, 0.1, 1.0):
+            assert not ask(24, eta, 0)[0] and not ask(63, eta, 0)[0] and ask(64, eta, 0) == [8, 8] and ask(256, eta, 0) == [16, 16]
+        assert ask(24, 0.99 * bwd_most, 1)[0] and ask(128, 0.99 * bwd_most, 1)[0]
+        assert not any(ask(N, 1.01 * bwd_most, 1)[0] for N in (24, 64, 256))
