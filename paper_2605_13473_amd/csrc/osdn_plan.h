@@ -111,6 +111,9 @@ inline int seg_begin(int N, int S, int s) {
 //  - backward, only with a retention gate (without, the solved form has the shorter chain), gates of 0.999, then of 1: 16 chains of
 //    24 chunks 142 and 130, 141 and 146, of 32 173 and 142, 183 and 173, of 128 567 and 437, 571 and 503, of 512 1927 and 1602, 1954
 //    and 1802; pieces of four chunks at least (16 chains of 32 chunks: pieces of two 146).
+//    Not for long sequences of many chains, where segments keep phase 1 beside phase 2 (gates of 0.999, then of 1): 32 chains of 64
+//    chunks 447 and 378, 492 and 458, of 128 703 and 681, 803 and 846, of 256 1328 and 1290, 1483 and 1594; with fp32 I/O and K = 128
+//    16 chains of 96 961 and 916, 964 and 950, of 128 1242 and 1215, 1246 and 1291, of 256 2321 and 2348, 2324 and 2495.
 //  - all this for eta up to what K allows (the sweeps over the pieces need the more the larger eta / K is, and beyond a limit do not
 //    settle: 0.003 is within it by a factor of 2.1 and 1.07 for the forward pass, K = 128 and 64, of 11 and 5 for the
 //    backward pass).  16 chains of 48 chunks, gates of 1, segments and pieces: forward, K = 128, eta 0.01 256 and 160, 0.03 310 and 219,
@@ -132,6 +135,7 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
         if (chains * 8 > NUM_CU || N < 24) return;
         target = (int)(NUM_CU / chains);
         const bool gentle = p->eta <= (backward ? 2.5e-4f : 5e-5f) * p->K;
+        if (backward && N > (chains > 16 ? 64 : p->io_dtype == OSDN_F32 && p->K == 128 && chains > 8 ? 96 : N)) return;
         if (!gentle) {
             if (backward || N < 64) return;
             min_chunks = 8;

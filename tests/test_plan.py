@@ -91,3 +91,10 @@ def test_pieces_by_eta(plan):
             assert not ask(24, eta, 0)[0] and not ask(63, eta, 0)[0] and ask(64, eta, 0) == [8, 8] and ask(256, eta, 0) == [16, 16]
         assert ask(24, 0.99 * bwd_most, 1)[0] and ask(128, 0.99 * bwd_most, 1)[0]
         assert not any(ask(N, 1.01 * bwd_most, 1)[0] for N in (24, 64, 256))
+
+
+@pytest.mark.parametrize("chains,K,bf16,most", [(16, 128, 1, 4096), (17, 128, 1, 64), (32, 64, 1, 64), (32, 128, 0, 64), (16, 128, 0, 96), (9, 128, 0, 96),
+                                                (8, 128, 0, 4096), (16, 64, 0, 4096)])
+def test_no_pieces_in_reverse_for_long_sequences_of_many_chains(plan, chains, K, bf16, most):
+    got = {N: plan([(chains, N, K, 128, bf16, 1, 0.003, 0, 1)])[0][0] for N in (24, 64, 65, 96, 97, 256, 4096)}
+    assert all((P > 0) == (N <= most) for N, P in got.items()), got
