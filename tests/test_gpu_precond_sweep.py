@@ -97,6 +97,16 @@ def test_first_guess_where_d_fades_and_where_the_face_holds_it(K):
     compare_forward(x, hp, False)
 
 
+def test_first_guess_with_a_large_eta():
+    """The updates hold d up against gates of 0.999: no more sweeps than with gates of 1 (a chunk in twenty may differ)."""
+    x = make_stress_inputs(2, 64 * 16, 4, 64, 64, seed=165, bf16=False, retention=0.97)
+    total = {}
+    for gate in (1.0, 0.999):
+        x["retention"] = np.full((2, 64 * 16, 4), gate, np.float32)
+        total[gate] = float(_sweeps(x, ob.Hyper(eta=1.0, p1_pieces=-1, segments=1)).sum())
+    assert total[0.999] <= 1.05 * total[1.0], total
+
+
 def test_carried_d_is_bit_for_bit_across_calls_with_retention():
     """Which first guess a chunk takes must follow from its own d and gates."""
     rng = np.random.Generator(np.random.Philox(13))
