@@ -107,6 +107,15 @@ def test_long_packed_axis_many_sequences():
     _compare(lens, H=1, K=64, V=64, seed=63, bf16=False, hp=ob.Hyper(eta=0.3))
 
 
+@pytest.mark.parametrize("n_seqs", [255, 256, 511])
+@pytest.mark.parametrize("whole", [False, True])
+def test_more_sequences_than_one_launch_of_the_tables_takes(n_seqs, whole):
+    """The index tables are written 255 sequences a launch; whole chunks and ragged ones, a long sequence among the last."""
+    lens = [64] * n_seqs if whole else [1 + (7 * s) % 66 for s in range(n_seqs)]
+    lens[-2] = 192 if whole else 131
+    _compare(lens, H=1, K=64, V=64, seed=70, bf16=False, hp=ob.Hyper(eta=0.3))
+
+
 @pytest.mark.parametrize("lens", [[150, 3000, 100, 200], [2500, 70, 1]])
 def test_dominant_sequence_is_pipelined_over_segments(lens):
     """One sequence makes up most of the axis: the two phases are pipelined over segments of the

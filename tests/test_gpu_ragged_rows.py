@@ -80,3 +80,38 @@ def test_ragged_equals_padded_by_the_caller(lens, packed, K, V, vec, bf16):
     token_wise = (0, 3, 4, 5, 6, 7, 8)          # o and the gradients of the token inputs
     for i, (g, w) in enumerate(zip(got, want)):
         assert torch.equal(g, w[:, idx] if i in token_wise else w), i
+
+
+@pytest.mark.parametrize("bf16,offset", [(False, 4), (True, 2), (True, 8)])
+@pytest.mark.parametrize("vec", [False, True])
+@pytest.mark.parametrize("lens,packed,H,K,V", [([65, 65], False, 2, 128, 64), ([321], False, 2, 64, 128), ([127, 1, 64, 200], True, 2, 128, 128),
+                                               ([77] * 70, True, 4, 64, 64)])
+def test_ragged_tensors_off_a_16_byte_boundary(lens, packed, H, K, V, vec, bf16, offset):
+    """q, k, v and dO of ragged calls are read where they are: off a 16-byte boundary, with rows that are not numbers on both
+    sides of them, they give what aligned tensors give (few chains and many, slices of 16 and of 32 values)."""
+    B, T = (1, sum(lens)) if packed else (len(lens), lens[0])
+    x = make_stress_inputs(B, T, H, K, V, seed=T + V, bf16=bf16, retention=0.97)
+    t = to_dev({n: x[n] for n in NAMES}, bf16)
+    if vec:
+        for n in ("log_alpha", "retention"):
+            t[n] = t[n].unsqueeze(-1).expand(B, T, H, K).contiguous()
+        t["log_alpha"] = t["log_alpha"].clamp(min=-0.5)
+    cu = None
+    if packed:
+        cu = [0]
+        for n in lens:
+            cu.append(cu[-1] + n)
+
+    def shifted(a):
+        row = a[0, 0].numel()
+        at = 64 * row + offset // a.element_size()
+        buf = torch.full((a.numel() + 129 * row,), float("nan"), dtype=a.dtype, device=a.device)
+        out = buf[at:at + a.numel()].view(a.shape)
+        out.copy_(a)
+        assert out.data_ptr() % 16 == offset
+        return out
+
+    hp = ob.Hyper(eta=0.3)
+    moved = {n: shifted(a) if n in ("q", "k", "v", "dO") else a for n, a in t.items()}
+    for a, b in zip(_call(t, hp, cu, B, T, H, K, V, bf16, vec), _call(moved, hp, cu, B, T, H, K, V, bf16, vec)):
+        assert torch.isfinite(a).all() and torch.equal(a, b)
