@@ -591,7 +591,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const long long chain_wgs = chains * (p->V / (c.narrow_slices ? 16 : 32)) + chains;     // of the chain kernels of both phases
     int pieces = 0, piece_chunks = 0, piece_sweeps = 0;
     if (!solved && p->segments <= 1) pieces_plan(p, N, chains, pk.n_seqs != 0, retention != nullptr, true, pieces, piece_chunks, piece_sweeps);
-    int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, chains, chain_wgs, true, (bf ? 2 : 1) * NUM_CU, !solved);   // (bwd_post: two workgroups a CU with bf16 I/O)
+    int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, chains, chain_wgs, true, (bf ? 2 : 1) * NUM_CU);   // (bwd_post: two workgroups a CU with bf16 I/O)
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
     auto seg_range = [&](int sidx, int &n0, int &n1) { n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1); };

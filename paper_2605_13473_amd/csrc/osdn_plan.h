@@ -27,16 +27,16 @@ constexpr int MAX_SEGMENTS = 16, MAX_PIECES = 512, MAX_PIECE_SWEEPS = 13;
 //    exposed tail against that cost is about sqrt(N / 15) (2 at 64 chunks, 4 at 256); when they
 //    all fit side by side, about 32 chunks per segment, at most four: of that count and the two
 //    above it, the one whose segments fill whole rounds of bwd_post workgroups (one per chunk and
-//    chain, post_round at a time) best; from 448 chunks on, where a segment is many rounds, seven,
-//    or twelve if phase 1 sweeps (p1_sweeps: it is slower then, and its last segment what is exposed).
+//    chain, post_round at a time) best; from 448 chunks on, where a segment is many rounds, seven.
 //    16 chains, bf16, backward pass alone: 128 chunks 494, 499, 493, 515, 546, 575 us with 3 to 8 segments
 //    (5 taken); 256 chunks, V = 256 993, 1014, 1057, 1063, 1097, 1023 with 4 to 9 (5); 512 chunks 1648, 1625, 1621,
-//    1619, 1643, 1816 with 4 to 8 and 12.
+//    1619, 1643, 1816 with 4 to 8 and 12; chains that are swept, with retention, 512 chunks with 4 to 8, 10 and 12: 33 chains 2662,
+//    2605, 2580, 2583, 2597, 2608, 2583; 48 3193, 3171, 3173, 3179, 3192, 3231, 3262; fp32, 8 chains 3801, 3778, 3695, 3793, 3897, 3760, 3923.
 // Segments cut the chunk axis as a whole.  With packed sequences the sequential kernels of a
 // segment only have the sequences that cross it to work on, one after the other segment by
 // segment, so cutting pays only while one sequence makes up most of the axis; otherwise the
 // many independent chains fill the chip by themselves and everything runs in one piece.
-inline int segment_count(int forced, int N, int longest, long long chains, long long chain_wgs, bool backward, int post_round = 0, bool p1_sweeps = false) {
+inline int segment_count(int forced, int N, int longest, long long chains, long long chain_wgs, bool backward, int post_round = 0) {
     if (forced <= 0 && (long long)longest * 4 < (long long)N * 3) return 1;
     int S = forced;
     if (forced <= 0) {
@@ -44,7 +44,7 @@ inline int segment_count(int forced, int N, int longest, long long chains, long 
         if (!backward) S = N / 16 > 6 ? 6 : N / 16;
         else if (chain_wgs > NUM_CU) S = (int)std::lround(std::sqrt(N / 15.0)) > 6 ? 6 : (int)std::lround(std::sqrt(N / 15.0));
         else {
-            S = N >= 448 ? (p1_sweeps ? 12 : 7) : N / 32 > 4 ? 4 : N / 32;
+            S = N >= 448 ? 7 : N / 32 > 4 ? 4 : N / 32;
             if (S < 2) S = 2;
             double best = 0.0;
             int pick = S;

@@ -98,3 +98,10 @@ def test_pieces_by_eta(plan):
 def test_no_pieces_in_reverse_for_long_sequences_of_many_chains(plan, chains, K, bf16, most):
     got = {N: plan([(chains, N, K, 128, bf16, 1, 0.003, 0, 1)])[0][0] for N in (24, 64, 65, 96, 97, 256, 4096)}
     assert all((P > 0) == (N <= most) for N, P in got.items()), got
+
+
+@pytest.mark.parametrize("chains,K,V,bf16,ret", [(33, 128, 128, 1, 1), (48, 128, 128, 1, 2), (16, 128, 128, 1, 0), (9, 128, 128, 0, 1)])
+def test_segments_of_long_sequences_in_reverse(plan, chains, K, V, bf16, ret):
+    """Seven from 448 chunks on, in the solved form and with sweeps."""
+    for N in (448, 512, 2000):
+        assert plan([(chains, N, K, V, bf16, ret, 0.003, 0, 1)])[0][4] == 7
