@@ -39,10 +39,17 @@
  *     capture and leaves it inside the call).  Calls on different streams share nothing; calls
  *     that share one stream must be issued one after the other, as any work on one stream.
  *     params->segments = 1 keeps everything on `stream`.
- *     With at most 32 (batch, head) chains of at least 24 chunks (with a retention gate 64; osdn_bwd: only
- *     with one) the preconditioner, and its reverse, is computed as a few sweeps over pieces of the
- *     sequence that run side by side, all on `stream` (same results to the tolerance of the sweeps, 1e-6
- *     relative; params->p1_pieces = -1 keeps the one sequential sweep per chain).
+ *     With at most 32 (batch, head) chains of at least 24 chunks (64, if eta > 5e-5 K) osdn_fwd computes the
+ *     preconditioner as a few sweeps over pieces of the sequence that run side by side, all on `stream`;
+ *     osdn_bwd does so with a retention gate and eta <= 2.5e-4 K, beyond 16 chains up to 64 chunks, with fp32
+ *     I/O and K = 128 beyond 8 chains up to 96.  params->p1_pieces = -1 keeps the one sequential sweep per
+ *     chain.  d, k~ and the adjoint of d then agree with the sequential sweep's to the tolerance of the sweeps,
+ *     1e-6 relative, and not bit for bit, and a call cut in two with (S, d) carried over agrees with the
+ *     whole one no closer than that (below those lengths bit for bit).  What is made of d can differ by more: the
+ *     projection decides for every coordinate whether it met the box, and where d comes within that tolerance of a
+ *     face the decision, and with it the gradients that pass through it, may fall the other way; without a
+ *     state gate and with bf16 I/O, S keeps every rounding of k~ that falls the other way (o and the gradients
+ *     2e-3 in norm over 3000 tokens, as far from the exact values as the sequential sweep's).
  *   - retention values are assumed >= 0 (they are sigmoid gates in the paper).  Wherever a
  *     signature says retention / dretention [B,T,H], params->retention_per_channel = 1 makes
  *     it [B,T,H,K]: one value per coordinate.  Likewise params->gate_per_channel = 1 makes

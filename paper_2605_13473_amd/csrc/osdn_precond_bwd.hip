@@ -752,7 +752,9 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
 // The chain where chunks that qualify take the solved form (no retention; see the top of this file).  Any
 // other chunk is swept: NSEG = 512 / K runs of TS tokens, one coordinate of one run per thread, abar_i kept as
 // L_i + P_i * carry; the runs are chained through LDS, the products s_i abar_i folded over the lanes, three
-// barriers a sweep (such chunks are few here: the library takes this form only where d stays inside the box).
+// barriers a sweep.  Which calls come here goes by sizes alone, not by d: with the default box such chunks are few, also where
+// the d that is carried in lies on a face, which it leaves within the chunk (16 chains of 64 chunks of 128 coordinates, backward
+// pass: 273 us, from d = d_max 276); a box so narrow that d keeps meeting it makes every chunk one of them.
 template <typename T, int K, bool RAG>
 __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a) {
     constexpr int NSEG = P1T / K;                 // runs per chunk
