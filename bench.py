@@ -296,7 +296,7 @@ def main():
     # a kernel may be launched once per segment of the sequence: durations and work are
     # summed over the launches of one step (= launch-weighted average rate)
     per_kernel = {k: ms / args.steps for k, (ms, n) in prof.items() if n > 0}
-    tables_ms = per_kernel.pop("pad", None)         # index tables of packed sequences
+    tables_ms = per_kernel.pop("tables", None)      # index tables of packed sequences
     unfold_ms = per_kernel.pop("unfold", None)      # per-channel gates: gradients of the folded operands mapped back
     launches = {k: n // args.steps for k, (ms, n) in prof.items() if n > 0}
     dominant = max(per_kernel, key=per_kernel.get)
@@ -319,7 +319,7 @@ def main():
             "mfma_frac_of_kernel": flops.get(dominant, 0.0) / dur / PEAK_BF16_FLOPS if cfg.bf16 else None,
             "per_kernel_ms": {k: round(v, 4) for k, v in per_kernel.items()}}
     if tables_ms is not None:
-        roof["per_kernel_ms"]["pad (tables)"] = round(tables_ms, 4)
+        roof["per_kernel_ms"]["tables"] = round(tables_ms, 4)
     if unfold_ms is not None:
         roof["per_kernel_ms"]["unfold"] = round(unfold_ms, 4)
 

@@ -15,11 +15,11 @@ using namespace osdn;
 // Optional per-kernel timing with HIP events on the caller's stream (off by default; the
 // only process-wide state the library has).  Not thread-safe; meant for benchmarks.
 enum { KID_PRECOND_FWD, KID_CHUNK_PREP, KID_STATE_FWD, KID_OUTPUT_FWD, KID_BWD_CHAIN,
-       KID_BWD_POST, KID_PRECOND_MASK, KID_PRECOND_CHAIN, KID_PRECOND_POST, KID_STEP, KID_PAD, KID_UNFOLD, KID_PRECOND_LIN,
+       KID_BWD_POST, KID_PRECOND_MASK, KID_PRECOND_CHAIN, KID_PRECOND_POST, KID_STEP, KID_TABLES, KID_UNFOLD, KID_PRECOND_LIN,
        KID_COUNT };
 const char *const kKernelNames[KID_COUNT] = {"precond_fwd", "chunk_prep", "state_fwd", "output_fwd",
                                              "bwd_chain", "bwd_post", "precond_mask",
-                                             "precond_chain", "precond_post", "step", "pad", "unfold", "precond_lin"};
+                                             "precond_chain", "precond_post", "step", "tables", "unfold", "precond_lin"};
 struct Timed { int id; hipEvent_t e0, e1; };
 bool g_prof_on = false;
 std::vector<Timed> g_prof;
@@ -383,7 +383,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     int *tables = reinterpret_cast<int *>(ws + L.tables);
     const int *seq_chunks = pk.n_seqs ? tables : nullptr;
     const int *chunk_row = tables + pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
-    if (pk.n_seqs && timed(KID_PAD, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
+    if (pk.n_seqs && timed(KID_TABLES, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
         return OSDN_ERR_SHAPE;
 
     // the workspace is laid out for whole chunks; the caller's tensors are read where they are
@@ -523,7 +523,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     int *tables = reinterpret_cast<int *>(ws + L.tables);
     const int *seq_chunks = pk.n_seqs ? tables : nullptr;
     const int *chunk_row = tables + pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
-    if (pk.n_seqs && timed(KID_PAD, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
+    if (pk.n_seqs && timed(KID_TABLES, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
         return OSDN_ERR_SHAPE;
 
     osdn_params whole = *p;                              // (as in the forward pass)
