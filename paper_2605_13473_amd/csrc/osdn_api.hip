@@ -570,7 +570,7 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     pb.n_seqs = pk.n_seqs; pb.seq_chunks = seq_chunks; pb.dd_last = dd_out;
     pb.rows = rows; pb.dk = dk; pb.dbeta = dbeta; pb.dretention = retention ? dretention : nullptr; pb.dd_in = dd_in;
     const bool general = retention && !p->retention_per_channel;      // the solved form with a retention gate and any masks
-    const bool solved = solved_plan(p, (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H, retention != nullptr);
+    const bool solved = solved_plan(p, (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H, pk.longest, retention != nullptr);
     if (solved) {
         pb.lin_clean = reinterpret_cast<int *>(ws + L.lin_clean);
         pb.lin_M = ws + L.lin_M;

@@ -163,12 +163,14 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
 // token-head.  It pays while the phase-1 chain is what the pass waits for (us of the backward pass, sweeps and solved, V = K
 // unless said; beta = sigmoid(N(0, 1)), then about 0.95, where a chunk takes three sweeps; the solved form knows neither):
 //  - chains on at most an eighth of the CUs (K = 128, bf16: 32 of 64 chunks 430 and 380, 485 and 380; K = 64: 302 and 250);
-//  - with bf16 I/O on a quarter (K = 64: 40 of 64 339 and 288, 64 of 32 201 and 191, of 64 395 and 352, of 128 639 and 701; K = 128:
+//  - with bf16 I/O on a quarter, from 16 chunks on (48 chains, K = 128: 8 chunks 84 and 88, 16 129 and 134, with V = 64 121 and 119; 33 of 8
+//    83 and 87, of 16 126 and 123; K = 64, 48 of 8 66 and 65, of 16 99 and 92; K = 64: 40 of 64 339 and 288, 64 of 32 201 and 191, of 64 395 and 352, of 128 639 and 701; K = 128:
 //    40 of 64 476 and 443, 527 and 443; V = 64: 64 of 64 514 and 510, 569 and 508, of 128 916 and 1014), but for K = 128 with
 //    V >= 128 beyond 48 chains, where the traffic of phase 2 fills the chip (48 of 64 507 and 500, 559 and 501; 64 of 32 319 and
 //    328, 350 and 327; 64 of 64 611 and 636, 668 and 637; 64 of 128 1102 and 1200, 1163 and 1200).
-inline bool solved_plan(const osdn_params *p, long long chains, bool retention) {
-    const bool bf = p->io_dtype == OSDN_BF16, quarter = bf && !(p->K == 128 && p->V >= 128 && chains > 48);
+// longest: chunks of the longest sequence
+inline bool solved_plan(const osdn_params *p, long long chains, int longest, bool retention) {
+    const bool bf = p->io_dtype == OSDN_BF16, quarter = bf && longest >= 16 && !(p->K == 128 && p->V >= 128 && chains > 48);
     if (retention) return !p->retention_per_channel && p->p1_solved > 0;       // (the form with a retention gate and any masks)
     return p->p1_solved > 0 || (p->p1_solved == 0 && chains * (quarter ? 4 : 8) <= NUM_CU);
 }

@@ -343,24 +343,21 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
 #pragma unroll 4
                 for (int q = a.pieces - 1; q >= 0; --q) {
                     float4 m[CPT];
-                    float dx[CPT], dot = 0.f, sum = 0.f, big = 0.f;
+                    float dx[CPT], dot = 0.f, big = 0.f;
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) {
                         m[e] = prev[(size_t)q * K + c0 + e];
-                        if (q == piece) xs[e] = x[e];
+                        if (q == piece) { xs[e] = x[e]; gacc[PIECES ? e : 0] = m[e].w; }
                         dx[e] = x[e] - m[e].x;
                         big = fmaxf(big, fabsf(x[e]));
                         dot = __builtin_fmaf(m[e].w, dx[e], dot);
-                        sum += m[e].w;
                     }
                     big = wave_max(big);
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) moved = moved || !(fabsf(dx[e]) <= PIECE_TOL_BWD * big);   // (not a number: moved)
                     dot = wave_sum(dot);
-                    sum = wave_sum(sum);
-                    const float r = sum > 0.f ? dot / sum : 0.f;
 #pragma unroll
-                    for (int e = 0; e < CPT; ++e) dx[e] = __builtin_fmaf(-r, m[e].w, dx[e]);
+                    for (int e = 0; e < CPT; ++e) dx[e] = __builtin_fmaf(-dot, m[e].w, dx[e]);
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) x[e] = __builtin_fmaf(m[e].z, dx[e], m[e].y);
                 }
@@ -599,7 +596,7 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
             gdone[e] = ga[e];
             if (PIECES) PPdone[PIECES ? e : 0] = PP[e];
         }
-        if (PIECES && !again) {
+        if (PIECES && a.sweep == 0 && !again) {
 #pragma unroll
             for (int u = 0; u < RUN; ++u) {
                 const float c = lane_bcast(cn, fold_lane(u));
@@ -722,7 +719,7 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
         sdone = sig;
         done = n;
     }
-    if (PIECES) {                                // g of the piece: the sum over its runs
+    if (PIECES && a.sweep == 0) {                // g of the piece, the sum over its runs, over sqrt(<1, g>) (the same for every sweep)
         float v[CPT];
 #pragma unroll
         for (int e = 0; e < CPT; ++e) v[e] = gacc[PIECES ? e : 0];
@@ -737,6 +734,13 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
 #pragma unroll
             for (int e = 0; e < CPT; ++e) gacc[PIECES ? e : 0] += v[e];
         }
+        float sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) sum += gacc[PIECES ? e : 0];
+        sum = wave_sum(sum);
+        const float r = sum > 0.f ? rsqrtf(sum) : 0.f;
+#pragma unroll
+        for (int e = 0; e < CPT; ++e) gacc[PIECES ? e : 0] *= r;
     }
     if (run == 0) {
 #pragma unroll

@@ -36,5 +36,5 @@ def launches(chains, T, K, V, bf16, hp=ob.Hyper(), retention=None):
     (64, 128, 64, True, True), (33, 64, 64, True, True), (64, 64, 128, True, True), (65, 64, 64, True, False),
     (32, 64, 64, False, True), (33, 64, 64, False, False)])
 def test_solved_form_without_retention(chains, K, V, bf16, solved):
-    _, bwd = launches(chains, 128, K, V, bf16)
+    _, bwd = launches(chains, 1024, K, V, bf16)
     assert ("precond_lin" in bwd) == solved and ("precond_mask" in bwd) != solved

@@ -17,7 +17,7 @@ int main() {
         osdn_params p{};
         p.K = K; p.V = V; p.io_dtype = bf ? OSDN_BF16 : OSDN_F32; p.eta = eta; p.retention_per_channel = ret == 2; p.p1_pieces = forced;
         int pieces, len, sweeps;
-        const bool solved = back && solved_plan(&p, ch, ret != 0);
+        const bool solved = back && solved_plan(&p, ch, N, ret != 0);
         pieces_plan(&p, N, ch, false, ret != 0, back != 0, pieces, len, sweeps);
         if (solved) pieces = 0;
         const int S = pieces ? 1 : segment_count(0, N, N, ch, ch * (V / 32) + ch, back != 0, 512);
@@ -105,3 +105,11 @@ def test_segments_of_long_sequences_in_reverse(plan, chains, K, V, bf16, ret):
     """Seven from 448 chunks on, in the solved form and with sweeps."""
     for N in (448, 512, 2000):
         assert plan([(chains, N, K, V, bf16, ret, 0.003, 0, 1)])[0][4] == 7
+
+
+@pytest.mark.parametrize("chains,K,V,bf16,least", [(32, 128, 128, 1, 1), (33, 128, 128, 1, 16), (48, 128, 128, 1, 16), (49, 128, 128, 1, None),
+                                                   (64, 128, 64, 1, 16), (64, 64, 128, 1, 16), (65, 64, 64, 1, None), (32, 64, 64, 0, 1), (33, 64, 64, 0, None)])
+def test_solved_form_without_retention(plan, chains, K, V, bf16, least):
+    for N in (1, 8, 15, 16, 64, 1000):
+        assert plan([(chains, N, K, V, bf16, 0, 0.003, 0, 1)])[0][3] == (least is not None and N >= least), N
+    assert not any(r[3] for r in plan([(chains, 64, K, V, bf16, ret, 0.003, 0, 1) for ret in (1, 2)]))
