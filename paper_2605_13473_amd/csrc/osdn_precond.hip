@@ -62,7 +62,7 @@ namespace osdn {
 // Registers: with one gate per token, K = 128 in bf16 the compiler is held to 128, which it would pass by four: two workgroups
 // to a CU, which the pieces are laid out for (16 chains of 256 chunks, forward pass: 873 us with 132 registers, 753 with 128).
 template <typename T, int K, int RET, bool PIECES, bool TILES, bool RAG>
-__global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 2) void precond_fwd_kernel(PrecondArgs a) {
+__global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1) void precond_fwd_kernel(PrecondArgs a) {
     constexpr bool HAS_RET = RET != 0, RET_VEC = RET == 2;
     constexpr int RE = RET_VEC ? K / 64 : 1;      // retention values a thread keeps per token
     constexpr int CPT = K / 64;                   // coordinates per thread (adjacent)
@@ -223,26 +223,28 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 2
         // it up, or eta is so large that the updates do (from this chunk's d and gates alone: where a call or a launch begins must
         // not show; K = 64, gates of 0.999, eta 1: 6.00 us a chunk with the fading guess, 5.40 without)
         float left = 1.f;
-        bool fades = RET == 1 && a.eta <= 5e-4f * K && !__all(ret > 0.99995f);
-        if (fades) {
-            bool near = true;
+        if constexpr (RET == 1) {
+            bool fades = a.eta <= 5e-4f * K && !__all(ret > 0.99995f);
+            if (fades) {
+                bool near = true;
 #pragma unroll
-            for (int e = 0; e < CPT; ++e) near = near && dst[e] <= 1.02f * lo;
-            fades = !__all(near);
-        }
-        if (fades) {
-            float x = ret;
+                for (int e = 0; e < CPT; ++e) near = near && dst[e] <= 1.02f * lo;
+                fades = !__all(near);
+            }
+            if (fades) {
+                float x = ret;
 #define OSDN_P1_SCAN(ctrl_, rows_) x *= __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0x3f800000, __builtin_bit_cast(int, x), ctrl_, rows_, 0xF, false));
-            OSDN_P1_SCAN(0x111, 0xF) OSDN_P1_SCAN(0x112, 0xF) OSDN_P1_SCAN(0x114, 0xF) OSDN_P1_SCAN(0x118, 0xF)      // row_shr:1, 2, 4, 8
-            OSDN_P1_SCAN(0x142, 0xA) OSDN_P1_SCAN(0x143, 0xC)                                                        // row_bcast:15, 31
+                OSDN_P1_SCAN(0x111, 0xF) OSDN_P1_SCAN(0x112, 0xF) OSDN_P1_SCAN(0x114, 0xF) OSDN_P1_SCAN(0x118, 0xF)      // row_shr:1, 2, 4, 8
+                OSDN_P1_SCAN(0x142, 0xA) OSDN_P1_SCAN(0x143, 0xC)                                                        // row_bcast:15, 31
 #undef OSDN_P1_SCAN
-            const int t = run * RUN + u_own;
-            const float all = lane_bcast(x, 63);
-            x = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((t - 1) * 4, __builtin_bit_cast(int, x)));
-            bool faced = true;                  // every coordinate comes to the lower face within this chunk
+                const int t = run * RUN + u_own;
+                const float all = lane_bcast(x, 63);
+                x = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((t - 1) * 4, __builtin_bit_cast(int, x)));
+                bool faced = true;              // every coordinate comes to the lower face within this chunk
 #pragma unroll
-            for (int e = 0; e < CPT; ++e) faced = faced && dst[e] * all <= lo;
-            left = t > 0 && !__all(faced) ? x : 1.f;
+                for (int e = 0; e < CPT; ++e) faced = faced && dst[e] * all <= lo;
+                left = t > 0 && !__all(faced) ? x : 1.f;
+            }
         }
         // ---- the scalars of token (run, u_own): n_raw = sum s, first guess p = <d_0, s> times what retention leaves ----
         float nraw, cb, ca, p_cur, c_cur;
