@@ -339,27 +339,33 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
             bool moved = a.sweep == 0;
 #pragma unroll
             for (int e = 0; e < CPT; ++e) x[e] = xs[e] = ga[e];
-            if (a.sweep > 0) {
-#pragma unroll 4
-                for (int q = a.pieces - 1; q >= 0; --q) {
-                    float4 m[CPT];
+            // (WALK records at a time, asked for together: as in the forward kernel)
+            constexpr int WALK = 8;
+            for (int q0 = a.sweep > 0 ? a.pieces - 1 : -1; q0 >= 0; q0 -= WALK) {
+                float4 m[WALK][CPT];
+#pragma unroll
+                for (int j = 0; j < WALK; ++j)
+#pragma unroll
+                    for (int e = 0; e < CPT; ++e) m[j][e] = prev[(size_t)max(q0 - j, 0) * K + c0 + e];
+#pragma unroll
+                for (int j = 0; j < WALK; ++j) {
+                    if (q0 - j < 0) break;
                     float dx[CPT], dot = 0.f, big = 0.f;
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) {
-                        m[e] = prev[(size_t)q * K + c0 + e];
-                        if (q == piece) { xs[e] = x[e]; gacc[PIECES ? e : 0] = m[e].w; }
-                        dx[e] = x[e] - m[e].x;
+                        if (q0 - j == piece) { xs[e] = x[e]; gacc[PIECES ? e : 0] = m[j][e].w; }
+                        dx[e] = x[e] - m[j][e].x;
                         big = fmaxf(big, fabsf(x[e]));
-                        dot = __builtin_fmaf(m[e].w, dx[e], dot);
+                        dot = __builtin_fmaf(m[j][e].w, dx[e], dot);
                     }
                     big = wave_max(big);
 #pragma unroll
                     for (int e = 0; e < CPT; ++e) moved = moved || !(fabsf(dx[e]) <= PIECE_TOL_BWD * big);   // (not a number: moved)
                     dot = wave_sum(dot);
 #pragma unroll
-                    for (int e = 0; e < CPT; ++e) dx[e] = __builtin_fmaf(-dot, m[e].w, dx[e]);
+                    for (int e = 0; e < CPT; ++e) dx[e] = __builtin_fmaf(-dot, m[j][e].w, dx[e]);
 #pragma unroll
-                    for (int e = 0; e < CPT; ++e) x[e] = __builtin_fmaf(m[e].z, dx[e], m[e].y);
+                    for (int e = 0; e < CPT; ++e) x[e] = __builtin_fmaf(m[j][e].z, dx[e], m[j][e].y);
                 }
             }
             if (__any(moved)) moved = true;
