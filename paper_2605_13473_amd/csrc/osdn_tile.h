@@ -25,6 +25,18 @@ template <int ROWB> struct Swz {
         return ROWB >= 256 ? (r & 15u) : ROWB == 128 ? ((r >> 1) & 7u) : ROWB == 64 ? (((r >> 3) & 1u) << 1) : 0u;
     }
     static __device__ __forceinline__ uint32_t at(uint32_t r, uint32_t c) { return r * ROWB + ((c ^ f(r)) << 4); }
+    // f(r + rows) ^ f(r), the same for every r that LdsLoad::init meets
+    static __device__ __forceinline__ uint32_t step(uint32_t rows) { return ROWB >= 256 ? rows & 15u : 0u; }
+};
+// The same for a tile that is read transposed in runs of eight (RunFrag::tr): sixteen lanes take 8 bytes each of four rows and
+// four groups next to each other, which lie in sixteen different groups of 256 bytes here.
+template <int ROWB> struct SwzRun {
+    static_assert(ROWB == 128 || ROWB == 256, "row length");
+    static __device__ __forceinline__ uint32_t f(uint32_t r) {
+        return ROWB == 256 ? ((r & 3u) << 2) | ((r >> 2) & 3u) : (((r >> 1) & 1u) << 2) | ((r >> 2) & 3u);
+    }
+    static __device__ __forceinline__ uint32_t at(uint32_t r, uint32_t c) { return r * ROWB + ((c ^ f(r)) << 4); }
+    static __device__ __forceinline__ uint32_t step(uint32_t rows) { return ROWB == 256 ? (rows >> 2) & 3u : 0u; }
 };
 
 // MFMA fragments from a permuted tile.  kc: the contraction index runs along the row, tr: down the
@@ -74,6 +86,39 @@ template <int ROWB> struct TileFrag<float, ROWB> {
         *reinterpret_cast<f32x4 *>(tile + Swz<ROWB>::at(r0 + row, ((uint32_t)c0 >> 2) + q)) = acc;
     }
 };
+// Fragments for products whose result is the next product's operand without leaving its registers.  Two accumulator tiles of
+// 16 rows cover 32 rows (features, tokens) so that a lane's four rows of either are eight in a row: row m of the tile `half` is
+// row 8 (m / 4) + 4 half + m % 4 of the 32.  Rounded, the eight values are the fragment (32 rows along the contraction, 16
+// columns) of the next MFMA, and 16 bytes in a row for memory.
+template <int ROWB> struct RunFrag {
+    uint32_t rowl[2], trl;
+    __device__ __forceinline__ void init(int lane) {
+        const uint32_t m = lane & 15, q = lane >> 4;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) rowl[half] = Swz<ROWB>::at((m >> 2) * 8 + half * 4 + (m & 3), q);
+        trl = SwzRun<ROWB>::at(q * 8 + (m >> 2), m & 3);
+    }
+    // rows of `half` of the 32 from r0 on, contraction index from k0 on along the row
+    __device__ __forceinline__ bf16x8 rows(const char *tile, int r0, int half, int k0) const {
+        return *reinterpret_cast<const bf16x8 *>(tile + r0 * ROWB + (rowl[half] ^ (uint32_t)(k0 << 1)));
+    }
+    // columns of `half` of the 32 from r0 on, contraction index from k0 on down the rows (a tile permuted by SwzRun)
+    __device__ __forceinline__ bf16x8 tr(const char *tile, int k0, int r0, int half) const {
+        typedef short v4s __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) v4s *lds_v4s;
+        const uint32_t o = trl ^ (uint32_t)(r0 << 1);
+        const char *p = tile + k0 * ROWB + half * 8;
+        const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + o));
+        const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p + 4 * ROWB + (o ^ 16u)));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+    static __device__ __forceinline__ bf16x8 pack(f32x4 a, f32x4 b) {
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { o[e] = (bf16)a[e]; o[4 + e] = (bf16)b[e]; }
+        return o;
+    }
+};
 // a whole permuted tile to memory (rows gstride bytes apart), 16 bytes per thread and step
 template <int ROWB, int ROWS>
 __device__ __forceinline__ void tile_to_global(char *g, uint32_t gstride, const char *tile, int tid, int nthreads) {
@@ -96,13 +141,19 @@ __device__ __forceinline__ void load_lds4(const void *base, uint32_t voff, uint3
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                  :: "s"(lds), "v"(voff), "s"(base) : "m0", "memory");
 }
+// A line per lane on its way into the L2: 4 bytes of it go to LDS address lds + 4 * lane, where nothing reads them
+constexpr int LINE = 128;
+__device__ __forceinline__ void touch(const char *p, uint32_t lds) {
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p) & ~(uintptr_t)3;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(lds), "v"(at) : "m0", "memory");
+}
 // all but the newest N vector memory accesses of this wavefront are complete
 template <int N> __device__ __forceinline__ void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
 
 // A [ROWS x ROWB bytes] tile shared by the NW wavefronts of a workgroup; every load covers 1 KB.
-template <int ROWB, int ROWS, int NW> struct LdsLoad {
+template <int ROWB, int ROWS, int NW, typename SW = Swz<ROWB>> struct LdsLoad {
     static constexpr int NI = ROWB * ROWS / 1024;          // loads of the whole tile
     static constexpr int MIN = NI / NW;                    // every wavefront issues at least this many
     static constexpr int RPI = 1024 / ROWB;                // rows per load
@@ -114,7 +165,7 @@ template <int ROWB, int ROWS, int NW> struct LdsLoad {
     uint32_t voff;
     __device__ __forceinline__ void init(uint32_t gstride, int wave, int lane) {     // gstride: bytes between rows in memory
         const uint32_t r = wave * RPI + lane / (ROWB / 16), ph = lane % (ROWB / 16);
-        voff = r * gstride + ((ph ^ Swz<ROWB>::f(r)) << 4);
+        voff = r * gstride + ((ph ^ SW::f(r)) << 4);
     }
     // wide: the source is 16-byte aligned (only a caller's tensor may not be: then the tile goes
     // through registers, which is slower and does the same)
@@ -130,11 +181,11 @@ template <int ROWB, int ROWS, int NW> struct LdsLoad {
             const int m = (j + rot) & (M - 1), i = wave + m * NW;
             if (NI % NW == 0 || i < NI) {
                 const char *gm = g + (size_t)m * NW * RPI * gstride;
-                uint32_t vo = voff ^ (uint32_t)(((m * STEP) & 15 & (STEP % 16 ? 15 : 0)) << 4);
+                uint32_t vo = voff ^ (SW::step(m * STEP) << 4);
                 if (last < ROWS - 1) {              // (uniform) rows behind the last one that exists repeat it
                     const uint32_t r = i * RPI + lane / (ROWB / 16), ph = lane % (ROWB / 16);
                     gm = g;
-                    vo = min(r, (uint32_t)last) * gstride + ((ph ^ Swz<ROWB>::f(r)) << 4);
+                    vo = min(r, (uint32_t)last) * gstride + ((ph ^ SW::f(r)) << 4);
                 }
                 if (wide) load_lds16(gm, vo, lds + i * 1024);
                 else *reinterpret_cast<u32x4 *>(tile + i * 1024 + lane * 16) = *reinterpret_cast<const u32x4 *>(gm + vo);

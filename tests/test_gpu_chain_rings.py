@@ -74,3 +74,19 @@ def test_token_tensors_off_a_16_byte_boundary(B, H, K, V, segments, bf16, offset
 
     for a, b in zip(run(lambda a: a), run(shifted)):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("B,T,H,K,V", [
+    (1, 64 * 8, 1, 128, 128),        # as long as the lines are asked for ahead, one and four chunks longer
+    (1, 64 * 9, 1, 64, 192),
+    (2, 64 * 12, 1, 128, 512),
+    (1, 64 * 10 + 5, 2, 128, 64),    # a ragged last chunk; more than 64 lines a slice
+    (1, 64 * 8 + 63, 1, 64, 64),
+])
+@pytest.mark.parametrize("channel_gate", [False, True])
+def test_lines_asked_for_ahead(B, T, H, K, V, channel_gate):
+    """bf16, few chains: the forward chain kernel asks for the lines of a chunk eight chunks ahead of its tiles."""
+    x = make_stress_inputs(B, T, H, K, V, seed=161, bf16=True, retention=0.97)
+    if channel_gate:
+        x["log_alpha"] = (-0.1 * np.random.default_rng(162).random((B, T, H, K))).astype(np.float32)
+    compare_forward(x, ob.Hyper(eta=0.5, segments=1), True)
