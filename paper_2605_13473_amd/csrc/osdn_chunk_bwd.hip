@@ -742,15 +742,20 @@ static void launch_chain_t(const ChunkArgs &a, hipStream_t st) {
     dim3 grid((a.V / VS) * a.H * (a.seq_chunks ? a.n_seqs : a.B)), block(CT_);
     with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((bwd_chain_kernel<T, K, GV, VS, decltype(rag)::value>), grid, block, 0, st, a); });
 }
-// Slices of 32 values with bf16 I/O, of 16 with fp32 I/O at K = 128 (beside slices of 32 one chunk's operands
-// would fill the LDS, with nothing in flight for the next), either with fp32 I/O at K = 64 (few chains: see osdn_bwd).
+// Slices of 16 values with fp32 I/O at K = 128 (beside slices of 32 one chunk's operands would fill the LDS, with nothing in
+// flight for the next), else of 16 or 32 (osdn_bwd says which).
 template <typename T, bool GV>
 static int launch_chain_v(const ChunkArgs &a, hipStream_t st) {
     if ((GV && !a.gamC) || !a.Pm || !a.q || !a.dO) return -1;
     if (a.K != 64 && a.K != 128) return -1;
     if constexpr (sizeof(T) == 2) {
-        if (a.K == 64) launch_chain_t<T, 64, GV, 32>(a, st);
-        else launch_chain_t<T, 128, GV, 32>(a, st);
+        if (a.narrow_slices) {
+            if (a.K == 64) launch_chain_t<T, 64, GV, 16>(a, st);
+            else launch_chain_t<T, 128, GV, 16>(a, st);
+        } else {
+            if (a.K == 64) launch_chain_t<T, 64, GV, 32>(a, st);
+            else launch_chain_t<T, 128, GV, 32>(a, st);
+        }
     } else {
         if (a.K == 128) launch_chain_t<T, 128, GV, 16>(a, st);
         else if (a.narrow_slices) launch_chain_t<T, 64, GV, 16>(a, st);

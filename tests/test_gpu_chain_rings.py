@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("chunks,segments", [(1, 1), (2, 1), (3, 1), (4, 1), (5, 2), (9, 4)])
 @pytest.mark.parametrize("shape", [(1, 2, 128, 192), (2, 2, 64, 64)])
 def test_short_sequences(shape, chunks, segments, bf16):
-    """Few chains: slices of 16 values (but for the backward pass in bf16, which always takes slices of 32)."""
+    """Few chains: slices of 16 values (the backward pass in bf16: in one piece; cut into segments, slices of 32)."""
     B, H, K, V = shape
     x = make_stress_inputs(B, 64 * chunks, H, K, V, seed=131 + chunks, bf16=bf16, retention=0.97)
     hp = ob.Hyper(eta=0.5, segments=segments)
