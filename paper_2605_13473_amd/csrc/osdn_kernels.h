@@ -84,7 +84,8 @@ struct PrecondArgs {
     int kt_tiles;             // ... [B,T/64,H,64,K]: one contiguous tile per chunk and head
     float *d_out;             // [B,H,K]
     float *d_ckpt;            // [B,H,T/64,K] or null
-    float *tok_scalars;       // [B,T,H,4] or null: per token (step, <d,k^2>, sum k^2, unused), kept for the backward
+    float *tok_scalars;       // [B,T,H,4] or null: per token (step, <d,k^2>, sum k^2, unused), kept for the backward; without
+                              // retention the sum is kept with its sign flipped in chunks whose coordinates all stay off the box
     void *k_tail;             // [sequences,64,H,K] io: k of ragged last chunks, whole, kept for the backward
     float *beta_tail, *ret_tail;      // [sequences,64,H], as retention
     // Sweeps over the whole sequence (pieces > 0, plain batches only): a chain is cut into
@@ -112,7 +113,7 @@ struct PrecondBwdArgs {
     const float *beta_tail, *ret_tail;
     const float *d_ckpt;     // retention [B,T,H], or [B,T,H,K] with ret_vec
     int ret_vec;
-    float *tok_scalars;       // [B,T,H,4] from the forward sweep: (step, <d,k^2>, sum k^2, -); the chain
+    float *tok_scalars;       // [B,T,H,4] from the forward sweep: (step, <d,k^2>, +-sum k^2, -); the chain
                               // kernel puts sigma_t into the fourth slot for the post kernel
     uint2 *masks;             // [B,H,T/64,K]: bit i = token i of the chunk stayed inside the box
     float *a_ckpt;            // [B,H,T/64,K]: adjoint of d at the right end of every chunk

@@ -102,6 +102,10 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
     const size_t bth = (size_t)bt * a.H + h;                  // indexes the per-chunk buffers
     const bool project = a.d_min <= a.d_max;
     const float lo = project ? a.d_min : -INFINITY, hi = project ? a.d_max : INFINITY;
+    // What a sweep without the box has to stay within: so far from either face that a replay of the tokens one after the other,
+    // which rounds differently (64 sums: 4e-6 of d), stays off it too.  Such a chunk is marked by the sign of its tokens' sum k^2: the
+    // backward pass knows then that every mask bit is set.
+    const float lo_in = isinf(lo) ? lo : lo + 2e-5f * fabsf(lo), hi_in = isinf(hi) ? hi : hi - 2e-5f * fabsf(hi);
     const int N = (a.T + C - 1) / C;
     const uint32_t kstride = (uint32_t)a.H * K;   // elements between consecutive tokens
     const ChainRows<RAG> rows(a.rows, a.seq_chunks, b, a.n0);
@@ -391,14 +395,14 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
                     d[e] = dst[e];
 #pragma unroll
                     for (int j = 0; j < NRUN - 1; ++j) d[e] += j < run ? Bm[j][e] : 0.f;
-                    within = within && d[e] >= lo;
+                    within = within && d[e] >= lo_in;
 #pragma unroll
                     for (int u = 0; u < RUN; ++u) {
                         dtr[u][e] = d[e];
                         vp[u] = e == 0 ? sv[u][e] * d[e] : __builtin_fmaf(sv[u][e], d[e], vp[u]);
                         d[e] = __builtin_fmaf(cv[u], sv[u][e], d[e]);
                     }
-                    within = within && d[e] <= hi;
+                    within = within && d[e] <= hi_in;
                     dend[e] = d[e];
                 }
                 within = within && (c_cur >= 0.f || !project);
@@ -457,7 +461,7 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
         }
         if (TILES || (a.tok_scalars && valid)) {       // (eight lanes store the same)
             const size_t th = ((size_t)bt * a.T + t0) * a.H + h;
-            lane_elem(reinterpret_cast<float4 *>(a.tok_scalars) + th, (run * RUN + u_own) * a.H) = make_float4(c_acc, p_acc, nraw, (float)sweeps_used);
+            lane_elem(reinterpret_cast<float4 *>(a.tok_scalars) + th, (run * RUN + u_own) * a.H) = make_float4(c_acc, p_acc, RET == 0 ? (FAST && !boxed ? -nraw : fabsf(nraw)) : nraw, (float)sweeps_used);
         }
         if (PIECES && tid < K) {                 // the accepted run maps, applied after the piece so far
             const int acc = pub == 0 ? NBUF - 1 : pub - 1;       // (the last published ones were dropped)

@@ -176,3 +176,29 @@ def test_segments_in_a_captured_graph():
         step()
         torch.cuda.synchronize()
         assert all(torch.equal(a, r) for a, r in zip(fwd + grads, ref))
+
+
+@pytest.mark.parametrize("eta", [0.003, 0.05])
+@pytest.mark.parametrize("T", [64 * 6, 64 * 4 + 7])
+@pytest.mark.parametrize("K", [64, 128])
+def test_masks_of_chunks_off_the_box_and_close_to_it(K, T, eta):
+    """Without retention the forward sweep marks the chunks that stay off the box and the backward pass does not replay them: heads
+    whose coordinates are far from the faces, start on one, within the margin of the mark and just outside it, or come to
+    one along the sequence; every decision is checked one by one.  A second backward pass on the same context gives the same."""
+    H = 6
+    x = make_stress_inputs(1, T, H, K, 64, seed=177, bf16=False)
+    x["retention"] = None
+    d = np.full((1, H, K), 1.0, np.float32)
+    d[0, 1, 3] = 2.0
+    d[0, 2, 5] = np.float32(2.0) * np.float32(1 - 1e-5)
+    d[0, 3, 7] = np.float32(2.0) * np.float32(1 - 4e-5)
+    d[0, 4, 0], d[0, 4, 1] = 0.5, np.float32(0.5) * np.float32(1 + 1e-5)
+    d[0, 5, ::2] = 1.98
+    x["d_in"] = d
+    hp = ob.Hyper(eta=eta, p1_solved=-1, segments=1)
+    compare_backward(x, hp, False)
+    t = to_dev(x, False)
+    _, _, _, ctx = ob.forward(t["q"], t["k"], t["v"], t["beta"], t["log_alpha"], None, t["d_in"], t["S_in"], hp, for_backward=True)
+    a, b = ob.backward(ctx, t["dO"]), ob.backward(ctx, t["dO"])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a[n], b[n]) for n in a if a[n] is not None)
