@@ -21,6 +21,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libosdn.so")
 _lib = None
+_step_native = None        # _native.step, once the library is loaded (None: the module is not built)
 
 OSDN_F32, OSDN_BF16 = 0, 1
 
@@ -47,7 +48,7 @@ class OsdnError(RuntimeError):
 
 def lib():
     """Load libosdn.so (built in-tree by ``build.py``); raises if it is not there."""
-    global _lib
+    global _lib, _step_native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(
@@ -87,6 +88,13 @@ def lib():
         L.osdn_profile_kernel_name.argtypes = [ctypes.c_int]
         L.osdn_profile_read.restype = ctypes.c_int
         L.osdn_profile_read.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int), ctypes.c_int]
+        try:
+            from . import _native
+        except ImportError:
+            _step_native = None
+        else:
+            _native.bind(ctypes.cast(L.osdn_step, vp).value)
+            _step_native = _native.step
         _lib = L
     return _lib
 
@@ -162,8 +170,7 @@ def osdn_precond_update(params, k, beta, retention, d_in, k_tilde, d_out, d_ckpt
 
 
 def osdn_step(params, q, k, v, beta, log_alpha, retention, d_in, S_in, o, S_out, d_out, stream=None):
-    # A decode step of few sequences takes the device 4 us: the time of a call is that of this function and of `step`.
-    # 16 heads of 128 x 128, one token, through `step`: 16.5 -> 11.7 us a call.
+    # (`step` comes here with what the extension module leaves to it.)
     p = params
     B, T, H, K, V = p.B, p.T, p.H, p.K, p.V
     io, f32 = _io_torch_dtype(p), torch.float32
@@ -389,6 +396,17 @@ def step(q, k, v, beta, log_alpha=None, retention=None, d_in=None, S_in=None, hp
          in_place: bool = False):
     """Recurrent form for 1..64 tokens: returns (o, S_out, d_out); with in_place the state S_in
     is updated where it is (and returned)."""
+    if _lib is None:
+        lib()
+    if _step_native is not None and isinstance(k, torch.Tensor) and k.is_cuda:
+        # a call without anything out of the ordinary (osdn_native.cpp); else None
+        dev = torch._C._cuda_getDevice()
+        r = _step_native(q, k, v, beta, log_alpha, retention, d_in, S_in, hp, in_place, dev,
+                         torch._C._cuda_getCurrentRawStream(dev))
+        if r is not None:
+            if type(r) is tuple:
+                return r
+            _check(r)
     B, T, H, K = k.shape
     V = v.shape[-1]
     p = _shape_params(B, T, H, K, V, k.dtype == torch.bfloat16, hp, _per_channel(retention), _per_channel(log_alpha))

@@ -1,14 +1,16 @@
-"""Build libosdn.so (the HIP library) in-tree for gfx950 with hipcc."""
+"""Build libosdn.so (the HIP library) in-tree for gfx950 with hipcc, and _native.so (binding.step's way to it) with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libosdn.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["osdn_api.hip", "osdn_precond.hip", "osdn_precond_bwd.hip", "osdn_precond_gen.hip", "osdn_step.hip", "osdn_tables.hip",
            "osdn_chunk_fwd.hip", "osdn_chunk_bwd.hip"]
 FLAGS = [
@@ -46,10 +48,29 @@ def build(verbose: bool = False, only=None) -> str:
             raise subprocess.CalledProcessError(r.returncode, cmd)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
+    with ThreadPoolExecutor(max_workers=8) as pool:
+        native = pool.submit(build_native) if only is None or not os.path.exists(NATIVE) else None
         objs = list(pool.map(compile_one, SOURCES))
+        if native is not None:
+            native.result()
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs])
     return LIB
+
+
+def build_native() -> str:
+    """The extension module: host code alone, against the tensor library's headers."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    lib = os.path.join(root, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-o", NATIVE, os.path.join(CSRC, "osdn_native.cpp"), "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        print(r.stdout)
+        raise subprocess.CalledProcessError(r.returncode, cmd)
+    return NATIVE
 
 
 if __name__ == "__main__":
