@@ -4,8 +4,10 @@
 #include "osdn_kernels.h"
 #include "osdn_plan.h"
 
+#include <algorithm>
 #include <map>
 #include <mutex>
+#include <numeric>
 #include <vector>
 
 namespace {
@@ -85,7 +87,8 @@ struct Packing {
     bool ragged = false;         // some sequence is not a whole number of chunks
     const int32_t *cu = nullptr; // the caller's offsets, n_seqs + 1
     std::vector<int> seq_chunks; // first chunk of every sequence, n_seqs + 1
-    size_t table_ints() const { return n_seqs ? (size_t)n_seqs + 1 + 2 * (size_t)N : 0; }   // seq_chunks, chunk_row [N], chunk_seq [N] on the device
+    std::vector<int> order;      // the sequences, longest first
+    size_t table_ints() const { return n_seqs ? 2 * (size_t)n_seqs + 1 + 2 * (size_t)N : 0; }   // seq_chunks, order, chunk_row [N], chunk_seq [N] on the device
 };
 
 // cu_seqlens: n_seqs + 1 ascending token offsets, from 0 to T, on the host
@@ -112,6 +115,11 @@ int make_packing(const osdn_params *p, const int32_t *cu, int n_seqs, Packing &p
         c += (cu[s + 1] - cu[s] + C - 1) / C;
     }
     pk.seq_chunks[n_seqs] = c;
+    pk.order.resize((size_t)n_seqs);
+    std::iota(pk.order.begin(), pk.order.end(), 0);
+    std::stable_sort(pk.order.begin(), pk.order.end(), [&](int a, int b) {
+        return pk.seq_chunks[a + 1] - pk.seq_chunks[a] > pk.seq_chunks[b + 1] - pk.seq_chunks[b];
+    });
     return OSDN_OK;
 }
 
@@ -382,8 +390,8 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const bool bf = p->io_dtype == OSDN_BF16;
     int *tables = reinterpret_cast<int *>(ws + L.tables);
     const int *seq_chunks = pk.n_seqs ? tables : nullptr;
-    const int *chunk_row = tables + pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
-    if (pk.n_seqs && timed(KID_TABLES, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
+    const int *chunk_row = tables + 2 * pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
+    if (pk.n_seqs && timed(KID_TABLES, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.order.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
         return OSDN_ERR_SHAPE;
 
     // the workspace is laid out for whole chunks; the caller's tensors are read where they are
@@ -522,8 +530,8 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const bool bf = p->io_dtype == OSDN_BF16;
     int *tables = reinterpret_cast<int *>(ws + L.tables);
     const int *seq_chunks = pk.n_seqs ? tables : nullptr;
-    const int *chunk_row = tables + pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
-    if (pk.n_seqs && timed(KID_TABLES, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
+    const int *chunk_row = tables + 2 * pk.n_seqs + 1, *chunk_seq = chunk_row + pk.N;
+    if (pk.n_seqs && timed(KID_TABLES, st, [&] { return launch_seq_tables(pk.cu, pk.seq_chunks.data(), pk.order.data(), pk.n_seqs, pk.N, tables, st); }) != 0)
         return OSDN_ERR_SHAPE;
 
     osdn_params whole = *p;                              // (as in the forward pass)

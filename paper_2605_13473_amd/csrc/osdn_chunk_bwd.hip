@@ -91,9 +91,11 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
 
     int chain, slice;
     chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
-    const int vs = slice * VS, h = chain % a.H, b = chain / a.H;   // b: batch entry, or packed sequence
+    const int vs = slice * VS, h = chain % a.H;
+    int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
     if (a.seq_chunks) {
+        b = sequence_of(a.seq_chunks, a.n_seqs, b);
         bool begins, ends;
         if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
         a.dS_out = ends ? a.dS_last : a.dS_in;

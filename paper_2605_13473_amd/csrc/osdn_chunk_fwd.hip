@@ -235,9 +235,11 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
 
     int chain, slice;
     chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
-    const int vs = slice * VS, h = chain % a.H, b = chain / a.H;   // b: batch entry, or packed sequence
+    const int vs = slice * VS, h = chain % a.H;
+    int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
     if (a.seq_chunks) {
+        b = sequence_of(a.seq_chunks, a.n_seqs, b);
         bool begins, ends;
         if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
         a.S_in = begins ? a.S_first : a.S_out;
@@ -458,9 +460,11 @@ __global__ __launch_bounds__(RT_<VS>, 1) void state_fwd_run_kernel(ChunkArgs a) 
 
     int chain, slice;
     chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
-    const int vs = slice * VS, h = chain % a.H, b = chain / a.H;   // b: batch entry, or packed sequence
+    const int vs = slice * VS, h = chain % a.H;
+    int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
     if (a.seq_chunks) {
+        b = sequence_of(a.seq_chunks, a.n_seqs, b);
         bool begins, ends;
         if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
         a.S_in = begins ? a.S_first : a.S_out;

@@ -437,6 +437,11 @@ __device__ __forceinline__ void chain_slice_of(int wg, int nslices, int nchains,
 }
 
 
+// Packed sequences: the one that the i-th chains of a launch (one per head) work on, longest first (the order stands behind
+// seq_chunks): workgroups are dealt out in order, and a long chain that starts last runs by itself at the end.  54 documents of up to
+// 64 chunks, 16 heads, us in the caller's order and longest first: precond_chain 257 and 198, precond_fwd 232 and 190, state_fwd 471 and 458,
+// bwd_chain 588 and 584.
+__device__ __forceinline__ int sequence_of(const int *seq_chunks, int n_seqs, int i) { return seq_chunks[n_seqs + 1 + i]; }
 // Packed sequences: clip the chunk range [n0, n1) of a launch to the chunks of sequence s.
 // begins / ends: the sequence starts / stops inside the launch's range.  False: nothing left.
 __device__ __forceinline__ bool clip_to_sequence(const int *seq_chunks, int s, int &n0, int &n1, bool &begins,

@@ -70,7 +70,7 @@ struct PrecondArgs {
     int B, T, H, K;
     int n0, n1;
     int n_seqs;               // 0: plain batch
-    const int *seq_chunks;    // [n_seqs + 1] or null
+    const int *seq_chunks;    // [n_seqs + 1] or null; behind them the sequences, longest first [n_seqs]
     const float *d_first;     // packed sequences: d before the first token, [n_seqs,H,K] or null
     float eta, d_min, d_max, eps;
     int beta_aware;
@@ -206,7 +206,7 @@ struct ChunkArgs {
 
 int launch_precond_fwd(const PrecondArgs &a, bool bf16_io, hipStream_t st);
 int launch_step(const StepArgs &a, bool bf16_io, hipStream_t st);
-int launch_seq_tables(const int *cu, const int *seq_chunks, int n_seqs, int N, int *tables, hipStream_t st);
+int launch_seq_tables(const int *cu, const int *seq_chunks, const int *order, int n_seqs, int N, int *tables, hipStream_t st);
 int launch_precond_mask(const PrecondBwdArgs &a, bool bf16_io, hipStream_t st);
 // solved form with a retention gate per (token, head): which = 0 masks, inverse and indicators (forward
 // data only), 1 rho0 and t0 (needs dL/dk~), 2 the chain; chunks [n0, n1)

@@ -84,21 +84,23 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
     const int u_own = fold_token(lane);      // the token of the run whose scalars this lane keeps
     const int piece = PIECES ? blockIdx.x % a.pieces : 0;
     const int chain = PIECES ? blockIdx.x / a.pieces : blockIdx.x;
-    const int b = chain / a.H, h = chain % a.H;               // b: batch entry, or packed sequence
+    const int h = chain % a.H;
+    int b = chain / a.H;                                      // batch entry, or packed sequence
     if (a.settled && !(PIECES && a.sweep == 0) && a.settled[chain]) return;
     if (PIECES) {
         a.n0 += piece * a.piece_chunks;
         a.n1 = min(a.n1, a.n0 + a.piece_chunks);
         if (a.n0 >= a.n1) return;
     }
-    const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes d_in / d_out
     int bt = b;                                               // batch entry of the token tensors
     if (a.seq_chunks) {
+        b = sequence_of(a.seq_chunks, a.n_seqs, b);
         bool begins, ends;
         if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
         a.d_in = begins ? a.d_first : a.d_out;
         bt = 0;
     }
+    const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes d_in / d_out
     const size_t bth = (size_t)bt * a.H + h;                  // indexes the per-chunk buffers
     const bool project = a.d_min <= a.d_max;
     const float lo = project ? a.d_min : -INFINITY, hi = project ? a.d_max : INFINITY;

@@ -302,8 +302,8 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     const int u_own = fold_token(lane);          // the token of the run whose scalars this lane keeps
     const int piece = PIECES ? blockIdx.x % a.pieces : 0;
     const int chain = PIECES ? blockIdx.x / a.pieces : blockIdx.x;
-    const int b = chain / a.H, h = chain % a.H;               // b: batch entry, or packed sequence
-    const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes dd_out / dd_in
+    const int h = chain % a.H;
+    int b = chain / a.H;                                      // batch entry, or packed sequence
     if (a.settled && !(PIECES && a.sweep == 0) && a.settled[chain]) return;
     if (PIECES) {
         a.n0 += piece * a.piece_chunks;
@@ -312,11 +312,13 @@ __global__ __launch_bounds__(P1F) void precond_chain_kernel(PrecondBwdArgs a) {
     }
     int bt = b;                                               // batch entry of the token tensors
     if (a.seq_chunks) {
+        b = sequence_of(a.seq_chunks, a.n_seqs, b);
         bool begins, ends;
         if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
         a.dd_out = ends ? a.dd_last : a.dd_in;
         bt = 0;
     }
+    const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes dd_out / dd_in
     const size_t bth = (size_t)bt * a.H + h;                  // indexes the per-chunk buffers
     const bool project = a.d_min <= a.d_max;
     const int N = a.T / C;
@@ -795,15 +797,17 @@ __global__ __launch_bounds__(P1T) void precond_chain_lin_kernel(PrecondBwdArgs a
     const int c = tid % K, sg = tid / K;          // coordinate and run of this thread
     const int li = tid >> 3, lpart = tid & 7;     // row layout of the solved form: token, slice
     const int lc = tid / NG, ltg = tid % NG;      // column layout: coordinate, token group
-    const int b = blockIdx.x / a.H, h = blockIdx.x % a.H;     // b: batch entry, or packed sequence
-    const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes dd_out / dd_in
+    const int h = blockIdx.x % a.H;
+    int b = blockIdx.x / a.H;                                 // batch entry, or packed sequence
     int bt = b;                                               // batch entry of the token tensors
     if (a.seq_chunks) {
+        b = sequence_of(a.seq_chunks, a.n_seqs, b);
         bool begins, ends;
         if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
         a.dd_out = ends ? a.dd_last : a.dd_in;
         bt = 0;
     }
+    const size_t bh = (size_t)b * a.H + h;                    // the chain: indexes dd_out / dd_in
     const size_t bth = (size_t)bt * a.H + h;                  // indexes the per-chunk buffers
     const bool project = a.d_min <= a.d_max;
     const int N = a.T / C;

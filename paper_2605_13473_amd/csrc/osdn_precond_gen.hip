@@ -344,16 +344,17 @@ __global__ __launch_bounds__(P1T) void precond_gen_chain_kernel(PrecondBwdArgs a
     const int c = tid % K;
     const int li = tid >> 3, lpart = tid & 7;
     const int lc = tid / NG, ltg = tid % NG;
-    const int b = blockIdx.x / a.H, h = blockIdx.x % a.H;
-    const size_t bh = (size_t)b * a.H + h;
+    const int h = blockIdx.x % a.H;
+    int b = blockIdx.x / a.H;
     int bt = b;
     if (a.seq_chunks) {
+        b = sequence_of(a.seq_chunks, a.n_seqs, b);
         bool begins, ends;
         if (!clip_to_sequence(a.seq_chunks, b, a.n0, a.n1, begins, ends)) return;
         a.dd_out = ends ? a.dd_last : a.dd_in;
         bt = 0;
     }
-    const size_t bth = (size_t)bt * a.H + h;
+    const size_t bh = (size_t)b * a.H + h, bth = (size_t)bt * a.H + h;
     const int N = a.T / C;
     const uint32_t kstride = (uint32_t)a.H * K;
     const ChainIn<T, K, 0, true> src(a, b, a.n0, h);

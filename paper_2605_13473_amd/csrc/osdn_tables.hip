@@ -9,9 +9,10 @@ namespace osdn {
 // sequences a launch; a workgroup writes the entries of one sequence.  65536 packed tokens in 67 sequences: one launch of
 // 4.5 us, where the tables themselves took five.
 constexpr int TABLE_SEQS = 255;
-struct SeqBlock { int row[TABLE_SEQS + 1], chunk[TABLE_SEQS + 1]; };
-__global__ __launch_bounds__(64) void seq_tables_kernel(SeqBlock blk, int *seq_chunks, int *chunk_row, int *chunk_seq, int first_seq) {
+struct SeqBlock { int row[TABLE_SEQS + 1], chunk[TABLE_SEQS + 1], order[TABLE_SEQS]; };
+__global__ __launch_bounds__(64) void seq_tables_kernel(SeqBlock blk, int *seq_chunks, int *order, int *chunk_row, int *chunk_seq, int first_seq) {
     const int s = blockIdx.x, c0 = blk.chunk[s], c1 = blk.chunk[s + 1], row = blk.row[s], end = blk.row[s + 1];
+    if (threadIdx.x == 0) order[s] = blk.order[s];
     if (threadIdx.x < 2) seq_chunks[s + threadIdx.x] = threadIdx.x ? c1 : c0;        // (the next sequence's too: the last has none)
     for (int c = c0 + (int)threadIdx.x; c < c1; c += 64) {
         const int r = row + (c - c0) * C;
@@ -20,16 +21,18 @@ __global__ __launch_bounds__(64) void seq_tables_kernel(SeqBlock blk, int *seq_c
     }
 }
 
-// tables: seq_chunks [n_seqs + 1], chunk_row [N], chunk_seq [N]; cu and seq_chunks: n_seqs + 1 entries on the host
-int launch_seq_tables(const int *cu, const int *seq_chunks, int n_seqs, int N, int *tables, hipStream_t st) {
+// tables: seq_chunks [n_seqs + 1], order [n_seqs], chunk_row [N], chunk_seq [N]; cu and seq_chunks (n_seqs + 1 entries) and order on the host
+int launch_seq_tables(const int *cu, const int *seq_chunks, const int *order, int n_seqs, int N, int *tables, hipStream_t st) {
     for (int at = 0; at < n_seqs; at += TABLE_SEQS) {
         SeqBlock blk;
         const int n = n_seqs - at < TABLE_SEQS ? n_seqs - at : TABLE_SEQS;
         for (int i = 0; i <= TABLE_SEQS; ++i) {
             blk.row[i] = i <= n ? cu[at + i] : 0;
             blk.chunk[i] = i <= n ? seq_chunks[at + i] : 0;
+            if (i < TABLE_SEQS) blk.order[i] = i < n ? order[at + i] : 0;
         }
-        hipLaunchKernelGGL(seq_tables_kernel, dim3(n), dim3(64), 0, st, blk, tables + at, tables + n_seqs + 1, tables + n_seqs + 1 + N, at);
+        hipLaunchKernelGGL(seq_tables_kernel, dim3(n), dim3(64), 0, st, blk, tables + at, tables + n_seqs + 1 + at,
+                           tables + 2 * n_seqs + 1, tables + 2 * n_seqs + 1 + N, at);
     }
     return 0;
 }
