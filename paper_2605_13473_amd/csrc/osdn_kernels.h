@@ -73,6 +73,10 @@ struct PrecondArgs {
     const int *seq_chunks;    // [n_seqs + 1] or null; behind them the sequences, longest first [n_seqs]
     const float *d_first;     // packed sequences: d before the first token, [n_seqs,H,K] or null
     float eta, d_min, d_max, eps;
+    // What a sweep without the box has to stay within: so far from either face that a replay of the tokens one after the other,
+    // which rounds differently (64 sums: 4e-6 of d), stays off it too.  Such a chunk is marked by the sign of its tokens' sum k^2: the
+    // backward pass knows then that every mask bit is set.
+    float lo_in, hi_in;
     int beta_aware;
     Rows rows;                // of k, beta, retention
     const void *k;            // [B,T,H,K] io
