@@ -2,7 +2,7 @@
 //
 // A decode step of few sequences takes the device 4 us; checking eleven tensors, allocating two and marshalling fifteen
 // arguments in Python took 12 (8 chains of 128 x 128, one token: 11.8 us a call, so 6.0).  Anything out of the
-// ordinary (a subclass of Tensor, another device, a wrong type, shape or layout, a value outside its field) is left
+// ordinary (a subclass of Tensor, a torch function mode, another device, a wrong type, shape or layout, a value outside its field) is left
 // to the Python code, which says what is wrong with it: then this returns None and has done nothing.
 #include <Python.h>
 
@@ -10,6 +10,7 @@
 #include <climits>
 #include <cmath>
 
+#include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
 #include <ATen/ops/empty_like.h>
@@ -58,7 +59,7 @@ bool as_int(PyObject *hp, int f, int32_t &out) {
 // of a call that failed, or None
 PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     HANDLE_TH_ERRORS
-    if (!g_step || n != 12) Py_RETURN_NONE;
+    if (!g_step || n != 12 || at::impl::PythonTorchFunctionTLS::stack_len() > 0) Py_RETURN_NONE;
     const at::Tensor *t[8];
     for (int i = 0; i < 8; ++i) {
         t[i] = nullptr;

@@ -57,6 +57,8 @@ def test_what_is_out_of_the_ordinary_goes_through_python():
     call = lambda hp=ob.Hyper(), in_place=False, **kw: ob._step_native(*dict(x, **kw).values(), hp, in_place, dev, st)
     step = lambda hp=ob.Hyper(), **kw: ob.step(*dict(x, **kw).values(), hp)
 
+    call_outside = call()[0]
+
     class Sub(torch.Tensor):
         pass
 
@@ -67,6 +69,8 @@ def test_what_is_out_of_the_ordinary_goes_through_python():
         with pytest.raises(error):
             step(**kw)
     assert call(q=x["q"].as_subclass(Sub)) is None
+    with torch.device("cuda"):                                                      # (a torch function mode)
+        assert call() is None and torch.equal(step()[0], call_outside)
     assert call(dataclasses.replace(ob.Hyper(), eta=1)) is None                     # (an int: taken as Python takes it)
     assert torch.equal(step(dataclasses.replace(ob.Hyper(), eta=1))[0], step(dataclasses.replace(ob.Hyper(), eta=1.0))[0])
     assert type(call(ob.Hyper(eps=-1.0))) is int                                    # (a status: nothing was launched)
