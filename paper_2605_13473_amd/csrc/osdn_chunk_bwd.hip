@@ -62,7 +62,7 @@ __device__ __forceinline__ float scale_frag(float f, const float *g) { return f 
 // and dO, whose product and whose scaled fragments are formed at once; the gates) is prepared in
 // phase C of the chunk before, what phase C needs (-W, q) in phase B.  64 chains of 64 chunks, K = V =
 // 128 in bf16: 134 us; with the tiles staged through registers by loader wavefronts, 157 us (16 chains of
-// 128 chunks, V = 256: 206 against 282 us).
+// 128 chunks, V = 256: 206 against 282 us; with slices of 16 whose lines are asked for ahead 161).
 constexpr int CW_ = 8, CM_ = 2, CS_ = 2, CT_ = (CW_ + CM_ + CS_) * 64;     // wavefronts that compute, load, store; threads
 // ring depths, from what fits the LDS (see state_fwd)
 template <typename T, int K> constexpr int BC_NSB = sizeof(T) == 2 ? 2 : (K == 64 ? 2 : 1);
@@ -88,6 +88,9 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
     __shared__ __attribute__((aligned(1024))) char ringC[NSC * C_BYTES];
     __shared__ __attribute__((aligned(1024))) char dSb[VS * RK];        // dS' in the I/O type [v][kf]
     __shared__ __attribute__((aligned(1024))) char dEs[VS * RC];        // dE^T [v][i]
+    constexpr bool TOUCH = PRE && VS == 16;
+    constexpr int PF = 8;
+    __shared__ __attribute__((aligned(1024))) char dump[TOUCH ? 256 : 16];
 
     int chain, slice;
     chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
@@ -184,13 +187,59 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
         return;
     }
     if (storer) {
+        // TOUCH: this slice's share of the lines of a chunk's operands, in the order K~, -W, P, gates, q, dO, asked for PF chunks ahead
+        // (whole chunks all, as only a sequence's last may be ragged): lane l asks for the l-th, the (64 + l)-th and the
+        // (128 + l)-th, whose addresses step from chunk to chunk
+        constexpr int GS = (GV ? K : 3 * C) * 4, LK = C * RK / LINE, LP = C * RC / LINE, LG = (GV ? K : 2 * C) * 4 / LINE, L0 = 2 * LK + LP + LG;
+        constexpr int QR = RK / LINE;           // lines of a row of q
+        const int lpr = a.V * ES / LINE, all = L0 + C * QR + C * lpr, share = (all + a.V / VS - 1) / (a.V / VS);
+        // From 128 workgroups on, whose loads make lines from HBM late (training step, us, without and with: 256 workgroups, 128 chunks 834 and
+        // 794 (the kernel 202 and 161), 40 chunks 412 and 407; 128, 24 chunks 214 and 214; 16, 300 chunks 698 and 698; 64 with K = 64, 16 chunks
+        // 131.7 and 132.2; 32 with channel gates, 40 chunks 243 and 247).
+        const bool touches = TOUCH && gridDim.x >= 128 && wave == CW_ + CM_ + 1;
+        const char *lp[TOUCH ? 3 : 1] = {};
+        uint32_t ls[TOUCH ? 3 : 1] = {};
+        bool own[TOUCH ? 3 : 1] = {};
+        if (touches) {
+            const size_t t1 = ((size_t)bt * a.N + a.n1 - 1) * a.H + h;
+#pragma unroll
+            for (int j = 0; j < (TOUCH ? 3 : 1); ++j) {
+                const int i = lane + 64 * j, l = slice * share + i;
+                own[j] = i < share && l < all;
+                if (l < LK) { lp[j] = static_cast<const char *>(a.kt) + t1 * C * RK + l * LINE; ls[j] = C * RK; }
+                else if (l < 2 * LK) { lp[j] = static_cast<const char *>(a.Wn) + t1 * C * RK + (l - LK) * LINE; ls[j] = C * RK; }
+                else if (l < 2 * LK + LP) { lp[j] = static_cast<const char *>(a.Pm) + t1 * C * RC + (l - 2 * LK) * LINE; ls[j] = C * RC; }
+                else if (l < L0) { lp[j] = reinterpret_cast<const char *>(GV ? a.gamC : a.gates + C) + t1 * GS + (l - 2 * LK - LP) * LINE; ls[j] = GS; }
+                else if (l < L0 + C * QR) {
+                    const int r = (l - L0) / QR, c = (l - L0) % QR;
+                    lp[j] = static_cast<const char *>(a.q) + (GV ? t1 * C + r : (rows.first(a.n1 - 1) + r) * a.H + h) * RK + c * LINE;
+                    ls[j] = C * RK;
+                } else {
+                    const int r = (l - L0 - C * QR) / lpr;
+                    lp[j] = static_cast<const char *>(a.dO) + ((rows.first(a.n1 - 1) + r) * a.H + h) * a.V * ES + (l - L0 - C * QR) % lpr * LINE;
+                    ls[j] = C * a.V * ES;
+                }
+            }
+        }
+        int stand = a.n1 - 1;                   // the chunk that lp stands at
         for (int n = a.n1 - 1; n >= a.n0; --n) {
             const size_t bhn = ((size_t)bt * a.N + n) * a.H + h;
             __syncthreads();                                        // barrier 1
             tile_to_global<RK, VS>(static_cast<char *>(a.dS_ckpt) + (bhn * a.V + vs) * RK, RK, dSb, mt, CS_ * 64);
             __syncthreads();                                        // barrier 2
             tile_to_global<RC, VS>(static_cast<char *>(a.dEt) + (bhn * a.V + vs) * RC, RC, dEs, mt, CS_ * 64);
+            if (touches && n - PF >= a.n0) {
+                const size_t step = (size_t)(stand - (n - PF)) * a.H;
+                stand = n - PF;
+#pragma unroll
+                for (int j = 0; j < (TOUCH ? 3 : 1); ++j) {
+                    if (64 * j >= share) break;
+                    lp[j] -= step * ls[j];
+                    if (own[j]) touch(lp[j], lds_offset(dump));
+                }
+            }
         }
+        if (touches) wait_vm<0>();
         return;
     }
     TileFrag<T, RK> fK;

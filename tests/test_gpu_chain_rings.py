@@ -90,3 +90,16 @@ def test_lines_asked_for_ahead(B, T, H, K, V, channel_gate):
     if channel_gate:
         x["log_alpha"] = (-0.1 * np.random.default_rng(162).random((B, T, H, K))).astype(np.float32)
     compare_forward(x, ob.Hyper(eta=0.5, segments=1), True)
+
+
+@pytest.mark.parametrize("B,T,H,K,V", [
+    (4, 64 * 9 + 5, 8, 128, 64),     # 128 workgroups, more than two lines a lane; a ragged last chunk
+    (2, 64 * 10, 4, 64, 256),
+])
+@pytest.mark.parametrize("channel_gate", [False, True])
+def test_lines_asked_for_ahead_in_the_backward_pass(B, T, H, K, V, channel_gate):
+    """bf16, slices of 16 values, enough workgroups: the backward chain kernel asks ahead too, right to left."""
+    x = make_stress_inputs(B, T, H, K, V, seed=163, bf16=True, retention=0.97)
+    if channel_gate:
+        x["log_alpha"] = (-0.1 * np.random.default_rng(164).random((B, T, H, K))).astype(np.float32)
+    compare_backward(x, ob.Hyper(eta=0.5, segments=1), True)
