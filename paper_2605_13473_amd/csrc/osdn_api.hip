@@ -190,9 +190,6 @@ PrecondArgs precond_args(const osdn_params *p) {
     PrecondArgs a{};
     a.B = p->B; a.T = p->T; a.H = p->H; a.K = p->K;
     a.eta = p->eta; a.d_min = p->d_min; a.d_max = p->d_max; a.eps = p->eps;
-    const bool project = p->d_min <= p->d_max;
-    a.lo_in = !project ? -INFINITY : std::isinf(p->d_min) ? p->d_min : p->d_min + 2e-5f * std::fabs(p->d_min);
-    a.hi_in = !project ? INFINITY : std::isinf(p->d_max) ? p->d_max : p->d_max - 2e-5f * std::fabs(p->d_max);
     a.beta_aware = p->beta_aware;
     a.ret_vec = p->retention_per_channel;
     return a;

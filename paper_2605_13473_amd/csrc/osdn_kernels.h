@@ -73,10 +73,6 @@ struct PrecondArgs {
     const int *seq_chunks;    // [n_seqs + 1] or null; behind them the sequences, longest first [n_seqs]
     const float *d_first;     // packed sequences: d before the first token, [n_seqs,H,K] or null
     float eta, d_min, d_max, eps;
-    // What a sweep without the box has to stay within: so far from either face that a replay of the tokens one after the other,
-    // which rounds differently (64 sums: 4e-6 of d), stays off it too.  Such a chunk is marked by the sign of its tokens' sum k^2: the
-    // backward pass knows then that every mask bit is set.
-    float lo_in, hi_in;
     int beta_aware;
     Rows rows;                // of k, beta, retention
     const void *k;            // [B,T,H,K] io
@@ -89,7 +85,7 @@ struct PrecondArgs {
     float *d_out;             // [B,H,K]
     float *d_ckpt;            // [B,H,T/64,K] or null
     float *tok_scalars;       // [B,T,H,4] or null: per token (step, <d,k^2>, sum k^2, unused), kept for the backward; without
-                              // retention the sum is kept with its sign flipped in chunks whose coordinates all stay off the box
+                              // retention the sum is kept with its sign flipped in chunks whose coordinates all stay well off the box
     void *k_tail;             // [sequences,64,H,K] io: k of ragged last chunks, whole, kept for the backward
     float *beta_tail, *ret_tail;      // [sequences,64,H], as retention
     // Sweeps over the whole sequence (pieces > 0, plain batches only): a chain is cut into

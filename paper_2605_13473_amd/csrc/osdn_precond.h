@@ -2,6 +2,8 @@
 #pragma once
 #include "osdn_kernels.h"
 
+#include <cfloat>
+
 namespace osdn {
 
 constexpr int P1_MAX_SWEEPS = 66;       // 64 guarantee exactness
@@ -17,6 +19,14 @@ __device__ __forceinline__ float clip3(float x, float lo, float hi) { return __b
 template <bool HAS_RET>
 __device__ __forceinline__ float d_bar(float r, float d, float step, float s) {
     return HAS_RET ? __builtin_fmaf(step, s, r * d) : __builtin_fmaf(step, s, d);
+}
+// Without retention the forward sweep marks a chunk, by the sign of its tokens' sum k^2, if a replay of the tokens one after the other
+// (lands_inside, below) finds all of them inside the box: it was swept without the box, so that every c >= 0 and d rose, and d ends at or
+// below this bound.  At the lower face, where d begins, rounding then does not matter; at the upper one the sums over runs and the
+// replay may differ by the rounding of 64 sums each, 8e-6 of the largest |d|, which is at most that of the larger face.  (No lower
+// face: -infinity, and nothing is marked.)
+__device__ __forceinline__ float mark_bound(float lo, float hi) {
+    return isinf(hi) ? FLT_MAX : hi - 2e-5f * fmaxf(fabsf(lo), fabsf(hi));
 }
 // Did the step land inside the box (the projection's gradient mask)?  Decided from the signs
 // of (r d - face) + step s, each evaluated with a single rounding at its own scale, rather

@@ -49,8 +49,6 @@
 // settled chain return at once).
 #include "osdn_precond.h"
 
-#include <cfloat>
-
 namespace osdn {
 
 // RET: 0 = no retention, 1 = one gate per (token, head), 2 = one per coordinate (diag(r_t))
@@ -104,10 +102,6 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
     const size_t bth = (size_t)bt * a.H + h;                  // indexes the per-chunk buffers
     const bool project = a.d_min <= a.d_max;
     const float lo = project ? a.d_min : -INFINITY, hi = project ? a.d_max : INFINITY;
-    // (formed again at K = 128: the compiler keeps the sweep's other operands where it had them, 32 chunks of 64 chains 212.5 us;
-    // as arguments 214.5; at K = 64 the other way round, 2 chains of 4 chunks 39.8 and 39.6)
-    const float lo_in = K == 64 ? a.lo_in : isinf(lo) ? lo : lo + 2e-5f * fabsf(lo);
-    const float hi_in = K == 64 ? a.hi_in : isinf(hi) ? hi : hi - 2e-5f * fabsf(hi);
     const int N = (a.T + C - 1) / C;
     const uint32_t kstride = (uint32_t)a.H * K;   // elements between consecutive tokens
     const ChainRows<RAG> rows(a.rows, a.seq_chunks, b, a.n0);
@@ -397,14 +391,14 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
                     d[e] = dst[e];
 #pragma unroll
                     for (int j = 0; j < NRUN - 1; ++j) d[e] += j < run ? Bm[j][e] : 0.f;
-                    within = within && d[e] >= lo_in;
+                    within = within && d[e] >= lo;
 #pragma unroll
                     for (int u = 0; u < RUN; ++u) {
                         dtr[u][e] = d[e];
                         vp[u] = e == 0 ? sv[u][e] * d[e] : __builtin_fmaf(sv[u][e], d[e], vp[u]);
                         d[e] = __builtin_fmaf(cv[u], sv[u][e], d[e]);
                     }
-                    within = within && d[e] <= hi_in;
+                    within = within && d[e] <= hi;
                     dend[e] = d[e];
                 }
                 within = within && (c_cur >= 0.f || !project);
@@ -461,9 +455,17 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
                 }
             }
         }
+        // (RET == 0) off the box, by the margin at the upper face: d only rose, so that what the last run says counts (32 chunks of 64
+        // chains: 93.2 us; 92.1 where the sweeps themselves kept the margin, which swept a chain that stands within it in vain)
+        bool clear = true;
+        if (RET == 0) {
+#pragma unroll
+            for (int e = 0; e < CPT; ++e) clear = clear && dend[e] <= mark_bound(lo, hi);
+            clear = FAST && !boxed && __all(clear);
+        }
         if (TILES || (a.tok_scalars && valid)) {       // (eight lanes store the same)
             const size_t th = ((size_t)bt * a.T + t0) * a.H + h;
-            lane_elem(reinterpret_cast<float4 *>(a.tok_scalars) + th, (run * RUN + u_own) * a.H) = make_float4(c_acc, p_acc, RET == 0 ? (FAST && !boxed ? -nraw : fabsf(nraw)) : nraw, (float)sweeps_used);
+            lane_elem(reinterpret_cast<float4 *>(a.tok_scalars) + th, (run * RUN + u_own) * a.H) = make_float4(c_acc, p_acc, RET == 0 ? (clear ? -nraw : fabsf(nraw)) : nraw, (float)sweeps_used);
         }
         if (PIECES && tid < K) {                 // the accepted run maps, applied after the piece so far
             const int acc = pub == 0 ? NBUF - 1 : pub - 1;       // (the last published ones were dropped)

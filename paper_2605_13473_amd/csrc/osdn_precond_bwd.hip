@@ -44,9 +44,9 @@ __global__ __launch_bounds__(K) void precond_mask_kernel(PrecondBwdArgs a) {
     const int N = a.T / C;
     const size_t bh = (size_t)b * a.H + h;
     const size_t tokc = ((size_t)b * a.T + (size_t)n * C) * a.H + h;
-    // Without retention, a chunk that the forward sweep marked: every bit is set, and neither k nor d is read (no chunk near
+    // Without retention, a chunk that the forward sweep marked (mark_bound; its last run says): every bit is set, and neither k nor d is read (no chunk near
     // the box: 1072 chains, 78 us of 3346; 64 chains of 64 chunks, beside bwd_chain, training step 1011 -> 998).
-    if (!HAS_RET && __builtin_bit_cast(int, a.tok_scalars[tokc * 4 + 2]) < 0) {
+    if (!HAS_RET && __builtin_bit_cast(int, a.tok_scalars[(tokc + (size_t)(C - 1) * a.H) * 4 + 2]) < 0) {
         a.masks[(bh * N + n) * K + tid] = make_uint2(0xffffffffu, 0xffffffffu);
         return;
     }
