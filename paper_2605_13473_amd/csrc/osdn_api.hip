@@ -589,22 +589,14 @@ static int bwd_impl(const osdn_params *p, const void *q, const void *k, const vo
 
     const int N = p->T / C;
     const long long chains = (long long)(pk.n_seqs ? pk.n_seqs : p->B) * p->H;
-    // Slices of bwd_chain.  bf16 takes 32 values beside a phase-1 chain: with 16 its workgroups hold twice the CUs, and what they
-    // take from that chain, which bounds the pass there, costs more than the kernel gains.  With everything on one stream it takes 16 while the
-    // workgroups find a CU each (training step, us, 32 and 16: 16 chains of 128 chunks, V = 256 848 and 836, of 24, V = 128 224 and
-    // 214, without retention of 32 245 and 234; 8 of 16 163 and 158; 2 of 300 799 and 697; 32 of 40 416 and 410).
-    // fp32 I/O at K = 64: 16 values while the
-    // workgroups find a CU each (64 chains of 32 chunks, V = 64: training step 705 against 721 us; 16 chains of
-    // 128 chunks, V = 128: 1240 against 1400), above that 32, which read the shared tiles half as often
-    // (256 chains of 16 chunks, V = 64: 1109 against 1155; 128 chains, V = 256: 1330 against 1404).
-    c.narrow_slices = !bf && (p->K == 128 || chains * (p->V / 16) <= NUM_CU);
+    c.narrow_slices = narrow_backward(p, chains, true);
     const long long chain_wgs = chains * (p->V / (c.narrow_slices ? 16 : 32)) + chains;     // of the chain kernels of both phases
     int pieces = 0, piece_chunks = 0, piece_sweeps = 0;
     if (!solved && p->segments <= 1) pieces_plan(p, N, chains, pk.n_seqs != 0, retention != nullptr, true, pieces, piece_chunks, piece_sweeps);
     int S = pieces ? 1 : segment_count(p->segments, N, pk.longest, chains, chain_wgs, true, (bf ? 2 : 1) * NUM_CU);   // (bwd_post: two workgroups a CU with bf16 I/O)
     Pipeline *pl = S > 1 ? pipeline_for(st) : nullptr;
     if (!pl) S = 1;
-    if (bf && S == 1) c.narrow_slices = chains * (p->V / 16) <= NUM_CU;
+    if (S == 1) c.narrow_slices = narrow_backward(p, chains, false);
     auto seg_range = [&](int sidx, int &n0, int &n1) { n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1); };
     auto phase2 = [&](int kid, int sidx) {
         seg_range(sidx, c.n0, c.n1);

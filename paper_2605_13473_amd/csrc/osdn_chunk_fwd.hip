@@ -233,8 +233,9 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     __shared__ __attribute__((aligned(1024))) char Eo[VS * RC];         // E^T  [v][i]
     __shared__ __attribute__((aligned(1024))) char Ew[GV ? 16 : VS * RC];   // (rho E)^T
 
-    int chain, slice;
-    chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
+    int chain = 0, slice = 0;
+    chain_slice_of(blockIdx.x, gridDim.x, a.V / VS, chain, slice);
+    if (chain >= (a.seq_chunks ? a.n_seqs : a.B) * a.H) return;
     const int vs = slice * VS, h = chain % a.H;
     int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
@@ -458,8 +459,9 @@ __global__ __launch_bounds__(RT_<VS>, 1) void state_fwd_run_kernel(ChunkArgs a) 
     __shared__ __attribute__((aligned(1024))) f32x4 Ub[NV][4][64];          // (T diag(beta)) V as accumulator tiles
     __shared__ __attribute__((aligned(1024))) char dump[256];
 
-    int chain, slice;
-    chain_slice_of(blockIdx.x, a.V / VS, (a.seq_chunks ? a.n_seqs : a.B) * a.H, chain, slice);
+    int chain = 0, slice = 0;
+    chain_slice_of(blockIdx.x, gridDim.x, a.V / VS, chain, slice);
+    if (chain >= (a.seq_chunks ? a.n_seqs : a.B) * a.H) return;
     const int vs = slice * VS, h = chain % a.H;
     int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
@@ -811,7 +813,7 @@ int launch_chunk_prep(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
 }
 template <bool BF16, bool GV, int VS>
 static int launch_state_t(const ChunkArgs &a, hipStream_t st) {
-    dim3 grid((a.V / VS) * a.H * (a.seq_chunks ? a.n_seqs : a.B)), block(BF16 ? RT_<VS> : CT_);
+    dim3 grid(chain_workgroups(a.V / VS, a.H * (long long)(a.seq_chunks ? a.n_seqs : a.B), VS == 16)), block(BF16 ? RT_<VS> : CT_);
     if (GV && !a.gamC) return -1;
     auto launch = [&](auto k) {
         constexpr int K = decltype(k)::value;

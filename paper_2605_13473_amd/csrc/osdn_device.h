@@ -11,6 +11,8 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "osdn_plan.h"
+
 namespace osdn {
 
 typedef __bf16 bf16;
@@ -420,22 +422,6 @@ __device__ __forceinline__ float wave_suffix_sum(float x, int lane) {
     }
     return x;
 }
-
-// Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  The chain kernels
-// run V/VS workgroups per (batch, head) chain that all read the same W / K~ / Q tiles: this
-// maps a 1-D workgroup id so that the slices of one chain share an XCD (and its L2).
-constexpr int NUM_XCD = 8;
-__device__ __forceinline__ void chain_slice_of(int wg, int nslices, int nchains, int &chain, int &slice) {
-    if (nchains % NUM_XCD == 0) {
-        const int xcd = wg % NUM_XCD, j = wg / NUM_XCD;
-        slice = j % nslices;
-        chain = xcd + NUM_XCD * (j / nslices);
-    } else {
-        slice = wg % nslices;
-        chain = wg / nslices;
-    }
-}
-
 
 // Packed sequences: the one that the i-th chains of a launch (one per head) work on, longest first (the order stands behind
 // seq_chunks): workgroups are dealt out in order, and a long chain that starts last runs by itself at the end.  54 documents of up to

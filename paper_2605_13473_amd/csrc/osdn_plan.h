@@ -1,5 +1,5 @@
 // The rules by which osdn_fwd and osdn_bwd cut the work: segments of the sequence, pieces of a chain, the solved form of the
-// reverse sweep.  Plain host code without a device in it, so that the rules can be tested by themselves.
+// reverse sweep, and the slices of the chain kernels.  Plain code without a device in it, so that the rules can be tested by themselves.
 #pragma once
 #include "../../include/osdn.h"
 
@@ -7,8 +7,31 @@
 
 namespace osdn {
 
-constexpr int NUM_CU = 256;
+constexpr int NUM_CU = 256, NUM_XCD = 8;         // (workgroups are dealt to the XCDs in turn; each has its own L2)
 constexpr int MAX_SEGMENTS = 16, MAX_PIECES = 512, MAX_PIECE_SWEEPS = 13;
+
+// The chain kernels run V/VS workgroups (slices) per chain that all read the same tiles (-W, K~, P, ...): they are to share an XCD.
+// Where the chains are not a multiple of the XCDs, narrow slices (VS = 16) are filled up to one with workgroups that end at once, if all still
+// find a CU each; else the slices of a chain stand side by side on as many XCDs.  20 chains of 40 chunks, V = 128, us, side by
+// side and filled up: forward 161 and 136, backward 222 and 189 (with slices of 32 203); of 128 chunks, forward 446 and 399; 28 chains of
+// 128 chunks, forward 605 and 491; 12 of 64, V = 256, 181 and 163; fp32, 10 of 32, backward 336 and 328.  Not up to eight chains, which leave the L2s
+// time (2 chains of 512 chunks, V = 256, forward 598 and 608, 6 of 64 with K = 64 118 and 122, 4 of 512 599 and 555), nor for slices of 32
+// (50 chains of 64 chunks, forward 360 and 366, backward 521 and 527).
+inline bool chains_filled_up(int nslices, long long chains, bool narrow) {
+    return narrow && chains > NUM_XCD && (chains + NUM_XCD - 1) / NUM_XCD * nslices * NUM_XCD <= NUM_CU;
+}
+inline int chain_workgroups(int nslices, long long chains, bool narrow) {
+    return (int)((chains_filled_up(nslices, chains, narrow) ? (chains + NUM_XCD - 1) / NUM_XCD * NUM_XCD : chains) * nslices);
+}
+
+// which slice of which chain a workgroup of such a launch is (constexpr: for the device too); a chain that there is not: none
+constexpr bool slices_share_xcd(int workgroups, int nslices) { return workgroups % (NUM_XCD * nslices) == 0; }
+constexpr void chain_slice_of(int wg, int workgroups, int nslices, int &chain, int &slice) {
+    const bool share = slices_share_xcd(workgroups, nslices);
+    const int xcd = wg % NUM_XCD, j = share ? wg / NUM_XCD : wg;
+    slice = j % nslices;
+    chain = share ? xcd + NUM_XCD * (j / nslices) : j / nslices;
+}
 
 // Number of segments for a sequence of N chunks (params->segments > 0 overrides it; 1 = no
 // pipelining).  A segment more shortens the stretch of phase 1 that runs with nothing beside it (the
@@ -156,6 +179,23 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
     if (P < 2) return;
     pieces = P; piece_chunks = len;
     if (p->p1_piece_sweeps >= 1) sweeps = p->p1_piece_sweeps;
+}
+
+// Slices of bwd_chain, 16 values or 32 (beside: a phase-1 chain runs on another stream; fp32 I/O at K = 128 always takes 16).
+//  - bf16 takes 32 values beside a phase-1 chain: with 16 its workgroups hold twice the CUs, and what they
+//    take from that chain, which bounds the pass there, costs more than the kernel gains.  With everything on one stream it takes 16 while the
+//    workgroups find a CU each (training step, us, 32 and 16: 16 chains of 128 chunks, V = 256 848 and 836, of 24, V = 128 224 and
+//    214, without retention of 32 245 and 234; 8 of 16 163 and 158; 2 of 300 799 and 697; 32 of 40 416 and 410), unless that puts the
+//    slices of a chain on more XCDs than slices of 32 (backward pass: 21 chains of 32 chunks, V = 192 167 and 182).
+//  - fp32 I/O at K = 64: 16 values while the
+//    workgroups find a CU each (64 chains of 32 chunks, V = 64: training step 705 against 721 us; 16 chains of
+//    128 chunks, V = 128: 1240 against 1400), above that 32, which read the shared tiles half as often
+//    (256 chains of 16 chunks, V = 64: 1109 against 1155; 128 chains, V = 256: 1330 against 1404).
+inline bool narrow_backward(const osdn_params *p, long long chains, bool beside) {
+    const int slices = p->V / 16;
+    if (p->io_dtype == OSDN_F32) return p->K == 128 || chains * slices <= NUM_CU;
+    return !beside && chains * slices <= NUM_CU &&
+           (chains <= NUM_XCD || chains % NUM_XCD == 0 || slices >= 2 * NUM_XCD || chains_filled_up(slices, chains, true));
 }
 
 // Without retention, chunks that never met the box can take the solved form of the reverse

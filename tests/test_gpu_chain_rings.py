@@ -103,3 +103,17 @@ def test_lines_asked_for_ahead_in_the_backward_pass(B, T, H, K, V, channel_gate)
     if channel_gate:
         x["log_alpha"] = (-0.1 * np.random.default_rng(164).random((B, T, H, K))).astype(np.float32)
     compare_backward(x, ob.Hyper(eta=0.5, segments=1), True)
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+@pytest.mark.parametrize("B,T,H,K,V", [
+    (1, 64 * 3, 9, 128, 64),         # filled up to 16 chains
+    (3, 64 * 2 + 9, 10, 64, 128),    # 32
+    (3, 64 * 2, 7, 128, 192),        # not filled up: 24 chains of 12 slices find no CU each
+    (2, 64, 5, 64, 256),             # 16 chains of 16 slices: the whole chip
+])
+def test_chains_that_are_not_a_multiple_of_the_xcds(B, T, H, K, V, bf16):
+    x = make_stress_inputs(B, T, H, K, V, seed=165, bf16=bf16, retention=0.97)
+    hp = ob.Hyper(eta=0.5, segments=1)
+    compare_forward(x, hp, bf16)
+    compare_backward(x, hp, bf16)

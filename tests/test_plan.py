@@ -9,9 +9,35 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 MAIN = r"""
 #include "osdn_plan.h"
 #include <cstdio>
+#include <vector>
 using namespace osdn;
 // in: chains chunks K V bf16 retention(0, 1, 2) eta forced_pieces backward; out: pieces, chunks of one, sweeps, solved, segments, begins
-int main() {
+// or, with an argument, in: slices chains narrow V bf16 K; out: workgroups, 1 if every slice of every chain is one of them once, 1 if the slices of
+// a chain share an XCD, slices of 16 in the backward pass beside a phase-1 chain and without one
+int slices() {
+    int ns, narrow, V, bf, K; long long ch;
+    while (std::scanf("%d %lld %d %d %d %d", &ns, &ch, &narrow, &V, &bf, &K) == 6) {
+        osdn_params p{};
+        p.K = K; p.V = V; p.io_dtype = bf ? OSDN_BF16 : OSDN_F32;
+        const int wgs = chain_workgroups(ns, ch, narrow);
+        std::vector<int> seen(ch * ns, 0), xcd(ch, -1);
+        bool share = true;
+        for (int w = 0; w < wgs; ++w) {
+            int c = -1, s = -1;
+            chain_slice_of(w, wgs, ns, c, s);
+            if (c >= ch) continue;
+            ++seen.at(c * ns + s);
+            if (xcd[c] >= 0 && xcd[c] != w % NUM_XCD) share = false;
+            xcd[c] = w % NUM_XCD;
+        }
+        bool once = true;
+        for (int x : seen) once = once && x == 1;
+        std::printf("%d %d %d %d %d\n", wgs, once, share, narrow_backward(&p, ch, true), narrow_backward(&p, ch, false));
+    }
+    return 0;
+}
+int main(int argc, char **) {
+    if (argc > 1) return slices();
     long long ch; int N, K, V, bf, ret, forced, back; float eta;
     while (std::scanf("%lld %d %d %d %d %d %f %d %d", &ch, &N, &K, &V, &bf, &ret, &eta, &forced, &back) == 9) {
         osdn_params p{};
@@ -35,10 +61,10 @@ def plan(tmp_path_factory):
     (d / "main.cpp").write_text(MAIN)
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, "-o", str(d / "plan"), str(d / "main.cpp")])
 
-    def ask(calls):
+    def ask(calls, *which):
         """calls: (chains, chunks, K, V, bf16, retention, eta, forced, backward) each."""
         text = "\n".join(" ".join(str(x) for x in c) for c in calls) + "\n"
-        r = subprocess.run([str(d / "plan")], input=text, capture_output=True, text=True, check=True)
+        r = subprocess.run([str(d / "plan"), *which], input=text, capture_output=True, text=True, check=True)
         return [[int(x) for x in line.split()] for line in r.stdout.splitlines()]
     return ask
 
@@ -113,3 +139,18 @@ def test_solved_form_without_retention(plan, chains, K, V, bf16, least):
     for N in (1, 8, 15, 16, 64, 1000):
         assert plan([(chains, N, K, V, bf16, 0, 0.003, 0, 1)])[0][3] == (least is not None and N >= least), N
     assert not any(r[3] for r in plan([(chains, 64, K, V, bf16, ret, 0.003, 0, 1) for ret in (1, 2)]))
+
+
+def test_slices_of_the_chain_kernels(plan):
+    calls = [(V // (16 if narrow else 32), ch, narrow, V, bf, K)
+             for V in range(64, 513, 64) for ch in (*range(1, 70), 127, 128, 256, 1000) for narrow in (0, 1) for bf in (0, 1) for K in (64, 128)]
+    for (ns, ch, narrow, V, bf, K), (wgs, once, share, beside, alone) in zip(calls, plan(calls, "slices")):
+        assert once, (ns, ch)
+        filled = narrow and ch > 8 and -(-ch // 8) * 8 * ns <= 256
+        assert wgs == (-(-ch // 8) * 8 if filled else ch) * ns
+        assert share or not (filled or ch % 8 == 0)
+        if bf:
+            # never on more XCDs than slices of 32, but with up to eight chains
+            assert not beside and alone == (ch * (V // 16) <= 256 and (ch <= 8 or ch % 8 == 0 or V >= 256 or -(-ch // 8) * (V // 16) <= 32))
+        else:
+            assert beside == alone == (K == 128 or ch * (V // 16) <= 256)
