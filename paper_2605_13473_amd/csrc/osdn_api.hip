@@ -441,6 +441,7 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     // still find a CU each (beside those of phase 1, unless phase 1 runs ahead as sweeps over pieces):
     // its time per chunk is latency, not work, and half the work per workgroup shortens it.
     c.narrow_slices = cg.narrow_slices = cs.narrow_slices = chains * (p->V / 16) + (pieces ? 0 : chains) <= NUM_CU;
+    c.asks_ahead = cg.asks_ahead = cs.asks_ahead = asks_ahead(p, (long long)p->B * N * p->H, chains);
     auto seg_range = [&](int sidx, int &n0, int &n1) {
         if (crowded) { n0 = seg_begin_grow(N, S, sidx, 1.7); n1 = seg_begin_grow(N, S, sidx + 1, 1.7); return; }
         n0 = seg_begin(N, S, sidx); n1 = seg_begin(N, S, sidx + 1);

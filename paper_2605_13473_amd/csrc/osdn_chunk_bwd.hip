@@ -64,7 +64,7 @@ __device__ __forceinline__ float scale_frag(float f, const float *g) { return f 
 // 128 in bf16: 134 us; with the tiles staged through registers by loader wavefronts, 157 us (16 chains of
 // 128 chunks, V = 256: 206 against 282 us; with slices of 16 whose lines are asked for ahead 161).
 constexpr int CW_ = 8, CM_ = 2, CS_ = 2, CT_ = (CW_ + CM_ + CS_) * 64;     // wavefronts that compute, load, store; threads
-// ring depths, from what fits the LDS (see state_fwd)
+// ring depths (chunks of operands in LDS) of what phase B takes and of what phase C takes, from what fits the LDS
 template <typename T, int K> constexpr int BC_NSB = sizeof(T) == 2 ? 2 : (K == 64 ? 2 : 1);
 template <typename T, int K> constexpr int BC_NSC = sizeof(T) == 2 ? 2 : 1;
 
@@ -194,9 +194,12 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
         constexpr int GS = (GV ? K : 3 * C) * 4, LK = C * RK / LINE, LP = C * RC / LINE, LG = (GV ? K : 2 * C) * 4 / LINE, L0 = 2 * LK + LP + LG;
         constexpr int QR = RK / LINE;           // lines of a row of q
         const int lpr = a.V * ES / LINE, all = L0 + C * QR + C * lpr, share = (all + a.V / VS - 1) / (a.V / VS);
-        // From 128 workgroups on, whose loads make lines from HBM late (training step, us, without and with: 256 workgroups, 128 chunks 834 and
-        // 794 (the kernel 202 and 161), 40 chunks 412 and 407; 128, 24 chunks 214 and 214; 16, 300 chunks 698 and 698; 64 with K = 64, 16 chunks
-        // 131.7 and 132.2; 32 with channel gates, 40 chunks 243 and 247).
+        // From 128 workgroups on, whose loads make lines from HBM late (backward pass, us, without and with, calls repeated, then with the caches
+        // cleared between them: 128 workgroups, 16 chains of 32 chunks 134.0 and 134.8, 169.6 and 160.0, of 128 chunks 415 and 382, 465 and 418, a
+        // gate per channel, 32 chunks 149.2 and 149.7, 194.2 and 185.2, 4 chains of 128, V = 512, on eight XCDs each 288 and 276, 357 and 315;
+        // 256, 16 chains of 32, V = 256, a gate per channel 188 and 179, 216 and 204; 160, 10 of 32, V = 384 152.7 and 156.0, 198 and 187;
+        // training step, calls repeated: 16, 300 chunks 698 and 698; 64 with K = 64, 16 chunks 131.7 and 132.2; 32 with channel gates, 40 chunks 243
+        // and 247).
         const bool touches = TOUCH && gridDim.x >= 128 && wave == CW_ + CM_ + 1;
         const char *lp[TOUCH ? 3 : 1] = {};
         uint32_t ls[TOUCH ? 3 : 1] = {};

@@ -432,8 +432,8 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
 // What bounds it (cycles a chunk, measured with the clock in every wavefront; 16 chains of 512 chunks, K = V = 128, slices of
 // 16): the chain itself takes 1050 of 1980; the rest is waiting for the loaders, whose accesses (22 of 1 KB each) are
 // taken the slower the more lines are on their way from HBM, and by the stores beside them (without stores 1500; with both
-// out of the L2 1650).  Hence the lines that the slices of a chain share (they sit on one XCD) are asked for PF chunks ahead,
-// each slice a share of them, 4 bytes a line: without that 2360.  Eight wavefronts with a tile of 16 x 16 each, S and E all
+// out of the L2 1650).  Hence the lines that the slices of a chain share are asked for PF chunks ahead where they sit on one XCD and
+// come from HBM (asks_ahead in osdn_plan.h), each slice a share of them, 4 bytes a line: without that 2360.  Eight wavefronts with a tile of 16 x 16 each, S and E all
 // through LDS, read 82 KB of LDS a chunk instead of 44 (at 64 bytes a clock) and took 2250: state_fwd 535 -> 467 us; 16 chains
 // of 128 chunks, V = 256 155 -> 139; in all 1026 -> 944 and 862 -> 845 us.  With -W and T diag(beta) straight from memory
 // to registers, 16 rows of 64 bytes an access, 2750.
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(RT_<VS>, 1) void state_fwd_run_kernel(ChunkArgs a) 
             sw = next(sw, NSW);
             __syncthreads();                                        // barrier 2
             keep();
-            if (VS == 16 && n + PF < a.n1) ahead(n + PF);
+            if (VS == 16 && a.asks_ahead && n + PF < a.n1) ahead(n + PF);
         }
         wait_vm<0>();
         return;

@@ -182,6 +182,7 @@ struct ChunkArgs {
     void *Pm;                         // [B,N,H,64,64] io  P = tril(Gamma . Q K~^T), from output_fwd for the backward
                                       //                   chain (null: not kept; Tm may be null likewise)
     int narrow_slices;                // chain kernels: 16 rows of the state per workgroup instead of 32 (bwd_chain with fp32 at K = 128: always 16)
+    int asks_ahead;                   // state_fwd with bf16 I/O and slices of 16: the lines of its operands ahead of the tiles
     // one state gate per key channel (gate_vec: log_alpha is [B,T,H,K]; forward only): chunk_prep
     // folds the cumulative channel decays Gamma into the operands and leaves
     int gate_vec;

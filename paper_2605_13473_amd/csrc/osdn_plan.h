@@ -33,6 +33,21 @@ constexpr void chain_slice_of(int wg, int workgroups, int nslices, int &chain, i
     chain = share ? xcd + NUM_XCD * (j / nslices) : j / nslices;
 }
 
+// state_fwd_run_kernel with slices of 16: whether it asks for the lines of its operands ahead of its tiles (tiles: chunks of all chains).
+// That pays where they come from HBM and the slices that share them share an L2: what the forward pass reads and writes around the chain
+// kernel (-W, K~, T diag(beta), V, the checkpoint of S, E; three more with a gate per channel) is then more than the 256 MB
+// of the last level cache hold beside the inputs.  Forward pass, us, without and with, K = V = 128 unless said, calls repeated: 16 chains of 64
+// chunks (106 MB) 172.9 and 174.5, of 96 (160) 244.4 and 247.8, of 128 (213) 343 and 338, of 256 with retention 542 and 509; 24 of 48 (120)
+// 178.7 and 180.6, of 128 (319) 456 and 451; V = 256: 16 of 64 (172) 180.8 and 182.7, of 128 (344) 331 and 324, 8 of 128 (172) 219.8 and 231.3, of
+// 256 430 and 415; V = 64: 32 of 64 (147) 264.5 and 265.8, of 128 (295) 478 and 456, 8 of 512 (295) 945 and 890; K = V = 64: 8 of 512 (197)
+// 707 and 729; V = 128: 16 of 512 (590) 747 and 738; a gate per channel: 16 of 64 (156) 207.9 and 209.9, 24 of 64 (233) 284 and 278, 16 of 128 (311)
+// 413 and 393.  With the caches cleared between calls the line is the same (16 of 96 277 and 280, of 128 357 and 357; 8 of 512 773 and 722).  Slices
+// on eight XCDs: 4 chains of 512 585 and 598, 2 of 512 431 and 463.
+inline bool asks_ahead(const osdn_params *p, long long tiles, long long chains) {
+    const long long K = p->K, V = p->V, kept = 2 * (64 * 64 + (p->gate_per_channel ? 5 : 2) * 64 * K + 2 * 64 * V + V * K);
+    return slices_share_xcd(chain_workgroups(p->V / 16, chains, true), p->V / 16) && tiles * kept > 200ll << 20;
+}
+
 // Number of segments for a sequence of N chunks (params->segments > 0 overrides it; 1 = no
 // pipelining).  A segment more shortens the stretch of phase 1 that runs with nothing beside it (the
 // first segment of the forward pass, the last of the backward pass) and costs launches, cross-stream

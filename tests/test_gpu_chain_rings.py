@@ -85,7 +85,8 @@ def test_token_tensors_off_a_16_byte_boundary(B, H, K, V, segments, bf16, offset
 ])
 @pytest.mark.parametrize("channel_gate", [False, True])
 def test_lines_asked_for_ahead(B, T, H, K, V, channel_gate):
-    """bf16, few chains: the forward chain kernel asks for the lines of a chunk eight chunks ahead of its tiles."""
+    """bf16, few chains: the forward chain kernel with slices of 16, in lengths about the eight chunks by which it asks for lines ahead
+    (which it does for longer calls: below)."""
     x = make_stress_inputs(B, T, H, K, V, seed=161, bf16=True, retention=0.97)
     if channel_gate:
         x["log_alpha"] = (-0.1 * np.random.default_rng(162).random((B, T, H, K))).astype(np.float32)
@@ -117,3 +118,30 @@ def test_chains_that_are_not_a_multiple_of_the_xcds(B, T, H, K, V, bf16):
     hp = ob.Hyper(eta=0.5, segments=1)
     compare_forward(x, hp, bf16)
     compare_backward(x, hp, bf16)
+
+
+@pytest.mark.parametrize("B,T,H,K,V,channel_gate", [
+    (2, 64 * 160, 8, 128, 128, False),
+    (2, 64 * 160 + 5, 8, 128, 128, False),       # a ragged last chunk
+    (1, 64 * 400 + 63, 8, 128, 64, False),       # more than 64 lines a slice
+    (1, 64 * 600, 8, 64, 64, False),
+    (1, 64 * 100, 8, 128, 512, False),           # 32 slices
+    (3, 64 * 120, 4, 128, 256, False),           # filled up to 16 chains
+    (2, 64 * 100 + 1, 8, 128, 128, True),
+])
+def test_a_long_call_that_asks_for_lines_ahead(B, T, H, K, V, channel_gate):
+    """bf16, slices that share an XCD and more than the last level cache holds: the same bits as two calls of half the length, which do
+    not ask for lines ahead."""
+    g = torch.Generator(device="cuda").manual_seed(167)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    unit = lambda a: (a / a.norm(dim=-1, keepdim=True)).bfloat16()
+    q, k, v, beta = unit(rnd(B, T, H, K)), unit(rnd(B, T, H, K)), rnd(B, T, H, V).bfloat16(), torch.sigmoid(rnd(B, T, H))
+    la = -0.1 * torch.rand(B, T, H, K, device="cuda", generator=g) if channel_gate else -torch.nn.functional.softplus(rnd(B, T, H))
+    hp = ob.Hyper(eta=0.05, segments=1, p1_pieces=-1)         # (pieces go by the length of the call)
+    o, S, d, _ = ob.forward(q, k, v, beta, la, hp=hp)
+    m = T // 128 * 64
+    part = lambda a, b: [x[:, a:b].contiguous() for x in (q, k, v, beta, la)]
+    o1, S1, d1, _ = ob.forward(*part(0, m), hp=hp)
+    o2, S2, d2, _ = ob.forward(*part(m, T), None, d1, S1, hp=hp)
+    same = [torch.equal(a, b) for a, b in ((d, d2), (S, S2), (o[:, :m], o1), (o[:, m:], o2))]
+    assert all(same), same

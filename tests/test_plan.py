@@ -13,7 +13,8 @@ MAIN = r"""
 using namespace osdn;
 // in: chains chunks K V bf16 retention(0, 1, 2) eta forced_pieces backward; out: pieces, chunks of one, sweeps, solved, segments, begins
 // or, with an argument, in: slices chains narrow V bf16 K; out: workgroups, 1 if every slice of every chain is one of them once, 1 if the slices of
-// a chain share an XCD, slices of 16 in the backward pass beside a phase-1 chain and without one
+// a chain share an XCD, slices of 16 in the backward pass beside a phase-1 chain and without one, lines asked
+// for ahead in a long call
 int slices() {
     int ns, narrow, V, bf, K; long long ch;
     while (std::scanf("%d %lld %d %d %d %d", &ns, &ch, &narrow, &V, &bf, &K) == 6) {
@@ -32,7 +33,7 @@ int slices() {
         }
         bool once = true;
         for (int x : seen) once = once && x == 1;
-        std::printf("%d %d %d %d %d\n", wgs, once, share, narrow_backward(&p, ch, true), narrow_backward(&p, ch, false));
+        std::printf("%d %d %d %d %d %d\n", wgs, once, share, narrow_backward(&p, ch, true), narrow_backward(&p, ch, false), asks_ahead(&p, 1 << 20, ch));
     }
     return 0;
 }
@@ -144,11 +145,12 @@ def test_solved_form_without_retention(plan, chains, K, V, bf16, least):
 def test_slices_of_the_chain_kernels(plan):
     calls = [(V // (16 if narrow else 32), ch, narrow, V, bf, K)
              for V in range(64, 513, 64) for ch in (*range(1, 70), 127, 128, 256, 1000) for narrow in (0, 1) for bf in (0, 1) for K in (64, 128)]
-    for (ns, ch, narrow, V, bf, K), (wgs, once, share, beside, alone) in zip(calls, plan(calls, "slices")):
+    for (ns, ch, narrow, V, bf, K), (wgs, once, share, beside, alone, ahead) in zip(calls, plan(calls, "slices")):
         assert once, (ns, ch)
         filled = narrow and ch > 8 and -(-ch // 8) * 8 * ns <= 256
         assert wgs == (-(-ch // 8) * 8 if filled else ch) * ns
         assert share or not (filled or ch % 8 == 0)
+        assert not narrow or ahead == (share and (filled or ch % 8 == 0))
         if bf:
             # never on more XCDs than slices of 32, but with up to eight chains
             assert not beside and alone == (ch * (V // 16) <= 256 and (ch <= 8 or ch % 8 == 0 or V >= 256 or -(-ch // 8) * (V // 16) <= 32))
