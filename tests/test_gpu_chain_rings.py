@@ -145,3 +145,30 @@ def test_a_long_call_that_asks_for_lines_ahead(B, T, H, K, V, channel_gate):
     o2, S2, d2, _ = ob.forward(*part(m, T), None, d1, S1, hp=hp)
     same = [torch.equal(a, b) for a, b in ((d, d2), (S, S2), (o[:, :m], o1), (o[:, m:], o2))]
     assert all(same), same
+
+
+def test_packed_sequences_with_channel_gates_that_ask_for_lines_ahead():
+    """bf16, enough chains and tiles for both chain kernels to ask ahead, ragged documents longer than the eight chunks: the same bits as
+    one call per document, which has too few of either."""
+    lens, H, K, V = [64 * 180, 64 * 90 + 5, 64 * 100, 64 * 40 + 63], 8, 128, 64
+    cu = [0, *np.cumsum(lens).tolist()]
+    T = cu[-1]
+    g = torch.Generator(device="cuda").manual_seed(169)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    unit = lambda a: (a / a.norm(dim=-1, keepdim=True)).bfloat16()
+    x = [unit(rnd(1, T, H, K)), unit(rnd(1, T, H, K)), rnd(1, T, H, V).bfloat16(), torch.sigmoid(rnd(1, T, H)),
+         -0.1 * torch.rand(1, T, H, K, device="cuda", generator=g)]
+    dO = rnd(1, T, H, V).bfloat16()
+    hp = ob.Hyper(eta=0.05, segments=1, p1_pieces=-1, p1_solved=-1)
+
+    def run(lo, hi, cu_seqlens):
+        part = [a[:, lo:hi].contiguous() for a in x]
+        o, S, d, ctx = ob.forward(*part, hp=hp, for_backward=True, cu_seqlens=cu_seqlens)
+        return dict(ob.backward(ctx, dO[:, lo:hi].contiguous()), o=o, S_out=S, d_out=d)
+
+    whole = run(0, T, cu)
+    for s, (lo, hi) in enumerate(zip(cu, cu[1:])):
+        for name, a in run(lo, hi, None).items():
+            if a is not None:
+                ref = whole[name][s:s + 1] if name in ("S_out", "d_out", "dd_in", "dS_in") else whole[name][:, lo:hi]
+                assert torch.equal(a, ref), (name, s)
