@@ -21,7 +21,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libosdn.so")
 _lib = None
-_step_native = None        # _native.step, once the library is loaded (None: the module is not built)
+_step_native = None        # _native.step, once the library is loaded (None: no module that fits it)
 
 OSDN_F32, OSDN_BF16 = 0, 1
 
@@ -88,14 +88,13 @@ def lib():
         L.osdn_profile_kernel_name.argtypes = [ctypes.c_int]
         L.osdn_profile_read.restype = ctypes.c_int
         L.osdn_profile_read.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int), ctypes.c_int]
+        _lib = L
         try:
             from . import _native
-        except ImportError:
-            _step_native = None
-        else:
-            _native.bind(ctypes.cast(L.osdn_step, vp).value)
+            _native.bind(ctypes.cast(L.osdn_step, vp).value, ctypes.sizeof(OsdnParams), torch.__version__)
             _step_native = _native.step
-        _lib = L
+        except (ImportError, TypeError):       # (TypeError: one of an earlier interface)
+            pass
     return _lib
 
 

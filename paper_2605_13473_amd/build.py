@@ -1,6 +1,7 @@
-"""Build libosdn.so (the HIP library) in-tree for gfx950 with hipcc, and _native.so (binding.step's way to it) with g++."""
+"""Build libosdn.so (the HIP library) in-tree for gfx950 with hipcc, and the extension module _native (binding.step's way to it) with g++."""
 from __future__ import annotations
 
+import glob
 import os
 import subprocess
 import sysconfig
@@ -10,7 +11,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libosdn.so")
-NATIVE = os.path.join(HERE, "_native.so")
+NATIVE = os.path.join(HERE, "_native" + sysconfig.get_config_var("EXT_SUFFIX"))     # (the name says for which Python)
+NATIVE_SOURCE = os.path.join(CSRC, "osdn_native.cpp")
 SOURCES = ["osdn_api.hip", "osdn_precond.hip", "osdn_precond_bwd.hip", "osdn_precond_gen.hip", "osdn_step.hip", "osdn_tables.hip",
            "osdn_chunk_fwd.hip", "osdn_chunk_bwd.hip"]
 FLAGS = [
@@ -49,7 +51,7 @@ def build(verbose: bool = False, only=None) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=8) as pool:
-        native = pool.submit(build_native) if only is None or not os.path.exists(NATIVE) else None
+        native = None if only is not None and native_is_current() else pool.submit(build_native)
         objs = list(pool.map(compile_one, SOURCES))
         if native is not None:
             native.result()
@@ -57,15 +59,24 @@ def build(verbose: bool = False, only=None) -> str:
     return LIB
 
 
+def native_is_current() -> bool:
+    """The rule of the objects: the module fills a struct of osdn.h."""
+    sources = (NATIVE_SOURCE, os.path.join(os.path.dirname(HERE), "include", "osdn.h"))
+    return os.path.exists(NATIVE) and os.path.getmtime(NATIVE) > max(os.path.getmtime(f) for f in sources)
+
+
 def build_native() -> str:
     """The extension module: host code alone, against the tensor library's headers."""
     import torch
+    for old in glob.glob(os.path.join(HERE, "_native*.so")):
+        os.remove(old)
     root = os.path.dirname(torch.__file__)
     lib = os.path.join(root, "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + sysconfig.get_paths()["include"],
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DOSDN_TORCH_VERSION="{torch.__version__}"',
+           "-I" + sysconfig.get_paths()["include"],
            "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           "-o", NATIVE, os.path.join(CSRC, "osdn_native.cpp"), "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+           "-o", NATIVE, NATIVE_SOURCE, "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         print(r.stdout)

@@ -9,6 +9,7 @@
 #include <cfloat>
 #include <climits>
 #include <cmath>
+#include <cstring>
 
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/Tensor.h>
@@ -131,17 +132,25 @@ PyObject *step(PyObject *, PyObject *const *a, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// bind(address): where osdn_step is
-PyObject *bind(PyObject *, PyObject *addr) {
+// bind(address, size, version): where osdn_step is.  Refused where its struct or the tensor library are not those this was built for.
+PyObject *bind(PyObject *, PyObject *args) {
+    PyObject *addr;
+    Py_ssize_t size;
+    const char *version;
+    if (!PyArg_ParseTuple(args, "Ons", &addr, &size, &version)) return nullptr;
     void *p = PyLong_AsVoidPtr(addr);
     if (PyErr_Occurred()) return nullptr;
+    if (size != (Py_ssize_t)sizeof(osdn_params))
+        return PyErr_Format(PyExc_ImportError, "built for an osdn_params of %zd bytes, not %zd", (Py_ssize_t)sizeof(osdn_params), size);
+    if (std::strcmp(version, OSDN_TORCH_VERSION) != 0)
+        return PyErr_Format(PyExc_ImportError, "built for torch " OSDN_TORCH_VERSION ", not %s", version);
     g_step = reinterpret_cast<StepFn>(p);
     Py_RETURN_NONE;
 }
 
 PyMethodDef kMethods[] = {
     {"step", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(step)), METH_FASTCALL, "osdn_step on plain tensors, or None"},
-    {"bind", bind, METH_O, "address of osdn_step"},
+    {"bind", bind, METH_VARARGS, "address of osdn_step, size of osdn_params, version of the tensor library"},
     {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
 
