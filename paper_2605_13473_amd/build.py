@@ -1,10 +1,13 @@
-"""Build libosdn.so (the HIP library) in-tree for gfx950 with hipcc, and the extension module _native (binding.step's way to it) with g++."""
+"""Build libosdn.so (the HIP library) in-tree for gfx950 with hipcc, and the extension module _native (binding.step's way to it)
+with g++.  The library needs hipcc alone: without g++ or the headers of Python and the tensor library it is built, and
+the module, which only saves time, is not (binding.step then goes through Python, and says so)."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -65,23 +68,29 @@ def native_is_current() -> bool:
     return os.path.exists(NATIVE) and os.path.getmtime(NATIVE) > max(os.path.getmtime(f) for f in sources)
 
 
-def build_native() -> str:
-    """The extension module: host code alone, against the tensor library's headers."""
-    import torch
+def build_native():
+    """The extension module: host code alone, against the tensor library's headers.  Returns its path, or None, with a word of why, where it
+    cannot be built; what stood there before is gone then."""
     for old in glob.glob(os.path.join(HERE, "_native*.so")):
         os.remove(old)
-    root = os.path.dirname(torch.__file__)
-    lib = os.path.join(root, "lib")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DOSDN_TORCH_VERSION="{torch.__version__}"',
-           "-I" + sysconfig.get_paths()["include"],
-           "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           "-o", NATIVE, NATIVE_SOURCE, "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        print(r.stdout)
-        raise subprocess.CalledProcessError(r.returncode, cmd)
-    return NATIVE
+    try:
+        import torch
+        root = os.path.dirname(torch.__file__)
+        lib = os.path.join(root, "lib")
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DOSDN_TORCH_VERSION="{torch.__version__}"',
+               "-I" + sysconfig.get_paths()["include"],
+               "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               "-o", NATIVE, NATIVE_SOURCE, "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"]
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        why = r.stdout if r.returncode != 0 else None
+    except (ImportError, OSError) as e:
+        why = str(e)
+    if why is None:
+        return NATIVE
+    print(why)
+    warnings.warn("the extension module was not built: binding.step goes through Python, at twice the time of a small call")
+    return None
 
 
 if __name__ == "__main__":
