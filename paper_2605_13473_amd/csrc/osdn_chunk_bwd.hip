@@ -49,16 +49,16 @@ __device__ __forceinline__ bf16x8 scale_frag(bf16x8 f, const float *g) {      //
 __device__ __forceinline__ float scale_frag(float f, const float *g) { return f * *g; }
 
 // ------------------------------------------------------------- bwd_chain ----
-// Mirror image of state_fwd, right to left: eight wavefronts on the chain (two barriers per chunk),
-// four that move the operands in and the dS' checkpoint and dE^T out:
+// Right to left over the chunks of one chain, one workgroup per slice of VS rows of dS: eight wavefronts on the chain (two barriers per
+// chunk), four that move the operands in and the dS' checkpoint and dE^T out (as in state_fwd_kernel):
 //   A  dS', rounded to the I/O type, into LDS                                        | barrier 1
 //   B  dE = scale P^T dO + rho . (K~ dS'^T), one 16x16 tile per wavefront, into LDS  | barrier 2
 //   C  dS <- gamma_C dS' + scale (gamma . dO)^T Q - dE^T W in the MFMA accumulators (the part
 //      without dE already in phase B)
 // The operands come as the forward pass and the caller left them (K~, -W, P, q, the slice of dO, all
 // in their natural [token][feature] layout; those whose contraction index runs down the rows are
-// fetched with the LDS transpose read), by direct global -> LDS loads into two rings, and are in
-// registers when the phase that multiplies them begins, as in state_fwd: what phase B needs (K~; P
+// fetched with the LDS transpose read), by direct global -> LDS loads into two rings, and with bf16 I/O are in
+// registers when the phase that multiplies them begins (PRE; fp32 fragments would not fit): what phase B needs (K~; P
 // and dO, whose product and whose scaled fragments are formed at once; the gates) is prepared in
 // phase C of the chunk before, what phase C needs (-W, q) in phase B.  64 chains of 64 chunks, K = V =
 // 128 in bf16: 134 us; with the tiles staged through registers by loader wavefronts, 157 us (16 chains of
@@ -172,9 +172,14 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
         // (all is there; said to the compiler too, which does not count wait_vm: it would wait for the state's loads where
         // their registers are used again in the loop, and with them for every tile on its way: 122 -> 142 us)
         __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+        // A slot is refilled once its operands have been read.  PRE: those of phase B are read in phase C of the chunk before, those of phase
+        // C in phase B, so that B's slot is free behind barrier 1 and C's behind barrier 2.  Barrier 1 then opens on C of this chunk, behind which B and
+        // C of the next NSC - 1 have been asked for (NEWER_C), barrier 2 on B of the next, behind which C of it and B of the one after have
+        // (NSB = 2: NEWER_B).  Not PRE: either is read in its own phase; barrier 1 opens on B of this chunk, behind which C of the chunk before and
+        // B of the next have been asked for (NSB = 2; NSB = 1: nothing), barrier 2 on C, asked for behind barrier 1.
         for (int n = a.n1 - 1; n >= a.n0; --n) {
             const bool full = n - NMAX >= a.n0; // everything counted as newer has been asked for
-            if (full) wait_vm<PRE ? NEWER_C : NEWER_B>(); else wait_vm<0>();   // (as in state_fwd)
+            if (full) wait_vm<PRE ? NEWER_C : NEWER_B>(); else wait_vm<0>();
             __syncthreads();                                        // barrier 1
             if (PRE && n - NSB >= a.n0) loadB(n - NSB, sb);
             if (!PRE && n + 1 - NSC >= a.n0) loadC(n + 1 - NSC, sc == 0 ? NSC - 1 : sc - 1);

@@ -53,11 +53,11 @@ inline bool asks_ahead(const osdn_params *p, long long tiles, long long chains) 
 // first segment of the forward pass, the last of the backward pass) and costs launches, cross-stream
 // waits (25 us a call for the first) and partly filled rounds of workgroups.  Times below: one stream against the best
 // of two to six segments, us, K = V = 128 in bf16.
-//  - short sequences take one stream: forward up to 32 chunks (2 chains of 4 chunks 34 and 80, 64 of 16 107 and
-//    129, 64 of 32 221 and 231; 64 of 48 322 and 309), backward up to 48 (2 of 4 49 and 113, 64 of 16
-//    156 and 208, 8 of 32 128 and 158, 64 of 48 463 and 465, 128 of 48 790 and 802; 32 of 64 409 and 380).
-//  - so do many chains, which fill the chip by themselves: 256 of 64 forward 1141 and 1206, backward 1935 and 1997;
-//    from 128 chains on the forward pass takes two at most (128 of 128 1249, with six 1298).
+//  - short sequences take one stream: forward up to 32 chunks (2 chains of 4 chunks 34 and 79, 64 of 16 106 and
+//    127, 64 of 32 215 and 220; 64 of 48 319 and 304), backward up to 48 (2 of 4 53 and 117, 64 of 16
+//    149 and 179, 8 of 32 116 and 159, 64 of 48 449 and 443, 128 of 48 773 and 755; 32 of 64 368 and 370).
+//  - so do many chains, which fill the chip by themselves: 256 of 64 forward 1122 and 1182, backward 1779 and 1944;
+//    from 128 chains on the forward pass takes two at most (128 of 128 1253, with four 1238, with six 1291).
 //  - forward otherwise: about 16 chunks per segment, at most six segments (measured flat beyond).
 //  - backward otherwise: a segment more costs more there, because every launch of the phase-2 chain kernel
 //    meets a phase-1 chain kernel on the other stream and the two do not fit on one CU together:
@@ -66,10 +66,10 @@ inline bool asks_ahead(const osdn_params *p, long long tiles, long long chains) 
 //    all fit side by side, about 32 chunks per segment, at most four: of that count and the two
 //    above it, the one whose segments fill whole rounds of bwd_post workgroups (one per chunk and
 //    chain, post_round at a time) best; from 448 chunks on, where a segment is many rounds, seven.
-//    16 chains, bf16, backward pass alone: 128 chunks 494, 499, 493, 515, 546, 575 us with 3 to 8 segments
-//    (5 taken); 256 chunks, V = 256 993, 1014, 1057, 1063, 1097, 1023 with 4 to 9 (5); 512 chunks 1648, 1625, 1621,
-//    1619, 1643, 1816 with 4 to 8 and 12; chains that are swept, with retention, 512 chunks with 4 to 8, 10 and 12: 33 chains 2662,
-//    2605, 2580, 2583, 2597, 2608, 2583; 48 3193, 3171, 3173, 3179, 3192, 3231, 3262; fp32, 8 chains 3801, 3778, 3695, 3793, 3897, 3760, 3923.
+//    16 chains, bf16, backward pass alone: 128 chunks 483, 503, 493, 517, 546, 575 us with 3 to 8 segments
+//    (5 taken); 256 chunks, V = 256 989, 989, 1045, 1056, 1094, 1020 with 4 to 9 (5); 512 chunks 1603, 1593, 1604,
+//    1599, 1623, 1769 with 4 to 8 and 12; chains that are swept, gates of 0.999, 512 chunks with 4 to 8, 10 and 12: 33 chains 2381,
+//    2436, 2342, 2426, 2369, 2472, 2463; 48 2939, 2970, 2936, 2984, 2954, 3055, 3050; fp32, 8 chains 3653, 3647, 3616, 3704, 3810, 3675, 3867.
 // Segments cut the chunk axis as a whole.  With packed sequences the sequential kernels of a
 // segment only have the sequences that cross it to work on, one after the other segment by
 // segment, so cutting pays only while one sequence makes up most of the axis; otherwise the
@@ -133,30 +133,30 @@ inline int seg_begin(int N, int S, int s) {
 // pieces per chain (-1: never), params->p1_piece_sweeps the sweep limit.
 //
 // Where the line lies (us per pass, sequential or in segments against pieces; K = V = 128 in bf16):
-//  - forward, chains on an eighth of the CUs or fewer, from 24 chunks on: 16 chains of 24 110 and 96, with a retention
-//    gate 131 and 105, of 32 137 and 107, 167 and 116, of 64 229 and 187 (pieces of 4 chunks; of 8: 229), 32 of
-//    32 166 and 138; 16 chains of 16 79 and 82.
+//  - forward, chains on an eighth of the CUs or fewer, from 24 chunks on: 16 chains of 24 108 and 90, with a retention
+//    gate 121 and 109, of 32 136 and 97, 149 and 116, of 64 260 and 174 (pieces of 4 chunks; of 8: 221), 32 of
+//    32 162 and 134; 16 chains of 16, with a gate, 90 and 94.
 //  - not for more chains: how many sweeps the pieces need with a retention gate goes by how much it fades, two with gates of 0.999,
 //    three to five with 0.9999 or 1, and with 33 to 64 chains only two pay (64 chains, segments and pieces, gates of 0.999, then of
-//    1: forward of 32 chunks 240 and 219, 250 and 252, of 64 427 and 389, 435 and 471, of 128 770 and 695, 834 and 915, of 256 1354 and
-//    1312, 1476 and 1947; backward of 64 625 and 583, 629 and 632, of 128 1115 and 1093, 1118 and 1193).
-//  - how many pieces, forward without retention: 4 chains of 64 chunks 205 with 8 pieces, 159 with 16, 148 with 32; of 256 410 with
-//    32, 390 with 64, 469 with 128; of 512 883, 783, 852; 2 of 1024 1649, 1346, 1298 and with 256 1516; 1 of 1024 1192 with 64, 1141
-//    with 128, 1317 with 256.
+//    1: forward of 32 chunks 226 and 214, 246 and 250, of 64 420 and 395, 426 and 468, of 128 761 and 697, 792 and 917, of 256 1336 and
+//    1261, 1468 and 1947; backward of 64 572 and 564, 593 and 620, of 128 1025 and 1057, 1070 and 1170).
+//  - how many pieces, forward without retention: 4 chains of 64 chunks 193 with 8 pieces, 144 with 16, 126 with 32; of 256 380 with
+//    32, 337 with 64, 367 with 128; of 512 848, 721, 741; 2 of 1024 1600, 1270, 1152 and with 256 1238; 1 of 1024 1082 with 64, 959
+//    with 128, 986 with 256.
 //  - two workgroups a CU where they fit (us, one and two): forward, K = 128, one gate in bf16 (127 registers) 16 chains of 256 chunks
-//    581 and 567, with gates of 1 790 and 754; where they do not, the pieces run in two rounds: one gate in fp32 (136) 1302 and 1347,
-//    1537 and 1645; a gate per coordinate (159) 597 and 668, 826 and 939; backward (153 and more) 826 and 863, 972 and 1090.
+//    525 and 514, with gates of 1 739 and 686; where they do not, the pieces run in two rounds: one gate in fp32 (136) 1285 and 1311,
+//    1526 and 1573; a gate per coordinate (159) 557 and 606, 774 and 825; backward (153 and more) 698 and 733, 807 and 844.
 //  - backward, only with a retention gate (without, the solved form has the shorter chain), gates of 0.999, then of 1: 16 chains of
-//    24 chunks 142 and 130, 141 and 146, of 32 173 and 142, 183 and 173, of 128 567 and 437, 571 and 503, of 512 1927 and 1602, 1954
-//    and 1802; pieces of four chunks at least (16 chains of 32 chunks: pieces of two 146).
+//    24 chunks 121 and 131, 133 and 131, of 32 144 and 141, 161 and 141, of 128 500 and 378, 569 and 408, of 512 1677 and 1341, 1897
+//    and 1569; pieces of four chunks at least (16 chains of 32 chunks, gates of 0.999: pieces of two 131).
 //    Not for long sequences of many chains, where segments keep phase 1 beside phase 2 (gates of 0.999, then of 1): 32 chains of 64
-//    chunks 447 and 378, 492 and 458, of 128 703 and 681, 803 and 846, of 256 1328 and 1290, 1483 and 1594; with fp32 I/O and K = 128
-//    16 chains of 96 961 and 916, 964 and 950, of 128 1242 and 1215, 1246 and 1291, of 256 2321 and 2348, 2324 and 2495.
+//    chunks 391 and 317, 431 and 347, of 128 710 and 577, 694 and 679, of 256 1216 and 1133, 1277 and 1352; with fp32 I/O and K = 128
+//    16 chains of 96 959 and 910, 966 and 965, of 128 1232 and 1200, 1240 and 1268, of 256 2331 and 2344, 2336 and 2487.
 //  - all this for eta up to what K allows (the sweeps over the pieces need the more the larger eta / K is, and beyond a limit do not
 //    settle: 0.003 is within it by a factor of 2.1 and 1.07 for the forward pass, K = 128 and 64, of 11 and 5 for the
-//    backward pass).  16 chains of 48 chunks, gates of 1, segments and pieces: forward, K = 128, eta 0.01 256 and 160, 0.03 310 and 219,
-//    0.1 310 and 471; K = 64, 0.003 199 and 132, 0.01 233 and 157, 0.03 233 and 354; backward, K = 128, 0.03 283 and 249, 1 433 and
-//    768, K = 64, 16 chains of 128 chunks 0.01 500 and 382, 0.1 676 and 1000.  Beyond it only the forward pass of 64 chunks and more is
+//    backward pass).  16 chains of 48 chunks, gates of 1, segments and pieces: forward, K = 128, eta 0.01 257 and 151, 0.03 312 and 206,
+//    0.1 311 and 459; K = 64, 0.003 198 and 118, 0.01 235 and 143, 0.03 235 and 340; backward, K = 128, 0.03 266 and 222, 1 416 and
+//    728, K = 64, 16 chains of 128 chunks 0.01 495 and 323, 0.1 672 and 976.  Beyond it only the forward pass of 64 chunks and more is
 //    cut, into pieces of eight chunks.
 inline void pieces_plan(const osdn_params *p, int N, long long chains, bool packed, bool retention, bool backward, int &pieces,
                         int &piece_chunks, int &sweeps) {
@@ -180,7 +180,7 @@ inline void pieces_plan(const osdn_params *p, int N, long long chains, bool pack
         } else {
             const bool two = p->K == 64 || (!backward && (!retention || (p->io_dtype == OSDN_BF16 && !p->retention_per_channel)));
             if (two && N >= 16 * target) target *= 2;
-            // (every workgroup walks the maps of all pieces of its chain; but pieces of more than eight chunks cost more than that walk)
+            // (every workgroup walks the maps of all pieces of its chain, eight at a time; but pieces of more than eight chunks cost more than that walk)
             const int most = N <= 64 ? 16 : N <= 256 ? 32 : (N + 7) / 8;
             if (target > most) target = most;
             min_chunks = backward ? 4 : 2;
