@@ -93,8 +93,8 @@ __global__ __launch_bounds__(CT_) void bwd_chain_kernel(ChunkArgs a) {
     __shared__ __attribute__((aligned(1024))) char dump[TOUCH ? 256 : 16];
 
     int chain = 0, slice = 0;
-    chain_slice_of(blockIdx.x, gridDim.x, a.V / VS, chain, slice);
-    if (chain >= (a.seq_chunks ? a.n_seqs : a.B) * a.H) return;
+    chain_slice_of(blockIdx.x, a.map, chain, slice);
+    if (chain >= a.map.chains) return;
     const int vs = slice * VS, h = chain % a.H;
     int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
@@ -799,8 +799,10 @@ __global__ __launch_bounds__(PW_ * 64, (BP_WGS<T>) * PW_ / 4) void bwd_post_kern
 // -------------------------------------------------------------- launchers ----
 template <typename T, int K, bool GV, int VS>
 static void launch_chain_t(const ChunkArgs &a, hipStream_t st) {
-    dim3 grid(chain_workgroups(a.V / VS, a.H * (long long)(a.seq_chunks ? a.n_seqs : a.B), VS == 16)), block(CT_);
-    with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((bwd_chain_kernel<T, K, GV, VS, decltype(rag)::value>), grid, block, 0, st, a); });
+    ChunkArgs b = a;
+    b.map = slice_map(a.V / VS, a.H * (long long)(a.seq_chunks ? a.n_seqs : a.B), VS == 16);
+    dim3 grid(chain_workgroups(b.map)), block(CT_);
+    with_rows(a.rows, [&](auto rag) { hipLaunchKernelGGL((bwd_chain_kernel<T, K, GV, VS, decltype(rag)::value>), grid, block, 0, st, b); });
 }
 // Slices of 16 values with fp32 I/O at K = 128 (beside slices of 32 one chunk's operands would fill the LDS, with nothing in
 // flight for the next), else of 16 or 32 (narrow_backward in osdn_plan.h says which).

@@ -234,8 +234,8 @@ __global__ __launch_bounds__(CT_) void state_fwd_kernel(ChunkArgs a) {
     __shared__ __attribute__((aligned(1024))) char Ew[GV ? 16 : VS * RC];   // (rho E)^T
 
     int chain = 0, slice = 0;
-    chain_slice_of(blockIdx.x, gridDim.x, a.V / VS, chain, slice);
-    if (chain >= (a.seq_chunks ? a.n_seqs : a.B) * a.H) return;
+    chain_slice_of(blockIdx.x, a.map, chain, slice);
+    if (chain >= a.map.chains) return;
     const int vs = slice * VS, h = chain % a.H;
     int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
@@ -460,8 +460,8 @@ __global__ __launch_bounds__(RT_<VS>, 1) void state_fwd_run_kernel(ChunkArgs a) 
     __shared__ __attribute__((aligned(1024))) char dump[256];
 
     int chain = 0, slice = 0;
-    chain_slice_of(blockIdx.x, gridDim.x, a.V / VS, chain, slice);
-    if (chain >= (a.seq_chunks ? a.n_seqs : a.B) * a.H) return;
+    chain_slice_of(blockIdx.x, a.map, chain, slice);
+    if (chain >= a.map.chains) return;
     const int vs = slice * VS, h = chain % a.H;
     int b = chain / a.H;                        // batch entry, or packed sequence
     int bt = b;                                 // batch entry of the token tensors
@@ -813,14 +813,16 @@ int launch_chunk_prep(const ChunkArgs &a, bool bf16_io, hipStream_t st) {
 }
 template <bool BF16, bool GV, int VS>
 static int launch_state_t(const ChunkArgs &a, hipStream_t st) {
-    dim3 grid(chain_workgroups(a.V / VS, a.H * (long long)(a.seq_chunks ? a.n_seqs : a.B), VS == 16)), block(BF16 ? RT_<VS> : CT_);
+    ChunkArgs b = a;
+    b.map = slice_map(a.V / VS, a.H * (long long)(a.seq_chunks ? a.n_seqs : a.B), VS == 16);
+    dim3 grid(chain_workgroups(b.map)), block(BF16 ? RT_<VS> : CT_);
     if (GV && !a.gamC) return -1;
     auto launch = [&](auto k) {
         constexpr int K = decltype(k)::value;
         with_rows(a.rows, [&](auto rag) {
             constexpr bool RAG = decltype(rag)::value;
-            if constexpr (BF16) hipLaunchKernelGGL((state_fwd_run_kernel<K, GV, VS, RAG>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((state_fwd_kernel<K, GV, VS, RAG>), grid, block, 0, st, a);
+            if constexpr (BF16) hipLaunchKernelGGL((state_fwd_run_kernel<K, GV, VS, RAG>), grid, block, 0, st, b);
+            else hipLaunchKernelGGL((state_fwd_kernel<K, GV, VS, RAG>), grid, block, 0, st, b);
         });
     };
     if (a.K == 64) launch(std::integral_constant<int, 64>{});

@@ -157,6 +157,7 @@ struct StepArgs {
 // (numbered head first) or the chains of a chain kernel (in step) touch at one time is then
 // contiguous in memory and spreads over all its channels.
 struct ChunkArgs {
+    SliceMap map;             // chain kernels: the slices of the launch (the launchers say; first, with the sizes: one line of arguments)
     int B, T, H, K, V, N;
     int n0, n1;
     int n_seqs;

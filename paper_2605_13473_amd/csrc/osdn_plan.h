@@ -20,17 +20,18 @@ constexpr int MAX_SEGMENTS = 16, MAX_PIECES = 512, MAX_PIECE_SWEEPS = 13;
 inline bool chains_filled_up(int nslices, long long chains, bool narrow) {
     return narrow && chains > NUM_XCD && (chains + NUM_XCD - 1) / NUM_XCD * nslices * NUM_XCD <= NUM_CU;
 }
-inline int chain_workgroups(int nslices, long long chains, bool narrow) {
-    return (int)((chains_filled_up(nslices, chains, narrow) ? (chains + NUM_XCD - 1) / NUM_XCD * NUM_XCD : chains) * nslices);
+// How the workgroups of such a launch are laid out, with what a workgroup needs to find its slice: a multiplication in place of a division
+// (reciprocal: the next above 2^32 / slices, exact below 2^27 workgroups), and nothing that it would have to wait for twice.
+struct SliceMap { int slices, chains, share; unsigned reciprocal; };
+inline SliceMap slice_map(int nslices, long long chains, bool narrow) {
+    return {nslices, (int)chains, chains % NUM_XCD == 0 || chains_filled_up(nslices, chains, narrow), (unsigned)(((1ull << 32) + nslices - 1) / nslices)};
 }
-
-// which slice of which chain a workgroup of such a launch is (constexpr: for the device too); a chain that there is not: none
-constexpr bool slices_share_xcd(int workgroups, int nslices) { return workgroups % (NUM_XCD * nslices) == 0; }
-constexpr void chain_slice_of(int wg, int workgroups, int nslices, int &chain, int &slice) {
-    const bool share = slices_share_xcd(workgroups, nslices);
-    const int xcd = wg % NUM_XCD, j = share ? wg / NUM_XCD : wg;
-    slice = j % nslices;
-    chain = share ? xcd + NUM_XCD * (j / nslices) : j / nslices;
+inline int chain_workgroups(const SliceMap &m) { return (m.share ? (m.chains + NUM_XCD - 1) / NUM_XCD * NUM_XCD : m.chains) * m.slices; }
+// (constexpr: for the device too; a chain that there is not: nothing to do)
+constexpr void chain_slice_of(int wg, const SliceMap &m, int &chain, int &slice) {
+    const unsigned j = m.share ? (unsigned)wg / NUM_XCD : (unsigned)wg, c = (unsigned)(((unsigned long long)j * m.reciprocal) >> 32);
+    slice = (int)(j - c * m.slices);
+    chain = m.share ? (int)(wg % NUM_XCD + NUM_XCD * c) : (int)c;
 }
 
 // state_fwd_run_kernel with slices of 16: whether it asks for the lines of its operands ahead of its tiles (tiles: chunks of all chains).
@@ -45,7 +46,7 @@ constexpr void chain_slice_of(int wg, int workgroups, int nslices, int &chain, i
 // on eight XCDs: 4 chains of 512 585 and 598, 2 of 512 431 and 463.
 inline bool asks_ahead(const osdn_params *p, long long tiles, long long chains) {
     const long long K = p->K, V = p->V, kept = 2 * (64 * 64 + (p->gate_per_channel ? 5 : 2) * 64 * K + 2 * 64 * V + V * K);
-    return slices_share_xcd(chain_workgroups(p->V / 16, chains, true), p->V / 16) && tiles * kept > 200ll << 20;
+    return slice_map(p->V / 16, chains, true).share && tiles * kept > 200ll << 20;
 }
 
 // Number of segments for a sequence of N chunks (params->segments > 0 overrides it; 1 = no

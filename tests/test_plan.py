@@ -20,12 +20,13 @@ int slices() {
     while (std::scanf("%d %lld %d %d %d %d", &ns, &ch, &narrow, &V, &bf, &K) == 6) {
         osdn_params p{};
         p.K = K; p.V = V; p.io_dtype = bf ? OSDN_BF16 : OSDN_F32;
-        const int wgs = chain_workgroups(ns, ch, narrow);
+        const SliceMap m = slice_map(ns, ch, narrow);
+        const int wgs = chain_workgroups(m);
         std::vector<int> seen(ch * ns, 0), xcd(ch, -1);
         bool share = true;
         for (int w = 0; w < wgs; ++w) {
             int c = -1, s = -1;
-            chain_slice_of(w, wgs, ns, c, s);
+            chain_slice_of(w, m, c, s);
             if (c >= ch) continue;
             ++seen.at(c * ns + s);
             if (xcd[c] >= 0 && xcd[c] != w % NUM_XCD) share = false;
@@ -144,7 +145,7 @@ def test_solved_form_without_retention(plan, chains, K, V, bf16, least):
 
 def test_slices_of_the_chain_kernels(plan):
     calls = [(V // (16 if narrow else 32), ch, narrow, V, bf, K)
-             for V in range(64, 513, 64) for ch in (*range(1, 70), 127, 128, 256, 1000) for narrow in (0, 1) for bf in (0, 1) for K in (64, 128)]
+             for V in range(64, 513, 64) for ch in (*range(1, 70), 127, 128, 256, 1000, 65537) for narrow in (0, 1) for bf in (0, 1) for K in (64, 128)]
     for (ns, ch, narrow, V, bf, K), (wgs, once, share, beside, alone, ahead) in zip(calls, plan(calls, "slices")):
         assert once, (ns, ch)
         filled = narrow and ch > 8 and -(-ch // 8) * 8 * ns <= 256
