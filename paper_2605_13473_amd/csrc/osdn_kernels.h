@@ -85,7 +85,7 @@ struct PrecondArgs {
     float *d_out;             // [B,H,K]
     float *d_ckpt;            // [B,H,T/64,K] or null
     float *tok_scalars;       // [B,T,H,4] or null: per token (step, <d,k^2>, sum k^2, unused), kept for the backward; without
-                              // retention the sum is kept with its sign flipped in chunks whose coordinates all stay well off the box
+                              // retention the sum's sign is a mark: the last token's is flipped in a chunk that stays well off the box (mark_bound)
     void *k_tail;             // [sequences,64,H,K] io: k of ragged last chunks, whole, kept for the backward
     float *beta_tail, *ret_tail;      // [sequences,64,H], as retention
     // Sweeps over the whole sequence (pieces > 0, plain batches only): a chain is cut into

@@ -455,13 +455,18 @@ __global__ __launch_bounds__(P1F, K == 128 && RET == 1 && sizeof(T) == 2 ? 4 : 1
                 }
             }
         }
-        // (RET == 0) off the box, by the margin at the upper face: d only rose, so that what the last run says counts (32 chunks of 64
-        // chains: 93.2 us; 92.1 where the sweeps themselves kept the margin, which swept a chain that stands within it in vain)
+        // (RET == 0) off the box, by the margin at the upper face: d only rose, so that the last run's end counts (64 chains of
+        // 64 chunks: 178.8 us, with every run looking 180.2; 177.7 where the sweeps themselves kept the margin, which swept a chain that stands within
+        // it in vain)
         bool clear = true;
         if (RET == 0) {
+            clear = FAST && !boxed;
+            if (clear && run == NRUN - 1) {
+                bool in = true;
 #pragma unroll
-            for (int e = 0; e < CPT; ++e) clear = clear && dend[e] <= mark_bound(lo, hi);
-            clear = FAST && !boxed && __all(clear);
+                for (int e = 0; e < CPT; ++e) in = in && dend[e] <= mark_bound(lo, hi);
+                clear = __all(in);
+            }
         }
         if (TILES || (a.tok_scalars && valid)) {       // (eight lanes store the same)
             const size_t th = ((size_t)bt * a.T + t0) * a.H + h;
