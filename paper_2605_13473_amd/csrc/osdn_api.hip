@@ -439,7 +439,10 @@ static int fwd_impl(const osdn_params *p, const void *q, const void *k, const vo
     const bool crowded = chains * (p->V / 32) + chains > NUM_CU;
     // Few chains: the state kernel takes slices of 16 values instead of 32 when its workgroups then
     // still find a CU each (beside those of phase 1, unless phase 1 runs ahead as sweeps over pieces):
-    // its time per chunk is latency, not work, and half the work per workgroup shortens it.
+    // its time per chunk is latency, not work, and half the work per workgroup shortens it.  (Forward pass, us, slices of 16 and 32:
+    // 16 chains of 512 chunks 957 and 1097, of 128 with V = 256 323 and 337; 2 of 4 33 and 34, 8 of 32 89 and 96, 24 of 32 123 and 131, 28 of 128 494 and
+    // 540; K = 64, V = 128, 32 of 32 119 and 125; fp32, 32 of 32 291 and 337, 16 of 128 with K = 64 524 and 635.  With everything on one stream
+    // more would take 16 gladly: 64 of 32, K = V = 64, 142 and 148.)
     c.narrow_slices = cg.narrow_slices = cs.narrow_slices = chains * (p->V / 16) + (pieces ? 0 : chains) <= NUM_CU;
     c.asks_ahead = cg.asks_ahead = cs.asks_ahead = asks_ahead(p, (long long)p->B * N * p->H, chains);
     auto seg_range = [&](int sidx, int &n0, int &n1) {
